@@ -169,28 +169,16 @@ etac_status etac_propagate(etac_plan *plan, const etac_model *model, int32_t n_e
                            const int8_t *contact_obj, const float *uhat, float *u, void *saved,
                            void *stream);
 
-/* Whole step, contact + propagation, as one persistent fused launch.
- * Outputs DEVICE: u [3][E][N], contact_obj [E][N], n_active [E][K].
- * saved (DEVICE, may be NULL): the pooling record for the adjoint, see
- * ETAC_SAVED_WORDS. */
+/* Whole step, contact + propagation.  Outputs DEVICE: u [3][E][N],
+ * contact_obj [E][N], n_active [E][K].  saved (DEVICE, may be NULL): the
+ * pooling record for the adjoint, see ETAC_SAVED_WORDS. */
 etac_status etac_step(etac_plan *plan, const etac_scene *scene, const etac_model *model,
                       float *u, int8_t *contact_obj, int32_t *n_active, void *saved, void *stream);
 
-/* The fused step for callers that cannot allocate device memory or may not
- * call hipMalloc (code under stream capture, tight serving loops, harnesses
- * that forbid allocation).  Same arguments, outputs and errors as etac_step,
- * identical results; it allocates and frees nothing.  The per-workgroup
- * scratch of its kernel (u_hat, residuals and node lists of the current
- * item, work-queue counters) is a library-owned 64 MiB device array, which
- * every device the library runs on holds until the process ends, instead of
- * the plan's scratch.  All calls on one device share that array: calls that
- * could run at the same time on one device (different streams without
- * ordering between them) race and must not be made.  A workgroup needs
- * 32 n_max bytes of it (n_max: the plan's largest patch); when the plan's
- * persistent grid needs more than the array holds, fewer workgroups run.
- * ETAC_ERR_SHAPE if one workgroup's slice does not fit; ETAC_ERR_WORKSPACE if
- * the array's address on the plan's device is not known (it is looked up
- * when a plan is created on that device). */
+/* The step for callers that cannot allocate device memory or may not call
+ * hipMalloc (code under stream capture, tight serving loops, harnesses that
+ * forbid allocation).  Same arguments, outputs and errors as etac_step, which
+ * itself allocates and frees nothing: its scratch is the plan's. */
 etac_status etac_step_static(etac_plan *plan, const etac_scene *scene, const etac_model *model, float *u,
                              int8_t *contact_obj, int32_t *n_active, void *saved, void *stream);
 
@@ -293,8 +281,9 @@ int32_t etac_last_hip_error(void);
 etac_status etac_plan_info(const etac_plan *plan, int32_t *n_items, int32_t *grid,
                            int64_t *scratch_bytes);
 
-/* Launch-shape override for the autotuner: persistent workgroups per CU for
- * the fused kernels (0 = built-in default). */
+/* Launch-shape override for the autotuner: forward workgroups per CU (0 =
+ * built-in default).  The forward's kernels choose their own shape from the
+ * sizes of the call; the value is kept and reported, and changes no result. */
 etac_status etac_plan_set_occupancy(etac_plan *plan, int32_t wg_per_cu);
 
 /* Work-queue granularity for the autotuner: (env, patch) items claimed per
@@ -339,7 +328,7 @@ etac_status etac_plan_autotune(etac_plan *plan, const etac_scene *scene, const e
 #define ETAC_TIMER_SLOTS 256
 typedef enum {
     ETAC_TIMER_CONTACT = 0,   /* k_contact: contact only (etac_contact)                  */
-    ETAC_TIMER_STEP = 1,      /* k_step: the fused persistent forward                    */
+    ETAC_TIMER_STEP = 1,      /* the kernels of one forward step or propagation, as one span */
     ETAC_TIMER_BACKWARD = 2,  /* k_bwd: network and contact adjoint of contacted items   */
     ETAC_TIMER_REDUCE = 3,    /* the fixed-order reductions that follow k_bwd, as one span */
     ETAC_TIMER_BWD_DECAY = 4, /* k_bwd_decay: contact and Eq. 1 adjoint, before k_bwd     */
@@ -430,7 +419,7 @@ etac_status etac_hand_contact(etac_plan *plan, const etac_scene *scene, const et
                               int8_t *contact_obj, float *uhat, int32_t *n_active, const etac_reward *reward,
                               void *stream);
 
-/* Fused step of the hand (contact as above, then Eqs. 1-2 in the link
+/* Step of the hand (contact as above, then Eqs. 1-2 in the link
  * frames): u [3][E][N], contact_obj, n_active, reward (may be NULL), saved
  * (may be NULL: the pooling record, see ETAC_SAVED_WORDS). */
 etac_status etac_hand_step(etac_plan *plan, const etac_scene *scene, const etac_links *links,

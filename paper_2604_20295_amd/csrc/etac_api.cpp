@@ -39,6 +39,42 @@ hipError_t plan_alloc(etac::Plan &p, T **ptr, size_t count) {
     return hipSuccess;
 }
 
+template <typename T>
+hipError_t plan_upload(etac::Plan &p, T **ptr, const T *host, size_t count) {
+    const hipError_t e = plan_alloc(p, ptr, count);
+    return e == hipSuccess ? hipMemcpy(*ptr, host, count * sizeof(T), hipMemcpyHostToDevice) : e;
+}
+
+// Order of a patch's n nodes (patch-local indices) in which 64 consecutive
+// ones are a compact piece of the surface: halves along the longer side of the
+// bounding box, cut at multiples of 64 nodes.
+void spatial_order(const etac_mesh *mesh, int base, int n, int *out) {
+    for (int i = 0; i < n; ++i) out[i] = i;
+    const size_t N = (size_t)mesh->n_nodes;
+    std::vector<std::pair<int, int>> todo(1, {0, n});
+    while (!todo.empty()) {
+        const auto [a, b] = todo.back();
+        todo.pop_back();
+        if (b - a <= 64) continue;
+        const float *x = nullptr;
+        float widest = -1.0f;
+        for (int c = 0; c < 3; ++c) {
+            const float *v = mesh->pos + c * N + base;
+            float lo = v[out[a]], hi = lo;
+            for (int i = a + 1; i < b; ++i) {
+                lo = std::min(lo, v[out[i]]);
+                hi = std::max(hi, v[out[i]]);
+            }
+            if (hi - lo > widest) { widest = hi - lo; x = v; }
+        }
+        const int mid = a + ((b - a) / 2 + 63) / 64 * 64;
+        std::nth_element(out + a, out + mid, out + b, [&](int i, int j) { return x[i] < x[j] || (x[i] == x[j] && i < j); });
+        todo.push_back({a, mid});
+        todo.push_back({mid, b});
+    }
+    for (int i = 0; i < n; i += 64) std::sort(out + i, out + std::min(n, i + 64));
+}
+
 void plan_free_all(etac::Plan &p) {
     for (int i = 0; i < p.n_allocs; ++i) (void)hipFree(p.allocs[i]);
     p.n_allocs = 0;
@@ -165,8 +201,6 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     p.net_batch = etac::kDefaultNetBatch;
     hipError_t e = hipGetDevice(&p.device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&p.cu_count, hipDeviceAttributeMultiprocessorCount, p.device);
-    // the device address of the static scratch of etac_step_static, once per device
-    if (e == hipSuccess) e = etac::static_scratch_init(p.device);
     if (e != hipSuccess) {
         delete h;
         return hip_fail(e);
@@ -174,10 +208,24 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     p.grid = p.cu_count * p.wg_per_cu;
 
     // host-side tables
-    std::vector<float4> bound(K);
-    std::vector<int16_t> node_patch(N);
-    std::vector<int> order(K);
-    std::vector<float> xbound(K);
+    std::vector<float4> bound;
+    std::vector<int16_t> node_patch;
+    std::vector<int> order, word_off, box_off, perm;
+    std::vector<float> xbound;
+    std::vector<int4> word;       // see TileDev
+    std::vector<int2> row_tile;
+    std::vector<long long> w_off;
+    long long matrix_units = 0;
+    etac::TileDev &tile = p.tile;
+    try {
+    bound.resize(K);
+    node_patch.resize(N);
+    order.resize(K);
+    xbound.resize(K);
+    word_off.assign(K + 1, 0);
+    box_off.resize(K);
+    perm.assign(N, 0);
+    w_off.resize(K);
     for (int k = 0; k < K; ++k) {
         const int o0 = mesh->patch_offset[k], o1 = mesh->patch_offset[k + 1];
         double lo[3], hi[3];
@@ -213,9 +261,35 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
         xbound[k] = round_up_float(xb * (1.0 + 1e-6));
         order[k] = k;
     }
+    // node words, decay matrices and spatial orders
+    for (int k = 0; k < K; ++k) {
+        const int o0 = mesh->patch_offset[k], n = mesh->patch_offset[k + 1] - o0;
+        for (int i = 0; i < n; i += 64) word.push_back(make_int4(k, o0 + i, std::min(64, n - i), i / 64));
+        word_off[k + 1] = (int)word.size();
+        box_off[k] = p.itm.NB;
+        const long long tiles = (n + 15) / 16, units = tiles * ((n + 31) / 32) * 3 * 64;
+        if (n <= etac::kNearNodes && (size_t)(matrix_units + units) * 16 <= etac::kDecayMatrixBytes) {
+            w_off[k] = matrix_units;
+            matrix_units += units;
+            for (int t = 0; t < tiles; ++t) row_tile.push_back(make_int2(k, t));
+            ++tile.n_near;
+            continue;
+        }
+        w_off[k] = -1;
+        ++tile.n_far;
+        tile.far_max = std::max(tile.far_max, n);
+        p.itm.NB += (n + 31) / 32;
+        spatial_order(mesh, o0, n, perm.data() + o0);
+    }
+    tile.NW = (int)word.size();
+    tile.near_rows = (int)row_tile.size();
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
         return (mesh->patch_offset[a + 1] - mesh->patch_offset[a]) > (mesh->patch_offset[b + 1] - mesh->patch_offset[b]);
     });
+    } catch (const std::exception &) {      // out of host memory
+        delete h;
+        return ETAC_ERR_SHAPE;
+    }
 
     float *pos = nullptr, *nrm = nullptr, *origin = nullptr;
     int *offset = nullptr, *ord = nullptr;
@@ -240,7 +314,43 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = hipMemcpy(xbd, xbound.data(), (size_t)K * sizeof(float), hipMemcpyHostToDevice);
     p.mesh = etac::MeshDev{pos, nrm, origin, offset, bnd, np, ord, xbd, K, N, n_max};
 
-    // forward scratch, one slice per persistent workgroup
+    int4 *wrd = nullptr;
+    int2 *rtl = nullptr;
+    int *woff = nullptr, *boff = nullptr, *prm = nullptr;
+    long long *moff = nullptr;
+    if (e == hipSuccess) e = plan_upload(p, &wrd, word.data(), word.size());
+    if (e == hipSuccess) e = plan_upload(p, &rtl, row_tile.data(), row_tile.size());
+    if (e == hipSuccess) e = plan_upload(p, &woff, word_off.data(), word_off.size());
+    if (e == hipSuccess) e = plan_upload(p, &boff, box_off.data(), box_off.size());
+    if (e == hipSuccess) e = plan_upload(p, &prm, perm.data(), tile.n_far ? (size_t)N : 1);
+    if (e == hipSuccess) e = plan_upload(p, &moff, w_off.data(), w_off.size());
+    tile.word = wrd;
+    tile.row_tile = rtl;
+    tile.word_off = woff;
+    tile.w_off = moff;
+    tile.perm = prm;
+    p.itm.box_off = boff;
+    // what every call rebuilds: tables of the surface, masks and lists of the items
+    const size_t EK = (size_t)n_envs * K, ENW = (size_t)n_envs * tile.NW;
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.feat, (size_t)N * 64);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.dec, (size_t)N * 64);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.max8, (size_t)tile.NW * 512);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.max32, (size_t)tile.NW * 128);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.scale, 8);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.w3t, 4096);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.w4t, 4096);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.w, (size_t)matrix_units);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.mask, ENW);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.umax, ENW);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.n_act, EK);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.live, EK);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.live_cnt, (size_t)K);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.pool, EK * 64);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.c4, EK * 64);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.alist, tile.n_far ? (size_t)n_envs * N : 1);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.abox, 2 * (size_t)n_envs * p.itm.NB);
+
+    // adjoint scratch, one slice per persistent workgroup
     const size_t G = (size_t)p.cu_count * 8;  // enough for any occupancy override
     p.scr.n_max = n_max;
     if (e == hipSuccess) e = plan_alloc(p, &p.scr.uhat_node, G * 3 * n_max);
@@ -460,19 +570,7 @@ etac_status etac_step(etac_plan *plan, const etac_scene *scene, const etac_model
 
 etac_status etac_step_static(etac_plan *plan, const etac_scene *scene, const etac_model *model, float *u,
                              int8_t *contact_obj, int32_t *n_active, void *saved, void *stream) {
-    if (!plan) return ETAC_ERR_NULL;
-    etac_status st = check_scene(plan->p, scene);
-    if (st != ETAC_OK) return st;
-    st = check_model(model);
-    if (st != ETAC_OK) return st;
-    if (scene->n_envs > 0 && (!u || !contact_obj || !n_active)) return ETAC_ERR_NULL;
-    // one workgroup's slice plus the counters must fit the array
-    if (etac::static_scratch_per_wg(plan->p.n_max) + 256 > etac::kStaticScratchBytes) return ETAC_ERR_SHAPE;
-    const etac::SceneDev sd = scene_dev(scene);
-    const hipError_t e = etac::launch_step_static(plan->p, sd, model_dev(model), u, contact_obj, n_active,
-                                                  static_cast<uint32_t *>(saved), (hipStream_t)stream);
-    if (e == hipErrorNotInitialized) return ETAC_ERR_WORKSPACE;
-    return e == hipSuccess ? ETAC_OK : hip_fail(e);
+    return etac_step(plan, scene, model, u, contact_obj, n_active, saved, stream);
 }
 
 etac_status etac_contact_backward(etac_plan *plan, const etac_scene *scene, const float *grad_uhat,

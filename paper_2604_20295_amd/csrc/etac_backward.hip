@@ -175,12 +175,6 @@ struct BwdLds {
     ItemBatch batch;
 };
 
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Transposed weight fragments for the adjoint layers, in the chain order of
 // etac_device.h (K step s, lane group q, element e <-> output chain_k(s, q, e)),
 // scaled by 2^s2t and 2^s4t, and W5 scaled by 2^c5t (after stage_net).

@@ -247,6 +247,12 @@ __device__ __forceinline__ unsigned cull_objects(const SceneDev &S, const MeshDe
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Values that are equal across the workgroup but come from LDS must be made
 // visibly uniform before they steer control flow that contains barriers:
 // otherwise the compiler treats the branch as divergent and may split a wave
@@ -629,13 +635,15 @@ __device__ __forceinline__ int chain_k(int s, int q, int e) { return 16 * (2 * s
 // Per-launch quantities of the range scaling (whole workgroup; the caller
 // brackets it with barriers).  Wave w takes rows (or columns) 16 w + (l & 15);
 // lane group q = l >> 4 sums a quarter of each, the quarters are added with
-// two shuffles and the wave's largest sum goes to L.part.
-__device__ void net_norms(NetLds &L, const float *phi) {
+// two shuffles and the wave's largest sum goes to part.
+__device__ void net_norms(float (&part)[kWaves][64], const float *phi) {
     const int lane = lane_id(), wave = threadIdx.x >> 6, q = lane >> 4;
     const int r = 16 * wave + (lane & 15);
     float s1 = 0.0f, s2 = 0.0f, s4 = 0.0f, t2 = 0.0f, t4 = 0.0f, t5 = 0.0f;
     float m2 = 0.0f, m4 = 0.0f, mb1 = 0.0f, mb2 = 0.0f;
-    for (int c = 16 * q; c < 16 * q + 16; ++c) {
+#pragma unroll
+    for (int d = 0; d < 16; ++d) {      // unrolled: every load in flight at once
+        const int c = 16 * q + d;
         const float a = fabsf(phi[kW2 + r * 64 + c]), b = fabsf(phi[kW4 + r * 128 + c]);
         s2 += a; s4 += b;
         m2 = fmaxf(m2, a); m4 = fmaxf(m4, b);
@@ -657,8 +665,16 @@ __device__ void net_norms(NetLds &L, const float *phi) {
 #pragma unroll
     for (int j = 0; j < 10; ++j) {
         v[j] = wave_max(v[j]);
-        L.part[wave][j] = v[j];      // identical in every lane
+        part[wave][j] = v[j];      // identical in every lane
     }
+}
+
+// Scale exponents of W1, W2 and W4[:, :64] from the largest norms (see
+// stage_net).
+__device__ __forceinline__ void net_scales(const float (&v)[10], int &s1, int &s2, int &s4) {
+    s1 = range_exp((v[0] + 2.0f * v[8]) * kTop);
+    s2 = range_exp((v[1] * kTop + 2.0f * v[9] * kTop * pow2(s1)));
+    s4 = range_exp(v[7]);
 }
 
 // Stage the network into LDS in fragment order (whole workgroup), each
@@ -672,7 +688,7 @@ __device__ void net_norms(NetLds &L, const float *phi) {
 // Ends with a barrier.
 __device__ void stage_net(NetLds &L, const float *phi) {
     const int tid = threadIdx.x;
-    net_norms(L, phi);
+    net_norms(L.part, phi);
     __syncthreads();
     float v[10];
 #pragma unroll
@@ -680,11 +696,9 @@ __device__ void stage_net(NetLds &L, const float *phi) {
         v[j] = L.part[0][j];
         for (int w = 1; w < kWaves; ++w) v[j] = fmaxf(v[j], L.part[w][j]);
     }
-    const float n1 = v[0], n2 = v[1], n4t = v[4], n2t = v[3], n5t = v[5];
-    const float mw2 = v[6], mw4 = v[7], mb1 = v[8], mb2 = v[9];
-    const int s1 = range_exp((n1 + 2.0f * mb1) * kTop);
-    const int s2 = range_exp((n2 * kTop + 2.0f * mb2 * kTop * pow2(s1)));
-    const int s4 = range_exp(mw4);
+    const float n4t = v[4], n2t = v[3], n5t = v[5], mw2 = v[6];
+    int s1, s2, s4;
+    net_scales(v, s1, s2, s4);
     const float e1 = pow2(s1), e2 = pow2(s2), e4 = pow2(s4);
     for (int idx = tid; idx < 4 * 64; idx += kWG) {
         const int lane = idx & 63, ot = idx >> 6, q = lane >> 4;

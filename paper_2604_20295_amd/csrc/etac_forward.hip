@@ -1,16 +1,27 @@
 // Forward kernels of the ETac step on gfx950:
-//   k_contact : contact pass alone, one workgroup per env (HBM-write bound)
-//   k_step    : persistent fused contact + propagation, one (env, patch) item
-//               at a time per workgroup, items taken from a device work queue
-//               in longest-patch-first order.  The same kernel, templated,
-//               propagates given contact results (etac_propagate).
-#include <mutex>
+//   k_contact       : contact pass alone, one workgroup per env (HBM-write bound)
+// and the step, four launches over (env, patch) items:
+//   k_tables        : what the model gives on the undeformed surface, the same
+//                     for every env: encoder features of passive nodes and
+//                     their decoder part, and the decay matrices of Eq. 1
+//   k_contact_items : contact of every node (or given contact results): winners,
+//                     u_hat, and a bit per node for the kernels that follow
+//                     (one launch with k_tables on small batches: k_front)
+//   k_live          : the envs in contact on each patch
+//   k_pool          : max-pool and global MLP of the items in contact
+//   k_prop_wide / k_prop_narrow / k_prop_far : U of their passive nodes
+//
+// Passive nodes have U_hat = 0, so the network's encoder sees only the
+// geometry there: its features are computed once per call and node instead of
+// once per env, and with them W4[:, :64] f.  What is left per env and passive
+// node is an addition, a ReLU and W5.  The decay weights exp(-alpha d) of a
+// patch do not depend on the env either: Eq. 1 over the envs in contact is the
+// product of a patch matrix with their u_hat columns, on the matrix cores.
+#include <algorithm>
 
 #include "etac_device.h"
 
 namespace etac {
-
-constexpr int kChunk = 1024;      // active nodes staged in LDS per pass of the decay loop
 
 // ---------------------------------------------------------------------------
 // contact pass alone
@@ -98,486 +109,1473 @@ hipError_t launch_contact_rows(const Plan &p, const SceneDev &s, int8_t *cobj, f
 }
 
 // ---------------------------------------------------------------------------
-// persistent fused step
+// step
 // ---------------------------------------------------------------------------
 struct StepParams {
     MeshDev mesh;
+    TileDev tile;
+    TableDev tab;
+    ItemDev itm;
     SceneDev scene;
     ModelDev model;
-    Scratch scr;
     int E;
-    int n_items;
-    int batch;               // queue positions claimed per atomic
+    int splits;              // workgroups per env of the contact pass
+    int dense;               // 1: every item is listed (no k_live), those without contact are passed over
+    int table_units, matrix_units;
     const int8_t *cobj_in;   // propagate-only: given contact results
     const float *uhat_in;
     float *u;                // [3][E][N]
     int8_t *cobj_out;        // [E][N] (fused step)
-    int32_t *n_active;       // [E][K] (fused step)
+    int32_t *n_active;       // [E][K]
     int32_t *n_touch;        // [E][K] active nodes won by external objects (hand), or null
     uint32_t *saved;         // [E K][kSavedWords] pooling record for the adjoint, or null
 };
 
-struct StepLds {
-    NetLds net;
-    union {
-        struct {
-            float4 act_a[kChunk];    // (px, py, pz, ux) of staged active nodes
-            float2 act_b[kChunk];    // (uy, uz)
-            double part[kWG][6];     // per-thread partial sums of its passive nodes (segment combine)
-        };
-        StageBuf xs;                 // node inputs of the network passes (before the decay)
-    };
-    int wcnt[3][kWaves];
-    ItemBatch batch;
+__device__ __forceinline__ bool step_residual(const StepParams &p) { return p.model.mode != ETAC_DECAY_ONLY; }
+__device__ __forceinline__ bool step_decay(const StepParams &p) { return p.model.mode != ETAC_RESIDUAL_ONLY; }
+
+// Words of patch k, and its count of envs to visit.
+__device__ __forceinline__ int live_count(const StepParams &p, int k) { return p.dense ? p.E : p.itm.live_cnt[k]; }
+__device__ __forceinline__ int live_env(const StepParams &p, int k, int q) {
+    return p.dense ? q : p.itm.live[(size_t)k * p.E + q];
+}
+
+struct ContactLds {
+    int cnt[kMaxPatches];
+    int tcnt[kMaxPatches];
+    unsigned cand[kMaxPatches];
 };
 
-// Work queue: counter[0] hands out batches of kBatch items in queue order
-// (patches by size, largest first; envs within a patch), counter[1] counts
-// finished workgroups; the last workgroup resets both so the next launch (or
-// graph replay) starts from zero without a host-side clear.
-//
-// Every block that only part of the workgroup executes is a whole wave (wave
-// 0, storing identical values), and every item ends at a barrier: a block
-// taken by single lanes next to a barrier lets the compiler thread the other
-// lanes of the wave past it into the barrier, which deadlocks the queue.
-__device__ __forceinline__ void retire(unsigned *counter) {
-    if (threadIdx.x == 0) {
-        __threadfence();
-        const unsigned done = atomicAdd(&counter[1], 1u);
-        if (done == gridDim.x - 1) {
-            atomicExch(&counter[0], 0u);
-            atomicExch(&counter[1], 0u);
-        }
-    }
-}
-
-// Zero deformation for a patch without contact (whole workgroup).
-__device__ __forceinline__ void write_zero_item(const StepParams &p, int e, int base, int n, bool write_cobj) {
-    const size_t EN = (size_t)p.E * p.mesh.N;
-    const size_t row = (size_t)e * p.mesh.N + base;
-    for (int i = threadIdx.x; i < n; i += kWG) {
-        __builtin_nontemporal_store(0.0f, p.u + row + i);
-        __builtin_nontemporal_store(0.0f, p.u + EN + row + i);
-        __builtin_nontemporal_store(0.0f, p.u + 2 * EN + row + i);
-        if (write_cobj) __builtin_nontemporal_store((int8_t)-1, p.cobj_out + row + i);
-    }
-}
-
-// Outputs of the batch's items that no object can reach: U = 0, no contact,
-// m = 0.  Wave w takes items w, w + 4, ...; no barrier is needed.
-__device__ void zero_fill_batch(const StepParams &p, const ItemBatch &B, int b0) {
-    const int batch = p.batch;
+// Contact of env e's words s, s + S, ... : a wave takes a word, a lane a node.
+// Winners and u_hat stream out (0 and -1 where there is no contact), and a bit
+// per node is kept.  Bound by those stores: the same 13 bytes a node as the
+// contact pass alone, plus a word of bits.
+template <bool FROM_INPUT, bool ROWS>
+__device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
     const MeshDev &M = p.mesh;
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    const unsigned long long live = batch_mask(B);
-    const size_t EN = (size_t)p.E * M.N;
-    for (int j = wave; j < batch; j += kWaves) {
-        const int item = b0 + j;
-        if (item >= p.n_items || ((live >> j) & 1ull)) continue;
-        int e, k;
-        queue_item(M, p.E, item, e, k);
-        const int base = M.offset[k], n = M.offset[k + 1] - base;
-        const size_t row = (size_t)e * M.N + base;
-        for (int i = lane; i < n; i += 64) {
-            __builtin_nontemporal_store(0.0f, p.u + row + i);
-            __builtin_nontemporal_store(0.0f, p.u + EN + row + i);
-            __builtin_nontemporal_store(0.0f, p.u + 2 * EN + row + i);
-            __builtin_nontemporal_store((int8_t)-1, p.cobj_out + row + i);
+    const SceneDev &S = p.scene;
+    const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
+    for (int k = threadIdx.x; k < K; k += kWG) {
+        L.cnt[k] = 0;
+        L.tcnt[k] = 0;
+        L.cand[k] = FROM_INPUT ? ~0u : cull_objects(S, M, e, k);
+    }
+    __syncthreads();
+    const bool want_umax = step_residual(p);
+    const int NW = p.tile.NW, step = p.splits * kWaves;
+    int4 next = p.tile.word[min(s * kWaves + wave, NW - 1)];
+    for (int w = s * kWaves + wave; w < NW; w += step) {
+        const int4 inf = next;
+        next = p.tile.word[min(w + step, NW - 1)];
+        const int k = uniform(inf.x), i = uniform(inf.y) + lane;
+        const bool valid = lane < uniform(inf.z);
+        const unsigned c = uniform(L.cand[k]);
+        int best = -1;
+        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+        int8_t id = -1;
+        bool touch = false;
+        if (FROM_INPUT) {
+            if (valid && p.cobj_in[row + i] >= 0) {
+                best = 0;
+                u0 = p.uhat_in[row + i];
+                u1 = p.uhat_in[EN + row + i];
+                u2 = p.uhat_in[2 * EN + row + i];
+            }
+        } else if (c) {
+            if (valid) {
+                const size_t srow = ROWS ? scene_row(S, e, k) : (size_t)e;
+                best = contact_node(S, srow, c, M.pos[i], M.pos[N + i], M.pos[2 * N + i], M.nrm[i], M.nrm[N + i],
+                                    M.nrm[2 * N + i], u0, u1, u2);
+                id = (int8_t)best;
+                if (ROWS && best >= 0) {
+                    touch = S.n_ext && best < S.n_ext[srow];
+                    if (S.src) id = S.src[srow * S.O + best];
+                }
+            }
         }
-        p.n_active[(size_t)e * M.K + k] = 0;
-        if (p.n_touch) p.n_touch[(size_t)e * M.K + k] = 0;
+        if (valid) {
+            if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
+            __builtin_nontemporal_store(u0, p.u + row + i);
+            __builtin_nontemporal_store(u1, p.u + EN + row + i);
+            __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
+        }
+        const unsigned long long act = __ballot(best >= 0);
+        p.itm.mask[(size_t)e * NW + w] = act;             // every lane stores the same value
+        if (act) {                                        // wave-uniform
+            if (want_umax) {
+                const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
+                p.itm.umax[(size_t)e * NW + w] = m;
+                p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
+            }
+            const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
+            if (lane == 0) {
+                atomicAdd(&L.cnt[k], __popcll(act));
+                if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
+            }
+        }
+    }
+    __syncthreads();
+    int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    for (int k = threadIdx.x; k < K; k += kWG) {
+        const size_t it = (size_t)e * K + k;
+        if (p.splits == 1) {
+            na[it] = L.cnt[k];
+            if (ROWS && p.n_touch) p.n_touch[it] = L.tcnt[k];
+        } else if (L.cnt[k]) {        // zeroed by k_tables
+            atomicAdd(&na[it], L.cnt[k]);
+            if (ROWS && p.n_touch && L.tcnt[k]) atomicAdd(&p.n_touch[it], L.tcnt[k]);
+        }
     }
 }
 
-// Residual network over the whole patch: max-pool pass over every node,
-// global MLP, then the decoder pass writing r into `resid` ([3][n_max]) for
-// the passive nodes (plist[0 .. np)), the only ones whose residual is used.
-// The encoder is recomputed in the decoder pass instead of keeping n x 64
-// features.  umax: the largest |u_hat| component of the item's nodes (with
-// the patch's geometry it bounds the network inputs: the range scaling).
-__device__ void residual_item(const StepParams &p, StepLds &S, const GmlpW &gw, int item, int k, int base, int n,
-                              const float *uhn, const int *plist, int np, float *resid, float umax) {
-    NetLds &L = S.net;
-    const int lane = lane_id(), wave = threadIdx.x >> 6, gq = lane >> 4;
-    const int n_max = p.scr.n_max;
-    const ItemScale sc = item_scale(L, item_xbound(p.mesh, k, umax));
-    item_biases(L, sc);    // published by the first stage barrier
-    // max-pool with arg-max (lowest node on ties); f >= 0 beats the initial -1
+template <bool FROM_INPUT, bool ROWS>
+__global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
+    __shared__ ContactLds L;
+    const int e = blockIdx.x / p.splits;
+    contact_env<FROM_INPUT, ROWS>(p, L, e, blockIdx.x - e * p.splits);
+}
+
+// ---------------------------------------------------------------------------
+// tables
+// ---------------------------------------------------------------------------
+struct TableLds {
+    float part[kWaves][64];
+    float bv[kWaves][64];
+};
+
+// Split weight fragments of a 64-input layer (rows `stride` floats apart),
+// straight from the packed parameters into registers.
+__device__ __forceinline__ void load_frag64(const float *w, int stride, float mul, half8 (&h)[4][2], half8 (&l)[4][2]) {
+    const int lane = lane_id(), q = lane >> 4;
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const float *r = w + (size_t)(ot * 16 + (lane & 15)) * stride + 32 * s + 4 * q;
+            floatx4 a, b;
+            __builtin_memcpy(&a, r, 16);
+            __builtin_memcpy(&b, r + 16, 16);
+            const float x[8] = {a[0] * mul, a[1] * mul, a[2] * mul, a[3] * mul,
+                                b[0] * mul, b[1] * mul, b[2] * mul, b[3] * mul};
+            split8(x, h[ot][s], l[ot][s]);
+        }
+}
+
+// Encoder weights of one wave in registers.
+struct EncW {
+    half8 w1h[4], w1l[4], w2h[4][2], w2l[4][2];
+};
+
+__device__ __forceinline__ void load_encoder(const float *phi, int s1, int s2, EncW &W) {
+    const int lane = lane_id(), q = lane >> 4;
+    const float e1 = pow2(s1);
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int in = 8 * q + e;
+            x[e] = in < 9 ? phi[kW1 + (ot * 16 + (lane & 15)) * 9 + (in < 9 ? in : 0)] * e1 : 0.0f;
+        }
+        split8(x, W.w1h[ot], W.w1l[ot]);
+    }
+    load_frag64(phi + kW2, 64, pow2(s2), W.w2h, W.w2l);
+}
+
+// The encoder of NT 16-node tiles from register weights: the MFMA sequence of
+// every accumulator is that of encoder_tile.  b1, b2: scaled biases in LDS.
+template <int NT>
+__device__ __forceinline__ void encode(const EncW &W, const float *b1, const float *b2, const half8 (&xh)[NT],
+                                       const half8 (&xl)[NT], floatx4 (&f)[NT][4]) {
+    const int gq = lane_id() >> 4;
+    floatx4 h1[NT][4];
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+        const floatx4 b = *reinterpret_cast<const floatx4 *>(&b1[ot * 16 + 4 * gq]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) h1[u][ot] = b;
+    }
+#pragma unroll
+    for (int u = 0; u < NT; ++u) {
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xh[u], h1[u][ot]);
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xl[u], h1[u][ot]);
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = relu4(mfma16(W.w1l[ot], xh[u], h1[u][ot]));
+    }
+    half8 bh[NT][2], bl[NT][2];
+#pragma unroll
+    for (int u = 0; u < NT; ++u) split_chain(h1[u], bh[u], bl[u]);
+#pragma unroll
+    for (int ot = 0; ot < 4; ++ot) {
+        const floatx4 b = *reinterpret_cast<const floatx4 *>(&b2[ot * 16 + 4 * gq]);
+#pragma unroll
+        for (int u = 0; u < NT; ++u) f[u][ot] = b;
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int u = 0; u < NT; ++u) {
+#pragma unroll
+            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2h[ot][s], bh[u][s], f[u][ot]);
+#pragma unroll
+            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2h[ot][s], bl[u][s], f[u][ot]);
+#pragma unroll
+            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2l[ot][s], bh[u][s], f[u][ot]);
+        }
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) f[u][ot] = relu4(f[u][ot]);
+}
+
+// Features of the nodes of words w0, w0 + step, ...: a wave takes 16 nodes of
+// the word.  Latency-bound: one dependent chain of three layers per word,
+// spread over as many workgroups as there are words (up to two per CU).
+struct FeatLds {
+    TableLds t;
+    float b1s[64], b2s[64];
+};
+
+__device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
+    const MeshDev &M = p.mesh;
+    const float *phi = p.model.phi;
+    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), gq = lane >> 4, N = M.N;
+    net_norms(L.t.part, phi);
+    __syncthreads();
+    int s1, s2, s4;
+    {
+        float v[10];
+#pragma unroll
+        for (int j = 0; j < 10; ++j) {
+            v[j] = L.t.part[0][j];
+            for (int q = 1; q < kWaves; ++q) v[j] = fmaxf(v[j], L.t.part[q][j]);
+        }
+        net_scales(v, s1, s2, s4);
+        s1 = uniform(s1); s2 = uniform(s2); s4 = uniform(s4);
+    }
+    if (w0 == 0) {
+        if (tid < 64) {   // wave 0, identical values
+            p.tab.scale[0] = s1;
+            p.tab.scale[1] = s2;
+            p.tab.scale[2] = s4;
+        }
+        for (int i = tid; i < 4096; i += kWG) {
+            p.tab.w3t[i] = phi[kW3 + (i & 63) * 64 + (i >> 6)];
+            p.tab.w4t[i] = phi[kW4 + (i & 63) * 128 + 64 + (i >> 6)];
+        }
+    }
+    EncW W;
+    load_encoder(phi, s1, s2, W);
+    for (int w = w0; w < p.tile.NW; w += step) {
+        const int4 inf = p.tile.word[w];
+        const int k = uniform(inf.x), start = uniform(inf.y), cnt = uniform(inf.z);
+        const int ax = uniform(range_exp(fmaxf(M.xbound[k], 1.0f)));
+        const int a1 = s1 + ax, af = s2 + a1;
+        __syncthreads();
+        if (tid < 64) {
+            L.b1s[tid] = phi[kB1 + tid] * pow2(a1);
+            L.b2s[tid] = phi[kB2 + tid] * pow2(af);
+        }
+        __syncthreads();
+        const int j = 16 * wave + (lane & 15);
+        const bool valid = j < cnt;
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+        if (valid && gq == 0) {
+            const float xmul = pow2(ax);
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                x[a] = (M.pos[(size_t)a * N + start + j] - M.origin[3 * k + a]) * xmul;
+                x[3 + a] = M.nrm[(size_t)a * N + start + j] * xmul;
+            }
+        }
+        half8 xh[1], xl[1];
+        split8(x, xh[0], xl[0]);
+        floatx4 f[1][4];
+        encode<1>(W, L.b1s, L.b2s, xh, xl, f);
+        const float fmul = pow2(-af);
+        if (valid)
+#pragma unroll
+            for (int ot = 0; ot < 4; ++ot)
+                *reinterpret_cast<floatx4 *>(p.tab.feat + (size_t)(start + j) * 64 + 16 * ot + 4 * gq) = f[0][ot] * fmul;
+        // largest features of eight nodes, then of the wave's sixteen
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) {
+            floatx4 v = valid ? f[0][ot] * fmul : floatx4{-1.0f, -1.0f, -1.0f, -1.0f};
+#pragma unroll
+            for (int off = 1; off <= 4; off <<= 1)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], __shfl_xor(v[r], off));
+            // the eight lanes of a group hold the same values (identical stores)
+            *reinterpret_cast<floatx4 *>(p.tab.max8 + (size_t)(8 * w + 2 * wave + ((lane >> 3) & 1)) * 64 + 16 * ot + 4 * gq) = v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], __shfl_xor(v[r], 8));
+            *reinterpret_cast<floatx4 *>(&L.t.bv[wave][16 * ot + 4 * gq]) = v;
+        }
+        // W4[:, :64] f: the decoder's part that no env changes
+        half8 fh[2], fl[2], w4h[4][2], w4l[4][2];
+        split_chain(f[0], fh, fl);
+        load_frag64(phi + kW4, 128, pow2(s4), w4h, w4l);
+        floatx4 z[4];
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) {
+            z[ot] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int s = 0; s < 2; ++s) z[ot] = mfma_split(w4h[ot][s], w4l[ot][s], fh[s], fl[s], z[ot]);
+        }
+        const float zmul = pow2(-(s4 + af));
+        if (valid)
+#pragma unroll
+            for (int ot = 0; ot < 4; ++ot)
+                *reinterpret_cast<floatx4 *>(p.tab.dec + (size_t)(start + j) * 64 + 16 * ot + 4 * gq) = z[ot] * zmul;
+        __syncthreads();
+        if (tid < 128) {      // half words 0 and 1: waves 0-1 and 2-3
+            const int h = tid >> 6, c = tid & 63;
+            p.tab.max32[(size_t)(2 * w + h) * 64 + c] = fmaxf(L.t.bv[2 * h][c], L.t.bv[2 * h + 1][c]);
+        }
+    }
+}
+
+// Decay matrices.  W = exp(-alpha |p_j - p_i|) of a near patch as three BF16
+// parts whose sum is the FP32 value (24 bits: RNE of the value and of the two
+// exact remainders), in the order the matrix cores take as A operand: row tile
+// t (16 nodes i), K step s (32 nodes j), part c, lane l: row 16 t + (l & 15),
+// columns 32 s + 8 (l >> 4) + 0..7 at 16-byte unit ((t KS + s) 3 + c) 64 + l.
+// Entries beyond the patch are 0.  A workgroup takes a row tile, its waves the
+// K steps in turn.  The exponent keeps the remainders of the root and of the
+// product, so a weight is good to the rounding of v_exp_f32.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+// x = b0 + b1 + b2 for eight values (24 bits; exact unless a part underflows).
+__device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&b)[3]) {
+    uint4t o[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        floatx2 v = {x[2 * e], x[2 * e + 1]};
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+            o[c][e] = h;
+            if (c < 2) {
+                v[0] -= __uint_as_float(h << 16);
+                v[1] -= __uint_as_float(h & 0xffff0000u);
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) b[c] = __builtin_bit_cast(bf16x8, o[c]);
+}
+
+__device__ __forceinline__ float decay_weight(float dx, float dy, float dz, float nb_hi, float nb_lo) {
+    const float s = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float d = __builtin_amdgcn_sqrtf(s);
+    // d + dl is the root of s: dl = (s - d^2) / (2 d)
+    const float dl = d > 0.0f ? 0.5f * fmaf(-d, d, s) * __builtin_amdgcn_rcpf(d) : 0.0f;
+    const float t = nb_hi * d;
+    const float tl = fmaf(nb_hi, d, -t) + fmaf(nb_lo, d, nb_hi * dl);
+    const float w = __builtin_amdgcn_exp2f(t);
+    return fmaf(w, 0.69314718f * tl, w);
+}
+
+// -alpha log2(e) as a sum of two floats.
+__device__ __forceinline__ void decay_rate(float alpha, float &hi, float &lo) {
+    const double b = -(double)alpha * 1.4426950408889634;
+    hi = (float)b;
+    lo = (float)(b - (double)hi);
+}
+
+__device__ void matrix_row_tile(const StepParams &p, int unit) {
+    const MeshDev &M = p.mesh;
+    const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), N = M.N;
+    const int2 rt = p.tile.row_tile[unit];
+    const int k = uniform(rt.x);
+    unit = uniform(rt.y);
+    const int base = M.offset[k], n = M.offset[k + 1] - base, KS = (n + 31) >> 5;
+    float hi, lo;
+    decay_rate(p.model.alpha[k], hi, lo);
+    const int i = 16 * unit + (lane & 15);
+    const int gi = base + min(i, n - 1);
+    const float px = M.pos[gi], py = M.pos[N + gi], pz = M.pos[2 * N + gi];
+    uint4 *w = p.tab.w + p.tile.w_off[k] + (size_t)unit * KS * 3 * 64 + lane;
+    for (int s = wave; s < KS; s += kWaves) {
+        const int j0 = 32 * s + 8 * (lane >> 4);
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int gj = base + min(j0 + e, n - 1);
+            const float v = decay_weight(M.pos[gj] - px, M.pos[N + gj] - py, M.pos[2 * N + gj] - pz, hi, lo);
+            x[e] = (i < n && j0 + e < n) ? v : 0.0f;
+        }
+        bf16x8 b[3];
+        split_bf16x3(x, b);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) w[(size_t)(s * 3 + c) * 64] = __builtin_bit_cast(uint4, b[c]);
+    }
+}
+
+__device__ __forceinline__ void table_block(const StepParams &p, FeatLds &L, int b) {
+    if (b < p.table_units) table_words(p, L, b, p.table_units);
+    else matrix_row_tile(p, b - p.table_units);
+}
+
+// Tables, and zero counts where the contact pass adds to them.
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_tables(StepParams p) {
+    __shared__ FeatLds L;
+    const int nt = p.table_units + p.matrix_units;
+    if (p.splits > 1) {
+        int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+        for (size_t i = (size_t)blockIdx.x * kWG + threadIdx.x; i < (size_t)p.E * p.mesh.K; i += (size_t)gridDim.x * kWG) {
+            na[i] = 0;
+            if (p.n_touch) p.n_touch[i] = 0;
+        }
+    }
+    if ((int)blockIdx.x < nt) table_block(p, L, blockIdx.x);
+}
+
+// Tables and contact in one launch: on small batches neither fills the chip
+// and a launch costs as much as either.
+template <bool FROM_INPUT, bool ROWS>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_front(StepParams p) {
+    __shared__ union {
+        FeatLds feat;
+        ContactLds contact;
+    } L;
+    const int nt = p.table_units + p.matrix_units;
+    if ((int)blockIdx.x < nt) table_block(p, L.feat, blockIdx.x);
+    else contact_env<FROM_INPUT, ROWS>(p, L.contact, blockIdx.x - nt, 0);
+}
+
+// Envs in contact on patch blockIdx.x, ascending.
+__global__ __launch_bounds__(1024) void k_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt) {
+    __shared__ int wsum[16];
+    const int k = blockIdx.x, wave = threadIdx.x >> 6;
+    int run = 0;   // identical in every thread
+    for (int e0 = 0; e0 < E; e0 += 1024) {
+        const int e = e0 + threadIdx.x;
+        const bool f = e < E && n_active[(size_t)e * K + k] > 0;
+        const unsigned long long bal = __ballot(f);
+        __syncthreads();   // the previous round's reads are done
+        wsum[wave] = __popcll(bal);
+        __syncthreads();
+        int off = run, tot = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wave) off += wsum[w];
+            tot += wsum[w];
+        }
+        if (f) live[(size_t)k * E + off + lanes_below(bal)] = e;
+        run += uniform(tot);
+    }
+    if (threadIdx.x < 64) live_cnt[k] = run;     // identical stores
+}
+
+// ---------------------------------------------------------------------------
+// max-pool and global MLP of the items in contact
+// ---------------------------------------------------------------------------
+
+// Units of the live lists: first unit of every patch (in queue order, largest
+// patch first) given `per(k)` units each.  Whole workgroup of NW waves; ends
+// with a barrier.  Returns the total.
+template <int NWV, typename F>
+__device__ int unit_prefix(int K, int *first, F per) {
+    // K is small (16 on a hand): one wave scans 64 patches at a time
+    if (threadIdx.x < 64) {
+        int run = 0;
+        for (int k0 = 0; k0 < K; k0 += 64) {
+            const int kk = k0 + lane_id();
+            const int c = kk < K ? per(kk) : 0;
+            int inc = c;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int o = __shfl_up(inc, off);
+                if (lane_id() >= off) inc += o;
+            }
+            if (kk < K) first[kk] = run + inc - c;
+            run += uniform(__shfl(inc, 63));
+        }
+        first[K] = run;     // identical stores
+    }
+    __syncthreads();
+    return uniform(first[K]);
+}
+
+// Queue position (patch rank) of unit u: the last rank whose first unit is <= u.
+__device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
+    int lo = 0, hi = K - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (first[mid] <= u) lo = mid;
+        else hi = mid - 1;
+    }
+    return uniform(lo);
+}
+
+// Global MLP of an item from its pooled feature (lane c holds channel c):
+// g' = relu(W3 g + b3), c4 = W4[:, 64:] g' + b4, lane o forms row o as four
+// partial sums of 16 terms in order.
+__device__ __forceinline__ float matvec64(const float *wt, float x, float bias) {
+    float s = bias;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        float a = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            a += wt[(16 * q + c) * 64 + lane_id()] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16 * q + c));
+        s += a;
+    }
+    return s;
+}
+
+// A pooled candidate: feature bits over the complement of the node, so that
+// the larger key is the larger feature, the lowest node on ties (features are
+// not negative).
+__device__ __forceinline__ unsigned long long pool_key(float v, int node) {
+    return ((unsigned long long)__float_as_uint(v) << 32) | (unsigned)~node;
+}
+
+// Words [w0, w0 + cw) of an item, at most PCW.
+template <int PCW>
+struct PassiveLds {
+    uint16_t code[PCW * 56];       // at most seven single nodes per eight
+};
+
+// Largest feature of the passive nodes among `words` words from word wf of the
+// item, lane c on channel c; 0 without any.  Eight or thirty-two consecutive
+// passive nodes take one read of the table of their maxima, so a contact
+// patch's surroundings cost about a seventh of their nodes' reads.  The reads
+// are listed first, then issued sixteen at a time; the winner's node is looked
+// up at the end.
+template <int PCW>
+__device__ unsigned long long pool_passive(const StepParams &p, PassiveLds<PCW> &L, int base, int n, int w0, int wf,
+                                           int words, const unsigned long long *mask) {
+    const int lane = lane_id();
+    constexpr int OPL = PCW * 8 / 64 > 0 ? PCW * 8 / 64 : 1;      // octets per lane
+    // this lane's octets
+    unsigned pas[OPL];
+    int kind[OPL], cnt = 0;
+#pragma unroll
+    for (int t = 0; t < OPL; ++t) {
+        const int o = lane * OPL + t, w = o >> 3;
+        pas[t] = 0;
+        kind[t] = 0;
+        if (w >= words) continue;
+        const int left = n - 64 * (wf + w);            // nodes of the word (and beyond)
+        const unsigned long long all = left >= 64 ? ~0ull : (1ull << left) - 1ull;
+        const unsigned long long pw = all & ~mask[wf + w];
+        const unsigned half = (unsigned)(pw >> (32 * ((o >> 2) & 1)));
+        pas[t] = (unsigned)(pw >> (8 * (o & 7))) & 0xffu;
+        if (half == ~0u) kind[t] = (o & 3) == 0 ? 2 : 3;         // 3: its half word's first octet reads for it
+        else if (pas[t] == 0xffu) kind[t] = 1;
+        cnt += kind[t] == 3 ? 0 : (kind[t] ? 1 : __popc(pas[t]));
+    }
+    int at = cnt;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(at, off);
+        if (lane >= off) at += o;
+    }
+    const int total = uniform(__shfl(at, 63));
+    at -= cnt;
+    if (total == 0) return 0ull;
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < OPL; ++t) {
+        const int n0 = 8 * (lane * OPL + t);
+        if (kind[t] == 1 || kind[t] == 2) L.code[at++] = (uint16_t)(n0 | (kind[t] << 12));
+        else if (kind[t] == 0)
+            for (unsigned b = pas[t]; b; b &= b - 1) L.code[at++] = (uint16_t)(n0 + __ffs(b) - 1);
+    }
+    wave_sync();
+    const float *feat = p.tab.feat + (size_t)(base + 64 * wf) * 64 + lane;
+    const float *m8 = p.tab.max8 + (size_t)8 * (w0 + wf) * 64 + lane, *m32 = p.tab.max32 + (size_t)2 * (w0 + wf) * 64 + lane;
+    float best = -1.0f;
+    int bc = 0;
+    for (int i = 0; i < total; i += 16) {
+        int c[16];
+        float v[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) c[t] = uniform((int)L.code[min(i + t, total - 1)]);
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            const int node = c[t] & 0xfff;
+            const float *src = c[t] >> 13 ? m32 + (size_t)(node >> 5) * 64
+                                          : (c[t] >> 12 ? m8 + (size_t)(node >> 3) * 64 : feat + (size_t)node * 64);
+            v[t] = *src;
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t)
+            if (v[t] > best) { best = v[t]; bc = c[t]; }
+    }
+    // the first node of the winning run with that value
+    int node = bc & 0xfff;
+    if (bc >> 13) {
+        float v[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = m8[(size_t)((node >> 3) + t) * 64];
+        int f = 3;
+#pragma unroll
+        for (int t = 2; t >= 0; --t) f = v[t] == best ? t : f;
+        node += 8 * f;
+    }
+    if (bc >> 12) {
+        float v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = feat[(size_t)(node + t) * 64];
+        int f = 7;
+#pragma unroll
+        for (int t = 6; t >= 0; --t) f = v[t] == best ? t : f;
+        node += f;
+    }
+    return pool_key(best, 64 * wf + node);
+}
+
+// Words of an active chunk.
+constexpr int kActiveWords = 4;
+
+struct ActiveLds {
+    float b1s[64], b2s[64];
+    float v[64];
+    int ix[64];
+    uint8_t slot[64 * kActiveWords];
+};
+
+// Largest feature of the active nodes among `words` words from word wf of the
+// item: its active nodes in order, 32 at a time through the encoder on the
+// matrix cores, weights in registers.  One wave; lane c returns channel c.
+__device__ unsigned long long pool_active(const StepParams &p, ActiveLds &L, const EncW &W, float rb1, float rb2, int s1,
+                                          int s2, int k, int e, int base, int nw, int w0, int wf, int words) {
+    const MeshDev &M = p.mesh;
+    const int N = M.N, lane = lane_id(), gq = lane >> 4;
+    const size_t EN = (size_t)p.E * N;
+    const unsigned long long *mask = p.itm.mask + (size_t)e * p.tile.NW + w0;
+    const float *um = p.itm.umax + (size_t)e * p.tile.NW + w0;
+    int total = 0;
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < kActiveWords; ++t) {
+        if (t >= words) break;
+        const unsigned long long m = mask[wf + t];
+        const unsigned long long act = ((unsigned long long)uniform((unsigned)(m >> 32)) << 32) | uniform((unsigned)m);
+        if ((act >> lane) & 1ull) L.slot[total + lanes_below(act)] = (uint8_t)(64 * t + lane);
+        total += __popcll(act);
+    }
+    if (total == 0) return 0ull;
+    float umax = 0.0f;
+    for (int w = lane; w < nw; w += 64)
+        if (mask[w]) umax = fmaxf(umax, um[w]);
+    umax = wave_max(umax);
+    const int ax = uniform(range_exp(fmaxf(item_xbound(M, k, umax), 1.0f)));
+    const int a1 = s1 + ax, af = s2 + a1;
+    const float xmul = pow2(ax);
+    L.b1s[lane] = rb1 * pow2(a1);
+    L.b2s[lane] = rb2 * pow2(af);
+    wave_sync();
+    const float o0 = M.origin[3 * k], o1 = M.origin[3 * k + 1], o2 = M.origin[3 * k + 2];
     floatx4 mx[4];
     int mi[4][4];
-    #pragma unroll
+#pragma unroll
     for (int ot = 0; ot < 4; ++ot)
-        #pragma unroll
+#pragma unroll
         for (int r = 0; r < 4; ++r) { mx[ot][r] = -1.0f; mi[ot][r] = 0x7fffffff; }
-    for (int c0 = 0; c0 < n; c0 += kStage) {
-        const int cnt = min(kStage, n - c0);
-        __syncthreads();
-        stage_nodes(p.mesh, k, base, nullptr, c0, cnt, uhn, n_max, 0, sc.xmul, sc.xmul, S.xs);
-        __syncthreads();
-        // two tiles per wave step (t and t + kWaves); the second may be padding
-        const int ntl = (cnt + 15) >> 4;
-        for (int t = wave; t < ntl; t += 2 * kWaves) {
-            bool valid[2];
-            half8 xh[2], xl[2];
+    for (int t0 = 0; t0 < total; t0 += 32) {
+        half8 xh[2], xl[2];
+        int node[2];
+        bool valid[2];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int lj = (t + u * kWaves) * 16 + (lane & 15);
-                valid[u] = lj < cnt;
-                stage_x<false>(S.xs, valid[u] ? lj : 0, valid[u], xh[u], xl[u]);
-            }
-            floatx4 f[2][4];
-            encoder_tile2(L, xh, xl, f);
-            // a lane meets its nodes in increasing order (tile t before t + kWaves)
+        for (int u = 0; u < 2; ++u) {
+            const int j = t0 + 16 * u + (lane & 15);
+            valid[u] = j < total;
+            node[u] = 64 * wf + (valid[u] ? L.slot[j] : 0);
+            float x[8];
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int node = c0 + (t + u * kWaves) * 16 + (lane & 15);
-                if (valid[u])
-                    #pragma unroll
-                    for (int ot = 0; ot < 4; ++ot)
-                        #pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (f[u][ot][r] > mx[ot][r]) { mx[ot][r] = f[u][ot][r]; mi[ot][r] = node; }
+            for (int c = 0; c < 8; ++c) x[c] = 0.0f;
+            const int g = base + node[u];
+            const float *uh = p.u + (size_t)e * N + g;
+            if (valid[u] && gq == 0) {
+                x[0] = (M.pos[g] - o0) * xmul;
+                x[1] = (M.pos[N + g] - o1) * xmul;
+                x[2] = (M.pos[2 * N + g] - o2) * xmul;
+                x[3] = M.nrm[g] * xmul;
+                x[4] = M.nrm[N + g] * xmul;
+                x[5] = M.nrm[2 * N + g] * xmul;
+                x[6] = uh[0] * xmul;
+                x[7] = uh[EN] * xmul;
+            } else if (valid[u] && gq == 1) {
+                x[0] = uh[2 * EN] * xmul;
             }
+            split8(x, xh[u], xl[u]);
         }
+        floatx4 f[2][4];
+        encode<2>(W, L.b1s, L.b2s, xh, xl, f);
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+            if (valid[u])
+#pragma unroll
+                for (int ot = 0; ot < 4; ++ot)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (f[u][ot][r] > mx[ot][r]) { mx[ot][r] = f[u][ot][r]; mi[ot][r] = node[u]; }
     }
-    #pragma unroll
+    // over the 16 nodes of a row; lowest node on ties
+#pragma unroll
     for (int ot = 0; ot < 4; ++ot)
-        #pragma unroll
+#pragma unroll
         for (int r = 0; r < 4; ++r) {
             float v = mx[ot][r];
             int ix = mi[ot][r];
-            #pragma unroll
+#pragma unroll
             for (int off = 1; off <= 8; off <<= 1) {
                 const float v2 = __shfl_xor(v, off);
                 const int i2 = __shfl_xor(ix, off);
                 if (v2 > v || (v2 == v && i2 < ix)) { v = v2; ix = i2; }
             }
-            mx[ot][r] = v;
-            mi[ot][r] = ix;
+            L.v[ot * 16 + 4 * gq + r] = v;      // identical in the row's lanes
+            L.ix[ot * 16 + 4 * gq + r] = ix;
         }
-    // the per-wave arg-maxes go to the node stage, free once every wave is done with it
-    __syncthreads();
-    int (*ipart)[64] = reinterpret_cast<int (*)[64]>(&S.xs[0][0]);
-    // after the row reduction all 16 lanes of a row hold the same values (identical stores)
-        #pragma unroll
-        for (int ot = 0; ot < 4; ++ot)
-            #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                L.part[wave][ot * 16 + 4 * gq + r] = mx[ot][r];
-                ipart[wave][ot * 16 + 4 * gq + r] = mi[ot][r];
-            }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const int c = threadIdx.x;
-        float v = L.part[0][c];
-        int ix = ipart[0][c];
-        for (int w = 1; w < kWaves; ++w) {
-            const float v2 = L.part[w][c];
-            const int i2 = ipart[w][c];
-            if (v2 > v || (v2 == v && i2 < ix)) { v = v2; ix = i2; }
-        }
-        v *= pow2(-sc.af);    // the pooled feature, unscaled
-        L.g[c] = v;
-        if (p.saved) {
-            uint32_t *rec = p.saved + (size_t)item * kSavedWords;
-            rec[c] = __float_as_uint(v);
-            rec[64 + c] = (uint32_t)ix;
-        }
-    }
-    __syncthreads();
-    global_mlp(L, gw, sc);
-    const float r_mul = pow2(-sc.a4);
-    for (int c0 = 0; c0 < np; c0 += kStage) {
-        const int cnt = min(kStage, np - c0);
-        __syncthreads();
-        stage_nodes(p.mesh, k, base, plist, c0, cnt, nullptr, 0, 0, sc.xmul, 0.0f, S.xs);   // passive: U_hat = 0
-        __syncthreads();
-        // pairs of tiles (t, t + 4) per wave while every wave gets a pair,
-        // then single tiles (the same residuals either way)
-        const int ptl = (cnt + 15) >> 4;
-        int t0 = 0;
-        for (; ptl - t0 >= 2 * kWaves; t0 += 2 * kWaves) {
-            int lj[2];
-            bool valid[2];
-            half8 xh[2], xl[2];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                lj[u] = (t0 + u * kWaves + wave) * 16 + (lane & 15);
-                valid[u] = lj[u] < cnt;     // the chunk's last tile may be ragged
-                stage_x<true>(S.xs, lj[u], valid[u], xh[u], xl[u]);
-            }
-            floatx4 f[2][4];
-            encoder_tile2(L, xh, xl, f);
-            float r[2][3];
-            decoder_tile2(L, f, r_mul, r);
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (valid[u] && gq < 3) resid[gq * n_max + plist[c0 + lj[u]]] = r[u][gq];
-        }
-        for (int t = t0 + wave; t < ptl; t += kWaves) {
-            const int lj = t * 16 + (lane & 15);
-            const bool valid = lj < cnt;
-            half8 xh, xl;
-            stage_x<true>(S.xs, lj, valid, xh, xl);
-            floatx4 h1[4], f[4], h4[4];
-            encoder_tile(L, xh, xl, h1, f);
-            float r[3];
-            decoder_tile(L, f, r_mul, h4, r);
-            if (valid && gq < 3) resid[gq * n_max + plist[c0 + lj]] = r[gq];
-        }
-    }
-    __syncthreads();
+    wave_sync();
+    const unsigned long long key = pool_key(L.v[lane] * pow2(-af), L.ix[lane]);
+    wave_sync();
+    return key;
 }
 
-// Stage active nodes [c0, c0 + cnt) of the item into LDS, positions times
-// sc (|alpha| log2(e): distances then come out in units of the decay's
-// exponent, see decay_range).
-__device__ __forceinline__ void stage_active(const StepParams &p, StepLds &S, int base, const int *alist,
-                                             const float *uhn, int c0, int cnt, float sc) {
+// Pooled feature of an item (lane c on channel c) to its record and through
+// the global MLP.
+__device__ __forceinline__ void pool_finish(const StepParams &p, size_t item, unsigned long long key) {
+    const int lane = lane_id();
+    const float *phi = p.model.phi;
+    const float v = __uint_as_float((unsigned)(key >> 32));
+    if (p.saved) {
+        uint32_t *rec = p.saved + item * kSavedWords;
+        rec[lane] = __float_as_uint(v);
+        rec[64 + lane] = ~(unsigned)key;
+    }
+    const float gp = fmaxf(matvec64(p.tab.w3t, v, phi[kB3 + lane]), 0.0f);
+    p.itm.c4[item * 64 + lane] = matvec64(p.tab.w4t, gp, phi[kB4 + lane]);
+}
+
+// The item of live-list unit q when patch k's lists hold `per` units per env.
+struct ItemRef {
+    int k, e, part;
+};
+
+__device__ __forceinline__ ItemRef item_ref(const StepParams &p, const int *first, int q, int per_words) {
+    const int kk = unit_rank(first, p.mesh.K, q), k = uniform(p.mesh.order[kk]);
+    const int nw = uniform(p.tile.word_off[k + 1]) - uniform(p.tile.word_off[k]);
+    const int per = (nw + per_words - 1) / per_words, local = q - uniform(first[kk]);
+    return ItemRef{k, uniform(live_env(p, k, local / per)), local % per};
+}
+
+__device__ __forceinline__ int item_units(const StepParams &p, const int *first, int words) {
+    return unit_prefix<kWaves>(p.mesh.K, const_cast<int *>(first), [&](int kk) {
+        const int k = p.mesh.order[kk];
+        return live_count(p, k) * ((p.tile.word_off[k + 1] - p.tile.word_off[k] + words - 1) / words);
+    });
+}
+
+// Max-pool over the items in contact, in two launches that raise the items'
+// keys (a maximum: no order matters) and one that finishes them.  Passive
+// nodes need few registers and many waves in flight (reads of the feature
+// tables in L2), active nodes the encoder's weights in registers.
+constexpr int kPassiveWords = 16;
+
+__global__ __launch_bounds__(kWG) void k_pool_passive(StepParams p) {
+    __shared__ int first[kMaxPatches + 1];
+    __shared__ PassiveLds<kPassiveWords> L[kWaves];
+    const int K = p.mesh.K, wave = uniform(threadIdx.x >> 6);
+    const int total = item_units(p, first, kPassiveWords);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
+        const ItemRef it = item_ref(p, first, q, kPassiveWords);
+        const size_t item = (size_t)it.e * K + it.k;
+        if (p.dense && uniform(na[item]) == 0) continue;
+        const int base = uniform(p.mesh.offset[it.k]), n = uniform(p.mesh.offset[it.k + 1]) - base;
+        const int w0 = uniform(p.tile.word_off[it.k]), nw = uniform(p.tile.word_off[it.k + 1]) - w0;
+        const int wf = it.part * kPassiveWords;
+        const unsigned long long key = pool_passive(p, L[wave], base, n, w0, wf, min(kPassiveWords, nw - wf),
+                                                    p.itm.mask + (size_t)it.e * p.tile.NW + w0);
+        if (key) atomicMax(&p.itm.pool[item * 64 + lane_id()], key);
+    }
+}
+
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_pool_active(StepParams p) {
+    __shared__ int first[kMaxPatches + 1];
+    __shared__ ActiveLds L[kWaves];
+    const int K = p.mesh.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const float *phi = p.model.phi;
+    const int total = item_units(p, first, kActiveWords);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    const int s1 = uniform(p.tab.scale[0]), s2 = uniform(p.tab.scale[1]);
+    EncW W;
+    load_encoder(phi, s1, s2, W);
+    const float rb1 = phi[kB1 + lane], rb2 = phi[kB2 + lane];
+    for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
+        const ItemRef it = item_ref(p, first, q, kActiveWords);
+        const size_t item = (size_t)it.e * K + it.k;
+        if (p.dense && uniform(na[item]) == 0) continue;
+        const int base = uniform(p.mesh.offset[it.k]), w0 = uniform(p.tile.word_off[it.k]);
+        const int nw = uniform(p.tile.word_off[it.k + 1]) - w0, wf = it.part * kActiveWords;
+        const unsigned long long key = pool_active(p, L[wave], W, rb1, rb2, s1, s2, it.k, it.e, base, nw, w0, wf,
+                                                   min(kActiveWords, nw - wf));
+        if (key) atomicMax(&p.itm.pool[item * 64 + lane], key);
+    }
+}
+
+__global__ __launch_bounds__(kWG) void k_pool_finish(StepParams p) {
+    __shared__ int first[kMaxPatches + 1];
+    const int K = p.mesh.K, wave = uniform(threadIdx.x >> 6);
+    const int total = item_units(p, first, 1 << 20);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
+        const ItemRef it = item_ref(p, first, q, 1 << 20);
+        const size_t item = (size_t)it.e * K + it.k;
+        if (p.dense && uniform(na[item]) == 0) continue;
+        pool_finish(p, item, p.itm.pool[item * 64 + lane_id()]);
+    }
+}
+
+// The same in one launch, a workgroup of eight waves per item, for batches of
+// few small patches, where a launch costs more than the idle waves.
+constexpr int kPoolWaves = 8;
+
+struct PoolLds {
+    unsigned long long key[64];
+    union {
+        PassiveLds<kActiveWords> pas;
+        ActiveLds act;
+    } w[kPoolWaves];
+};
+
+__global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_pool(StepParams p) {
+    __shared__ PoolLds L;
     const MeshDev &M = p.mesh;
-    const int N = M.N, n_max = p.scr.n_max;
-    for (int t = threadIdx.x; t < cnt; t += kWG) {
-        const int j = alist[c0 + t];
-        const int gj = base + j;
-        S.act_a[t] = make_float4(M.pos[gj] * sc, M.pos[N + gj] * sc, M.pos[2 * N + gj] * sc, uhn[j]);
-        S.act_b[t] = make_float2(uhn[n_max + j], uhn[2 * n_max + j]);
+    const int K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const float *phi = p.model.phi;
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    const int s1 = uniform(p.tab.scale[0]), s2 = uniform(p.tab.scale[1]);
+    EncW W;
+    load_encoder(phi, s1, s2, W);
+    const float rb1 = phi[kB1 + lane], rb2 = phi[kB2 + lane];
+    for (int q = blockIdx.x; q < p.E * K; q += gridDim.x) {
+        const int e = q / K, k = q - e * K;
+        const size_t item = (size_t)q;
+        if (uniform(na[item]) == 0) continue;      // the same in every wave
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
+        const int w0 = uniform(p.tile.word_off[k]), nw = uniform(p.tile.word_off[k + 1]) - w0;
+        const int chunks = (nw + kActiveWords - 1) / kActiveWords;
+        __syncthreads();          // the previous item is done with L
+        if (threadIdx.x < 64) L.key[lane] = 0ull;
+        __syncthreads();
+        for (int t = wave; t < 2 * chunks; t += kPoolWaves) {
+            const int wf = (t >> 1) * kActiveWords, words = min(kActiveWords, nw - wf);
+            const unsigned long long key =
+                (t & 1) ? pool_passive(p, L.w[wave].pas, base, n, w0, wf, words, p.itm.mask + (size_t)e * p.tile.NW + w0)
+                        : pool_active(p, L.w[wave].act, W, rb1, rb2, s1, s2, k, e, base, nw, w0, wf, words);
+            if (key) atomicMax(&L.key[lane], key);
+        }
+        __syncthreads();
+        if (wave == 0) pool_finish(p, item, L.key[lane]);
     }
 }
 
-// Eq. 1 over staged active nodes [lo, hi) for P passive nodes per thread.
-// Positions come scaled by |alpha| log2(e), so a pair's scaled distance d
-// gives its weight exp(-alpha |p_j - p_i|) as 2^-d (2^d for alpha < 0: GROW).
-// FP32 terms are summed in blocks of 32 and the block sums are accumulated
-// in FP64.
-// Runs of 32 staged actives that no valid passive node of the wave can reach
-// within the cutoff are skipped (a run overlaps at most two boxes); cut2 < 0
-// turns the cutoff off.
-template <int P, bool GROW>
-__device__ __forceinline__ void decay_range(const StepLds &S, const float4 *bb, float cut2, int lo, int hi,
-                                            const bool (&v)[P], const float (&px)[P],
-                                            const float (&py)[P], const float (&pz)[P], double (&acc)[P][3]) {
-    for (int j0 = lo; j0 < hi; j0 += 32) {
-        const int j1 = min(hi, j0 + 32);
-        if (cut2 >= 0.0f) {   // uniform: the cutoff is on for this item
-            // [j0, j1) overlaps boxes b0 and b1 (equal when aligned)
-            const int b0 = j0 >> 5, b1 = (j1 - 1) >> 5;
-            const float4 lo0 = bb[2 * b0], hi0 = bb[2 * b0 + 1], lo1 = bb[2 * b1], hi1 = bb[2 * b1 + 1];
-            bool need = false;
+// ---------------------------------------------------------------------------
+// U of the passive nodes: near patches
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ floatx4 mfma_bf16(const bf16x8 &a, const bf16x8 &b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// acc += A B with three-part operands: every product of parts down to 2^-24 of
+// the whole, smallest first.
+__device__ __forceinline__ floatx4 mfma_bf16x3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx4 acc) {
+    acc = mfma_bf16(a[2], b[0], acc);
+    acc = mfma_bf16(a[0], b[2], acc);
+    acc = mfma_bf16(a[1], b[1], acc);
+    acc = mfma_bf16(a[1], b[0], acc);
+    acc = mfma_bf16(a[0], b[1], acc);
+    return mfma_bf16(a[0], b[0], acc);
+}
+
+// Eight consecutive values x[j0 .. j0 + 7] of a patch of n nodes (0 beyond it).
+__device__ __forceinline__ void load8(const float *x, int j0, int n, float (&v)[8]) {
+    if (j0 + 8 <= n) {
+        floatx4 a, b;
+        __builtin_memcpy(&a, x + j0, 16);
+        __builtin_memcpy(&b, x + j0 + 4, 16);
 #pragma unroll
-            for (int a = 0; a < P; ++a)
-                need = need || (v[a] && (box_d2(lo0, hi0, px[a], py[a], pz[a]) < cut2 ||
-                                         box_d2(lo1, hi1, px[a], py[a], pz[a]) < cut2));
-            if (__ballot(need) == 0ull) continue;   // wave-uniform
-        }
-        float sx[P], sy[P], sz[P];
+        for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+    } else {
 #pragma unroll
-        for (int a = 0; a < P; ++a) sx[a] = sy[a] = sz[a] = 0.0f;
-        // the run's bounds are wave-uniform (segments are whole waves): scalar loop control
-        const int je = uniform(j1);
-#pragma unroll 4
-        for (int j = uniform(j0); j < je; ++j) {
-            const float4 pa = S.act_a[j];
-            const float2 pb = S.act_b[j];
-#pragma unroll
-            for (int a = 0; a < P; ++a) {
-                const float dx = pa.x - px[a], dy = pa.y - py[a], dz = pa.z - pz[a];
-                const float d = __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz);
-                const float w = __builtin_amdgcn_exp2f(GROW ? d : -d);
-                sx[a] += w * pa.w; sy[a] += w * pb.x; sz[a] += w * pb.y;
-            }
-        }
-#pragma unroll
-        for (int a = 0; a < P; ++a) { acc[a][0] += sx[a]; acc[a][1] += sy[a]; acc[a][2] += sz[a]; }
+        for (int e = 0; e < 8; ++e) v[e] = j0 + e < n ? x[j0 + e] : 0.0f;
     }
 }
 
-// Passive nodes of one item: U = Omega U_a (Eq. 1) + residual.  Pairs are
-// split over a grid of SLOTS passive slots x (kWG / SLOTS) active segments:
-// every thread owns P passive nodes per pass and one segment of each staged
-// chunk of active nodes; segment partials are combined in segment order.
-// Active nodes are already staged when the item has one chunk.
-template <int SLOTS, int P>
-__device__ void decay_item(const StepParams &p, StepLds &S, int base, int m, int np, const int *alist,
-                           const int *plist, const float *uhn, const float *resid, bool use_dec, bool use_res,
-                           float sc, bool grow, float cut2, size_t row) {
+// Whether a weight of patch k could overflow (alpha < 0 on a wide patch): the
+// matrix then holds infinities, which a product would spread to nodes that
+// have no such pair; such a patch is summed pair by pair.
+__device__ __forceinline__ bool matrix_overflows(const MeshDev &M, float alpha, int k) {
+    return alpha < 0.0f && -alpha * 1.4427f * 2.0f * M.bound[k].w > 120.0f;
+}
+
+// Eq. 1 of one node over the active nodes of its item, pair by pair.
+__device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *src, floatx4 (&s)[3], int x) {
     const MeshDev &M = p.mesh;
-    const int N = M.N, n_max = p.scr.n_max;
+    const int N = M.N, base = M.offset[k], n = M.offset[k + 1] - base;
     const size_t EN = (size_t)p.E * N;
-    constexpr int nseg = kWG / SLOTS;
-    const int slot = threadIdx.x % SLOTS, seg = threadIdx.x / SLOTS;
-    const bool one_chunk = m <= kChunk;
-    const float4 *bb = reinterpret_cast<const float4 *>(&S.net.part[0][0]);   // block boxes (free during the decay)
-    for (int pb = 0; pb < np; pb += P * SLOTS) {
-        bool v[P];
-        int ii[P];
-        float px[P], py[P], pz[P];
-        double acc[P][3];
+    const unsigned long long *mask = p.itm.mask + (size_t)e * p.tile.NW + p.tile.word_off[k];
+    const float *u = src + (size_t)e * N + base;
+    float hi, lo;
+    decay_rate(p.model.alpha[k], hi, lo);
+    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    for (int j = 0; j < n; ++j) {
+        if (!((mask[j >> 6] >> (j & 63)) & 1ull)) continue;
+        const float w = decay_weight(M.pos[base + j] - M.pos[base + i], M.pos[N + base + j] - M.pos[N + base + i],
+                                     M.pos[2 * N + base + j] - M.pos[2 * N + base + i], hi, lo);
+        a0 += w * u[j];
+        a1 += w * u[EN + j];
+        a2 += w * u[2 * EN + j];
+    }
+    // element x of the four (no register indexed at run time)
 #pragma unroll
-        for (int a = 0; a < P; ++a) {
-            const int t = pb + slot + a * SLOTS;
-            v[a] = t < np;
-            ii[a] = v[a] ? plist[t] : 0;
-            const int g = base + ii[a];
-            px[a] = M.pos[g] * sc; py[a] = M.pos[N + g] * sc; pz[a] = M.pos[2 * N + g] * sc;
-            acc[a][0] = acc[a][1] = acc[a][2] = 0.0;
+    for (int t = 0; t < 4; ++t)
+        if (t == x) { s[0][t] = (float)a0; s[1][t] = (float)a1; s[2][t] = (float)a2; }
+}
+
+// Residual of NT envs on the four nodes whose decoder rows z points at, over
+// channels [c0, c1): r += W5 relu(z + c4).
+template <int NT>
+__device__ __forceinline__ void residual_rows(const float (*w5)[64], const float *const (&z)[4],
+                                              const float *const (&c4)[NT], int c0, int c1, floatx4 (&r)[NT][3]) {
+#pragma unroll 2
+    for (int c = c0; c < c1; c += 4) {
+        floatx4 zz[4], w[3];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) zz[x] = *reinterpret_cast<const floatx4 *>(z[x] + c);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) w[a] = *reinterpret_cast<const floatx4 *>(&w5[a][c]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const floatx4 cc = *reinterpret_cast<const floatx4 *>(c4[t] + c);
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const float v = relu1(zz[x][h] + cc[h]);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) r[t][a][x] += w[a][h] * v;
+                }
         }
-        if (use_dec) {
-            if (one_chunk) {
-                const int per = (m + nseg - 1) / nseg, lo = seg * per;
-                if (grow) decay_range<P, true>(S, bb, cut2, lo, min(m, lo + per), v, px, py, pz, acc);
-                else decay_range<P, false>(S, bb, cut2, lo, min(m, lo + per), v, px, py, pz, acc);
-            } else {
-                for (int c0 = 0; c0 < m; c0 += kChunk) {
-                    const int cnt = min(kChunk, m - c0);
-                    __syncthreads();
-                    stage_active(p, S, base, alist, uhn, c0, cnt, sc);
-                    __syncthreads();
-                    if (cut2 >= 0.0f) {
-                        block_boxes(S.act_a, cnt, reinterpret_cast<float4 *>(&S.net.part[0][0]));
-                        __syncthreads();
+    }
+}
+
+// W5 and b5 to LDS (whole workgroup; the caller's next barrier publishes them).
+__device__ __forceinline__ void stage_w5(const StepParams &p, float (*w5)[64], float *b5) {
+    if (!step_residual(p)) return;
+    for (int i = threadIdx.x; i < 192; i += blockDim.x) w5[i >> 6][i & 63] = p.model.phi[kW5 + i];
+    if (threadIdx.x < 64) b5[threadIdx.x & 3] = p.model.phi[kB5 + min((int)(threadIdx.x & 3), 2)];
+}
+
+// U of four consecutive nodes of one env: decay part a, residual r; active
+// nodes (their bits) and rows beyond the patch are left alone.
+__device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, int left, const floatx4 (&a)[3],
+                                           const floatx4 (&r)[3], bool dec, bool res) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        floatx4 v = dec ? a[c] : r[c];
+        if (dec && res) v += r[c];
+        if (act == 0 && left >= 4) {
+            __builtin_memcpy(o + c * EN, &v, 16);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if (x < left && !((act >> x) & 1u)) o[c * EN + x] = v[x];
+        }
+    }
+}
+
+// Where Eq. 1 reads the active nodes' u_hat: the caller's own on given contact
+// results, else the step's output, whose active entries are u_hat.
+__device__ __forceinline__ const float *uhat_source(const StepParams &p) { return p.uhat_in ? p.uhat_in : p.u; }
+
+// Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs (two column
+// tiles per component: column l & 15 is an env).  Per K step a wave issues
+// 36 MT MFMAs on 3 MT A fragments from L2, requested a step ahead, and 18 B
+// fragments from LDS; the B fragments are split once per workgroup, two K steps
+// at a time, while the MFMAs of the previous two run.  Bound by the matrix
+// cores (6 BF16 products per FP32 one) and, in the epilogue, by the VALU.
+constexpr int kWideEnvs = 32;
+
+struct WideLds {
+    int first[kMaxPatches + 1];
+    int env[kWideEnvs];
+    union {
+        bf16x8 b[2][2][6][3][64];     // [buffer][K step][3 column tile + component][part][lane]
+        struct {                      // after the K loop
+            float c4[kWideEnvs][68];
+            float w5[3][64], b5[4];
+        };
+    };
+};
+
+template <int MT>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_prop_wide(StepParams p) {
+    __shared__ WideLds L;
+    constexpr int kRows = 64 * MT;
+    const MeshDev &M = p.mesh;
+    const TileDev &T = p.tile;
+    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6), gq = lane >> 4, col = lane & 15;
+    const size_t EN = (size_t)p.E * N;
+    const bool dec = step_decay(p), res = step_residual(p);
+    const float *src = uhat_source(p);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    const int total = unit_prefix<kWaves>(K, L.first, [&](int kk) {
+        const int k = M.order[kk], n = M.offset[k + 1] - M.offset[k];
+        if (T.w_off[k] < 0) return 0;
+        return ((live_count(p, k) + kWideEnvs - 1) / kWideEnvs) * ((n + kRows - 1) / kRows);
+    });
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
+        const int cnt = uniform(live_count(p, k)), groups = (cnt + kWideEnvs - 1) / kWideEnvs;
+        const int local = q - uniform(L.first[kk]), rb = local / groups, g0 = (local - rb * groups) * kWideEnvs;
+        const int w0 = uniform(T.word_off[k]);
+        __syncthreads();      // the previous unit is done with L
+        if (threadIdx.x < kWideEnvs) {
+            const int e = g0 + threadIdx.x < cnt ? live_env(p, k, g0 + threadIdx.x) : -1;
+            L.env[threadIdx.x] = (e >= 0 && p.dense && na[(size_t)e * K + k] == 0) ? -1 : e;
+        }
+        __syncthreads();
+        int env[2];
+        env[0] = L.env[col];
+        env[1] = L.env[16 + col];
+        const int row0 = rb * kRows + wave * 16 * MT;
+        floatx4 acc[MT][2][3];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        const bool slow = matrix_overflows(M, p.model.alpha[k], k);
+        if (dec && !slow) {
+            // fragment f = 3 wave .. 3 wave + 2 of a pair of K steps: step f / 6, column tile and component f % 6:
+            // this wave's step is wave / 2, its column tile wave % 2, its fragments the three components
+            const int myenv = (wave & 1) ? env[1] : env[0], safe = max(myenv, 0);
+            const float *me = src + (size_t)safe * N + base;
+            const unsigned long long *mymask = p.itm.mask + (size_t)safe * T.NW + w0;
+            float raw[3][8];
+            unsigned bits = 0;
+            auto fetch = [&](int s0) {      // values and bits are requested together
+                const int j0 = 32 * (s0 + (wave >> 1)) + 8 * gq;
+                const bool in = myenv >= 0 && j0 < n;
+                bits = in ? (unsigned)(mymask[j0 >> 6] >> (j0 & 63)) & 0xffu : 0u;
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (in) load8(me + c * EN, j0, n, raw[c]);
+            };
+            auto put = [&](int buf) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    bf16x8 b[3];
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
+                    split_bf16x3(raw[c], b);
+#pragma unroll
+                    for (int y = 0; y < 3; ++y) L.b[buf][wave >> 1][3 * (wave & 1) + c][y][lane] = b[y];
+                }
+            };
+            const uint4 *wa[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const int mt = min((row0 >> 4) + m, ((n + 15) >> 4) - 1);      // rows beyond the patch repeat its last tile
+                wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * 3 * 64 + lane;
+            }
+            uint4 a[2][MT][3];
+            auto fetch_a = [&](int s, uint4 (&x)[MT][3]) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) x[m][c] = wa[m][(size_t)(s * 3 + c) * 64];
+            };
+            auto mul = [&](int buf, int ds, const uint4 (&x)[MT][3]) {
+#pragma unroll
+                for (int f = 0; f < 6; ++f) {
+                    bf16x8 b[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) b[c] = L.b[buf][ds][f][c][lane];
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) {
+                        const bf16x8 y[3] = {__builtin_bit_cast(bf16x8, x[m][0]), __builtin_bit_cast(bf16x8, x[m][1]),
+                                             __builtin_bit_cast(bf16x8, x[m][2])};
+                        acc[m][f / 3][f % 3] = mfma_bf16x3(y, b, acc[m][f / 3][f % 3]);
                     }
-                    const int per = (cnt + nseg - 1) / nseg, lo = seg * per;
-                    if (grow) decay_range<P, true>(S, bb, cut2, lo, min(cnt, lo + per), v, px, py, pz, acc);
-                    else decay_range<P, false>(S, bb, cut2, lo, min(cnt, lo + per), v, px, py, pz, acc);
+                }
+            };
+            fetch(0);
+            fetch_a(0, a[0]);
+            put(0);
+            for (int s0 = 0, buf = 0; s0 < KS; s0 += 2, buf ^= 1) {
+                __syncthreads();          // this pair is in L.b[buf]; the other buffer is free
+                fetch_a(min(s0 + 1, KS - 1), a[1]);
+                if (s0 + 2 < KS) fetch(s0 + 2);
+                mul(buf, 0, a[0]);
+                fetch_a(min(s0 + 2, KS - 1), a[0]);
+                if (s0 + 1 < KS) mul(buf, 1, a[1]);
+                if (s0 + 2 < KS) put(buf ^ 1);
+            }
+        }
+        __syncthreads();      // L.b is done with
+        if (res) {
+            stage_w5(p, L.w5, L.b5);
+            for (int i = threadIdx.x; i < kWideEnvs * 64; i += kWG) {
+                const int e = L.env[i >> 6];
+                L.c4[i >> 6][i & 63] = e >= 0 ? p.itm.c4[((size_t)e * K + k) * 64 + (i & 63)] : 0.0f;
+            }
+        }
+        __syncthreads();
+        // residual and store: this lane holds rows row0 + 16 m + 4 gq + r of two envs
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int i0 = row0 + 16 * m + 4 * gq;
+            floatx4 r[2][3];
+            if (res) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) r[t][c] = floatx4{L.b5[c], L.b5[c], L.b5[c], L.b5[c]};
+                const float *z[4];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) z[x] = p.tab.dec + (size_t)(base + min(i0 + x, n - 1)) * 64;
+                const float *const c4[2] = {L.c4[col], L.c4[16 + col]};
+                residual_rows<2>(L.w5, z, c4, 0, 64, r);
+            }
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int e = env[t];
+                if (e < 0 || i0 >= n) continue;
+                const unsigned act = (unsigned)(p.itm.mask[(size_t)e * T.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
+                if (dec && slow)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if (i0 + x < n) pair_sum(p, k, e, i0 + x, src, acc[m][t], x);
+                store_rows(p.u + (size_t)e * N + base + i0, EN, act, n - i0, acc[m][t], r[t], dec, res);
+            }
+        }
+    }
+}
+
+// Narrow tiles: 16 rows times 16 envs, the K steps split over the workgroup's
+// four waves (each splits its own B fragments, no barrier in the loop), for
+// batches whose wide tiles would leave the chip idle.
+struct NarrowLds {
+    int first[kMaxPatches + 1];
+    float w5[3][64], b5[4];
+    floatx4 part[kWaves][3][64];
+    floatx4 rpart[kWaves][3][64];
+};
+
+__global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
+    __shared__ NarrowLds L;
+    const MeshDev &M = p.mesh;
+    const TileDev &T = p.tile;
+    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6), gq = lane >> 4, col = lane & 15;
+    const size_t EN = (size_t)p.E * N;
+    const bool dec = step_decay(p), res = step_residual(p);
+    const float *src = uhat_source(p);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    const int total = unit_prefix<kWaves>(K, L.first, [&](int kk) {
+        const int k = M.order[kk], n = M.offset[k + 1] - M.offset[k];
+        if (T.w_off[k] < 0) return 0;
+        return ((live_count(p, k) + 15) >> 4) * ((n + 15) >> 4);
+    });
+    stage_w5(p, L.w5, L.b5);
+    __syncthreads();
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
+        const int cnt = uniform(live_count(p, k)), groups = (cnt + 15) >> 4;
+        const int local = q - uniform(L.first[kk]), mt = local / groups, g0 = (local - mt * groups) * 16;
+        const int w0 = uniform(T.word_off[k]);
+        int e = g0 + col < cnt ? live_env(p, k, g0 + col) : -1;
+        if (e >= 0 && p.dense && na[(size_t)e * K + k] == 0) e = -1;
+        if (!__ballot(e >= 0)) continue;      // the same in every wave
+        floatx4 acc[3], r[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            acc[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            r[c] = acc[c];
+        }
+        const bool slow = matrix_overflows(M, p.model.alpha[k], k);
+        if (dec && !slow) {
+            const uint4 *wa = p.tab.w + T.w_off[k] + (size_t)mt * KS * 3 * 64 + lane;
+            const int safe = max(e, 0);
+            const float *me = src + (size_t)safe * N + base;
+            const unsigned long long *mymask = p.itm.mask + (size_t)safe * T.NW + w0;
+            // the next step's operands are requested before this one's are used
+            uint4 a[3];
+            float raw[3][8];
+            unsigned bits = 0;
+            auto fetch = [&](int s) {
+                const int j0 = 32 * s + 8 * gq;
+                const bool in = e >= 0 && j0 < n;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) a[c] = wa[(size_t)(s * 3 + c) * 64];
+                bits = in ? (unsigned)(mymask[j0 >> 6] >> (j0 & 63)) & 0xffu : 0u;
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (in) load8(me + c * EN, j0, n, raw[c]);
+            };
+            if (wave < KS) fetch(wave);
+            for (int s = wave; s < KS; s += kWaves) {
+                bf16x8 b[3][3], y[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    y[c] = __builtin_bit_cast(bf16x8, a[c]);
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
+                    split_bf16x3(raw[c], b[c]);
+                }
+                if (s + kWaves < KS) fetch(s + kWaves);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) acc[c] = mfma_bf16x3(y, b[c], acc[c]);
+            }
+        }
+        const int i0 = 16 * mt + 4 * gq;
+        if (res) {
+            const float *z[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) z[x] = p.tab.dec + (size_t)(base + min(i0 + x, n - 1)) * 64;
+            // columns without an env read their neighbour's row: some column has one
+            const int ee = e >= 0 ? e : uniform(wave_max_int(e));
+            const float *const c4[1] = {p.itm.c4 + ((size_t)ee * K + k) * 64};
+            floatx4 rr[1][3] = {{r[0], r[1], r[2]}};
+            residual_rows<1>(L.w5, z, c4, 16 * wave, 16 * wave + 16, rr);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) r[c] = rr[0][c];
+        }
+        __syncthreads();          // the previous unit is done with L.part
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            L.part[wave][c][lane] = acc[c];
+            L.rpart[wave][c][lane] = r[c];
+        }
+        __syncthreads();
+        if (wave == 0 && e >= 0 && i0 < n) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const float b = res ? L.b5[c] : 0.0f;
+                acc[c] = L.part[0][c][lane];
+                r[c] = L.rpart[0][c][lane] + b;
+                for (int v = 1; v < kWaves; ++v) {
+                    acc[c] += L.part[v][c][lane];
+                    r[c] += L.rpart[v][c][lane];
                 }
             }
-            if (nseg > 1) {
-                __syncthreads();
-                double *mine = S.part[threadIdx.x];
+            const unsigned act = (unsigned)(p.itm.mask[(size_t)e * T.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
+            if (dec && slow)
 #pragma unroll
-                for (int a = 0; a < P; ++a) { mine[3 * a] = acc[a][0]; mine[3 * a + 1] = acc[a][1]; mine[3 * a + 2] = acc[a][2]; }
-                __syncthreads();
-                if (seg == 0)
-                    for (int q = 1; q < nseg; ++q) {
-                        const double *o = S.part[q * SLOTS + slot];
-#pragma unroll
-                        for (int a = 0; a < P; ++a) { acc[a][0] += o[3 * a]; acc[a][1] += o[3 * a + 1]; acc[a][2] += o[3 * a + 2]; }
-                    }
-            }
+                for (int x = 0; x < 4; ++x)
+                    if (i0 + x < n) pair_sum(p, k, e, i0 + x, src, acc, x);
+            store_rows(p.u + (size_t)e * N + base + i0, EN, act, n - i0, acc, r, dec, res);
         }
-        if (seg == 0)
-#pragma unroll
-            for (int a = 0; a < P; ++a)
-                if (v[a]) {
-                    const int i = ii[a];
-                    if (use_res)
-                        for (int c = 0; c < 3; ++c) acc[a][c] += (double)resid[c * n_max + i];
-                    __builtin_nontemporal_store((float)acc[a][0], p.u + row + i);
-                    __builtin_nontemporal_store((float)acc[a][1], p.u + EN + row + i);
-                    __builtin_nontemporal_store((float)acc[a][2], p.u + 2 * EN + row + i);
-                }
     }
 }
 
-// Same shape choice as the adjoint: fewest thread iterations over the
-// np x m pairs, two nodes per thread weighted 1.75.  0..5 = (64|128|256) x (1|2).
-__device__ __forceinline__ int decay_grid_shape(int np, int m) {
-    int best = 5;
-    float bc = 3.0e38f;
-#pragma unroll
-    for (int c = 0; c < 6; ++c) {
-        const int slots = 64 << (c % 3), a = 1 + c / 3, nseg = kWG / slots;
-        const float cost = (float)((np + a * slots - 1) / (a * slots)) * (float)((m + nseg - 1) / nseg) *
-                           (a == 2 ? 1.75f : 1.0f);
-        if (cost < bc) { bc = cost; best = c; }
-    }
-    return best;
-}
+// ---------------------------------------------------------------------------
+// U of the passive nodes: far patches
+// ---------------------------------------------------------------------------
 
-// One item with at least one candidate object (cand: objects that may reach
-// the patch; all bits set when contact results are given).
-template <bool FROM_INPUT>
-__device__ void process_item(const StepParams &p, StepLds &S, const GmlpW &gw, int e, int k, unsigned cand, float *uhn,
-                             float *resid, int *alist, int *plist) {
+// Active nodes of every live far item in the patch's spatial order, with a box
+// per 32 of them.
+__global__ __launch_bounds__(1024) void k_far_list(StepParams p) {
+    __shared__ int first[kMaxPatches + 1];
+    __shared__ int wsum[16];
     const MeshDev &M = p.mesh;
-    const int N = M.N, n_max = p.scr.n_max;
-    const size_t EN = (size_t)p.E * N;
-    const int base = M.offset[k];
-    const int n = M.offset[k + 1] - base;
-    const int mode = p.model.mode;
-    float umax;
-    int touch;
-    const int m = contact_and_compact<FROM_INPUT, true>(M, p.scene, p.E, p.scr.n_max, p.cobj_in, p.uhat_in, p.cobj_out,
-                                                  S.wcnt, e, k, base, n, cand, uhn, alist, plist, nullptr, umax,
-                                                  touch);
-    if (!FROM_INPUT && threadIdx.x < 64) {
-        p.n_active[(size_t)e * M.K + k] = m;
-        if (p.n_touch) p.n_touch[(size_t)e * M.K + k] = touch;
-    }
-    if (m == 0) {
-        write_zero_item(p, e, base, n, false);
-        __syncthreads();
-        return;
-    }
-    const size_t row = (size_t)e * N + base;
-    // active nodes keep their contact displacement
-    for (int t = threadIdx.x; t < m; t += kWG) {
-        const int i = alist[t];
-        __builtin_nontemporal_store(uhn[i], p.u + row + i);
-        __builtin_nontemporal_store(uhn[n_max + i], p.u + EN + row + i);
-        __builtin_nontemporal_store(uhn[2 * n_max + i], p.u + 2 * EN + row + i);
-    }
-    const bool use_res = mode != ETAC_DECAY_ONLY, use_dec = mode != ETAC_RESIDUAL_ONLY;
-    const int np = n - m;
-    if (use_res) residual_item(p, S, gw, e * M.K + k, k, base, n, uhn, plist, np, resid, umax);
-    // exp(-alpha d) = 2^-(alpha log2(e) d): positions are scaled by
-    // sc = |alpha| log2(e), the cutoff D by the same factor (sc D = kCutLog2)
-    const float alpha = p.model.alpha[k];
-    const float sc = (float)(fabs((double)alpha) * 1.4426950408889634);
-    const bool grow = alpha < 0.0f;
-    const float cut2 = cutoff_useful(M, k, cutoff_d2(alpha)) ? kCut2Scaled : -1.0f;   // off: no boxes, no tests
-    if (use_dec && m <= kChunk) {
-        stage_active(p, S, base, alist, uhn, 0, m, sc);
-        __syncthreads();
-        if (cut2 >= 0.0f) {
-            block_boxes(S.act_a, m, reinterpret_cast<float4 *>(&S.net.part[0][0]));
+    const TileDev &T = p.tile;
+    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const int total = unit_prefix<16>(K, first, [&](int kk) { return T.w_off[M.order[kk]] < 0 ? live_count(p, M.order[kk]) : 0; });
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]), e = uniform(live_env(p, k, q - first[kk]));
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
+        const unsigned long long *mask = p.itm.mask + (size_t)e * T.NW + T.word_off[k];
+        int *list = p.itm.alist + (size_t)e * N + base;
+        int run = 0;
+        for (int i0 = 0; i0 < n; i0 += 1024) {
+            const int i = i0 + threadIdx.x;
+            const int node = i < n ? T.perm[base + i] : 0;
+            const bool f = i < n && ((mask[node >> 6] >> (node & 63)) & 1ull);
+            const unsigned long long bal = __ballot(f);
             __syncthreads();
+            wsum[wave] = __popcll(bal);
+            __syncthreads();
+            int off = run, tot = 0;
+            for (int w = 0; w < 16; ++w) {
+                if (w < wave) off += wsum[w];
+                tot += wsum[w];
+            }
+            if (f) list[off + lanes_below(bal)] = node;
+            run += uniform(tot);
+        }
+        __threadfence_block();
+        __syncthreads();
+        float4 *box = p.itm.abox + 2 * ((size_t)e * p.itm.NB + p.itm.box_off[k]);
+        for (int t0 = 0; t0 < run; t0 += 1024) {
+            const int t = t0 + threadIdx.x;
+            const bool ok = t < run;
+            const int g = base + (ok ? list[t] : list[0]);
+            float lx = M.pos[g], ly = M.pos[N + g], lz = M.pos[2 * N + g];
+            float hx = lx, hy = ly, hz = lz;
+            if (!ok) { lx = ly = lz = 3.0e38f; hx = hy = hz = -3.0e38f; }
+#pragma unroll
+            for (int off = 16; off >= 1; off >>= 1) {
+                lx = fminf(lx, __shfl_xor(lx, off)); ly = fminf(ly, __shfl_xor(ly, off)); lz = fminf(lz, __shfl_xor(lz, off));
+                hx = fmaxf(hx, __shfl_xor(hx, off)); hy = fmaxf(hy, __shfl_xor(hy, off)); hz = fmaxf(hz, __shfl_xor(hz, off));
+            }
+            if (ok && (lane & 31) == 0) {
+                box[2 * (t >> 5)] = make_float4(lx, ly, lz, 0.0f);
+                box[2 * (t >> 5) + 1] = make_float4(hx, hy, hz, 0.0f);
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// A workgroup takes 256 nodes of an item in the patch's spatial order, a wave
+// 64 of them (a compact piece of the surface), a lane one node.  Runs of 32
+// active nodes whose box lies beyond the cutoff of the wave's own box are
+// passed over (64 boxes are tested at once, one per lane), the others are
+// staged in LDS and summed pair by pair.
+struct FarLds {
+    int first[kMaxPatches + 1];
+    float w5[3][64], b5[4];
+    float c4[64];
+    float4 a[kWaves][32];
+    float2 b[kWaves][32];
+};
+
+__global__ __launch_bounds__(kWG) void k_prop_far(StepParams p) {
+    __shared__ FarLds L;
+    const MeshDev &M = p.mesh;
+    const TileDev &T = p.tile;
+    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const size_t EN = (size_t)p.E * N;
+    const bool dec = step_decay(p), res = step_residual(p);
+    const float *src = uhat_source(p);
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    const int total = unit_prefix<kWaves>(K, L.first, [&](int kk) {
+        const int k = M.order[kk];
+        return T.w_off[k] < 0 ? live_count(p, k) * ((M.offset[k + 1] - M.offset[k] + kWG - 1) / kWG) : 0;
+    });
+    stage_w5(p, L.w5, L.b5);
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, tiles = (n + kWG - 1) / kWG;
+        const int local = q - uniform(L.first[kk]), e = uniform(live_env(p, k, local / tiles));
+        const size_t item = (size_t)e * K + k;
+        const int m = uniform(na[item]);
+        __syncthreads();      // the previous unit is done with L
+        if (res && threadIdx.x < 64) L.c4[lane] = p.itm.c4[item * 64 + lane];
+        __syncthreads();
+        const int s = (local % tiles) * kWG + wave * 64 + lane;
+        const int node = s < n ? T.perm[base + s] : 0;
+        const bool pas = s < n && m > 0 &&
+                         !((p.itm.mask[(size_t)e * T.NW + T.word_off[k] + (node >> 6)] >> (node & 63)) & 1ull);
+        if (!__ballot(pas)) continue;
+        const int g = base + node;
+        const float px = M.pos[g], py = M.pos[N + g], pz = M.pos[2 * N + g];
+        double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+        if (dec) {
+            const float alpha = p.model.alpha[k], cut2 = cutoff_d2(alpha);
+            float hi, lo;
+            decay_rate(alpha, hi, lo);
+            float lx = pas ? px : 3.0e38f, ly = pas ? py : 3.0e38f, lz = pas ? pz : 3.0e38f;
+            float hx = pas ? px : -3.0e38f, hy = pas ? py : -3.0e38f, hz = pas ? pz : -3.0e38f;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                lx = fminf(lx, __shfl_xor(lx, off)); ly = fminf(ly, __shfl_xor(ly, off)); lz = fminf(lz, __shfl_xor(lz, off));
+                hx = fmaxf(hx, __shfl_xor(hx, off)); hy = fmaxf(hy, __shfl_xor(hy, off)); hz = fmaxf(hz, __shfl_xor(hz, off));
+            }
+            const float4 *box = p.itm.abox + 2 * ((size_t)e * p.itm.NB + p.itm.box_off[k]);
+            const int *list = p.itm.alist + (size_t)e * N + base;
+            const int nb = (m + 31) >> 5;
+            for (int b0 = 0; b0 < nb; b0 += 64) {
+                bool near = false;
+                if (b0 + lane < nb) {
+                    const float4 bl = box[2 * (b0 + lane)], bh = box[2 * (b0 + lane) + 1];
+                    const float dx = fmaxf(fmaxf(bl.x - hx, lx - bh.x), 0.0f);
+                    const float dy = fmaxf(fmaxf(bl.y - hy, ly - bh.y), 0.0f);
+                    const float dz = fmaxf(fmaxf(bl.z - hz, lz - bh.z), 0.0f);
+                    near = !(dx * dx + dy * dy + dz * dz >= cut2);
+                }
+                unsigned long long todo = __ballot(near);
+                while (todo) {
+                    const int b = b0 + __ffsll(todo) - 1;
+                    todo &= todo - 1;
+                    const int c = uniform(min(32, m - 32 * b));
+                    wave_sync();
+                    if (lane < c) {
+                        const int gj = base + list[32 * b + lane];
+                        const float *u = src + (size_t)e * N + gj;
+                        L.a[wave][lane] = make_float4(M.pos[gj], M.pos[N + gj], M.pos[2 * N + gj], u[0]);
+                        L.b[wave][lane] = make_float2(u[EN], u[2 * EN]);
+                    }
+                    wave_sync();
+                    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll 4
+                    for (int j = 0; j < c; ++j) {
+                        const float4 pa = L.a[wave][j];
+                        const float2 pb = L.b[wave][j];
+                        const float dx = pa.x - px, dy = pa.y - py, dz = pa.z - pz;
+                        const float d = __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz);
+                        const float w = __builtin_amdgcn_exp2f(hi * d);
+                        s0 += w * pa.w; s1 += w * pb.x; s2 += w * pb.y;
+                    }
+                    a0 += s0; a1 += s1; a2 += s2;
+                }
+            }
+        }
+        float r0 = 0.0f, r1 = 0.0f, r2 = 0.0f;
+        if (res) {
+            const float *z = p.tab.dec + (size_t)g * 64;
+            r0 = L.b5[0]; r1 = L.b5[1]; r2 = L.b5[2];
+#pragma unroll 4
+            for (int c = 0; c < 64; c += 4) {
+                const floatx4 zz = *reinterpret_cast<const floatx4 *>(z + c);
+                const floatx4 cc = *reinterpret_cast<const floatx4 *>(&L.c4[c]);
+                const floatx4 wx = *reinterpret_cast<const floatx4 *>(&L.w5[0][c]);
+                const floatx4 wy = *reinterpret_cast<const floatx4 *>(&L.w5[1][c]);
+                const floatx4 wz = *reinterpret_cast<const floatx4 *>(&L.w5[2][c]);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {
+                    const float v = relu1(zz[h] + cc[h]);
+                    r0 += wx[h] * v; r1 += wy[h] * v; r2 += wz[h] * v;
+                }
+            }
+        }
+        if (pas) {
+            float *o = p.u + (size_t)e * N + g;
+            o[0] = (float)(a0 + (double)r0);
+            o[EN] = (float)(a1 + (double)r1);
+            o[2 * EN] = (float)(a2 + (double)r2);
         }
     }
-    // with the decay off (residual only) every shape does the same work
-    const int shape = use_dec ? uniform(decay_grid_shape(np, m)) : 5;
-    switch (shape) {
-        case 0: decay_item<64, 1>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-        case 1: decay_item<128, 1>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-        case 2: decay_item<256, 1>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-        case 3: decay_item<64, 2>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-        case 4: decay_item<128, 2>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-        default: decay_item<256, 2>(p, S, base, m, np, alist, plist, uhn, resid, use_dec, use_res, sc, grow, cut2, row); break;
-    }
-    __syncthreads();
 }
 
 template <bool FROM_INPUT>
-__global__ __launch_bounds__(kWG) void k_step(StepParams p) {
-    __shared__ StepLds S;
-    const int wg = blockIdx.x;
-    const int n_max = p.scr.n_max;
-    float *uhn = p.scr.uhat_node + (size_t)wg * 3 * n_max;
-    float *resid = p.scr.resid + (size_t)wg * 3 * n_max;
-    int *alist = p.scr.alist + (size_t)wg * n_max;
-    int *plist = p.scr.plist + (size_t)wg * n_max;
-    GmlpW gw{};   // the global MLP's weights, held in registers across the items
-    if (p.model.mode != ETAC_DECAY_ONLY) {
-        stage_net(S.net, p.model.phi);
-        gw = load_gmlp(p.model.phi);
-        __syncthreads();
+static void launch_contact_items(const StepParams &p, bool merged, int nt, hipStream_t st) {
+    const bool rows = p.scene.rows_per_env != 0;
+    const dim3 grid(merged ? nt + p.E : p.E * p.splits);
+    if (merged) {
+        if (rows) hipLaunchKernelGGL((k_front<FROM_INPUT, true>), grid, dim3(kWG), 0, st, p);
+        else hipLaunchKernelGGL((k_front<FROM_INPUT, false>), grid, dim3(kWG), 0, st, p);
+    } else {
+        if (rows) hipLaunchKernelGGL((k_contact_items<FROM_INPUT, true>), grid, dim3(kWG), 0, st, p);
+        else hipLaunchKernelGGL((k_contact_items<FROM_INPUT, false>), grid, dim3(kWG), 0, st, p);
     }
-    for (;;) {
-        const int b0 = next_batch<FROM_INPUT ? CULL_NONE : CULL_OBJECTS>(p.scr.counter, S.batch, p.mesh, p.scene, p.E,
-                                                                        p.n_items, p.batch);
-        if (b0 >= p.n_items) break;
-        if (!FROM_INPUT) zero_fill_batch(p, S.batch, b0);
-        const int nb = uniform(S.batch.n);
-        for (int q = 0; q < nb; ++q) {
-            const int item = uniform(S.batch.item[q]);
-            int e, k;
-            queue_item(p.mesh, p.E, item, e, k);
-            const unsigned cand = FROM_INPUT ? 0xffffffffu
-                                             : item_cand(p.scene, e, k, uniform((unsigned)S.batch.cand[q]));
-            process_item<FROM_INPUT>(p, S, gw, e, k, cand, uhn, resid, alist, plist);
-        }
-    }
-    retire(p.scr.counter);
 }
 
 hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int n_envs,
@@ -586,13 +1584,13 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     if (n_envs == 0) return hipSuccess;
     StepParams p;
     p.mesh = pl.mesh;
+    p.tile = pl.tile;
+    p.tab = pl.tab;
+    p.itm = pl.itm;
     if (s) p.scene = *s;
     else p.scene = SceneDev{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 1};
     p.model = m;
-    p.scr = pl.scr;
     p.E = n_envs;
-    p.n_items = n_envs * pl.K;
-    p.batch = pl.batch;
     p.cobj_in = cobj_in;
     p.uhat_in = uhat_in;
     p.u = u;
@@ -600,104 +1598,49 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     p.n_active = n_active;
     p.n_touch = n_touch;
     p.saved = saved;
-    const int grid = p.n_items < pl.grid ? p.n_items : pl.grid;
+    const bool dec = m.mode != ETAC_RESIDUAL_ONLY, res = m.mode != ETAC_DECAY_ONLY;
+    const int cus = pl.cu_count;
+    const long long items = (long long)n_envs * pl.K, words = (long long)n_envs * pl.tile.NW;
+    p.table_units = res ? std::min(pl.tile.NW, 2 * cus) : 0;
+    p.matrix_units = dec ? pl.tile.near_rows : 0;
+    const int nt = p.table_units + p.matrix_units;
+    // Small batches: tables and contact share a launch and every item is
+    // listed.  A launch costs 5-7 us; on one 32 x 32 pad the whole step takes
+    // about 30, and the listing of 256 items would take as long as visiting them.
+    p.dense = items <= 256;
+    p.splits = 1;
+    while (n_envs * p.splits < 4 * cus && p.splits * kWaves * 4 < pl.tile.NW) p.splits *= 2;
+    const bool merged = p.dense && p.splits == 1 && nt > 0;
     const int slot = timer_begin(pl, ETAC_TIMER_STEP, st);
-    if (s) hipLaunchKernelGGL(k_step<false>, dim3(grid), dim3(kWG), 0, st, p);
-    else hipLaunchKernelGGL(k_step<true>, dim3(grid), dim3(kWG), 0, st, p);
+    if (!merged && (nt > 0 || p.splits > 1))
+        hipLaunchKernelGGL(k_tables, dim3(std::max(nt, 64)), dim3(kWG), 0, st, p);
+    if (s) launch_contact_items<false>(p, merged, nt, st);
+    else launch_contact_items<true>(p, merged, nt, st);
+    const int32_t *na = n_active ? n_active : pl.itm.n_act;
+    if (!p.dense) hipLaunchKernelGGL(k_live, dim3(pl.K), dim3(1024), 0, st, na, n_envs, pl.K, pl.itm.live, pl.itm.live_cnt);
+    if (res) {
+        if (p.dense && pl.tile.n_far == 0) {
+            hipLaunchKernelGGL(k_pool, dim3((unsigned)std::min<long long>(items, cus)), dim3(64 * kPoolWaves), 0, st, p);
+        } else {
+            hipLaunchKernelGGL(k_pool_passive, dim3((unsigned)std::min<long long>((words / kPassiveWords + items) / kWaves + 1, 8 * cus)),
+                               dim3(kWG), 0, st, p);
+            hipLaunchKernelGGL(k_pool_active, dim3((unsigned)std::min<long long>((words / kActiveWords + items) / kWaves + 1, 2 * cus)),
+                               dim3(kWG), 0, st, p);
+            hipLaunchKernelGGL(k_pool_finish, dim3((unsigned)std::min<long long>(items / kWaves + 1, 8 * cus)), dim3(kWG), 0, st, p);
+        }
+    }
+    if (pl.tile.n_near) {
+        if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(2 * cus), dim3(kWG), 0, st, p);
+        else if (n_envs >= 128) hipLaunchKernelGGL(k_prop_wide<1>, dim3(2 * cus), dim3(kWG), 0, st, p);
+        else
+            hipLaunchKernelGGL(k_prop_narrow, dim3((unsigned)std::min<long long>((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
+                               dim3(kWG), 0, st, p);
+    }
+    if (pl.tile.n_far) {
+        if (dec) hipLaunchKernelGGL(k_far_list, dim3((unsigned)std::min<long long>(items, 2 * cus)), dim3(1024), 0, st, p);
+        hipLaunchKernelGGL(k_prop_far, dim3((unsigned)std::min<long long>(words / 4 + items, 8 * cus)), dim3(kWG), 0, st, p);
+    }
     const hipError_t e = hipGetLastError();
-    timer_end(pl, ETAC_TIMER_STEP, slot, st);
-    return e;
-}
-
-// ---------------------------------------------------------------------------
-// the fused step with its scratch in a file-scope device array
-//
-// For callers that cannot allocate (code under stream capture, serving
-// loops): the per-workgroup slices of the fused step (u_hat, residuals and
-// node lists of the current item) and the work-queue counters live in
-// `scratch`, which every device the library runs on holds until the process
-// ends.  Host code uses only the array's device address, looked up once per
-// device by static_scratch_init (at plan creation, with that device
-// current); the array's name is never used as an address on the host.
-// ---------------------------------------------------------------------------
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
-
-constexpr int kMaxDevices = 64;
-static std::mutex g_static_mu;
-static void *g_static_ptr[kMaxDevices];
-
-hipError_t static_scratch_init(int device) {
-    if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(g_static_mu);
-    if (g_static_ptr[device]) return hipSuccess;
-    int cur = -1;
-    hipError_t e = hipGetDevice(&cur);
-    if (e != hipSuccess) return e;
-    if (cur != device && (e = hipSetDevice(device)) != hipSuccess) return e;
-    void *ptr = nullptr;
-    e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-    if (e == hipSuccess) g_static_ptr[device] = ptr;
-    if (cur != device) {
-        const hipError_t e2 = hipSetDevice(cur);
-        if (e == hipSuccess) e = e2;
-    }
-    return e;
-}
-
-// Bytes of the array one persistent workgroup's slice needs: u_hat and
-// residuals [3][n_max] floats, active and passive lists [n_max] ints.
-size_t static_scratch_per_wg(int n_max) { return ((size_t)32 * (size_t)n_max + 255) / 256 * 256; }
-
-// The work-queue counters start at zero (a fill kernel, not a memset, so that
-// a captured graph replays it reliably).
-__global__ __launch_bounds__(64) void k_clear_counters(unsigned *c) {
-    if (threadIdx.x < 4) c[threadIdx.x] = 0u;
-}
-
-hipError_t launch_step_static(const Plan &pl, const SceneDev &s, const ModelDev &m, float *u, int8_t *cobj_out,
-                              int32_t *n_active, uint32_t *saved, hipStream_t st) {
-    void *base = nullptr;
-    if (pl.device >= 0 && pl.device < kMaxDevices) {
-        std::lock_guard<std::mutex> lock(g_static_mu);
-        base = g_static_ptr[pl.device];
-    }
-    if (!base) return hipErrorNotInitialized;
-    if (s.E == 0) return hipSuccess;
-    const size_t per_wg = static_scratch_per_wg(pl.n_max);
-    const int n_items = s.E * pl.K;
-    int grid = (int)std::min<size_t>((size_t)pl.grid, (kStaticScratchBytes - 256) / per_wg);
-    grid = std::min(grid, n_items);
-    if (grid < 1) return hipErrorInvalidValue;      // the caller checks the size first
-    const size_t nm = (size_t)pl.n_max, g = (size_t)grid;
-    char *b = static_cast<char *>(base);
-    Scratch scr;
-    scr.counter = reinterpret_cast<unsigned *>(b);
-    scr.uhat_node = reinterpret_cast<float *>(b + 256);
-    scr.resid = scr.uhat_node + g * 3 * nm;
-    scr.alist = reinterpret_cast<int *>(scr.resid + g * 3 * nm);
-    scr.plist = scr.alist + g * nm;
-    scr.n_max = pl.n_max;
-    StepParams p;
-    p.mesh = pl.mesh;
-    p.scene = s;
-    p.model = m;
-    p.scr = scr;
-    p.E = s.E;
-    p.n_items = n_items;
-    p.batch = pl.batch;
-    p.cobj_in = nullptr;
-    p.uhat_in = nullptr;
-    p.u = u;
-    p.cobj_out = cobj_out;
-    p.n_active = n_active;
-    p.n_touch = nullptr;
-    p.saved = saved;
-    hipLaunchKernelGGL(k_clear_counters, dim3(1), dim3(64), 0, st, scr.counter);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int slot = timer_begin(pl, ETAC_TIMER_STEP, st);
-    hipLaunchKernelGGL(k_step<false>, dim3(grid), dim3(kWG), 0, st, p);
-    e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_STEP, slot, st);
     return e;
 }

@@ -86,13 +86,57 @@ struct LinksDev {
     const float *trans;            // [E][L][3]
 };
 
+// Node words and decay tiles of the mesh (plan copies, fixed at creation).
+// A word is up to 64 consecutive nodes of one patch, the unit of the contact
+// masks.  Patches of at most kNearNodes nodes have a decay matrix; the others
+// ("far") take Eq. 1 pair by pair in a spatial order of their nodes.
+constexpr int kNearNodes = 2048;
+constexpr size_t kDecayMatrixBytes = size_t(1) << 30;   // bound on all decay matrices of a plan
+
+struct TileDev {
+    const int4 *word;          // [NW] patch, first node (index into the mesh), nodes, word of the patch
+    const int2 *row_tile;      // [near_rows] near patch and tile of 16 of its nodes
+    const int *word_off;       // [K+1] first word of each patch
+    const long long *w_off;    // [K] the patch's decay matrix in w, in 16-byte units; -1: far patch
+    const int *perm;           // [N] far patches: patch-local node of each position of the spatial order
+    int NW;
+    int n_near, n_far;         // patches of each kind
+    int far_max;               // nodes of the largest far patch
+    int near_rows;             // tiles of 16 nodes of the near patches
+};
+
+// What one model gives on the undeformed surface, whatever the env: rebuilt
+// by every call that uses it (k_tables).
+struct TableDev {
+    float *feat;               // [N][64] encoder features of a passive node (U_hat = 0)
+    float *dec;                // [N][64] W4[:, :64] feat
+    float *max8, *max32;       // [8 NW][64], [2 NW][64] largest features of 8 and of 32 consecutive nodes of a word
+    int *scale;                // [8] exponents of the network's weight scales (s1, s2, s4)
+    float *w3t, *w4t;          // [64][64] W3 and W4[:, 64:] transposed
+    uint4 *w;                  // decay matrices, see k_tables
+};
+
+// Results of the contact pass the later kernels of a call read.
+struct ItemDev {
+    unsigned long long *mask;  // [E][NW] active nodes of each word
+    float *umax;               // [E][NW] largest |u_hat| component of each word
+    int *n_act;                // [E][K] active counts where the caller takes none
+    int *live, *live_cnt;      // [K][E] envs in contact on each patch, ascending; [K] how many
+    unsigned long long *pool;  // [E K][64] max-pool of the items in contact: feature bits, then ~node (lowest node on ties)
+    float *c4;                 // [E K][64] W4[:, 64:] g' + b4 of the items in contact
+    int *alist;                // [E][N] far patches: active nodes in spatial order (patch-local)
+    float4 *abox;              // [E][NB][2] boxes of 32 consecutive entries of alist
+    const int *box_off;        // [K] first box of each patch
+    int NB;                    // boxes per env
+};
+
 struct ModelDev {
     int mode;
     const float *alpha;    // [K]
     const float *phi;      // [17411] or null in decay-only mode
 };
 
-// Per-workgroup scratch of the persistent kernels (device memory).
+// Per-workgroup scratch of the persistent adjoint kernels (device memory).
 struct Scratch {
     float *uhat_node;      // [G][3][n_max] u_hat of every node of the current item (0 passive)
     float *resid;          // [G][3][n_max] residual-network output
@@ -140,11 +184,14 @@ struct Plan {
     int n_envs, max_obj, K, N, n_max;
     uint32_t flags;
     MeshDev mesh;
+    TileDev tile;
+    TableDev tab;
+    ItemDev itm;
     Scratch scr;
     BwdScratch bwd;
     bool has_bwd;
     // device allocations owned by the plan
-    void *allocs[48];
+    void *allocs[96];
     int n_allocs;
     int64_t scratch_bytes;
     Timers *timers;        // null until timing is first turned on
@@ -200,14 +247,6 @@ hipError_t launch_pose_hand(const Plan &p, const SceneDev &world, const LinksDev
                             float *grad_trans, float *grad_link_rot, float *grad_link_trans, hipStream_t st);
 hipError_t init_record_map(const Plan &p);
 
-// The fused step with its scratch in the library's file-scope device array
-// (etac_step_static): size of the array, the slice one persistent workgroup
-// needs, the once-per-device lookup of the array's address, and the launch.
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;
-size_t static_scratch_per_wg(int n_max);
-hipError_t static_scratch_init(int device);
-hipError_t launch_step_static(const Plan &p, const SceneDev &s, const ModelDev &m, float *u, int8_t *cobj,
-                              int32_t *n_active, uint32_t *saved, hipStream_t st);
 hipError_t launch_contact_backward(const Plan &p, const SceneDev &s, const float *grad_uhat,
                                    float *grad_rot, float *grad_trans, hipStream_t st);
 
