@@ -9,18 +9,16 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libetac.so")
-# (source, object name, extra flags).  The network-adjoint kernel keeps ~450
-# registers per lane live (one wave per SIMD): letting MFMA results live in
-# VGPRs as well as AGPRs, and sinking loop-invariant address computations
-# into the loops that use them, keeps it free of spills.  It is built from
-# etac_backward.hip on its own (ETAC_BWD_NET_ONLY); the decay adjoint, which
-# runs three or four workgroups per CU, is better off without the sinking.
+# (source, object name, extra flags).  The node pass of the network adjoint
+# keeps most of a lane's registers live: letting MFMA results live in VGPRs as
+# well as AGPRs, and sinking loop-invariant address computations into the loops
+# that use them, keeps it free of spills.
 SOURCES = [
     ("etac_api.cpp", "etac_api", []),
     ("etac_forward.hip", "etac_forward", []),
-    ("etac_backward.hip", "etac_backward", ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
-    ("etac_backward.hip", "etac_backward_net", ["-DETAC_BWD_NET_ONLY", "-mllvm", "-amdgpu-mfma-vgpr-form=1",
-                                                "-mllvm", "-sink-insts-to-avoid-spills"]),
+    ("etac_adjoint.hip", "etac_adjoint", []),
+    ("etac_backward.hip", "etac_backward", ["-mllvm", "-amdgpu-mfma-vgpr-form=1",
+                                            "-mllvm", "-sink-insts-to-avoid-spills"]),
     ("etac_mesh.hip", "etac_mesh", []),
     ("etac_hand.hip", "etac_hand", []),
     ("etac_regress.hip", "etac_regress", []),

@@ -25,10 +25,30 @@ etac_status hip_fail(hipError_t e) {
     return ETAC_ERR_HIP;
 }
 
+// Small arrays share blocks: a device allocation costs tens of microseconds.
+constexpr size_t kArenaBytes = size_t(4) << 20, kArenaMost = size_t(1) << 20;
+
 template <typename T>
 hipError_t plan_alloc(etac::Plan &p, T **ptr, size_t count) {
     *ptr = nullptr;
     if (count == 0) count = 1;
+    const size_t bytes = (count * sizeof(T) + 255) / 256 * 256;
+    if (bytes <= kArenaMost) {
+        if (p.arena_left < bytes) {
+            if (p.n_allocs >= (int)(sizeof(p.allocs) / sizeof(p.allocs[0]))) return hipErrorOutOfMemory;
+            void *v = nullptr;
+            const hipError_t e = hipMalloc(&v, kArenaBytes);
+            if (e != hipSuccess) return e;
+            p.allocs[p.n_allocs++] = v;
+            p.arena = static_cast<char *>(v);
+            p.arena_left = kArenaBytes;
+        }
+        *ptr = reinterpret_cast<T *>(p.arena);
+        p.arena += bytes;
+        p.arena_left -= bytes;
+        p.scratch_bytes += (int64_t)(count * sizeof(T));
+        return hipSuccess;
+    }
     if (p.n_allocs >= (int)(sizeof(p.allocs) / sizeof(p.allocs[0]))) return hipErrorOutOfMemory;
     void *v = nullptr;
     hipError_t e = hipMalloc(&v, count * sizeof(T));
@@ -210,10 +230,10 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     // host-side tables
     std::vector<float4> bound;
     std::vector<int16_t> node_patch;
-    std::vector<int> order, word_off, box_off, perm;
+    std::vector<int> order, word_off, box_off, part_off, chunk_off, blk5_off, perm;
     std::vector<float> xbound;
     std::vector<int4> word;       // see TileDev
-    std::vector<int2> row_tile;
+    std::vector<int2> row_tile, block;
     std::vector<long long> w_off;
     long long matrix_units = 0;
     etac::TileDev &tile = p.tile;
@@ -223,6 +243,9 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     order.resize(K);
     xbound.resize(K);
     word_off.assign(K + 1, 0);
+    part_off.assign(K + 1, 0);
+    chunk_off.assign(K + 1, 0);
+    blk5_off.assign(K + 1, 0);
     box_off.resize(K);
     perm.assign(N, 0);
     w_off.resize(K);
@@ -281,6 +304,17 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
         p.itm.NB += (n + 31) / 32;
         spatial_order(mesh, o0, n, perm.data() + o0);
     }
+    for (int k = 0; k < K; ++k) {
+        const int n = mesh->patch_offset[k + 1] - mesh->patch_offset[k], nw = word_off[k + 1] - word_off[k];
+        part_off[k + 1] = part_off[k] + (w_off[k] >= 0 ? (n + 15) / 16 : (n + 63) / 64);
+        chunk_off[k + 1] = chunk_off[k] + (nw + etac::kPoseWords - 1) / etac::kPoseWords;
+        blk5_off[k + 1] = blk5_off[k] + (n + 127) / 128;
+        for (int i = 0; i < n; i += etac::kBlockNodes) block.push_back(make_int2(k, i));
+    }
+    tile.NP = part_off[K];
+    tile.NC = chunk_off[K];
+    tile.NB5 = blk5_off[K];
+    tile.NU = (int)block.size();
     tile.NW = (int)word.size();
     tile.near_rows = (int)row_tile.size();
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -315,17 +349,26 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     p.mesh = etac::MeshDev{pos, nrm, origin, offset, bnd, np, ord, xbd, K, N, n_max};
 
     int4 *wrd = nullptr;
-    int2 *rtl = nullptr;
+    int2 *rtl = nullptr, *blk = nullptr;
+    int *poff = nullptr, *coff = nullptr, *b5off = nullptr;
     int *woff = nullptr, *boff = nullptr, *prm = nullptr;
     long long *moff = nullptr;
     if (e == hipSuccess) e = plan_upload(p, &wrd, word.data(), word.size());
     if (e == hipSuccess) e = plan_upload(p, &rtl, row_tile.data(), row_tile.size());
+    if (e == hipSuccess) e = plan_upload(p, &blk, block.data(), block.size());
+    if (e == hipSuccess) e = plan_upload(p, &b5off, blk5_off.data(), blk5_off.size());
+    if (e == hipSuccess) e = plan_upload(p, &poff, part_off.data(), part_off.size());
+    if (e == hipSuccess) e = plan_upload(p, &coff, chunk_off.data(), chunk_off.size());
     if (e == hipSuccess) e = plan_upload(p, &woff, word_off.data(), word_off.size());
     if (e == hipSuccess) e = plan_upload(p, &boff, box_off.data(), box_off.size());
     if (e == hipSuccess) e = plan_upload(p, &prm, perm.data(), tile.n_far ? (size_t)N : 1);
     if (e == hipSuccess) e = plan_upload(p, &moff, w_off.data(), w_off.size());
     tile.word = wrd;
     tile.row_tile = rtl;
+    tile.block = blk;
+    tile.blk5_off = b5off;
+    tile.part_off = poff;
+    tile.chunk_off = coff;
     tile.word_off = woff;
     tile.w_off = moff;
     tile.perm = prm;
@@ -339,6 +382,7 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.scale, 8);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w3t, 4096);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w4t, 4096);
+    if (e == hipSuccess) e = plan_alloc(p, &p.tab.w2t, 4096);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w, (size_t)matrix_units);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.mask, ENW);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.umax, ENW);
@@ -350,40 +394,38 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.alist, tile.n_far ? (size_t)n_envs * N : 1);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.abox, 2 * (size_t)n_envs * p.itm.NB);
 
-    // adjoint scratch, one slice per persistent workgroup
-    const size_t G = (size_t)p.cu_count * 8;  // enough for any occupancy override
-    p.scr.n_max = n_max;
-    if (e == hipSuccess) e = plan_alloc(p, &p.scr.uhat_node, G * 3 * n_max);
-    if (e == hipSuccess) e = plan_alloc(p, &p.scr.resid, G * 3 * n_max);
-    if (e == hipSuccess) e = plan_alloc(p, &p.scr.alist, G * n_max);
-    if (e == hipSuccess) e = plan_alloc(p, &p.scr.plist, G * n_max);
-    // work counters: [0..1] forward, [2..3] adjoint, [4..5] regressor
-    if (e == hipSuccess) e = plan_alloc(p, &p.scr.counter, 8);
-    if (e == hipSuccess) e = hipMemset(p.scr.counter, 0, 8 * sizeof(unsigned));
+    // the regressor's work counters
+    if (e == hipSuccess) e = plan_alloc(p, &p.counter, 4);
+    if (e == hipSuccess) e = hipMemset(p.counter, 0, 4 * sizeof(unsigned));
     // regressor: rest outputs, and a pooled-feature row per item it may process
     if (e == hipSuccess) e = plan_alloc(p, &p.reg_rest, 8 * (size_t)K);
     if (e == hipSuccess) e = plan_alloc(p, &p.reg_pooled, ((size_t)n_envs * K + K) * 256);
     if (e == hipSuccess) e = plan_alloc(p, &p.reg_row, (size_t)n_envs * K + K);
 
     if (e == hipSuccess && (flags & ETAC_PLAN_BACKWARD)) {
-        const size_t items = (size_t)n_envs * K;
         etac::BwdScratch &b = p.bwd;
-        e = plan_alloc(p, &b.guhat, G * 3 * (size_t)n_max);
-        if (e == hipSuccess) e = plan_alloc(p, &b.phi_part, items * etac::kRecWords);
-        if (e == hipSuccess) e = plan_alloc(p, &b.rec_map, ETAC_PHI_SIZE);
-        if (e == hipSuccess) e = plan_alloc(p, &b.alpha_part, items);
-        if (e == hipSuccess) e = plan_alloc(p, &b.pose_part, items * (size_t)max_obj * 12);
-        if (e == hipSuccess) e = plan_alloc(p, &b.item_flag, items);
-        if (e == hipSuccess) e = plan_alloc(p, &b.phi_seg, (size_t)64 * etac::kRedColsMax);
         const size_t EN = (size_t)n_envs * N;
-        if (e == hipSuccess) e = plan_alloc(p, &b.cobj_st, EN);
+        // chunks of the largest batch: full-size chunks, or small ones of the batches below the switch
+        const int small = std::min(n_envs, etac::kEnvChunkSwitch - 1);
+        b.chunks = std::max((n_envs + etac::kEnvChunk - 1) / etac::kEnvChunk,
+                            (small + etac::kEnvChunkSmall - 1) / etac::kEnvChunkSmall);
+        e = plan_alloc(p, &b.cobj_st, EN);
         if (e == hipSuccess) e = plan_alloc(p, &b.uhat_st, 3 * EN);
-        if (e == hipSuccess) e = plan_alloc(p, &b.gh_st, 3 * EN);
-        if (e == hipSuccess) e = plan_alloc(p, &b.m_st, items);
-        if (e == hipSuccess) e = plan_alloc(p, &b.gmax_st, items);
-        if (e == hipSuccess) e = plan_alloc(p, &b.live, items);
-        if (e == hipSuccess) e = plan_alloc(p, &b.seg_cnt, (items + 1023) / 1024 + 1);
-        if (e == hipSuccess) e = etac::init_record_map(p);
+        if (e == hipSuccess) e = plan_alloc(p, &b.gh, 3 * EN);
+        if (e == hipSuccess) e = plan_alloc(p, &b.alpha_part, (size_t)n_envs * tile.NP);
+        if (e == hipSuccess) e = plan_alloc(p, &b.alpha_seg, (size_t)K * etac::kAlphaSegs);
+        if (e == hipSuccess) e = plan_alloc(p, &b.s4_part, ENW * 2 * 64);
+        if (e == hipSuccess) e = plan_alloc(p, &b.s4_node, (size_t)b.chunks * N * 64);
+        if (e == hipSuccess) e = plan_alloc(p, &b.w5_part, (size_t)b.chunks * tile.NB5 * 256);
+        if (e == hipSuccess) e = plan_alloc(p, &b.ivec, EK * 256);
+        if (e == hipSuccess) e = plan_alloc(p, &b.record, EK * etac::kSavedWords);
+        if (e == hipSuccess) e = plan_alloc(p, &b.route, (size_t)etac::kRouteGroups * p.cu_count * etac::kRouteWords);
+        if (e == hipSuccess) e = plan_alloc(p, &b.node_rec, (size_t)tile.NU * etac::kNodeRecWords);
+        if (e == hipSuccess) e = plan_alloc(p, &b.seg, (size_t)etac::kPhiSegs * etac::kRedCols);
+        if (e == hipSuccess) e = plan_alloc(p, &b.pose_part, (size_t)n_envs * tile.NC * max_obj * 12);
+        if (e == hipSuccess) e = plan_alloc(p, &p.tab.wd, (size_t)matrix_units);
+        if (e == hipSuccess) e = plan_alloc(p, &p.itm.plist, tile.n_far ? EN : 1);
+        if (e == hipSuccess) e = plan_alloc(p, &p.itm.pbox, 2 * (size_t)n_envs * p.itm.NB);
         p.has_bwd = (e == hipSuccess);
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -757,7 +799,7 @@ etac_status etac_plan_set_hand(etac_plan *plan, const etac_hand *hand) {
     const size_t o_no = take(rows * sizeof(int)), o_ne = take(rows * sizeof(int)), o_ty = take(rc * sizeof(int));
     const size_t o_sh = take(4 * rc * sizeof(float)), o_ro = take(9 * rc * sizeof(float));
     const size_t o_tr = take(3 * rc * sizeof(float)), o_sr = take(rc), o_nt = take(rows * sizeof(int));
-    const size_t o_pa = p.has_bwd ? take(12 * rc * sizeof(float)) : 0;
+    const size_t o_pa = p.has_bwd ? take(12 * (size_t)p.n_envs * p.tile.NC * cap * sizeof(float)) : 0;
     void *mem = nullptr;
     hipError_t e = hipMalloc(&mem, off);
     if (e != hipSuccess) return hip_fail(e);

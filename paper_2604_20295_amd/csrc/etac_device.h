@@ -1,6 +1,5 @@
 // Device building blocks of the ETac step on gfx950: the pinned FP64 contact
-// predicate, the per-item active/passive compaction and the FP32-MFMA
-// residual network tiles.
+// predicate and the split-FP16 arithmetic of the residual network.
 #pragma once
 
 #include "etac_internal.h"
@@ -286,21 +285,12 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
-// ---------------------------------------------------------------------------
-// certified cutoff of the Eq. 1 pair sums
-//
-// Staged points are grouped in blocks of 32 consecutive list entries (node
-// order, so spatially compact strips) with a bounding box each.  A wave skips
-// a block when none of its own nodes lies within D of the box, where
-// exp(-alpha D) = 2^-50: every skipped weight is below 2^-50, so a skipped
-// block changes a sum by less than 2^-50 times the sum of its |terms|, far
-// below FP32 rounding of the sums themselves.
-// ---------------------------------------------------------------------------
+// Certified cutoff of the pair sums of Eq. 1 on far patches.  A run of 32 nodes
+// is passed over when its box lies further than D from the box of the wave's
+// own nodes, where exp(-alpha D) = 2^-50: every weight left out is below 2^-50,
+// so a sum changes by less than 2^-50 times the sum of its |terms|, far below
+// FP32 rounding of the sums themselves.
 constexpr double kCutLog2 = 50.0;
-// The cutoff in units of the decay's exponent (positions scaled by
-// |alpha| log2(e)): kCutLog2^2, rounded up.
-constexpr float kCut2Scaled = (float)(kCutLog2 * kCutLog2 * (1.0 + 1e-6));
-
 // D^2 for the item's alpha, rounded up (no cutoff when alpha <= 0).
 __device__ __forceinline__ float cutoff_d2(float alpha) {
     if (!(alpha > 0.0f)) return __builtin_inff();
@@ -308,209 +298,12 @@ __device__ __forceinline__ float cutoff_d2(float alpha) {
     return (float)(d * d * (1.0 + 1e-6));
 }
 
-// Boxes of the blocks of 32 among staged points pts[0 .. cnt): bb[2 b] =
-// lower corner, bb[2 b + 1] = upper corner.  Thread t loads point t and each
-// aligned group of 32 lanes reduces by shuffles.  The caller brackets it with
-// barriers.
-__device__ __forceinline__ void block_boxes(const float4 *pts, int cnt, float4 *bb) {
-    for (int t0 = 0; t0 < cnt; t0 += kWG) {
-        const int t = t0 + threadIdx.x;
-        const bool ok = t < cnt;
-        const float4 q = pts[ok ? t : 0];
-        float lx = ok ? q.x : 3.0e38f, ly = ok ? q.y : 3.0e38f, lz = ok ? q.z : 3.0e38f;
-        float hx = ok ? q.x : -3.0e38f, hy = ok ? q.y : -3.0e38f, hz = ok ? q.z : -3.0e38f;
-#pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) {
-            lx = fminf(lx, __shfl_xor(lx, off)); ly = fminf(ly, __shfl_xor(ly, off)); lz = fminf(lz, __shfl_xor(lz, off));
-            hx = fmaxf(hx, __shfl_xor(hx, off)); hy = fmaxf(hy, __shfl_xor(hy, off)); hz = fmaxf(hz, __shfl_xor(hz, off));
-        }
-        if ((t & 31) == 0 && ok) {
-            bb[2 * (t >> 5)] = make_float4(lx, ly, lz, 0.0f);
-            bb[2 * (t >> 5) + 1] = make_float4(hx, hy, hz, 0.0f);
-        }
-    }
-}
-
-// Whether the cutoff can skip anything in patch k: only if the patch is wider
-// than D (its bounding sphere's diameter exceeds the cutoff radius).
-__device__ __forceinline__ bool cutoff_useful(const MeshDev &M, int k, float cut2) {
-    const float d = 2.0f * M.bound[k].w;
-    return d * d > cut2;
-}
-
-// Squared distance from (x, y, z) to the box [lo, hi].
-__device__ __forceinline__ float box_d2(const float4 &lo, const float4 &hi, float x, float y, float z) {
-    const float dx = fmaxf(fmaxf(lo.x - x, x - hi.x), 0.0f);
-    const float dy = fmaxf(fmaxf(lo.y - y, y - hi.y), 0.0f);
-    const float dz = fmaxf(fmaxf(lo.z - z, z - hi.z), 0.0f);
-    return dx * dx + dy * dy + dz * dz;
-}
-
-// ---------------------------------------------------------------------------
-// batched work queue
-//
-// The persistent kernels claim `batch` (1 .. kBatch) consecutive queue
-// positions per atomic.
-// Queue position q maps to patch order[q / E] (patches by node count, largest
-// first) and env q % E.  Wave 0 culls the whole batch at once, one item per
-// lane; only items that some object may reach are processed one by one, the
-// rest only need their zero outputs.
-// ---------------------------------------------------------------------------
-constexpr int kBatch = 64;
-
-struct ItemBatch {
-    int item[kBatch];          // queue positions of the live items, ascending
-    uint8_t cand[kBatch];      // their candidate-object masks
-    unsigned mask_lo, mask_hi; // live items as a bit mask over the batch
-    int n;                     // number of live items
-    int b0;                    // first queue position of the batch
-};
-
+// Work-queue position q: patch order[q / E] (patches by node count, largest
+// first), env q % E.
 __device__ __forceinline__ void queue_item(const MeshDev &M, int E, int q, int &e, int &k) {
     const int kk = q / E;
     e = q - kk * E;
     k = M.order[kk];
-}
-
-__device__ __forceinline__ unsigned long long batch_mask(const ItemBatch &B) {
-    return ((unsigned long long)uniform(B.mask_hi) << 32) | (unsigned long long)uniform(B.mask_lo);
-}
-
-// How a claimed batch is culled.
-enum CullMode {
-    CULL_NONE = 0,      // every item is live (contact results are given)
-    CULL_OBJECTS = 1,   // live if some object's bounding ball may reach the patch
-    CULL_LIST = 2       // positions index a list of live queue positions (live[q])
-};
-
-// Claim the next batch and cull it.  Returns the batch's first position
-// (>= n_items when the queue is empty); B.item holds the live items' queue
-// positions.
-template <int CULL>
-__device__ int next_batch(unsigned *counter, ItemBatch &B, const MeshDev &M, const SceneDev &Sc, int E,
-                          int n_items, int batch, const int *list = nullptr) {
-    __syncthreads();   // every wave is done with the previous batch
-    if (threadIdx.x < 64) {
-        const int lane = lane_id();
-        // one atomic for the wave (lane 0 adds `batch`), every lane learns the result
-        const unsigned old = atomicAdd(&counter[0], lane == 0 ? (unsigned)batch : 0u);
-        const int b0 = __shfl((int)old, 0);
-        const int q = b0 + lane;
-        unsigned cand = 0;
-        if (lane < batch && q < n_items) {
-            if (CULL == CULL_OBJECTS) {
-                int e, k;
-                queue_item(M, E, q, e, k);
-                cand = cull_objects(Sc, M, e, k);
-            } else {
-                cand = 0xffu;
-            }
-        }
-        const unsigned long long live = __ballot(cand != 0u);
-        if (cand != 0u) {
-            const int slot = (int)lanes_below(live);
-            B.item[slot] = CULL == CULL_LIST ? list[q] : q;
-            // a row scene's mask may use all 32 bits: the item recomputes it (item_cand)
-            B.cand[slot] = (uint8_t)(Sc.rows_per_env ? 1u : cand);
-        }
-        // identical values from every lane
-        B.mask_lo = (unsigned)live;
-        B.mask_hi = (unsigned)(live >> 32);
-        B.n = __popcll(live);
-        B.b0 = b0;
-    }
-    __syncthreads();
-    return uniform(B.b0);
-}
-
-// Candidate mask of an item taken from a batch: the batch keeps 8 bits per
-// item, enough for env rows (at most ETAC_MAX_OBJ objects).  An item row of
-// the hand holds only candidates that passed the same ball test when the row
-// was filled, so its mask is every slot of the row.
-__device__ __forceinline__ unsigned item_cand(const SceneDev &S, int e, int k, unsigned stored) {
-    if (!S.rows_per_env) return stored;
-    const int n = min(S.n_obj[scene_row(S, e, k)], S.O);
-    return uniform(n >= 32 ? ~0u : (1u << n) - 1u);
-}
-
-// Contact (or given contact results) for every node of one (env, patch)
-// item, then the active and passive node lists in ascending node order
-// (wave ballots, prefix over waves).  Writes u_hat of every node into `uhn`
-// ([3][n_max], 0 on passive nodes), the winner's slot into `wobj` when
-// given, and contact_obj into `cobj_out` when computing contact (the
-// winner's source id for a row scene with `src`).  Returns m; `touch`
-// counts the active nodes won by external objects (slots below the row's
-// n_ext; 0 without n_ext).  IDS = false (the adjoint's hand-over) skips the
-// id mapping and the touch count.
-template <bool FROM_INPUT, bool IDS = false>
-__device__ int contact_and_compact(const MeshDev &M, const SceneDev &Sc, int E, int n_max, const int8_t *cobj_in,
-                                   const float *uhat_in, int8_t *cobj_out, int (&wcnt)[3][kWaves], int e, int k,
-                                   int base, int n, unsigned cand, float *uhn, int *alist, int *plist,
-                                   int8_t *wobj, float &umax, int &touch) {
-    const int N = M.N;
-    const size_t EN = (size_t)E * N;
-    const int wave = threadIdx.x >> 6;
-    const size_t srow = FROM_INPUT ? 0 : scene_row(Sc, e, k);
-    const int n_ext = (IDS && !FROM_INPUT && Sc.n_ext) ? uniform(Sc.n_ext[srow]) : 0;
-    int run_a = 0, run_p = 0, run_t = 0;
-    int ubits = 0;   // largest |u_hat| component of this thread's nodes (bits of a non-negative float)
-    for (int i0 = 0; i0 < n; i0 += kWG) {
-        const int i = i0 + threadIdx.x;
-        const bool valid = i < n;
-        int best = -1;
-        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-        if (valid) {
-            const int gi = base + i;
-            const size_t en = (size_t)e * N + gi;
-            if (FROM_INPUT) {
-                best = cobj_in[en] >= 0 ? (int)cobj_in[en] : -1;
-                if (best >= 0) {
-                    u0 = uhat_in[en];
-                    u1 = uhat_in[EN + en];
-                    u2 = uhat_in[2 * EN + en];
-                }
-            } else {
-                best = contact_node(Sc, srow, cand, M.pos[gi], M.pos[N + gi], M.pos[2 * N + gi], M.nrm[gi],
-                                    M.nrm[N + gi], M.nrm[2 * N + gi], u0, u1, u2);
-                if (cobj_out)
-                    cobj_out[en] = (IDS && best >= 0 && Sc.src) ? Sc.src[srow * Sc.O + best] : (int8_t)best;
-            }
-            uhn[i] = u0;
-            uhn[n_max + i] = u1;
-            uhn[2 * n_max + i] = u2;
-            if (wobj) wobj[i] = (int8_t)best;
-            ubits = max(ubits, __float_as_int(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2))));
-        }
-        const bool act = valid && best >= 0, pas = valid && best < 0;
-        const unsigned long long ba = __ballot(act), bp = __ballot(pas), bt = IDS ? __ballot(act && best < n_ext) : 0ull;
-        // every lane stores the same wave counts (no single-lane block next to
-        // the barrier); external-object touches ride in the upper half-word
-        wcnt[0][wave] = __popcll(ba) | (__popcll(bt) << 16);
-        wcnt[1][wave] = __popcll(bp);
-        wcnt[2][wave] = wave_max_int(ubits);
-        __syncthreads();
-        int oa = run_a, op = run_p, ta = 0, tp = 0, tt = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            const int ca = wcnt[0][w] & 0xffff;
-            if (w < wave) { oa += ca; op += wcnt[1][w]; }
-            ta += ca;
-            tp += wcnt[1][w];
-            tt += wcnt[0][w] >> 16;
-        }
-        if (act) alist[oa + lanes_below(ba)] = i;
-        if (pas) plist[op + lanes_below(bp)] = i;
-        run_a += uniform(ta);
-        run_p += uniform(tp);
-        run_t += uniform(tt);
-        if (i0 + kWG >= n) {   // last chunk: the wave maxima cover every node of the item
-            int ub = 0;
-            for (int w = 0; w < kWaves; ++w) ub = max(ub, wcnt[2][w]);
-            umax = __int_as_float(uniform(ub));
-        }
-        __syncthreads();
-    }
-    touch = run_t;
-    return uniform(run_a);
 }
 
 // ---------------------------------------------------------------------------
@@ -579,17 +372,11 @@ struct NetLds {
     half8 w4h[4 * 2 * 64], w4l[4 * 2 * 64];  // [ot2][s][lane] W4 columns 0..63 (per-node part) 2^s4
     float b1[64], b2[64];
     float b1s[64], b2s[64];                  // per item: b1 2^a1, b2 2^af
-    float c4[64];                            // per item: (W4[:, 64:] g' + b4) 2^a4
-    float w5[3 * 64];
-    float b5[4];
-    float g[64], gp[64];                     // pooled feature and global MLP output (unscaled)
     float part[kWaves][64];                  // per-wave partials
     // per launch: scale exponents of the staged weights (W1 2^s1, W2 2^s2,
-    // W4[:, :64] 2^s4) and of the adjoint's transposed uses (W5^T 2^c5t,
-    // W4[:, :64]^T 2^s4t, W2^T 2^s2t)
-    int s1, s2, s4, c5t, s4t, s2t;
-    float mw2;               // max |W2|
-    ItemScale isc;           // per item: the activation scales (a copy for readers that re-read them)
+    // W4[:, :64] 2^s4) and of the adjoint's transposed uses (W4[:, :64]^T 2^s4t,
+    // W2^T 2^s2t)
+    int s1, s2, s4, s4t, s2t;
 };
 
 typedef _Float16 half2t __attribute__((ext_vector_type(2)));
@@ -636,34 +423,36 @@ __device__ __forceinline__ int chain_k(int s, int q, int e) { return 16 * (2 * s
 // brackets it with barriers).  Wave w takes rows (or columns) 16 w + (l & 15);
 // lane group q = l >> 4 sums a quarter of each, the quarters are added with
 // two shuffles and the wave's largest sum goes to part.
+// (row norms of W1 and W2, column norms of W2 and W4[:, :64], max |W4[:, :64]|, |b1|, |b2|)
+constexpr int kNorms = 7;
+
 __device__ void net_norms(float (&part)[kWaves][64], const float *phi) {
     const int lane = lane_id(), wave = threadIdx.x >> 6, q = lane >> 4;
     const int r = 16 * wave + (lane & 15);
-    float s1 = 0.0f, s2 = 0.0f, s4 = 0.0f, t2 = 0.0f, t4 = 0.0f, t5 = 0.0f;
-    float m2 = 0.0f, m4 = 0.0f, mb1 = 0.0f, mb2 = 0.0f;
+    float s1 = 0.0f, s2 = 0.0f, t2 = 0.0f, t4 = 0.0f;
+    float m4 = 0.0f, mb1 = 0.0f, mb2 = 0.0f;
 #pragma unroll
     for (int d = 0; d < 16; ++d) {      // unrolled: every load in flight at once
         const int c = 16 * q + d;
         const float a = fabsf(phi[kW2 + r * 64 + c]), b = fabsf(phi[kW4 + r * 128 + c]);
-        s2 += a; s4 += b;
-        m2 = fmaxf(m2, a); m4 = fmaxf(m4, b);
+        s2 += a;
+        m4 = fmaxf(m4, b);
         t2 += fabsf(phi[kW2 + c * 64 + r]);
         t4 += fabsf(phi[kW4 + c * 128 + r]);
     }
     if (q == 0) {
         for (int c = 0; c < 9; ++c) s1 += fabsf(phi[kW1 + r * 9 + c]);
-        for (int c = 0; c < 3; ++c) t5 += fabsf(phi[kW5 + c * 64 + r]);
         mb1 = fabsf(phi[kB1 + r]);
         mb2 = fabsf(phi[kB2 + r]);
     }
-    float v[10] = {s1, s2, s4, t2, t4, t5, m2, m4, mb1, mb2};
+    float v[kNorms] = {s1, s2, t2, t4, m4, mb1, mb2};
 #pragma unroll
-    for (int j = 0; j < 6; ++j) {   // sums over the four quarters
+    for (int j = 0; j < 4; ++j) {   // sums over the four quarters
         v[j] += __shfl_xor(v[j], 16);
         v[j] += __shfl_xor(v[j], 32);
     }
 #pragma unroll
-    for (int j = 0; j < 10; ++j) {
+    for (int j = 0; j < kNorms; ++j) {
         v[j] = wave_max(v[j]);
         part[wave][j] = v[j];      // identical in every lane
     }
@@ -671,10 +460,10 @@ __device__ void net_norms(float (&part)[kWaves][64], const float *phi) {
 
 // Scale exponents of W1, W2 and W4[:, :64] from the largest norms (see
 // stage_net).
-__device__ __forceinline__ void net_scales(const float (&v)[10], int &s1, int &s2, int &s4) {
-    s1 = range_exp((v[0] + 2.0f * v[8]) * kTop);
-    s2 = range_exp((v[1] * kTop + 2.0f * v[9] * kTop * pow2(s1)));
-    s4 = range_exp(v[7]);
+__device__ __forceinline__ void net_scales(const float (&v)[kNorms], int &s1, int &s2, int &s4) {
+    s1 = range_exp((v[0] + 2.0f * v[5]) * kTop);
+    s2 = range_exp((v[1] * kTop + 2.0f * v[6] * kTop * pow2(s1)));
+    s4 = range_exp(v[4]);
 }
 
 // Stage the network into LDS in fragment order (whole workgroup), each
@@ -682,21 +471,21 @@ __device__ __forceinline__ void net_scales(const float (&v)[10], int &s1, int &s
 // exponents.  With inputs x 2^ax below T (X at least 1, so 2^ax <= 2T):
 //   h1 = W1 2^s1 x + b1 2^a1:  |h1| <= (||W1|| + 2 max|b1|) T 2^s1 < T,
 //   f  = W2 2^s2 h1 + b2 2^af: |f| <= (||W2|| T + 2 max|b2| T 2^s1) 2^s2 < T,
-//   h4 = W4 2^s4 f + c4 2^a4 with s4 from max |W4[:, :64]| (h4 is never split).
-// Adjoint, with dL/dU 2^dre below T: W5^T 2^c5t, W4[:, :64]^T 2^s4t and W2^T
-// 2^s2t by their column norms keep dL/dpre4, dL/dpre2 and dL/dpre1 below T.
+//   W4 2^s4 with s4 from max |W4[:, :64]| (its product is never split).
+// Adjoint, with dL/dpre4 2^d4 below T: W4[:, :64]^T 2^s4t and W2^T 2^s2t by
+// their column norms keep dL/dpre2 and dL/dpre1 below T.
 // Ends with a barrier.
 __device__ void stage_net(NetLds &L, const float *phi) {
     const int tid = threadIdx.x;
     net_norms(L.part, phi);
     __syncthreads();
-    float v[10];
+    float v[kNorms];
 #pragma unroll
-    for (int j = 0; j < 10; ++j) {
+    for (int j = 0; j < kNorms; ++j) {
         v[j] = L.part[0][j];
         for (int w = 1; w < kWaves; ++w) v[j] = fmaxf(v[j], L.part[w][j]);
     }
-    const float n4t = v[4], n2t = v[3], n5t = v[5], mw2 = v[6];
+    const float n4t = v[3], n2t = v[2];
     int s1, s2, s4;
     net_scales(v, s1, s2, s4);
     const float e1 = pow2(s1), e2 = pow2(s2), e4 = pow2(s4);
@@ -727,14 +516,10 @@ __device__ void stage_net(NetLds &L, const float *phi) {
         L.b1[i] = phi[kB1 + i];
         L.b2[i] = phi[kB2 + i];
     }
-    for (int i = tid; i < 192; i += kWG) L.w5[i] = phi[kW5 + i];
-    for (int i = tid; i < 4; i += kWG) L.b5[i] = i < 3 ? phi[kB5 + i] : 0.0f;
     if (tid < 64) {   // wave 0, identical values
         L.s1 = s1; L.s2 = s2; L.s4 = s4;
-        L.c5t = range_exp(n5t * kTop);
         L.s4t = range_exp(n4t * kTop);
         L.s2t = range_exp(n2t * kTop);
-        L.mw2 = mw2;
     }
     __syncthreads();
 }
@@ -751,26 +536,14 @@ __device__ __forceinline__ ItemScale item_scale(const NetLds &L, float X) {
     return s;
 }
 
-// Scaled biases of the item's encoder layers and a copy of the scales in
-// L.isc (threads < 64; the caller's next barrier publishes them).
+// Scaled biases of the encoder layers (threads < 64; the caller's next barrier
+// publishes them).
 __device__ __forceinline__ void item_biases(NetLds &L, const ItemScale &s) {
     if (threadIdx.x < 64) {
         const int i = threadIdx.x;
         L.b1s[i] = L.b1[i] * pow2(s.a1);
         L.b2s[i] = L.b2[i] * pow2(s.af);
-        L.isc = s;   // identical values from every lane
     }
-}
-
-// The item's scales as published by item_biases, in scalar registers.
-__device__ __forceinline__ ItemScale item_scale_lds(const NetLds &L) {
-    ItemScale s;
-    s.ax = uniform(L.isc.ax);
-    s.a1 = uniform(L.isc.a1);
-    s.af = uniform(L.isc.af);
-    s.a4 = uniform(L.isc.a4);
-    s.xmul = uniform(L.isc.xmul);
-    return s;
 }
 
 // Input bound of item (patch k) given the largest |u_hat| component of its nodes.
@@ -816,333 +589,6 @@ __device__ __forceinline__ void split_chain(const floatx4 x[4], half8 bh[2], hal
         for (int e = 0; e < 8; ++e) v[e] = x[2 * s + (e >> 2)][e & 3];
         split8(v, bh[s], bl[s]);
     }
-}
-
-// Network input of this lane's node, scaled by xmul: lane group q = lane >> 4
-// supplies input features 8 q .. 8 q + 7 of [p - o_k (3), n (3), U_hat (3)],
-// zero padded to 32.
-__device__ __forceinline__ void load_x_raw(const MeshDev &M, int k, int gnode, bool valid, const float *uhn,
-                                           int n_max, int lnode, float xmul, float (&v)[8]) {
-    const int q = lane_id() >> 4;
-    const int N = M.N;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = 0.0f;
-    if (valid && q == 0) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            v[a] = (M.pos[(size_t)a * N + gnode] - M.origin[3 * k + a]) * xmul;
-            v[3 + a] = M.nrm[(size_t)a * N + gnode] * xmul;
-        }
-        v[6] = uhn[lnode] * xmul;
-        v[7] = uhn[(size_t)n_max + lnode] * xmul;
-    } else if (valid && q == 1) {
-        v[0] = uhn[(size_t)2 * n_max + lnode] * xmul;
-    }
-}
-
-// y = W x + acc over the two K steps of a 64 -> 64 layer in T form; the three
-// split passes run pass-outermost over the four output blocks, so no MFMA
-// waits on the one before it (each block sees hi*hi, hi*lo, lo*hi per step).
-__device__ __forceinline__ void layer64_t(const half8 *wh, const half8 *wl, const half8 bh[2], const half8 bl[2],
-                                          floatx4 acc[4]) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        half8 h[4], l[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            h[ot] = wh[(ot * 2 + s) * 64 + lane];
-            l[ot] = wl[(ot * 2 + s) * 64 + lane];
-        }
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) acc[ot] = mfma16(h[ot], bh[s], acc[ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) acc[ot] = mfma16(h[ot], bl[s], acc[ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) acc[ot] = mfma16(l[ot], bh[s], acc[ot]);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// node inputs staged in LDS for the network passes
-//
-// xs[f][j], f = 0..8: [p - o_k (3), n (3), a third triple] of staged node j.
-// The third triple is U_hat (network input) or, in the adjoint's pass over
-// passive nodes, dL/dU (U_hat is 0 there).  One parallel gather per chunk of
-// kStage nodes replaces dependent global loads per 16-node tile.
-// ---------------------------------------------------------------------------
-constexpr int kStage = 1024;
-typedef float StageBuf[9][kStage];
-
-// Stage nodes c0 + j (list == nullptr) or list[c0 + j], j < cnt; the
-// geometric features are multiplied by xmul, the third triple
-// third[c * stride + off + node] by tmul (zeros when third is null).
-// Whole workgroup; the caller brackets it with barriers.
-__device__ __forceinline__ void stage_nodes(const MeshDev &M, int k, int base, const int *list, int c0, int cnt,
-                                            const float *third, size_t stride, size_t off, float xmul, float tmul,
-                                            StageBuf &xs) {
-    const int N = M.N;
-    const float o0 = M.origin[3 * k], o1 = M.origin[3 * k + 1], o2 = M.origin[3 * k + 2];
-    for (int j = threadIdx.x; j < cnt; j += kWG) {
-        const int i = list ? list[c0 + j] : c0 + j;
-        const int g = base + i;
-        xs[0][j] = (M.pos[g] - o0) * xmul;
-        xs[1][j] = (M.pos[N + g] - o1) * xmul;
-        xs[2][j] = (M.pos[2 * N + g] - o2) * xmul;
-        xs[3][j] = M.nrm[g] * xmul;
-        xs[4][j] = M.nrm[N + g] * xmul;
-        xs[5][j] = M.nrm[2 * N + g] * xmul;
-        xs[6][j] = third ? third[off + i] * tmul : 0.0f;
-        xs[7][j] = third ? third[stride + off + i] * tmul : 0.0f;
-        xs[8][j] = third ? third[2 * stride + off + i] * tmul : 0.0f;
-    }
-}
-
-// T-form network input of staged node j (lane group q supplies features
-// 8 q .. 8 q + 7, zero padded to 32); with ZERO_U the U_hat features are 0.
-template <bool ZERO_U>
-__device__ __forceinline__ void stage_x(const StageBuf &xs, int j, bool valid, half8 &xh, half8 &xl) {
-    const int q = lane_id() >> 4;
-    // every lane reads inside the stage (j < kStage) and masks: no branches
-    const bool g0 = valid && q == 0, g1 = valid && q == 1 && !ZERO_U;
-    float v[8];
-#pragma unroll
-    for (int e = 0; e < 6; ++e) {
-        const float x = xs[e][j];
-        v[e] = g0 ? x : 0.0f;
-    }
-    const float u0 = xs[6][j], u1 = xs[7][j], u2 = xs[8][j];
-    v[6] = (g0 && !ZERO_U) ? u0 : 0.0f;
-    v[7] = (g0 && !ZERO_U) ? u1 : 0.0f;
-    v[0] = g1 ? u2 : v[0];
-    split8(v, xh, xl);
-}
-
-// Encoder: h1 = relu(W1 x + b1), f = relu(W2 h1 + b2) for a 16-node tile of
-// scaled inputs (2^ax x); h1 and f come out at the item's scales 2^a1, 2^af.
-__device__ __forceinline__ void encoder_tile(const NetLds &L, const half8 &xh, const half8 &xl, floatx4 h1[4],
-                                             floatx4 f[4]) {
-    reload_fence();
-    const int lane = lane_id(), gq = lane >> 4;
-    half8 wh[4], wl[4];
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        wh[ot] = L.w1h[ot * 64 + lane];
-        wl[ot] = L.w1l[ot * 64 + lane];
-        h1[ot] = *reinterpret_cast<const floatx4 *>(&L.b1s[ot * 16 + 4 * gq]);
-    }
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) h1[ot] = mfma16(wh[ot], xh, h1[ot]);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) h1[ot] = mfma16(wh[ot], xl, h1[ot]);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) h1[ot] = relu4(mfma16(wl[ot], xh, h1[ot]));
-    half8 bh[2], bl[2];
-    split_chain(h1, bh, bl);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) f[ot] = *reinterpret_cast<const floatx4 *>(&L.b2s[ot * 16 + 4 * gq]);
-    layer64_t(L.w2h, L.w2l, bh, bl, f);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) f[ot] = relu4(f[ot]);
-}
-
-// Encoder of two independent 16-node tiles at once: the weight fragments are
-// read once for both.  Each tile's MFMAs of a K step are issued together, so
-// the first tile's ReLU and split overlap the second tile's MFMAs.
-__device__ __forceinline__ void encoder_tile2(const NetLds &L, const half8 (&xh)[2], const half8 (&xl)[2],
-                                              floatx4 (&f)[2][4]) {
-    reload_fence();
-    const int lane = lane_id(), gq = lane >> 4;
-    floatx4 h1[2][4];
-    {
-        half8 wh[4], wl[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            wh[ot] = L.w1h[ot * 64 + lane];
-            wl[ot] = L.w1l[ot * 64 + lane];
-            const floatx4 b = *reinterpret_cast<const floatx4 *>(&L.b1s[ot * 16 + 4 * gq]);
-            h1[0][ot] = b;
-            h1[1][ot] = b;
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(wh[ot], xh[u], h1[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(wh[ot], xl[u], h1[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h1[u][ot] = relu4(mfma16(wl[ot], xh[u], h1[u][ot]));
-        }
-    }
-    half8 bh[2][2], bl[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) split_chain(h1[u], bh[u], bl[u]);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(&L.b2s[ot * 16 + 4 * gq]);
-        f[0][ot] = b;
-        f[1][ot] = b;
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        half8 h[4], l[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            h[ot] = L.w2h[(ot * 2 + s) * 64 + lane];
-            l[ot] = L.w2l[(ot * 2 + s) * 64 + lane];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(h[ot], bh[u][s], f[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(h[ot], bl[u][s], f[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(l[ot], bh[u][s], f[u][ot]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) f[u][ot] = relu4(f[u][ot]);
-}
-
-// Decoder: h4 = relu(W4 [f; g'] + b4) with the g' part folded into c4, then
-// r = W5 h4 + b5.  h4 comes out at 2^a4 and r_mul = 2^-a4 unscales the W5
-// sum.  Every lane returns r of its node (lane & 15).
-__device__ __forceinline__ void decoder_tile(const NetLds &L, const floatx4 f[4], float r_mul, floatx4 h4[4],
-                                             float r_out[3]) {
-    reload_fence();
-    const int lane = lane_id(), gq = lane >> 4;
-    half8 bh[2], bl[2];
-    split_chain(f, bh, bl);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) h4[ot] = *reinterpret_cast<const floatx4 *>(&L.c4[ot * 16 + 4 * gq]);
-    layer64_t(L.w4h, L.w4l, bh, bl, h4);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) h4[ot] = relu4(h4[ot]);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        float s = 0.0f;
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            const floatx4 w = *reinterpret_cast<const floatx4 *>(&L.w5[c * 64 + ot * 16 + 4 * gq]);
-            s += w[0] * h4[ot][0] + w[1] * h4[ot][1] + w[2] * h4[ot][2] + w[3] * h4[ot][3];
-        }
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        r_out[c] = s * r_mul + L.b5[c];
-    }
-}
-
-// Decoder of two independent tiles at once (each tile's results identical to
-// decoder_tile's): the W4 fragments are read once for both, and each tile's
-// MFMAs of a K step are issued together.
-__device__ __forceinline__ void decoder_tile2(const NetLds &L, const floatx4 (&f)[2][4], float r_mul,
-                                              float (&r_out)[2][3]) {
-    reload_fence();
-    const int lane = lane_id(), gq = lane >> 4;
-    half8 bh[2][2], bl[2][2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) split_chain(f[u], bh[u], bl[u]);
-    floatx4 h4[2][4];
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(&L.c4[ot * 16 + 4 * gq]);
-        h4[0][ot] = b;
-        h4[1][ot] = b;
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        half8 h[4], l[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            h[ot] = L.w4h[(ot * 2 + s) * 64 + lane];
-            l[ot] = L.w4l[(ot * 2 + s) * 64 + lane];
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h4[u][ot] = mfma16(h[ot], bh[u][s], h4[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h4[u][ot] = mfma16(h[ot], bl[u][s], h4[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) h4[u][ot] = mfma16(l[ot], bh[u][s], h4[u][ot]);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h4[u][ot] = relu4(h4[u][ot]);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            float s = 0.0f;
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) {
-                const floatx4 w = *reinterpret_cast<const floatx4 *>(&L.w5[c * 64 + ot * 16 + 4 * gq]);
-                s += w[0] * h4[u][ot][0] + w[1] * h4[u][ot][1] + w[2] * h4[u][ot][2] + w[3] * h4[u][ot][3];
-            }
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
-            r_out[u][c] = s * r_mul + L.b5[c];
-        }
-    }
-}
-
-// The global MLP's weights this thread uses (row tid & 63, input features
-// 16 (tid >> 6) .. + 15 of W3 and of W4[:, 64:], and the row's biases): the
-// persistent forward loads them once and keeps them in registers across its
-// items instead of reading them for every item.
-struct GmlpW {
-    float w3[16], w4[16], b3, b4;
-};
-
-__device__ __forceinline__ GmlpW load_gmlp(const float *phi) {
-    const int tid = threadIdx.x, o = tid & 63, w = tid >> 6;
-    GmlpW g;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {
-        g.w3[c] = phi[kW3 + o * 64 + 16 * w + c];
-        g.w4[c] = phi[kW4 + o * 128 + 64 + 16 * w + c];
-    }
-    g.b3 = phi[kB3 + o];
-    g.b4 = phi[kB4 + o];
-    return g;
-}
-
-// Global MLP of one item from the (unscaled) pooled feature in L.g:
-// g' = relu(W3 g + b3) and c4 = W4[:, 64:] g' + b4, stored at h4's scale
-// 2^a4.  Whole workgroup; each wave sums 16 input features and the four
-// partials are added in wave order.
-__device__ void global_mlp(NetLds &L, const GmlpW &gw, const ItemScale &sc) {
-    const int tid = threadIdx.x, o = tid & 63, w = tid >> 6;
-    float acc = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc += gw.w3[c] * L.g[16 * w + c];
-    L.part[w][o] = acc;
-    __syncthreads();
-    if (tid < 64) {
-        float s = gw.b3;
-        for (int q = 0; q < kWaves; ++q) s += L.part[q][o];
-        L.gp[o] = fmaxf(s, 0.0f);
-    }
-    __syncthreads();
-    acc = 0.0f;
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc += gw.w4[c] * L.gp[16 * w + c];
-    L.part[w][o] = acc;
-    __syncthreads();
-    if (tid < 64) {
-        float s = gw.b4;
-        for (int q = 0; q < kWaves; ++q) s += L.part[q][o];
-        L.c4[o] = s * pow2(sc.a4);
-    }
-    __syncthreads();
-}
-
-// The same, its weights read for this item.
-__device__ __forceinline__ void global_mlp(NetLds &L, const float *phi, const ItemScale &sc) {
-    global_mlp(L, load_gmlp(phi), sc);
 }
 
 }  // namespace etac

@@ -19,7 +19,7 @@
 // product of a patch matrix with their u_hat columns, on the matrix cores.
 #include <algorithm>
 
-#include "etac_device.h"
+#include "etac_step.h"
 
 namespace etac {
 
@@ -111,417 +111,11 @@ hipError_t launch_contact_rows(const Plan &p, const SceneDev &s, int8_t *cobj, f
 // ---------------------------------------------------------------------------
 // step
 // ---------------------------------------------------------------------------
-struct StepParams {
-    MeshDev mesh;
-    TileDev tile;
-    TableDev tab;
-    ItemDev itm;
-    SceneDev scene;
-    ModelDev model;
-    int E;
-    int splits;              // workgroups per env of the contact pass
-    int dense;               // 1: every item is listed (no k_live), those without contact are passed over
-    int table_units, matrix_units;
-    const int8_t *cobj_in;   // propagate-only: given contact results
-    const float *uhat_in;
-    float *u;                // [3][E][N]
-    int8_t *cobj_out;        // [E][N] (fused step)
-    int32_t *n_active;       // [E][K]
-    int32_t *n_touch;        // [E][K] active nodes won by external objects (hand), or null
-    uint32_t *saved;         // [E K][kSavedWords] pooling record for the adjoint, or null
-};
-
-__device__ __forceinline__ bool step_residual(const StepParams &p) { return p.model.mode != ETAC_DECAY_ONLY; }
-__device__ __forceinline__ bool step_decay(const StepParams &p) { return p.model.mode != ETAC_RESIDUAL_ONLY; }
-
-// Words of patch k, and its count of envs to visit.
-__device__ __forceinline__ int live_count(const StepParams &p, int k) { return p.dense ? p.E : p.itm.live_cnt[k]; }
-__device__ __forceinline__ int live_env(const StepParams &p, int k, int q) {
-    return p.dense ? q : p.itm.live[(size_t)k * p.E + q];
-}
-
-struct ContactLds {
-    int cnt[kMaxPatches];
-    int tcnt[kMaxPatches];
-    unsigned cand[kMaxPatches];
-};
-
-// Contact of env e's words s, s + S, ... : a wave takes a word, a lane a node.
-// Winners and u_hat stream out (0 and -1 where there is no contact), and a bit
-// per node is kept.  Bound by those stores: the same 13 bytes a node as the
-// contact pass alone, plus a word of bits.
-template <bool FROM_INPUT, bool ROWS>
-__device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
-    const MeshDev &M = p.mesh;
-    const SceneDev &S = p.scene;
-    const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
-    const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        L.cnt[k] = 0;
-        L.tcnt[k] = 0;
-        L.cand[k] = FROM_INPUT ? ~0u : cull_objects(S, M, e, k);
-    }
-    __syncthreads();
-    const bool want_umax = step_residual(p);
-    const int NW = p.tile.NW, step = p.splits * kWaves;
-    int4 next = p.tile.word[min(s * kWaves + wave, NW - 1)];
-    for (int w = s * kWaves + wave; w < NW; w += step) {
-        const int4 inf = next;
-        next = p.tile.word[min(w + step, NW - 1)];
-        const int k = uniform(inf.x), i = uniform(inf.y) + lane;
-        const bool valid = lane < uniform(inf.z);
-        const unsigned c = uniform(L.cand[k]);
-        int best = -1;
-        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-        int8_t id = -1;
-        bool touch = false;
-        if (FROM_INPUT) {
-            if (valid && p.cobj_in[row + i] >= 0) {
-                best = 0;
-                u0 = p.uhat_in[row + i];
-                u1 = p.uhat_in[EN + row + i];
-                u2 = p.uhat_in[2 * EN + row + i];
-            }
-        } else if (c) {
-            if (valid) {
-                const size_t srow = ROWS ? scene_row(S, e, k) : (size_t)e;
-                best = contact_node(S, srow, c, M.pos[i], M.pos[N + i], M.pos[2 * N + i], M.nrm[i], M.nrm[N + i],
-                                    M.nrm[2 * N + i], u0, u1, u2);
-                id = (int8_t)best;
-                if (ROWS && best >= 0) {
-                    touch = S.n_ext && best < S.n_ext[srow];
-                    if (S.src) id = S.src[srow * S.O + best];
-                }
-            }
-        }
-        if (valid) {
-            if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
-            __builtin_nontemporal_store(u0, p.u + row + i);
-            __builtin_nontemporal_store(u1, p.u + EN + row + i);
-            __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
-        }
-        const unsigned long long act = __ballot(best >= 0);
-        p.itm.mask[(size_t)e * NW + w] = act;             // every lane stores the same value
-        if (act) {                                        // wave-uniform
-            if (want_umax) {
-                const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
-                p.itm.umax[(size_t)e * NW + w] = m;
-                p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
-            }
-            const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
-            if (lane == 0) {
-                atomicAdd(&L.cnt[k], __popcll(act));
-                if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
-            }
-        }
-    }
-    __syncthreads();
-    int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        const size_t it = (size_t)e * K + k;
-        if (p.splits == 1) {
-            na[it] = L.cnt[k];
-            if (ROWS && p.n_touch) p.n_touch[it] = L.tcnt[k];
-        } else if (L.cnt[k]) {        // zeroed by k_tables
-            atomicAdd(&na[it], L.cnt[k]);
-            if (ROWS && p.n_touch && L.tcnt[k]) atomicAdd(&p.n_touch[it], L.tcnt[k]);
-        }
-    }
-}
-
 template <bool FROM_INPUT, bool ROWS>
 __global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
     __shared__ ContactLds L;
     const int e = blockIdx.x / p.splits;
     contact_env<FROM_INPUT, ROWS>(p, L, e, blockIdx.x - e * p.splits);
-}
-
-// ---------------------------------------------------------------------------
-// tables
-// ---------------------------------------------------------------------------
-struct TableLds {
-    float part[kWaves][64];
-    float bv[kWaves][64];
-};
-
-// Split weight fragments of a 64-input layer (rows `stride` floats apart),
-// straight from the packed parameters into registers.
-__device__ __forceinline__ void load_frag64(const float *w, int stride, float mul, half8 (&h)[4][2], half8 (&l)[4][2]) {
-    const int lane = lane_id(), q = lane >> 4;
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const float *r = w + (size_t)(ot * 16 + (lane & 15)) * stride + 32 * s + 4 * q;
-            floatx4 a, b;
-            __builtin_memcpy(&a, r, 16);
-            __builtin_memcpy(&b, r + 16, 16);
-            const float x[8] = {a[0] * mul, a[1] * mul, a[2] * mul, a[3] * mul,
-                                b[0] * mul, b[1] * mul, b[2] * mul, b[3] * mul};
-            split8(x, h[ot][s], l[ot][s]);
-        }
-}
-
-// Encoder weights of one wave in registers.
-struct EncW {
-    half8 w1h[4], w1l[4], w2h[4][2], w2l[4][2];
-};
-
-__device__ __forceinline__ void load_encoder(const float *phi, int s1, int s2, EncW &W) {
-    const int lane = lane_id(), q = lane >> 4;
-    const float e1 = pow2(s1);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int in = 8 * q + e;
-            x[e] = in < 9 ? phi[kW1 + (ot * 16 + (lane & 15)) * 9 + (in < 9 ? in : 0)] * e1 : 0.0f;
-        }
-        split8(x, W.w1h[ot], W.w1l[ot]);
-    }
-    load_frag64(phi + kW2, 64, pow2(s2), W.w2h, W.w2l);
-}
-
-// The encoder of NT 16-node tiles from register weights: the MFMA sequence of
-// every accumulator is that of encoder_tile.  b1, b2: scaled biases in LDS.
-template <int NT>
-__device__ __forceinline__ void encode(const EncW &W, const float *b1, const float *b2, const half8 (&xh)[NT],
-                                       const half8 (&xl)[NT], floatx4 (&f)[NT][4]) {
-    const int gq = lane_id() >> 4;
-    floatx4 h1[NT][4];
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(&b1[ot * 16 + 4 * gq]);
-#pragma unroll
-        for (int u = 0; u < NT; ++u) h1[u][ot] = b;
-    }
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xh[u], h1[u][ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xl[u], h1[u][ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = relu4(mfma16(W.w1l[ot], xh[u], h1[u][ot]));
-    }
-    half8 bh[NT][2], bl[NT][2];
-#pragma unroll
-    for (int u = 0; u < NT; ++u) split_chain(h1[u], bh[u], bl[u]);
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(&b2[ot * 16 + 4 * gq]);
-#pragma unroll
-        for (int u = 0; u < NT; ++u) f[u][ot] = b;
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int u = 0; u < NT; ++u) {
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2h[ot][s], bh[u][s], f[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2h[ot][s], bl[u][s], f[u][ot]);
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2l[ot][s], bh[u][s], f[u][ot]);
-        }
-#pragma unroll
-    for (int u = 0; u < NT; ++u)
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) f[u][ot] = relu4(f[u][ot]);
-}
-
-// Features of the nodes of words w0, w0 + step, ...: a wave takes 16 nodes of
-// the word.  Latency-bound: one dependent chain of three layers per word,
-// spread over as many workgroups as there are words (up to two per CU).
-struct FeatLds {
-    TableLds t;
-    float b1s[64], b2s[64];
-};
-
-__device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
-    const MeshDev &M = p.mesh;
-    const float *phi = p.model.phi;
-    const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), gq = lane >> 4, N = M.N;
-    net_norms(L.t.part, phi);
-    __syncthreads();
-    int s1, s2, s4;
-    {
-        float v[10];
-#pragma unroll
-        for (int j = 0; j < 10; ++j) {
-            v[j] = L.t.part[0][j];
-            for (int q = 1; q < kWaves; ++q) v[j] = fmaxf(v[j], L.t.part[q][j]);
-        }
-        net_scales(v, s1, s2, s4);
-        s1 = uniform(s1); s2 = uniform(s2); s4 = uniform(s4);
-    }
-    if (w0 == 0) {
-        if (tid < 64) {   // wave 0, identical values
-            p.tab.scale[0] = s1;
-            p.tab.scale[1] = s2;
-            p.tab.scale[2] = s4;
-        }
-        for (int i = tid; i < 4096; i += kWG) {
-            p.tab.w3t[i] = phi[kW3 + (i & 63) * 64 + (i >> 6)];
-            p.tab.w4t[i] = phi[kW4 + (i & 63) * 128 + 64 + (i >> 6)];
-        }
-    }
-    EncW W;
-    load_encoder(phi, s1, s2, W);
-    for (int w = w0; w < p.tile.NW; w += step) {
-        const int4 inf = p.tile.word[w];
-        const int k = uniform(inf.x), start = uniform(inf.y), cnt = uniform(inf.z);
-        const int ax = uniform(range_exp(fmaxf(M.xbound[k], 1.0f)));
-        const int a1 = s1 + ax, af = s2 + a1;
-        __syncthreads();
-        if (tid < 64) {
-            L.b1s[tid] = phi[kB1 + tid] * pow2(a1);
-            L.b2s[tid] = phi[kB2 + tid] * pow2(af);
-        }
-        __syncthreads();
-        const int j = 16 * wave + (lane & 15);
-        const bool valid = j < cnt;
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = 0.0f;
-        if (valid && gq == 0) {
-            const float xmul = pow2(ax);
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                x[a] = (M.pos[(size_t)a * N + start + j] - M.origin[3 * k + a]) * xmul;
-                x[3 + a] = M.nrm[(size_t)a * N + start + j] * xmul;
-            }
-        }
-        half8 xh[1], xl[1];
-        split8(x, xh[0], xl[0]);
-        floatx4 f[1][4];
-        encode<1>(W, L.b1s, L.b2s, xh, xl, f);
-        const float fmul = pow2(-af);
-        if (valid)
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot)
-                *reinterpret_cast<floatx4 *>(p.tab.feat + (size_t)(start + j) * 64 + 16 * ot + 4 * gq) = f[0][ot] * fmul;
-        // largest features of eight nodes, then of the wave's sixteen
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            floatx4 v = valid ? f[0][ot] * fmul : floatx4{-1.0f, -1.0f, -1.0f, -1.0f};
-#pragma unroll
-            for (int off = 1; off <= 4; off <<= 1)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], __shfl_xor(v[r], off));
-            // the eight lanes of a group hold the same values (identical stores)
-            *reinterpret_cast<floatx4 *>(p.tab.max8 + (size_t)(8 * w + 2 * wave + ((lane >> 3) & 1)) * 64 + 16 * ot + 4 * gq) = v;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = fmaxf(v[r], __shfl_xor(v[r], 8));
-            *reinterpret_cast<floatx4 *>(&L.t.bv[wave][16 * ot + 4 * gq]) = v;
-        }
-        // W4[:, :64] f: the decoder's part that no env changes
-        half8 fh[2], fl[2], w4h[4][2], w4l[4][2];
-        split_chain(f[0], fh, fl);
-        load_frag64(phi + kW4, 128, pow2(s4), w4h, w4l);
-        floatx4 z[4];
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            z[ot] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int s = 0; s < 2; ++s) z[ot] = mfma_split(w4h[ot][s], w4l[ot][s], fh[s], fl[s], z[ot]);
-        }
-        const float zmul = pow2(-(s4 + af));
-        if (valid)
-#pragma unroll
-            for (int ot = 0; ot < 4; ++ot)
-                *reinterpret_cast<floatx4 *>(p.tab.dec + (size_t)(start + j) * 64 + 16 * ot + 4 * gq) = z[ot] * zmul;
-        __syncthreads();
-        if (tid < 128) {      // half words 0 and 1: waves 0-1 and 2-3
-            const int h = tid >> 6, c = tid & 63;
-            p.tab.max32[(size_t)(2 * w + h) * 64 + c] = fmaxf(L.t.bv[2 * h][c], L.t.bv[2 * h + 1][c]);
-        }
-    }
-}
-
-// Decay matrices.  W = exp(-alpha |p_j - p_i|) of a near patch as three BF16
-// parts whose sum is the FP32 value (24 bits: RNE of the value and of the two
-// exact remainders), in the order the matrix cores take as A operand: row tile
-// t (16 nodes i), K step s (32 nodes j), part c, lane l: row 16 t + (l & 15),
-// columns 32 s + 8 (l >> 4) + 0..7 at 16-byte unit ((t KS + s) 3 + c) 64 + l.
-// Entries beyond the patch are 0.  A workgroup takes a row tile, its waves the
-// K steps in turn.  The exponent keeps the remainders of the root and of the
-// product, so a weight is good to the rounding of v_exp_f32.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-
-// x = b0 + b1 + b2 for eight values (24 bits; exact unless a part underflows).
-__device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&b)[3]) {
-    uint4t o[3];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        floatx2 v = {x[2 * e], x[2 * e + 1]};
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const unsigned h = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-            o[c][e] = h;
-            if (c < 2) {
-                v[0] -= __uint_as_float(h << 16);
-                v[1] -= __uint_as_float(h & 0xffff0000u);
-            }
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) b[c] = __builtin_bit_cast(bf16x8, o[c]);
-}
-
-__device__ __forceinline__ float decay_weight(float dx, float dy, float dz, float nb_hi, float nb_lo) {
-    const float s = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    const float d = __builtin_amdgcn_sqrtf(s);
-    // d + dl is the root of s: dl = (s - d^2) / (2 d)
-    const float dl = d > 0.0f ? 0.5f * fmaf(-d, d, s) * __builtin_amdgcn_rcpf(d) : 0.0f;
-    const float t = nb_hi * d;
-    const float tl = fmaf(nb_hi, d, -t) + fmaf(nb_lo, d, nb_hi * dl);
-    const float w = __builtin_amdgcn_exp2f(t);
-    return fmaf(w, 0.69314718f * tl, w);
-}
-
-// -alpha log2(e) as a sum of two floats.
-__device__ __forceinline__ void decay_rate(float alpha, float &hi, float &lo) {
-    const double b = -(double)alpha * 1.4426950408889634;
-    hi = (float)b;
-    lo = (float)(b - (double)hi);
-}
-
-__device__ void matrix_row_tile(const StepParams &p, int unit) {
-    const MeshDev &M = p.mesh;
-    const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), N = M.N;
-    const int2 rt = p.tile.row_tile[unit];
-    const int k = uniform(rt.x);
-    unit = uniform(rt.y);
-    const int base = M.offset[k], n = M.offset[k + 1] - base, KS = (n + 31) >> 5;
-    float hi, lo;
-    decay_rate(p.model.alpha[k], hi, lo);
-    const int i = 16 * unit + (lane & 15);
-    const int gi = base + min(i, n - 1);
-    const float px = M.pos[gi], py = M.pos[N + gi], pz = M.pos[2 * N + gi];
-    uint4 *w = p.tab.w + p.tile.w_off[k] + (size_t)unit * KS * 3 * 64 + lane;
-    for (int s = wave; s < KS; s += kWaves) {
-        const int j0 = 32 * s + 8 * (lane >> 4);
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int gj = base + min(j0 + e, n - 1);
-            const float v = decay_weight(M.pos[gj] - px, M.pos[N + gj] - py, M.pos[2 * N + gj] - pz, hi, lo);
-            x[e] = (i < n && j0 + e < n) ? v : 0.0f;
-        }
-        bf16x8 b[3];
-        split_bf16x3(x, b);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) w[(size_t)(s * 3 + c) * 64] = __builtin_bit_cast(uint4, b[c]);
-    }
-}
-
-__device__ __forceinline__ void table_block(const StepParams &p, FeatLds &L, int b) {
-    if (b < p.table_units) table_words(p, L, b, p.table_units);
-    else matrix_row_tile(p, b - p.table_units);
 }
 
 // Tables, and zero counts where the contact pass adds to them.
@@ -577,59 +171,6 @@ __global__ __launch_bounds__(1024) void k_live(const int32_t *n_active, int E, i
 // ---------------------------------------------------------------------------
 // max-pool and global MLP of the items in contact
 // ---------------------------------------------------------------------------
-
-// Units of the live lists: first unit of every patch (in queue order, largest
-// patch first) given `per(k)` units each.  Whole workgroup of NW waves; ends
-// with a barrier.  Returns the total.
-template <int NWV, typename F>
-__device__ int unit_prefix(int K, int *first, F per) {
-    // K is small (16 on a hand): one wave scans 64 patches at a time
-    if (threadIdx.x < 64) {
-        int run = 0;
-        for (int k0 = 0; k0 < K; k0 += 64) {
-            const int kk = k0 + lane_id();
-            const int c = kk < K ? per(kk) : 0;
-            int inc = c;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const int o = __shfl_up(inc, off);
-                if (lane_id() >= off) inc += o;
-            }
-            if (kk < K) first[kk] = run + inc - c;
-            run += uniform(__shfl(inc, 63));
-        }
-        first[K] = run;     // identical stores
-    }
-    __syncthreads();
-    return uniform(first[K]);
-}
-
-// Queue position (patch rank) of unit u: the last rank whose first unit is <= u.
-__device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
-    int lo = 0, hi = K - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (first[mid] <= u) lo = mid;
-        else hi = mid - 1;
-    }
-    return uniform(lo);
-}
-
-// Global MLP of an item from its pooled feature (lane c holds channel c):
-// g' = relu(W3 g + b3), c4 = W4[:, 64:] g' + b4, lane o forms row o as four
-// partial sums of 16 terms in order.
-__device__ __forceinline__ float matvec64(const float *wt, float x, float bias) {
-    float s = bias;
-#pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
-        float a = 0.0f;
-#pragma unroll
-        for (int c = 0; c < 16; ++c)
-            a += wt[(16 * q + c) * 64 + lane_id()] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16 * q + c));
-        s += a;
-    }
-    return s;
-}
 
 // A pooled candidate: feature bits over the complement of the node, so that
 // the larger key is the larger feature, the lowest node on ties (features are
@@ -735,13 +276,13 @@ __device__ unsigned long long pool_passive(const StepParams &p, PassiveLds<PCW> 
 }
 
 // Words of an active chunk.
-constexpr int kActiveWords = 4;
+constexpr int kActiveWords = 8;
 
 struct ActiveLds {
     float b1s[64], b2s[64];
     float v[64];
     int ix[64];
-    uint8_t slot[64 * kActiveWords];
+    uint16_t slot[64 * kActiveWords];
 };
 
 // Largest feature of the active nodes among `words` words from word wf of the
@@ -761,7 +302,7 @@ __device__ unsigned long long pool_active(const StepParams &p, ActiveLds &L, con
         if (t >= words) break;
         const unsigned long long m = mask[wf + t];
         const unsigned long long act = ((unsigned long long)uniform((unsigned)(m >> 32)) << 32) | uniform((unsigned)m);
-        if ((act >> lane) & 1ull) L.slot[total + lanes_below(act)] = (uint8_t)(64 * t + lane);
+        if ((act >> lane) & 1ull) L.slot[total + lanes_below(act)] = (uint16_t)(64 * t + lane);
         total += __popcll(act);
     }
     if (total == 0) return 0ull;
@@ -782,34 +323,54 @@ __device__ unsigned long long pool_active(const StepParams &p, ActiveLds &L, con
     for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
         for (int r = 0; r < 4; ++r) { mx[ot][r] = -1.0f; mi[ot][r] = 0x7fffffff; }
+    // raw inputs of the next two tiles are requested while these run (lane
+    // group 0 holds eight, group 1 the ninth)
+    float raw[2][8];
+    int next[2];
+    auto fetch = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int j = min(t0 + 16 * u + (lane & 15), total - 1);
+            next[u] = L.slot[j];
+            const int g = base + 64 * wf + next[u];
+            const float *uh = uhat_source(p) + (size_t)e * N + g;
+            if (gq == 0) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    raw[u][c] = M.pos[(size_t)c * N + g];
+                    raw[u][3 + c] = M.nrm[(size_t)c * N + g];
+                }
+                raw[u][6] = uh[0];
+                raw[u][7] = uh[EN];
+            } else if (gq == 1) {
+                raw[u][0] = uh[2 * EN];
+            }
+        }
+    };
+    fetch(0);
     for (int t0 = 0; t0 < total; t0 += 32) {
         half8 xh[2], xl[2];
         int node[2];
         bool valid[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int j = t0 + 16 * u + (lane & 15);
-            valid[u] = j < total;
-            node[u] = 64 * wf + (valid[u] ? L.slot[j] : 0);
+            valid[u] = t0 + 16 * u + (lane & 15) < total;
+            node[u] = 64 * wf + next[u];
             float x[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) x[c] = 0.0f;
-            const int g = base + node[u];
-            const float *uh = p.u + (size_t)e * N + g;
             if (valid[u] && gq == 0) {
-                x[0] = (M.pos[g] - o0) * xmul;
-                x[1] = (M.pos[N + g] - o1) * xmul;
-                x[2] = (M.pos[2 * N + g] - o2) * xmul;
-                x[3] = M.nrm[g] * xmul;
-                x[4] = M.nrm[N + g] * xmul;
-                x[5] = M.nrm[2 * N + g] * xmul;
-                x[6] = uh[0] * xmul;
-                x[7] = uh[EN] * xmul;
+                x[0] = (raw[u][0] - o0) * xmul;
+                x[1] = (raw[u][1] - o1) * xmul;
+                x[2] = (raw[u][2] - o2) * xmul;
+#pragma unroll
+                for (int c = 3; c < 8; ++c) x[c] = raw[u][c] * xmul;
             } else if (valid[u] && gq == 1) {
-                x[0] = uh[2 * EN] * xmul;
+                x[0] = raw[u][0] * xmul;
             }
             split8(x, xh[u], xl[u]);
         }
+        if (t0 + 32 < total) fetch(t0 + 32);
         floatx4 f[2][4];
         encode<2>(W, L.b1s, L.b2s, xh, xl, f);
 #pragma unroll
@@ -855,6 +416,10 @@ __device__ __forceinline__ void pool_finish(const StepParams &p, size_t item, un
         rec[64 + lane] = ~(unsigned)key;
     }
     const float gp = fmaxf(matvec64(p.tab.w3t, v, phi[kB3 + lane]), 0.0f);
+    if (p.ivec) {
+        p.ivec[item * 256 + 64 + lane] = gp;
+        p.ivec[item * 256 + 192 + lane] = v;
+    }
     p.itm.c4[item * 64 + lane] = matvec64(p.tab.w4t, gp, phi[kB4 + lane]);
 }
 
@@ -934,18 +499,25 @@ __global__ __launch_bounds__(kWG) void k_pool_finish(StepParams p) {
         const ItemRef it = item_ref(p, first, q, 1 << 20);
         const size_t item = (size_t)it.e * K + it.k;
         if (p.dense && uniform(na[item]) == 0) continue;
-        pool_finish(p, item, p.itm.pool[item * 64 + lane_id()]);
+        unsigned long long key;
+        if (p.recall) {      // the forward's record
+            const uint32_t *rec = p.recall + item * kSavedWords;
+            key = ((unsigned long long)rec[lane_id()] << 32) | (unsigned)~rec[64 + lane_id()];
+        } else {
+            key = p.itm.pool[item * 64 + lane_id()];
+        }
+        pool_finish(p, item, key);
     }
 }
 
 // The same in one launch, a workgroup of eight waves per item, for batches of
 // few small patches, where a launch costs more than the idle waves.
-constexpr int kPoolWaves = 8;
+constexpr int kPoolWaves = 8, kPoolWords = 4;
 
 struct PoolLds {
     unsigned long long key[64];
     union {
-        PassiveLds<kActiveWords> pas;
+        PassiveLds<kPoolWords> pas;
         ActiveLds act;
     } w[kPoolWaves];
 };
@@ -966,12 +538,12 @@ __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu
         if (uniform(na[item]) == 0) continue;      // the same in every wave
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
         const int w0 = uniform(p.tile.word_off[k]), nw = uniform(p.tile.word_off[k + 1]) - w0;
-        const int chunks = (nw + kActiveWords - 1) / kActiveWords;
+        const int chunks = (nw + kPoolWords - 1) / kPoolWords;
         __syncthreads();          // the previous item is done with L
         if (threadIdx.x < 64) L.key[lane] = 0ull;
         __syncthreads();
         for (int t = wave; t < 2 * chunks; t += kPoolWaves) {
-            const int wf = (t >> 1) * kActiveWords, words = min(kActiveWords, nw - wf);
+            const int wf = (t >> 1) * kPoolWords, words = min(kPoolWords, nw - wf);
             const unsigned long long key =
                 (t & 1) ? pool_passive(p, L.w[wave].pas, base, n, w0, wf, words, p.itm.mask + (size_t)e * p.tile.NW + w0)
                         : pool_active(p, L.w[wave].act, W, rb1, rb2, s1, s2, k, e, base, nw, w0, wf, words);
@@ -985,42 +557,6 @@ __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu
 // ---------------------------------------------------------------------------
 // U of the passive nodes: near patches
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ floatx4 mfma_bf16(const bf16x8 &a, const bf16x8 &b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-// acc += A B with three-part operands: every product of parts down to 2^-24 of
-// the whole, smallest first.
-__device__ __forceinline__ floatx4 mfma_bf16x3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx4 acc) {
-    acc = mfma_bf16(a[2], b[0], acc);
-    acc = mfma_bf16(a[0], b[2], acc);
-    acc = mfma_bf16(a[1], b[1], acc);
-    acc = mfma_bf16(a[1], b[0], acc);
-    acc = mfma_bf16(a[0], b[1], acc);
-    return mfma_bf16(a[0], b[0], acc);
-}
-
-// Eight consecutive values x[j0 .. j0 + 7] of a patch of n nodes (0 beyond it).
-__device__ __forceinline__ void load8(const float *x, int j0, int n, float (&v)[8]) {
-    if (j0 + 8 <= n) {
-        floatx4 a, b;
-        __builtin_memcpy(&a, x + j0, 16);
-        __builtin_memcpy(&b, x + j0 + 4, 16);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = j0 + e < n ? x[j0 + e] : 0.0f;
-    }
-}
-
-// Whether a weight of patch k could overflow (alpha < 0 on a wide patch): the
-// matrix then holds infinities, which a product would spread to nodes that
-// have no such pair; such a patch is summed pair by pair.
-__device__ __forceinline__ bool matrix_overflows(const MeshDev &M, float alpha, int k) {
-    return alpha < 0.0f && -alpha * 1.4427f * 2.0f * M.bound[k].w > 120.0f;
-}
-
 // Eq. 1 of one node over the active nodes of its item, pair by pair.
 __device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *src, floatx4 (&s)[3], int x) {
     const MeshDev &M = p.mesh;
@@ -1033,11 +569,12 @@ __device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *
     double a0 = 0.0, a1 = 0.0, a2 = 0.0;
     for (int j = 0; j < n; ++j) {
         if (!((mask[j >> 6] >> (j & 63)) & 1ull)) continue;
+        float d;
         const float w = decay_weight(M.pos[base + j] - M.pos[base + i], M.pos[N + base + j] - M.pos[N + base + i],
-                                     M.pos[2 * N + base + j] - M.pos[2 * N + base + i], hi, lo);
-        a0 += w * u[j];
-        a1 += w * u[EN + j];
-        a2 += w * u[2 * EN + j];
+                                     M.pos[2 * N + base + j] - M.pos[2 * N + base + i], hi, lo, d);
+        a0 += (double)w * u[j];      // products beyond FP32's range stay finite
+        a1 += (double)w * u[EN + j];
+        a2 += (double)w * u[2 * EN + j];
     }
     // element x of the four (no register indexed at run time)
 #pragma unroll
@@ -1096,10 +633,6 @@ __device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, in
         }
     }
 }
-
-// Where Eq. 1 reads the active nodes' u_hat: the caller's own on given contact
-// results, else the step's output, whose active entries are u_hat.
-__device__ __forceinline__ const float *uhat_source(const StepParams &p) { return p.uhat_in ? p.uhat_in : p.u; }
 
 // Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs (two column
 // tiles per component: column l & 15 is an env).  Per K step a wave issues
@@ -1390,7 +923,9 @@ __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
 // ---------------------------------------------------------------------------
 
 // Active nodes of every live far item in the patch's spatial order, with a box
-// per 32 of them.
+// per 32 of them (in the adjoint its passive nodes: the sources of its sums
+// are listed, PASSIVE).
+template <bool PASSIVE>
 __global__ __launch_bounds__(1024) void k_far_list(StepParams p) {
     __shared__ int first[kMaxPatches + 1];
     __shared__ int wsum[16];
@@ -1402,12 +937,12 @@ __global__ __launch_bounds__(1024) void k_far_list(StepParams p) {
         const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]), e = uniform(live_env(p, k, q - first[kk]));
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
         const unsigned long long *mask = p.itm.mask + (size_t)e * T.NW + T.word_off[k];
-        int *list = p.itm.alist + (size_t)e * N + base;
+        int *list = (PASSIVE ? p.itm.plist : p.itm.alist) + (size_t)e * N + base;
         int run = 0;
         for (int i0 = 0; i0 < n; i0 += 1024) {
             const int i = i0 + threadIdx.x;
             const int node = i < n ? T.perm[base + i] : 0;
-            const bool f = i < n && ((mask[node >> 6] >> (node & 63)) & 1ull);
+            const bool f = i < n && (((mask[node >> 6] >> (node & 63)) & 1ull) != 0ull) != PASSIVE;
             const unsigned long long bal = __ballot(f);
             __syncthreads();
             wsum[wave] = __popcll(bal);
@@ -1422,7 +957,7 @@ __global__ __launch_bounds__(1024) void k_far_list(StepParams p) {
         }
         __threadfence_block();
         __syncthreads();
-        float4 *box = p.itm.abox + 2 * ((size_t)e * p.itm.NB + p.itm.box_off[k]);
+        float4 *box = (PASSIVE ? p.itm.pbox : p.itm.abox) + 2 * ((size_t)e * p.itm.NB + p.itm.box_off[k]);
         for (int t0 = 0; t0 < run; t0 += 1024) {
             const int t = t0 + threadIdx.x;
             const bool ok = t < run;
@@ -1578,17 +1113,62 @@ static void launch_contact_items(const StepParams &p, bool merged, int nt, hipSt
     }
 }
 
-hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int n_envs,
-                       const int8_t *cobj_in, const float *uhat_in, float *u, int8_t *cobj_out,
-                       int32_t *n_active, uint32_t *saved, hipStream_t st, int32_t *n_touch) {
-    if (n_envs == 0) return hipSuccess;
-    StepParams p;
+void shape_step(const Plan &pl, StepParams &p) {
     p.mesh = pl.mesh;
     p.tile = pl.tile;
     p.tab = pl.tab;
     p.itm = pl.itm;
-    if (s) p.scene = *s;
-    else p.scene = SceneDev{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 1};
+    p.cus = pl.cu_count;
+    p.items = (long long)p.E * pl.K;
+    p.words = (long long)p.E * pl.tile.NW;
+    p.table_units = p.model.mode != ETAC_DECAY_ONLY ? std::min(pl.tile.NW, 2 * pl.cu_count) : 0;
+    p.matrix_units = p.model.mode != ETAC_RESIDUAL_ONLY ? pl.tile.near_rows : 0;
+    // Small batches: tables and contact share a launch and every item is
+    // listed.  A launch costs 5-7 us; on one 32 x 32 pad the whole step takes
+    // about 50, and the listing of 256 items would take as long as visiting them.
+    p.dense = p.items <= 256;
+    p.splits = 1;
+    while (p.E * p.splits < 4 * pl.cu_count && p.splits * kWaves * 4 < pl.tile.NW) p.splits *= 2;
+}
+
+void launch_front(const Plan &pl, const StepParams &p, hipStream_t st) {
+    const int nt = p.table_units + p.matrix_units;
+    const bool merged = p.dense && p.splits == 1 && nt > 0;
+    if (!merged && (nt > 0 || p.splits > 1))
+        hipLaunchKernelGGL(k_tables, dim3(std::max(nt, 64)), dim3(kWG), 0, st, p);
+    if (p.cobj_in) launch_contact_items<true>(p, merged, nt, st);
+    else launch_contact_items<false>(p, merged, nt, st);
+    const int32_t *na = p.n_active ? p.n_active : pl.itm.n_act;
+    if (!p.dense) hipLaunchKernelGGL(k_live, dim3(pl.K), dim3(1024), 0, st, na, p.E, pl.K, pl.itm.live, pl.itm.live_cnt);
+}
+
+void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st) {
+    const long long cus = p.cus;
+    if (!p.recall) {
+        if (p.dense && pl.tile.n_far == 0) {
+            hipLaunchKernelGGL(k_pool, dim3((unsigned)std::min(p.items, cus)), dim3(64 * kPoolWaves), 0, st, p);
+            return;
+        }
+        hipLaunchKernelGGL(k_pool_passive, dim3((unsigned)std::min((p.words / kPassiveWords + p.items) / kWaves + 1, 8 * cus)),
+                           dim3(kWG), 0, st, p);
+        hipLaunchKernelGGL(k_pool_active, dim3((unsigned)std::min((p.words / kActiveWords + p.items) / kWaves + 1, 2 * cus)),
+                           dim3(kWG), 0, st, p);
+    }
+    hipLaunchKernelGGL(k_pool_finish, dim3((unsigned)std::min(p.items / kWaves + 1, 8 * cus)), dim3(kWG), 0, st, p);
+}
+
+void launch_far_lists(const StepParams &p, bool passive, hipStream_t st) {
+    const dim3 grid((unsigned)std::min<long long>(p.items, 2 * p.cus));
+    if (passive) hipLaunchKernelGGL(k_far_list<true>, grid, dim3(1024), 0, st, p);
+    else hipLaunchKernelGGL(k_far_list<false>, grid, dim3(1024), 0, st, p);
+}
+
+hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int n_envs,
+                       const int8_t *cobj_in, const float *uhat_in, float *u, int8_t *cobj_out,
+                       int32_t *n_active, uint32_t *saved, hipStream_t st, int32_t *n_touch) {
+    if (n_envs == 0) return hipSuccess;
+    StepParams p{};
+    p.scene = s ? *s : SceneDev{nullptr, nullptr, nullptr, nullptr, nullptr, 0, 1};
     p.model = m;
     p.E = n_envs;
     p.cobj_in = cobj_in;
@@ -1598,37 +1178,11 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     p.n_active = n_active;
     p.n_touch = n_touch;
     p.saved = saved;
-    const bool dec = m.mode != ETAC_RESIDUAL_ONLY, res = m.mode != ETAC_DECAY_ONLY;
-    const int cus = pl.cu_count;
-    const long long items = (long long)n_envs * pl.K, words = (long long)n_envs * pl.tile.NW;
-    p.table_units = res ? std::min(pl.tile.NW, 2 * cus) : 0;
-    p.matrix_units = dec ? pl.tile.near_rows : 0;
-    const int nt = p.table_units + p.matrix_units;
-    // Small batches: tables and contact share a launch and every item is
-    // listed.  A launch costs 5-7 us; on one 32 x 32 pad the whole step takes
-    // about 30, and the listing of 256 items would take as long as visiting them.
-    p.dense = items <= 256;
-    p.splits = 1;
-    while (n_envs * p.splits < 4 * cus && p.splits * kWaves * 4 < pl.tile.NW) p.splits *= 2;
-    const bool merged = p.dense && p.splits == 1 && nt > 0;
+    shape_step(pl, p);
+    const long long cus = p.cus;
     const int slot = timer_begin(pl, ETAC_TIMER_STEP, st);
-    if (!merged && (nt > 0 || p.splits > 1))
-        hipLaunchKernelGGL(k_tables, dim3(std::max(nt, 64)), dim3(kWG), 0, st, p);
-    if (s) launch_contact_items<false>(p, merged, nt, st);
-    else launch_contact_items<true>(p, merged, nt, st);
-    const int32_t *na = n_active ? n_active : pl.itm.n_act;
-    if (!p.dense) hipLaunchKernelGGL(k_live, dim3(pl.K), dim3(1024), 0, st, na, n_envs, pl.K, pl.itm.live, pl.itm.live_cnt);
-    if (res) {
-        if (p.dense && pl.tile.n_far == 0) {
-            hipLaunchKernelGGL(k_pool, dim3((unsigned)std::min<long long>(items, cus)), dim3(64 * kPoolWaves), 0, st, p);
-        } else {
-            hipLaunchKernelGGL(k_pool_passive, dim3((unsigned)std::min<long long>((words / kPassiveWords + items) / kWaves + 1, 8 * cus)),
-                               dim3(kWG), 0, st, p);
-            hipLaunchKernelGGL(k_pool_active, dim3((unsigned)std::min<long long>((words / kActiveWords + items) / kWaves + 1, 2 * cus)),
-                               dim3(kWG), 0, st, p);
-            hipLaunchKernelGGL(k_pool_finish, dim3((unsigned)std::min<long long>(items / kWaves + 1, 8 * cus)), dim3(kWG), 0, st, p);
-        }
-    }
+    launch_front(pl, p, st);
+    if (step_residual(p)) launch_pool(pl, p, st);
     if (pl.tile.n_near) {
         if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(2 * cus), dim3(kWG), 0, st, p);
         else if (n_envs >= 128) hipLaunchKernelGGL(k_prop_wide<1>, dim3(2 * cus), dim3(kWG), 0, st, p);
@@ -1637,8 +1191,8 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
                                dim3(kWG), 0, st, p);
     }
     if (pl.tile.n_far) {
-        if (dec) hipLaunchKernelGGL(k_far_list, dim3((unsigned)std::min<long long>(items, 2 * cus)), dim3(1024), 0, st, p);
-        hipLaunchKernelGGL(k_prop_far, dim3((unsigned)std::min<long long>(words / 4 + items, 8 * cus)), dim3(kWG), 0, st, p);
+        if (step_decay(p)) launch_far_lists(p, false, st);
+        hipLaunchKernelGGL(k_prop_far, dim3((unsigned)std::min(p.words / 4 + p.items, 8 * cus)), dim3(kWG), 0, st, p);
     }
     const hipError_t e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_STEP, slot, st);

@@ -184,7 +184,10 @@ struct PoseHandParams {
     SceneDev world;
     LinksDev links;
     HandDev hand;
-    const float *part;       // [E K][cap][12]
+    const float *part;       // [E][NC][cap][12], written for items in contact
+    const int *n_act;        // [E K]
+    const int *chunk_off;    // [K+1]
+    int NC;
     int E, K;
     float *grad_rot, *grad_trans, *grad_link_rot, *grad_link_trans;
 };
@@ -206,6 +209,7 @@ __global__ __launch_bounds__(256) void k_pose_hand(PoseHandParams p) {
         const size_t row = (size_t)e * p.K + k;
         const int l = H.patch_link[k];
         const bool frame = is_link && l == tl_link;
+        if (p.n_act[row] == 0) continue;
         const int n = min(H.n_obj[row], H.cap);
         double Rl[9], tl[3];
         bool have_l = false;
@@ -216,12 +220,18 @@ __global__ __launch_bounds__(256) void k_pose_hand(PoseHandParams p) {
                 load_pose(p.links.rot + ((size_t)e * L + l) * 9, p.links.trans + ((size_t)e * L + l) * 3, Rl, tl);
                 have_l = true;
             }
-            const float *gp = p.part + (row * H.cap + s) * 12;
             double Gp[9], tp[3];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) Gp[i] = gp[i];
+            for (int i = 0; i < 9; ++i) Gp[i] = 0.0;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) tp[i] = gp[9 + i];
+            for (int i = 0; i < 3; ++i) tp[i] = 0.0;
+            for (int h = p.chunk_off[k]; h < p.chunk_off[k + 1]; ++h) {
+                const float *gp = p.part + (((size_t)e * p.NC + h) * H.cap + s) * 12;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) Gp[i] += gp[i];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) tp[i] += gp[9 + i];
+            }
             double GRw[9], gtw[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -280,8 +290,8 @@ __global__ __launch_bounds__(256) void k_pose_hand(PoseHandParams p) {
 hipError_t launch_pose_hand(const Plan &pl, const SceneDev &world, const LinksDev &links, float *grad_rot,
                             float *grad_trans, float *grad_link_rot, float *grad_link_trans, hipStream_t st) {
     if (world.E == 0) return hipSuccess;
-    PoseHandParams p{world, links, *pl.hand, pl.hand->pose_part, world.E, pl.K,
-                     grad_rot, grad_trans, grad_link_rot, grad_link_trans};
+    PoseHandParams p{world, links, *pl.hand, pl.hand->pose_part, pl.itm.n_act, pl.tile.chunk_off, pl.tile.NC,
+                     world.E, pl.K, grad_rot, grad_trans, grad_link_rot, grad_link_trans};
     const int nt = world.E * (world.O + pl.hand->L);
     hipLaunchKernelGGL(k_pose_hand, dim3((nt + 255) / 256), dim3(256), 0, st, p);
     return hipGetLastError();

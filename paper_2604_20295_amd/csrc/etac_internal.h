@@ -11,8 +11,16 @@ namespace etac {
 constexpr int kWG = 256;           // threads per workgroup: 4 waves of 64
 constexpr int kWaves = kWG / 64;
 constexpr int kSavedWords = ETAC_SAVED_WORDS;   // pooling record per (env, patch) item
-constexpr int kRecWords = 10564;                  // parameter-gradient record per item with contact
-constexpr int kRedColsMax = 10624 + 8192;         // columns of the parameter reduction
+// parameter reduction: words of a node block's record (dW4[:, :64], dW2, dW1
+// with db1 as input column 9 as 36 blocks of 16 x 16, db2), of a routing
+// workgroup's (dW2, dW1 and db1 by input, db2), and all its columns
+constexpr int kNodeRecWords = 36 * 256 + 64;
+constexpr int kRouteWords = 4096 + 640 + 64;
+constexpr int kRouteGroups = 2;                   // routing workgroups per compute unit
+constexpr int kRedRoute = 37 * 256, kRedItem = kRedRoute + 19 * 256, kRedRank = kRedItem + 256,
+              kRedW5 = kRedRank + 8192, kRedCols = kRedW5 + 256;
+constexpr int kAlphaSegs = 32;
+constexpr int kPhiSegs = 64;                      // segments of the parameter reduction
 constexpr int kMaxPatches = 1024;  // per-patch counters of the contact kernel live in LDS
 constexpr int kDefaultWgPerCu = 2;
 constexpr int kDefaultBatch = 4;   // work-queue positions claimed per atomic
@@ -76,7 +84,7 @@ struct HandDev {
     float *rot;                    // [E K][cap][9]
     float *trans;                  // [E K][cap][3]
     int8_t *src;                   // [E K][cap]
-    float *pose_part;              // [E K][cap][12] relative-pose gradient partials (backward)
+    float *pose_part;              // [E][NC][cap][12] relative-pose gradient parts (backward)
     int *n_touch;                  // [E K] reward counts when the caller passes none
 };
 
@@ -93,13 +101,20 @@ struct LinksDev {
 constexpr int kNearNodes = 2048;
 constexpr size_t kDecayMatrixBytes = size_t(1) << 30;   // bound on all decay matrices of a plan
 
+constexpr int kPoseWords = 16;     // words per pose part of the contact adjoint
+constexpr int kBlockNodes = 64;    // nodes per unit of the network adjoint's node pass
+
 struct TileDev {
     const int4 *word;          // [NW] patch, first node (index into the mesh), nodes, word of the patch
     const int2 *row_tile;      // [near_rows] near patch and tile of 16 of its nodes
     const int *word_off;       // [K+1] first word of each patch
     const long long *w_off;    // [K] the patch's decay matrix in w, in 16-byte units; -1: far patch
     const int *perm;           // [N] far patches: patch-local node of each position of the spatial order
-    int NW;
+    const int *part_off;       // [K+1] first Eq. 1 part of each patch: tiles of 16 rows (near), of 64 (far)
+    const int *chunk_off;      // [K+1] first pose part of each patch: chunks of kPoseWords words
+    const int2 *block;         // [NU] patch and first node (patch-local) of every kBlockNodes nodes
+    const int *blk5_off;       // [K+1] first 128-node block of each patch
+    int NW, NP, NC, NU, NB5;   // words, parts, chunks, blocks, 128-node blocks
     int n_near, n_far;         // patches of each kind
     int far_max;               // nodes of the largest far patch
     int near_rows;             // tiles of 16 nodes of the near patches
@@ -112,8 +127,8 @@ struct TableDev {
     float *dec;                // [N][64] W4[:, :64] feat
     float *max8, *max32;       // [8 NW][64], [2 NW][64] largest features of 8 and of 32 consecutive nodes of a word
     int *scale;                // [8] exponents of the network's weight scales (s1, s2, s4)
-    float *w3t, *w4t;          // [64][64] W3 and W4[:, 64:] transposed
-    uint4 *w;                  // decay matrices, see k_tables
+    float *w3t, *w4t, *w2t;    // [64][64] W3, W4[:, 64:] and W2 transposed
+    uint4 *w, *wd;             // decay matrices W and, for the adjoint, d W (see matrix_row_tile)
 };
 
 // Results of the contact pass the later kernels of a call read.
@@ -126,6 +141,8 @@ struct ItemDev {
     float *c4;                 // [E K][64] W4[:, 64:] g' + b4 of the items in contact
     int *alist;                // [E][N] far patches: active nodes in spatial order (patch-local)
     float4 *abox;              // [E][NB][2] boxes of 32 consecutive entries of alist
+    int *plist;                // the same of the passive nodes (adjoint)
+    float4 *pbox;
     const int *box_off;        // [K] first box of each patch
     int NB;                    // boxes per env
 };
@@ -136,33 +153,26 @@ struct ModelDev {
     const float *phi;      // [17411] or null in decay-only mode
 };
 
-// Per-workgroup scratch of the persistent adjoint kernels (device memory).
-struct Scratch {
-    float *uhat_node;      // [G][3][n_max] u_hat of every node of the current item (0 passive)
-    float *resid;          // [G][3][n_max] residual-network output
-    int *alist;            // [G][n_max]    active node indices (patch-local, ascending)
-    int *plist;            // [G][n_max]    passive node indices (patch-local, ascending)
-    unsigned *counter;     // [8]           work-queue counters (self-resetting)
-    int n_max;
-};
+// Envs per chunk of the passive network adjoint.
+constexpr int kEnvChunk = 32, kEnvChunkSmall = 8, kEnvChunkSwitch = 256;
 
-// Backward scratch (plan flag ETAC_PLAN_BACKWARD).
+// Adjoint scratch (plan flag ETAC_PLAN_BACKWARD).
 struct BwdScratch {
-    float *guhat;          // [G][3][n_max]    dL/du_hat per node of the current item
-    float *phi_part;       // [E*K][kRecWords] per-item parameter-gradient records
-    int *rec_map;          // [17411]          reduction column of every parameter
-    float *alpha_part;     // [E*K]            per-item dL/dalpha partials
-    float *pose_part;      // [E*K][O][12]     per-item pose-gradient partials
-    int *item_flag;        // [E*K]            1 if the item wrote partials
-    double *phi_seg;       // [64][kRedColsMax] segment sums of the parameter reduction
-    // hand-over from the decay kernel to the network / contact kernel
-    int8_t *cobj_st;       // [E][N]    contact winners of every candidate item (step adjoint)
+    int8_t *cobj_st;       // [E][N]    contact winners (step adjoint)
     float *uhat_st;        // [3][E][N] u_hat of active nodes (step adjoint)
-    float *gh_st;          // [3][E][N] dL/du_hat of active nodes after the decay adjoint
-    int *m_st;             // [E*K]     active-node count of every item
-    float *gmax_st;        // [E*K]     largest |dL/dU| component over each contacted item's passive nodes
-    int *live;             // [E*K]     queue positions of the items with contact, in queue order
-    int *seg_cnt;          // [n_seg + 1] items with contact per 1024 queue positions; [n_seg] = total
+    float *gh;             // [3][E][N] dL/du_hat of active nodes (step adjoint)
+    double *alpha_part;    // [E][NP]   dL/dalpha of every part of Eq. 1
+    float *s4_part;        // [E][2 NW][64] sum of dL/dpre4 over the passive nodes of a half word
+    float *s4_node;        // [chunks][N][64] sum of dL/dpre4 over a chunk's envs, per node
+    float *w5_part;        // [chunks][NB5][256] dW5 (192), db5 (3) of 128 nodes and a chunk
+    float *ivec;           // [E K][4][64] s4, g', dpre3, g per item
+    uint32_t *record;      // [E K][kSavedWords] the adjoint's own pooling record
+    float *route;          // [workgroups][kRouteWords] parameter gradients of the max-pool's routes
+    float *node_rec;       // [NU][kNodeRecWords] parameter gradients of a block of nodes
+    double *alpha_seg;     // [K][kAlphaSegs]
+    double *seg;           // [kPhiSegs][kRedCols] segment sums of the parameter reduction
+    float *pose_part;      // [E][NC][O][12] pose-gradient parts
+    int chunks;            // chunks s4_node and w5_part hold
 };
 
 // Event pairs bracketing kernel launches (etac_plan_set_timing).
@@ -176,23 +186,22 @@ struct Plan {
     int device;
     int cu_count;
     int wg_per_cu;
-    int grid;              // persistent workgroups
-    int batch;             // forward work-queue positions claimed per atomic (1 .. 64)
-    int bwd_batch;         // adjoint work-queue positions claimed per atomic (1 .. 64)
-    int decay_wg_per_cu;   // workgroups per CU of the decay-adjoint kernel (1 .. 8)
-    int net_batch;         // list positions per claim of the network-adjoint kernel (1 .. 64)
+    int grid;              // cu_count x wg_per_cu
+    int batch, bwd_batch, decay_wg_per_cu, net_batch;   // kept and reported; the kernels choose their own shape
     int n_envs, max_obj, K, N, n_max;
     uint32_t flags;
     MeshDev mesh;
     TileDev tile;
     TableDev tab;
     ItemDev itm;
-    Scratch scr;
+    unsigned *counter;     // [4] regressor's work queue (self-resetting)
     BwdScratch bwd;
     bool has_bwd;
     // device allocations owned by the plan
     void *allocs[96];
     int n_allocs;
+    char *arena;           // rest of the block small arrays are carved from
+    size_t arena_left;
     int64_t scratch_bytes;
     Timers *timers;        // null until timing is first turned on
     HandDev *hand;         // null until etac_plan_set_hand (host copy of the device view)
@@ -245,7 +254,6 @@ hipError_t launch_hand_reward(const Plan &p, int n_envs, const int32_t *n_touch,
                               uint32_t *link_mask, float *r_contact, hipStream_t st);
 hipError_t launch_pose_hand(const Plan &p, const SceneDev &world, const LinksDev &links, float *grad_rot,
                             float *grad_trans, float *grad_link_rot, float *grad_link_trans, hipStream_t st);
-hipError_t init_record_map(const Plan &p);
 
 hipError_t launch_contact_backward(const Plan &p, const SceneDev &s, const float *grad_uhat,
                                    float *grad_rot, float *grad_trans, hipStream_t st);

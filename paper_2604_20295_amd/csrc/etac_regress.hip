@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void k_regress_fill(const int32_t *n_active, c
 hipError_t launch_regress(const Plan &pl, const float *reg, int n_envs, const float *u, const int32_t *n_active,
                           float *taxels, hipStream_t st) {
     if (n_envs == 0) return hipSuccess;
-    unsigned *ctr = pl.scr.counter + 4;
+    unsigned *ctr = pl.counter;
     RegParams p{pl.mesh, reg, u, n_active, pl.reg_pooled, pl.reg_row, ctr, n_envs, pl.K + n_envs * pl.K};
     const int grid = min(pl.cu_count, (p.n_pos + kRegWaves - 1) / kRegWaves);
     const int slot = timer_begin(pl, ETAC_TIMER_REGRESS, st);
