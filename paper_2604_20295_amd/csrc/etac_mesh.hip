@@ -7,15 +7,16 @@
 //          clusters of 32 triangles by recursive splits of the triangle
 //          centroids, builds a conservative occupancy grid per mesh, and
 //          uploads it all.
-//   k_contact_mesh : one workgroup per env, as the primitive contact pass.
-//          Primitives are tested one node per lane.  For a mesh object the
-//          nodes inside its bounding ball and not in a cell of the grid that
-//          is certainly outside are queried one at a time by the whole wave:
-//          lanes take the clusters' lower bounds, then the triangles of the
-//          two nearest unvisited clusters (one cluster per half-wave, one
-//          triangle per lane), with DPP wave reductions for the minimum;
-//          clusters whose lower bound exceeds the best distance so far are
-//          never opened.
+//   k_mesh_items : 512 nodes of an env per workgroup.  Primitives are tested
+//          one node per lane.  For a mesh object the nodes inside its bounding
+//          ball and not in a cell of the grid that is certainly outside are
+//          queried one at a time by a whole wave: lanes take the clusters'
+//          lower bounds, then the triangles of the two nearest unvisited
+//          clusters (one cluster per half-wave, one triangle per lane), with
+//          DPP wave reductions for the minimum; clusters whose lower bound
+//          exceeds the best distance so far are never opened.
+//   k_mesh_adjoint : one workgroup per env, from the forward's records or from
+//          the same search.
 //
 // The closest point of a triangle follows the Voronoi-region classification
 // of Ericson ("Real-Time Collision Detection", 2005, Sec. 5.1.5).  All of it
@@ -357,27 +358,22 @@ __device__ __forceinline__ unsigned cull_mesh_objects(const MeshContactParams &p
     return cand;
 }
 
-// Four waves per SIMD (at most 128 registers): the queries are latency-bound.
-// ADJ: the adjoint (every node's pose gradient added to its winning object's
-// sums: per wave in a fixed order, then over the waves in wave order, so
-// results do not depend on timing), with contact recomputed or, REC, read
-// from the forward's records.
-template <bool ADJ, bool REC>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_contact_mesh(MeshContactParams p) {
-    __shared__ int cnt[kMaxPatches];
+// Adjoint: every node's pose gradient added to its winning object's sums, per
+// wave in a fixed order, then over the waves in wave order, so results do not
+// depend on timing; with contact recomputed or, REC, read from the forward's
+// records.  Four waves per SIMD (at most 128 registers): the queries are
+// latency-bound.
+template <bool REC>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_mesh_adjoint(MeshContactParams p) {
     __shared__ uint8_t cand[kMaxPatches];
-    __shared__ double sacc[ADJ ? kWaves : 1][ADJ ? ETAC_MAX_OBJ : 1][12];
+    __shared__ double sacc[kWaves][ETAC_MAX_OBJ][12];
     const int e = blockIdx.x;
     const MeshDev &M = p.mesh;
     const SceneDev &S = p.scene;
     const int N = M.N, K = M.K;
     const size_t EN = (size_t)S.E * N;
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        cnt[k] = 0;
-        cand[k] = (uint8_t)cull_mesh_objects(p, e, k);
-    }
-    if (ADJ)
-        for (int c = threadIdx.x; c < kWaves * ETAC_MAX_OBJ * 12; c += kWG) (&sacc[0][0][0])[c] = 0.0;
+    for (int k = threadIdx.x; k < K; k += kWG) cand[k] = (uint8_t)cull_mesh_objects(p, e, k);
+    for (int c = threadIdx.x; c < kWaves * ETAC_MAX_OBJ * 12; c += kWG) (&sacc[0][0][0])[c] = 0.0;
     __syncthreads();
     const int lane = lane_id();
     const int no = min(S.n_obj[e], S.O);
@@ -391,7 +387,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const float px = valid ? M.pos[i] : 0.0f, py = valid ? M.pos[N + i] : 0.0f;
         const float pz = valid ? M.pos[2 * N + i] : 0.0f;
         int best = -1, btri = -1;   // btri: winning triangle when a mesh wins
-        double bd = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
+        double bd = 0.0;
         if (REC) {
             // the forward's records; values that cannot come from it are skipped
             if (valid && c != 0u) {
@@ -429,7 +425,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                         best = o;
                         btri = -1;
                         bd = h.depth;
-                        b0 = h.u0; b1 = h.u1; b2 = h.u2;
                     }
                 } else if (ty == ETAC_MESH) {
                     const int m = mesh_of(sh, p.ms.M);
@@ -477,68 +472,240 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                             best = o;
                             btri = tri;
                             bd = h.depth;
-                            b0 = h.u0; b1 = h.u1; b2 = h.u2;
-                        }
+                            }
                     }
                 }
             }
         }
-        if (ADJ) {
-            if (__ballot(best >= 0)) {
-                double acc[12];
+        if (__ballot(best >= 0)) {
+            double acc[12];
 #pragma unroll
-                for (int q = 0; q < 12; ++q) acc[q] = 0.0;
-                if (best >= 0) {
-                    const size_t eo = (size_t)e * S.O + best;
-                    const double g[3] = {p.grad_uhat[row + i], p.grad_uhat[EN + row + i],
-                                         p.grad_uhat[2 * EN + row + i]};
-                    if (btri >= 0)
-                        mesh_adjoint_node(p.ms, btri, S.rot + 9 * eo, S.trans + 3 * eo, px, py, pz, g, acc);
-                    else
-                        contact_adjoint_node(S.type[eo], S.shape + 4 * eo, S.rot + 9 * eo, S.trans + 3 * eo, px, py,
-                                             pz, g, acc);
-                }
-                const int wave = threadIdx.x >> 6;
-                for (int o = 0; o < no; ++o) {
-                    if (!__ballot(best == o)) continue;
+            for (int q = 0; q < 12; ++q) acc[q] = 0.0;
+            if (best >= 0) {
+                const size_t eo = (size_t)e * S.O + best;
+                const double g[3] = {p.grad_uhat[row + i], p.grad_uhat[EN + row + i],
+                                     p.grad_uhat[2 * EN + row + i]};
+                if (btri >= 0)
+                    mesh_adjoint_node(p.ms, btri, S.rot + 9 * eo, S.trans + 3 * eo, px, py, pz, g, acc);
+                else
+                    contact_adjoint_node(S.type[eo], S.shape + 4 * eo, S.rot + 9 * eo, S.trans + 3 * eo, px, py,
+                                         pz, g, acc);
+            }
+            const int wave = threadIdx.x >> 6;
+            for (int o = 0; o < no; ++o) {
+                if (!__ballot(best == o)) continue;
 #pragma unroll
-                    for (int q = 0; q < 12; ++q) {
-                        const double v = wave_sum(best == o ? acc[q] : 0.0);
-                        if (lane == 0) sacc[wave][o][q] += v;   // one writer per wave, chunks in order
-                    }
+                for (int q = 0; q < 12; ++q) {
+                    const double v = wave_sum(best == o ? acc[q] : 0.0);
+                    if (lane == 0) sacc[wave][o][q] += v;   // one writer per wave, chunks in order
                 }
             }
-        } else if (valid) {
-            p.cobj[row + i] = (int8_t)best;
-            if (p.hit) p.hit[row + i] = best >= 0 ? btri : -1;
-            if (p.uhat) {
-                p.uhat[row + i] = (float)b0;
-                p.uhat[EN + row + i] = (float)b1;
-                p.uhat[2 * EN + row + i] = (float)b2;
-            }
-            if (best >= 0) atomicAdd(&cnt[k], 1);
         }
     }
     __syncthreads();
-    if (ADJ) {
-        for (int c = threadIdx.x; c < S.O * 12; c += kWG) {
-            const int o = c / 12, q = c % 12;
-            double v = 0.0;
-            for (int w = 0; w < kWaves; ++w) v += sacc[w][o][q];
-            const size_t eo = (size_t)e * S.O + o;
-            if (q < 9) p.grad_rot[eo * 9 + q] = (float)v;
-            else p.grad_trans[eo * 3 + q - 9] = (float)v;
-        }
-    } else {
-        for (int k = threadIdx.x; k < K; k += kWG) p.n_active[(size_t)e * K + k] = cnt[k];
+    for (int c = threadIdx.x; c < S.O * 12; c += kWG) {
+        const int o = c / 12, q = c % 12;
+        double v = 0.0;
+        for (int w = 0; w < kWaves; ++w) v += sacc[w][o][q];
+        const size_t eo = (size_t)e * S.O + o;
+        if (q < 9) p.grad_rot[eo * 9 + q] = (float)v;
+        else p.grad_trans[eo * 3 + q - 9] = (float)v;
     }
+}
+
+// The contact pass.  A workgroup takes kMeshNodes nodes of an env, a thread two
+// of them.  For every mesh object in turn the nodes that may be inside it are
+// listed in LDS, the workgroup's waves take the queries of the list in turn,
+// and each node's thread compares the result with its best.  A query is a
+// chain of dependent FP64 passes, so what counts is that every wave on the
+// chip has one: nodes in contact lie close together, and a wave that kept its
+// own nodes' queries had up to 64 of them while its neighbours had none
+// (256 hands with mesh objects: 1318 us with a workgroup per env and own
+// queries, 639 us like this).
+constexpr int kMeshNodes = 2 * kWG;
+
+struct MeshQuery {
+    double depth, u0, u1, u2;
+    int inside, tri;
+};
+
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_mesh_items(MeshContactParams p,
+                                                                                               int chunks) {
+    __shared__ MeshQuery res[kMeshNodes];
+    __shared__ uint16_t list[kMeshNodes];
+    __shared__ int wsum[2][kWaves];
+    __shared__ unsigned any;
+    const int e = blockIdx.x / chunks, i0 = (blockIdx.x - e * chunks) * kMeshNodes;
+    const MeshDev &M = p.mesh;
+    const SceneDev &S = p.scene;
+    const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const size_t EN = (size_t)S.E * N, row = (size_t)e * N;
+    const int no = uniform(min(S.n_obj[e], S.O));
+    int node[2], best[2], btri[2], kk[2];
+    unsigned cand[2];
+    float px[2], py[2], pz[2];
+    double bd[2], b0[2], b1[2], b2[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        node[h] = i0 + h * kWG + threadIdx.x;
+        const bool valid = node[h] < N;
+        const int i = valid ? node[h] : N - 1;
+        kk[h] = M.node_patch[i];
+        px[h] = M.pos[i];
+        py[h] = M.pos[N + i];
+        pz[h] = M.pos[2 * N + i];
+        cand[h] = valid ? ~0u : 0u;
+        best[h] = btri[h] = -1;
+        bd[h] = b0[h] = b1[h] = b2[h] = 0.0;
+    }
+    // objects whose ball may reach the patches of this chunk's nodes
+    if (threadIdx.x < 64) any = 0u;      // identical stores
+    __syncthreads();
+    {
+        const int k0 = M.node_patch[i0], k1 = M.node_patch[min(i0 + kMeshNodes, N) - 1];
+        for (int k = k0 + threadIdx.x; k <= k1; k += kWG) {
+            const unsigned c = cull_mesh_objects(p, e, k);
+            if (c) atomicOr(&any, c);
+        }
+    }
+    __syncthreads();
+    unsigned todo_obj = uniform(any);
+    while (todo_obj) {
+        const int o = __ffs(todo_obj) - 1;
+        todo_obj &= todo_obj - 1;
+        if (o >= no) break;
+        const size_t eo = (size_t)e * S.O + o;
+        const int ty = uniform(S.type[eo]);
+        const float *sh = S.shape + 4 * eo;
+        const float *R = S.rot + 9 * eo;
+        const float *t = S.trans + 3 * eo;
+        if (ty >= ETAC_SPHERE && ty <= ETAC_CAPSULE) {
+            const float rb = bounding_radius(ty, sh) * 1.001f + 1e-3f;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const float dx = px[h] - t[0], dy = py[h] - t[1], dz = pz[h] - t[2];
+                if (!cand[h] || dx * dx + dy * dy + dz * dz > rb * rb) continue;
+                const int i = node[h];
+                const Pen q = penetrate(ty, sh, R, t, px[h], py[h], pz[h], M.nrm[i], M.nrm[N + i], M.nrm[2 * N + i]);
+                if (q.inside && (best[h] < 0 || q.depth > bd[h])) {
+                    best[h] = o;
+                    btri[h] = -1;
+                    bd[h] = q.depth;
+                    b0[h] = q.u0; b1[h] = q.u1; b2[h] = q.u2;
+                }
+            }
+            continue;
+        }
+        const int m = uniform(ty == ETAC_MESH ? mesh_of(sh, p.ms.M) : -1);
+        if (m < 0) continue;
+        const float rb = p.ms.radius[m] * 1.001f + 1e-3f;
+        const float4 g = p.ms.grid_lo[m];
+        const int4 gd = p.ms.grid_dim[m];
+        bool near[2];
+        unsigned long long bal[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float dx = px[h] - t[0], dy = py[h] - t[1], dz = pz[h] - t[2];
+            near[h] = cand[h] && dx * dx + dy * dy + dz * dz <= rb * rb;
+            if (near[h]) {   // the occupancy grid rules out nodes certainly outside
+                const float qx = (R[0] * dx + R[3] * dy) + R[6] * dz;
+                const float qy = (R[1] * dx + R[4] * dy) + R[7] * dz;
+                const float qz = (R[2] * dx + R[5] * dy) + R[8] * dz;
+                const float gx = (qx - g.x) * g.w, gy = (qy - g.y) * g.w, gz = (qz - g.z) * g.w;
+                near[h] = gx >= 0.0f && gy >= 0.0f && gz >= 0.0f && gx < (float)gd.x && gy < (float)gd.y &&
+                          gz < (float)gd.z;
+                if (near[h]) {
+                    const int ix = min((int)gx, gd.x - 1), iy = min((int)gy, gd.y - 1);
+                    const int iz = min((int)gz, gd.z - 1);
+                    const unsigned bit = (unsigned)gd.w + (unsigned)((iz * gd.y + iy) * gd.x + ix);
+                    near[h] = (p.ms.grid_bits[bit >> 5] >> (bit & 31u)) & 1u;
+                }
+            }
+            bal[h] = __ballot(near[h]);
+            wsum[h][wave] = __popcll(bal[h]);      // identical in every lane
+        }
+        __syncthreads();
+        int off[2] = {0, 0}, total = 0, at[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                if (w == wave) off[h] = total;
+                total += wsum[h][w];
+            }
+        total = uniform(total);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            at[h] = off[h] + (int)lanes_below(bal[h]);
+            if (near[h]) list[at[h]] = (uint16_t)(h * kWG + threadIdx.x);
+        }
+        __syncthreads();
+        for (int q = wave; q < total; q += kWaves) {
+            const int i = i0 + uniform((int)list[q]);
+            double q0, q1, q2;
+            {
+#pragma clang fp contract(off)
+                const double d0 = (double)M.pos[i] - (double)t[0];
+                const double d1 = (double)M.pos[N + i] - (double)t[1];
+                const double d2 = (double)M.pos[2 * N + i] - (double)t[2];
+                q0 = ((double)R[0] * d0 + (double)R[3] * d1) + (double)R[6] * d2;
+                q1 = ((double)R[1] * d0 + (double)R[4] * d1) + (double)R[7] * d2;
+                q2 = ((double)R[2] * d0 + (double)R[5] * d1) + (double)R[8] * d2;
+            }
+            int tri;
+            const Pen h = mesh_query(p.ms, m, q0, q1, q2, R, tri);
+            // the same result in every lane: identical stores
+            res[q] = MeshQuery{h.depth, h.u0, h.u1, h.u2, h.inside ? 1 : 0, tri};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (near[h]) {
+                const MeshQuery &r = res[at[h]];
+                if (r.inside && (best[h] < 0 || r.depth > bd[h])) {
+                    best[h] = o;
+                    btri[h] = r.tri;
+                    bd[h] = r.depth;
+                    b0[h] = r.u0; b1[h] = r.u1; b2[h] = r.u2;
+                }
+            }
+        __syncthreads();      // list and results are rewritten
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int i = node[h];
+        if (i < N) {
+            p.cobj[row + i] = (int8_t)best[h];
+            if (p.hit) p.hit[row + i] = best[h] >= 0 ? btri[h] : -1;
+            if (p.uhat) {
+                p.uhat[row + i] = (float)b0[h];
+                p.uhat[EN + row + i] = (float)b1[h];
+                p.uhat[2 * EN + row + i] = (float)b2[h];
+            }
+        }
+        // active nodes per patch: a wave's nodes lie on few patches (counts were zeroed)
+        unsigned long long act = __ballot(i < N && best[h] >= 0);
+        while (act) {
+            const int k = __builtin_amdgcn_readlane(kk[h], __ffsll(act) - 1);
+            const unsigned long long same = __ballot(i < N && best[h] >= 0 && kk[h] == k);
+            if (lane == 0) atomicAdd(&p.n_active[(size_t)e * K + k], __popcll(same));
+            act &= ~same;
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void k_mesh_zero(int32_t *x, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) x[i] = 0;
 }
 
 hipError_t launch_contact_mesh(const Plan &p, const MeshSetDev &ms, const SceneDev &s, int8_t *cobj, float *uhat,
                                int32_t *n_active, int32_t *hit, hipStream_t st) {
     if (s.E == 0) return hipSuccess;
     MeshContactParams cp{p.mesh, s, ms, cobj, uhat, n_active, hit, nullptr, nullptr, nullptr, nullptr, nullptr};
-    hipLaunchKernelGGL((k_contact_mesh<false, false>), dim3(s.E), dim3(kWG), 0, st, cp);
+    const int items = s.E * p.K, chunks = (p.N + kMeshNodes - 1) / kMeshNodes;
+    hipLaunchKernelGGL(k_mesh_zero, dim3((items + 255) / 256), dim3(256), 0, st, n_active, items);
+    hipLaunchKernelGGL(k_mesh_items, dim3((unsigned)s.E * chunks), dim3(kWG), 0, st, cp, chunks);
     return hipGetLastError();
 }
 
@@ -548,8 +715,8 @@ hipError_t launch_contact_mesh_backward(const Plan &p, const MeshSetDev &ms, con
     if (s.E == 0) return hipSuccess;
     MeshContactParams cp{p.mesh, s, ms, nullptr, nullptr, nullptr, nullptr, grad_uhat, grad_rot, grad_trans,
                          hit ? cobj : nullptr, cobj ? hit : nullptr};
-    if (cp.hit_in) hipLaunchKernelGGL((k_contact_mesh<true, true>), dim3(s.E), dim3(kWG), 0, st, cp);
-    else hipLaunchKernelGGL((k_contact_mesh<true, false>), dim3(s.E), dim3(kWG), 0, st, cp);
+    if (cp.hit_in) hipLaunchKernelGGL(k_mesh_adjoint<true>, dim3(s.E), dim3(kWG), 0, st, cp);
+    else hipLaunchKernelGGL(k_mesh_adjoint<false>, dim3(s.E), dim3(kWG), 0, st, cp);
     return hipGetLastError();
 }
 
