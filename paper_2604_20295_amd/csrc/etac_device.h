@@ -115,27 +115,29 @@ __device__ __forceinline__ float bounding_radius(int type, const float *sh) {
     return sh[0] + sh[1];
 }
 
-// Contact of one node with the candidate objects of scene row `row` (bit o
-// of `cand`).  A cheap FP32 ball test with a relative margin of 1e-3 (far
-// above FP32 rounding) skips objects that cannot contain the node; survivors
-// take the exact FP64 test.  Deepest penetration wins, lowest index on ties.
-// Returns the winning slot or -1; u is the winner's u_hat rounded to FP32.
-__device__ __forceinline__ int contact_node(const SceneDev &S, size_t row, unsigned cand, float px, float py,
-                                            float pz, float nx, float ny, float nz, float &u0, float &u1,
-                                            float &u2) {
+// One object of a scene row as the contact test reads it.
+struct ObjRow {
+    int type;
+    float shape[4], rot[9], trans[3];
+    float reach2;      // square of the ball test's radius
+};
+constexpr int kObjWords = sizeof(ObjRow) / 4;
+
+// The ball that rules a node out in FP32, with a relative margin of 1e-3 (far
+// above FP32 rounding).
+__device__ __forceinline__ float ball_reach2(int type, const float *shape) {
+    const float rb = bounding_radius(type, shape) * 1.001f + 1e-3f;
+    return rb * rb;
+}
+
+struct NodeContact {
     int best = -1;
     double bd = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
-    const int no = min(S.n_obj[row], S.O);   // device contents are not validated on the host
-    for (int o = 0; o < no; ++o) {
-        if (!((cand >> o) & 1u)) continue;
-        const size_t eo = row * S.O + o;
-        const int ty = S.type[eo];
-        const float *sh = S.shape + 4 * eo;
-        const float *R = S.rot + 9 * eo;
-        const float *t = S.trans + 3 * eo;
+
+    __device__ __forceinline__ void test(int o, int ty, const float *sh, const float *R, const float *t, float reach2,
+                                         float px, float py, float pz, float nx, float ny, float nz) {
         const float dx = px - t[0], dy = py - t[1], dz = pz - t[2];
-        const float rb = bounding_radius(ty, sh) * 1.001f + 1e-3f;
-        if (dx * dx + dy * dy + dz * dz > rb * rb) continue;
+        if (dx * dx + dy * dy + dz * dz > reach2) return;
         const Pen h = penetrate(ty, sh, R, t, px, py, pz, nx, ny, nz);
         if (h.inside && (best < 0 || h.depth > bd)) {
             best = o;
@@ -143,8 +145,40 @@ __device__ __forceinline__ int contact_node(const SceneDev &S, size_t row, unsig
             b0 = h.u0; b1 = h.u1; b2 = h.u2;
         }
     }
-    u0 = (float)b0; u1 = (float)b1; u2 = (float)b2;
-    return best;
+};
+
+// Contact of one node with the candidate objects of scene row `row` (bit o
+// of `cand`).  The ball test skips objects that cannot contain the node;
+// survivors take the exact FP64 test.  Deepest penetration wins, lowest index
+// on ties.  Returns the winning slot or -1; u is the winner's u_hat rounded to
+// FP32.
+__device__ __forceinline__ int contact_node(const SceneDev &S, size_t row, unsigned cand, float px, float py,
+                                            float pz, float nx, float ny, float nz, float &u0, float &u1,
+                                            float &u2) {
+    NodeContact c;
+    const int no = min(S.n_obj[row], S.O);   // device contents are not validated on the host
+    for (int o = 0; o < no; ++o) {
+        if (!((cand >> o) & 1u)) continue;
+        const size_t eo = row * S.O + o;
+        const int ty = S.type[eo];
+        const float *sh = S.shape + 4 * eo;
+        c.test(o, ty, sh, S.rot + 9 * eo, S.trans + 3 * eo, ball_reach2(ty, sh), px, py, pz, nx, ny, nz);
+    }
+    u0 = (float)c.b0; u1 = (float)c.b1; u2 = (float)c.b2;
+    return c.best;
+}
+
+// The same from objects in LDS (an env's row).
+__device__ __forceinline__ int contact_node(const ObjRow *obj, unsigned cand, float px, float py, float pz, float nx,
+                                            float ny, float nz, float &u0, float &u1, float &u2) {
+    NodeContact c;
+    for (; cand; cand &= cand - 1) {     // ascending
+        const int o = __ffs(cand) - 1;
+        const ObjRow &r = obj[o];
+        c.test(o, r.type, r.shape, r.rot, r.trans, r.reach2, px, py, pz, nx, ny, nz);
+    }
+    u0 = (float)c.b0; u1 = (float)c.b1; u2 = (float)c.b2;
+    return c.best;
 }
 
 // dL/d(R, t) contribution of one active node from dL/du_hat = g (FP64),

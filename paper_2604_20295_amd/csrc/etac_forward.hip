@@ -1,12 +1,12 @@
 // Forward kernels of the ETac step on gfx950:
-//   k_contact       : contact pass alone, one workgroup per env (HBM-write bound)
-// and the step, four launches over (env, patch) items:
+// launches over (env, patch) items:
 //   k_tables        : what the model gives on the undeformed surface, the same
 //                     for every env: encoder features of passive nodes and
 //                     their decoder part, and the decay matrices of Eq. 1
 //   k_contact_items : contact of every node (or given contact results): winners,
 //                     u_hat, and a bit per node for the kernels that follow
-//                     (one launch with k_tables on small batches: k_front)
+//                     (one launch with k_tables on small batches: k_front);
+//                     also the contact pass alone
 //   k_live          : the envs in contact on each patch
 //   k_pool          : max-pool and global MLP of the items in contact
 //   k_prop_wide / k_prop_narrow / k_prop_far : U of their passive nodes
@@ -24,92 +24,7 @@
 namespace etac {
 
 // ---------------------------------------------------------------------------
-// contact pass alone
-// ---------------------------------------------------------------------------
-struct ContactParams {
-    MeshDev mesh;
-    SceneDev scene;
-    int8_t *cobj;      // [E][N]
-    float *uhat;       // [3][E][N] or null
-    int32_t *n_active; // [E][K]
-    int32_t *n_touch;  // [E][K] active nodes won by external objects, or null
-};
-
-// One workgroup per env.  The patches' candidate objects are culled first
-// (one mask per patch in LDS), so nodes of patches no object reaches only
-// store their empty result; the others are tested one node per thread,
-// consecutive threads on consecutive nodes.  ROWS: the hand's candidate rows
-// (ids mapped through src, object-won nodes counted).
-template <bool ROWS>
-__global__ __launch_bounds__(kWG) void k_contact(ContactParams p) {
-    __shared__ int cnt[kMaxPatches];
-    __shared__ int tcnt[ROWS ? kMaxPatches : 1];
-    __shared__ unsigned cand[kMaxPatches];
-    const int e = blockIdx.x;
-    const MeshDev &M = p.mesh;
-    const SceneDev &S = p.scene;
-    const int N = M.N, K = M.K;
-    const size_t EN = (size_t)S.E * N;
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        cnt[k] = 0;
-        if (ROWS) tcnt[k] = 0;
-        cand[k] = ROWS ? cull_objects(S, M, e, k) : cull_objects(S, M, e, k, (size_t)e);
-    }
-    __syncthreads();
-    const size_t row = (size_t)e * N;
-    for (int i = threadIdx.x; i < N; i += kWG) {
-        int best = -1;
-        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-        const int k = M.node_patch[i];
-        const unsigned c = cand[k];
-        int8_t id = -1;
-        if (c) {
-            const size_t srow = ROWS ? scene_row(S, e, k) : (size_t)e;
-            best = contact_node(S, srow, c, M.pos[i], M.pos[N + i], M.pos[2 * N + i], M.nrm[i], M.nrm[N + i],
-                                M.nrm[2 * N + i], u0, u1, u2);
-            if (best >= 0) {
-                atomicAdd(&cnt[k], 1);
-                id = (int8_t)best;
-                if (ROWS) {
-                    if (S.n_ext && best < S.n_ext[srow]) atomicAdd(&tcnt[k], 1);
-                    if (S.src) id = S.src[srow * S.O + best];
-                }
-            }
-        }
-        // results stream out: non-temporal stores keep them from displacing cached inputs
-        __builtin_nontemporal_store(id, p.cobj + row + i);
-        if (p.uhat) {
-            __builtin_nontemporal_store(u0, p.uhat + row + i);
-            __builtin_nontemporal_store(u1, p.uhat + EN + row + i);
-            __builtin_nontemporal_store(u2, p.uhat + 2 * EN + row + i);
-        }
-    }
-    __syncthreads();
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        p.n_active[(size_t)e * K + k] = cnt[k];
-        if (ROWS && p.n_touch) p.n_touch[(size_t)e * K + k] = tcnt[k];
-    }
-}
-
-hipError_t launch_contact(const Plan &p, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
-                          hipStream_t st) {
-    return launch_contact_rows(p, s, cobj, uhat, n_active, nullptr, st);
-}
-
-hipError_t launch_contact_rows(const Plan &p, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
-                               int32_t *n_touch, hipStream_t st) {
-    if (s.E == 0) return hipSuccess;
-    ContactParams cp{p.mesh, s, cobj, uhat, n_active, n_touch};
-    const int slot = timer_begin(p, ETAC_TIMER_CONTACT, st);
-    if (s.rows_per_env) hipLaunchKernelGGL(k_contact<true>, dim3(s.E), dim3(kWG), 0, st, cp);
-    else hipLaunchKernelGGL(k_contact<false>, dim3(s.E), dim3(kWG), 0, st, cp);
-    const hipError_t e = hipGetLastError();
-    timer_end(p, ETAC_TIMER_CONTACT, slot, st);
-    return e;
-}
-
-// ---------------------------------------------------------------------------
-// step
+// contact pass
 // ---------------------------------------------------------------------------
 template <bool FROM_INPUT, bool ROWS>
 __global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
@@ -1113,6 +1028,40 @@ static void launch_contact_items(const StepParams &p, bool merged, int nt, hipSt
     }
 }
 
+// Workgroups per env of the contact pass: enough to fill the chip.
+static int contact_splits(const Plan &pl, int E) {
+    int s = 1;
+    while (E * s < 4 * pl.cu_count && s * kWaves * 4 < pl.tile.NW) s *= 2;
+    return s;
+}
+
+hipError_t launch_contact(const Plan &p, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
+                          hipStream_t st) {
+    return launch_contact_rows(p, s, cobj, uhat, n_active, nullptr, st);
+}
+
+hipError_t launch_contact_rows(const Plan &pl, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
+                               int32_t *n_touch, hipStream_t st) {
+    if (s.E == 0) return hipSuccess;
+    StepParams p{};
+    p.mesh = pl.mesh;
+    p.tile = pl.tile;
+    p.scene = s;
+    p.model = ModelDev{ETAC_DECAY_ONLY, nullptr, nullptr};
+    p.E = s.E;
+    p.splits = contact_splits(pl, s.E);
+    p.u = uhat;
+    p.cobj_out = cobj;
+    p.n_active = n_active;
+    p.n_touch = n_touch;
+    const int slot = timer_begin(pl, ETAC_TIMER_CONTACT, st);
+    if (p.splits > 1) hipLaunchKernelGGL(k_tables, dim3(64), dim3(kWG), 0, st, p);      // counts to zero
+    launch_contact_items<false>(p, false, 0, st);
+    const hipError_t e = hipGetLastError();
+    timer_end(pl, ETAC_TIMER_CONTACT, slot, st);
+    return e;
+}
+
 void shape_step(const Plan &pl, StepParams &p) {
     p.mesh = pl.mesh;
     p.tile = pl.tile;
@@ -1127,8 +1076,7 @@ void shape_step(const Plan &pl, StepParams &p) {
     // listed.  A launch costs 5-7 us; on one 32 x 32 pad the whole step takes
     // about 50, and the listing of 256 items would take as long as visiting them.
     p.dense = p.items <= 256;
-    p.splits = 1;
-    while (p.E * p.splits < 4 * pl.cu_count && p.splits * kWaves * 4 < pl.tile.NW) p.splits *= 2;
+    p.splits = contact_splits(pl, p.E);
 }
 
 void launch_front(const Plan &pl, const StepParams &p, hipStream_t st) {

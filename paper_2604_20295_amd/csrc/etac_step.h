@@ -48,87 +48,188 @@ __device__ __forceinline__ int live_env(const StepParams &p, int k, int q) {
     return p.dense ? q : p.itm.live[(size_t)k * p.E + q];
 }
 
+constexpr int kScan = kWG;      // words listed at a time
+
 struct ContactLds {
     int cnt[kMaxPatches];
     int tcnt[kMaxPatches];
     unsigned cand[kMaxPatches];
+    int wsum[kWaves];
+    int list[kScan];
+    ObjRow obj[ETAC_MAX_OBJ];
 };
 
-// Contact of env e's words s, s + S, ... : a wave takes a word, a lane a node.
-// Winners and u_hat stream out (0 and -1 where there is no contact), and a bit
-// per node is kept.  Bound by those stores: the same 13 bytes a node as the
-// contact pass alone, plus a word of bits.
+// Stores of four consecutive values at any 4-byte (winners: 1-byte) address.
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned uint1u __attribute__((aligned(1)));
+
+// Contact of env e, workgroup s of p.splits: first the empty results of every
+// node of patches that no object reaches (five of six on a hand), four nodes a
+// thread; then the words of the other patches, listed in LDS, a word per wave
+// and a node per lane.  Winners and u_hat stream out, and a bit per node is
+// kept in p.itm.mask (null for the contact pass alone).  Bound by the stores,
+// 13 bytes a node: a lane's 16-byte stores issue a quarter of the instructions
+// of a node per lane, which ran at half the rate a fill of the same bytes does.
 template <bool FROM_INPUT, bool ROWS>
 __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
     const MeshDev &M = p.mesh;
     const SceneDev &S = p.scene;
-    const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const int N = M.N, K = M.K, NW = p.tile.NW, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
+    int no = 0;
+    if (!FROM_INPUT && !ROWS) {      // the env's objects: read once, then from LDS
+        no = min(uniform(S.n_obj[e]), S.O);
+        if ((int)threadIdx.x < no * 17) {
+            const int o = threadIdx.x / 17, c = threadIdx.x - 17 * o;
+            const size_t eo = (size_t)e * S.O + o;
+            ObjRow &r = L.obj[o];
+            if (c == 0) r.type = S.type[eo];
+            else if (c < 5) r.shape[c - 1] = S.shape[4 * eo + c - 1];
+            else if (c < 14) r.rot[c - 5] = S.rot[9 * eo + c - 5];
+            else r.trans[c - 14] = S.trans[3 * eo + c - 14];
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < no) L.obj[threadIdx.x].reach2 = ball_reach2(L.obj[threadIdx.x].type, L.obj[threadIdx.x].shape);
+    }
     for (int k = threadIdx.x; k < K; k += kWG) {
         L.cnt[k] = 0;
         L.tcnt[k] = 0;
-        L.cand[k] = FROM_INPUT ? ~0u : cull_objects(S, M, e, k);
+        unsigned c = FROM_INPUT ? ~0u : 0u;
+        if (!FROM_INPUT && ROWS) c = cull_objects(S, M, e, k);
+        if (!FROM_INPUT && !ROWS) {
+            const float4 b = M.bound[k];
+            for (int o = 0; o < no; ++o) {
+                const ObjRow &r = L.obj[o];
+                if ((unsigned)r.type <= (unsigned)ETAC_CAPSULE && ball_reaches(b, r.type, r.shape, r.trans)) c |= 1u << o;
+            }
+        }
+        L.cand[k] = c;
     }
     __syncthreads();
-    const bool want_umax = step_residual(p);
-    const int NW = p.tile.NW, step = p.splits * kWaves;
-    int4 next = p.tile.word[min(s * kWaves + wave, NW - 1)];
-    for (int w = s * kWaves + wave; w < NW; w += step) {
-        const int4 inf = next;
-        next = p.tile.word[min(w + step, NW - 1)];
-        const int k = uniform(inf.x), i = uniform(inf.y) + lane;
-        const bool valid = lane < uniform(inf.z);
-        const unsigned c = uniform(L.cand[k]);
-        int best = -1;
-        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-        int8_t id = -1;
-        bool touch = false;
-        if (FROM_INPUT) {
-            if (valid && p.cobj_in[row + i] >= 0) {
-                best = 0;
-                u0 = p.uhat_in[row + i];
-                u1 = p.uhat_in[EN + row + i];
-                u2 = p.uhat_in[2 * EN + row + i];
+    if (!FROM_INPUT) {
+        const floatx4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int i = 4 * (s * kWG + threadIdx.x); i < N; i += 4 * kWG * p.splits) {
+            unsigned c[4];
+            bool none = i + 4 <= N;
+            int k[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) k[x] = M.node_patch[min(i + x, N - 1)];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                c[x] = L.cand[k[x]];
+                none = none && c[x] == 0;
             }
-        } else if (c) {
-            if (valid) {
-                const size_t srow = ROWS ? scene_row(S, e, k) : (size_t)e;
-                best = contact_node(S, srow, c, M.pos[i], M.pos[N + i], M.pos[2 * N + i], M.nrm[i], M.nrm[N + i],
-                                    M.nrm[2 * N + i], u0, u1, u2);
-                id = (int8_t)best;
-                if (ROWS && best >= 0) {
-                    touch = S.n_ext && best < S.n_ext[srow];
-                    if (S.src) id = S.src[srow * S.O + best];
+            if (none) {
+                if (p.cobj_out) __builtin_nontemporal_store(~0u, reinterpret_cast<uint1u *>(p.cobj_out + row + i));
+                if (p.u)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        __builtin_nontemporal_store(zero, reinterpret_cast<floatx4u *>(p.u + a * EN + row + i));
+            } else {
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (i + x < N && c[x] == 0) {
+                        if (p.cobj_out) p.cobj_out[row + i + x] = -1;
+                        if (p.u)
+#pragma unroll
+                            for (int a = 0; a < 3; ++a) p.u[a * EN + row + i + x] = 0.0f;
+                    }
+            }
+        }
+    }
+    const bool want_umax = p.itm.mask && step_residual(p);
+    for (int w0 = 0; w0 < NW; w0 += kScan * p.splits) {
+        // words w0 + s, w0 + s + splits, ... of patches with candidates
+        const int mine = w0 + s + p.splits * (int)threadIdx.x;
+        const bool in = mine < NW;
+        const bool hit = in && L.cand[p.tile.word[min(mine, NW - 1)].x] != 0;
+        if (in && !hit && p.itm.mask) p.itm.mask[(size_t)e * NW + mine] = 0ull;
+        const unsigned long long bal = __ballot(hit);
+        L.wsum[wave] = __popcll(bal);      // identical in every lane
+        __syncthreads();
+        int off = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) off += L.wsum[w];
+            total += L.wsum[w];
+        }
+        total = uniform(total);
+        if (hit) L.list[off + lanes_below(bal)] = mine;
+        __syncthreads();
+        // the next word's geometry is requested while this one is tested
+        int4 inf{};
+        float x[6];
+        auto fetch = [&](int t) {
+            inf = p.tile.word[uniform(L.list[t])];
+            if (!FROM_INPUT) {
+                const int i = uniform(inf.y) + min(lane, uniform(inf.z) - 1);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    x[c] = M.pos[(size_t)c * N + i];
+                    x[3 + c] = M.nrm[(size_t)c * N + i];
+                }
+            }
+        };
+        if (wave < total) fetch(wave);
+        for (int t = wave; t < total; t += kWaves) {
+            const int w = uniform(L.list[t]);
+            const int k = uniform(inf.x), i = uniform(inf.y) + lane;
+            const bool valid = lane < uniform(inf.z);
+            const float px = x[0], py = x[1], pz = x[2], nx = x[3], ny = x[4], nz = x[5];
+            if (t + kWaves < total) fetch(t + kWaves);
+            int best = -1;
+            float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+            int8_t id = -1;
+            bool touch = false;
+            if (FROM_INPUT) {
+                if (valid && p.cobj_in[row + i] >= 0) {
+                    best = 0;
+                    u0 = p.uhat_in[row + i];
+                    u1 = p.uhat_in[EN + row + i];
+                    u2 = p.uhat_in[2 * EN + row + i];
+                }
+            } else if (valid) {
+                const unsigned c = uniform(L.cand[k]);
+                if (ROWS) {
+                    const size_t srow = scene_row(S, e, k);
+                    best = contact_node(S, srow, c, px, py, pz, nx, ny, nz, u0, u1, u2);
+                    if (best >= 0) touch = S.n_ext && best < S.n_ext[srow];
+                    id = best >= 0 && S.src ? S.src[srow * S.O + best] : (int8_t)best;
+                } else {
+                    best = contact_node(L.obj, c, px, py, pz, nx, ny, nz, u0, u1, u2);
+                    id = (int8_t)best;
+                }
+            }
+            if (FROM_INPUT && p.adjoint) {
+                if (valid) {
+                    p.u[row + i] = 0.0f;
+                    p.u[EN + row + i] = 0.0f;
+                    p.u[2 * EN + row + i] = 0.0f;
+                }
+            } else if (valid) {
+                if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
+                if (p.u) {
+                    __builtin_nontemporal_store(u0, p.u + row + i);
+                    __builtin_nontemporal_store(u1, p.u + EN + row + i);
+                    __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
+                }
+            }
+            const unsigned long long act = __ballot(best >= 0);
+            if (p.itm.mask) p.itm.mask[(size_t)e * NW + w] = act;      // every lane stores the same value
+            if (act) {                                                 // wave-uniform
+                if (want_umax) {
+                    const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
+                    p.itm.umax[(size_t)e * NW + w] = m;
+                }
+                const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
+                if (lane == 0) {
+                    atomicAdd(&L.cnt[k], __popcll(act));
+                    if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
                 }
             }
         }
-        if (FROM_INPUT && p.adjoint) {
-            if (valid) {
-                p.u[row + i] = 0.0f;
-                p.u[EN + row + i] = 0.0f;
-                p.u[2 * EN + row + i] = 0.0f;
-            }
-        } else if (valid) {
-            if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
-            __builtin_nontemporal_store(u0, p.u + row + i);
-            __builtin_nontemporal_store(u1, p.u + EN + row + i);
-            __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
-        }
-        const unsigned long long act = __ballot(best >= 0);
-        p.itm.mask[(size_t)e * NW + w] = act;             // every lane stores the same value
-        if (act) {                                        // wave-uniform
-            if (want_umax) {
-                const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
-                p.itm.umax[(size_t)e * NW + w] = m;
-            }
-            const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
-            if (lane == 0) {
-                atomicAdd(&L.cnt[k], __popcll(act));
-                if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
-            }
-        }
+        __syncthreads();      // the list is rewritten
     }
-    __syncthreads();
     if (want_umax)
         for (int k = wave; k < K; k += kWaves)
             if (uniform(L.cnt[k])) p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
