@@ -43,10 +43,10 @@ __device__ void pair_adjoint(const AdjParams &p, int k, int e, int j, float (&q)
     for (int i = 0; i < n; ++i) {
         if ((mask[i >> 6] >> (i & 63)) & 1ull) continue;
         float d;
-        const float w = decay_weight(M.pos[base + i] - M.pos[base + j], M.pos[N + base + i] - M.pos[N + base + j],
+        const double w = decay_weight_wide(M.pos[base + i] - M.pos[base + j], M.pos[N + base + i] - M.pos[N + base + j],
                                      M.pos[2 * N + base + i] - M.pos[2 * N + base + j], hi, lo, d);
         for (int c = 0; c < 3; ++c) {
-            const double wg = (double)w * (double)p.grad_u[c * EN + row + i];      // beyond FP32's range here
+            const double wg = w * (double)p.grad_u[c * EN + row + i];      // beyond FP32's range here
             a[c] += wg;
             b[c] += (double)d * wg;
         }
@@ -58,6 +58,17 @@ __device__ void pair_adjoint(const AdjParams &p, int k, int e, int j, float (&q)
     }
 }
 
+// Four consecutive values, the last ones 0 where fewer than four are left.
+__device__ __forceinline__ floatx4 load4(const float *x, int left) {
+    floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (left >= 4) __builtin_memcpy(&v, x, 16);
+    else
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < left) v[i] = x[i];
+    return v;
+}
+
 // dL/du_hat of the four consecutive nodes from local node i0 of one env: own
 // gradient plus the decay part; active nodes only.  Returns their part of
 // dL/dalpha (qd: the sums with d w).
@@ -65,38 +76,88 @@ __device__ __forceinline__ double finish_rows(const AdjParams &p, int k, int e, 
                                               const floatx4 (&q)[3], const floatx4 (&qd)[3], bool dec, bool slow) {
     const int N = p.s.mesh.N, w0 = p.s.tile.word_off[k];
     const size_t EN = (size_t)p.s.E * N, at = (size_t)e * N + base + i0;
-    const float *u = uhat_source(p.s);
-    unsigned act = (unsigned)(p.s.itm.mask[(size_t)e * p.s.tile.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
+    const unsigned act = (unsigned)(p.s.itm.mask[(size_t)e * p.s.tile.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
+    const float *u = uhat_source(p.s) + at;
+    floatx4 g[3], uh[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        g[c] = load4(p.grad_u + c * EN + at, left);
+        uh[c] = load4(u + c * EN, left);
+    }
     double da = 0.0;
+    floatx4 v[3] = {q[0], q[1], q[2]};
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-        if (x >= left || !((act >> x) & 1u)) continue;
-        float v[3] = {q[0][x], q[1][x], q[2][x]};
-        if (dec && slow) {
+        if (!((act >> x) & 1u) || !dec) continue;      // bits beyond the patch are clear
+        if (slow) {
             double d;
-            pair_adjoint(p, k, e, i0 + x, v, d);
+            float w[3];
+            pair_adjoint(p, k, e, i0 + x, w, d);
             da += d;
-        } else if (dec) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) da -= (double)u[c * EN + at + x] * (double)qd[c][x];
+            for (int c = 0; c < 3; ++c) v[c][x] = w[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) da -= (double)uh[c][x] * (double)qd[c][x];
         }
+    }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const float g = p.grad_u[c * EN + at + x];
-            p.gh[c * EN + at + x] = dec ? g + v[c] : g;
+    for (int c = 0; c < 3; ++c) {
+        const floatx4 o = dec ? g[c] + v[c] : g[c];
+        float *out = p.gh + c * EN + at;
+        if (act == 0xfu) {
+            __builtin_memcpy(out, &o, 16);
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                if ((act >> x) & 1u) out[x] = o[x];
         }
     }
     return da;
 }
 
-// Wide tiles: 64 rows (a wave takes one row tile) times 32 envs, as the
-// forward's, each B fragment against W and d W: 72 MFMAs per wave and K step.
+// Largest |dL/dU| component over an item's passive nodes, the range of its
+// values in the product.  A wave takes an item; bound by its one pass over
+// grad_u.
+__global__ __launch_bounds__(kWG) void k_grad_max(AdjParams p) {
+    __shared__ int first[kMaxPatches + 1];
+    const StepParams &S = p.s;
+    const MeshDev &M = S.mesh;
+    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const size_t EN = (size_t)S.E * N;
+    const int total = unit_prefix<kWaves>(K, first, [&](int kk) {
+        return S.tile.w_off[M.order[kk]] < 0 ? 0 : live_count(S, M.order[kk]);
+    });
+    for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
+        const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]);
+        const int e = uniform(live_env(S, k, q - uniform(first[kk])));
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, nw = (n + 63) >> 6;
+        const float *g = p.grad_u + (size_t)e * N + base;
+        const unsigned long long *mask = S.itm.mask + (size_t)e * S.tile.NW + uniform(S.tile.word_off[k]);
+        float m = 0.0f;
+#pragma unroll 4
+        for (int w = 0; w < nw; ++w) {
+            const int i = min(64 * w + lane, n - 1);
+            const float x = fmaxf(fmaxf(fabsf(g[i]), fabsf(g[EN + i])), fabsf(g[2 * EN + i]));
+            if (!((mask[w] >> (i & 63)) & 1ull)) m = fmaxf(m, x);      // beyond the patch: its last node
+        }
+        m = wave_max(m);
+        if (lane == 0) p.b.grad_max[(size_t)e * K + k] = m;
+    }
+}
+
+// Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs, as the
+// forward's, each B fragment against W and d W.  Bound by the matrix cores
+// (4096 hands: 17.8 M MFMAs, 116 us at full rate) and by the reading and
+// splitting of the envs' values, which a taller tile does for more rows: 414 us
+// at MT = 1 (261 us of them with neither), 331 us at MT = 2.
 struct AdjWideLds {
     int first[kMaxPatches + 1];
     int env[32];
-    bf16x8 b[2][2][6][3][64];     // [buffer][K step][3 column tile + component][part][lane]
+    ProductB b;
 };
 
+template <int MT>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_wide(AdjParams p) {
     __shared__ AdjWideLds L;
     const StepParams &S = p.s;
@@ -106,15 +167,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const size_t EN = (size_t)S.E * N;
     const bool dec = step_decay(S);
     const int32_t *na = S.itm.n_act;
-    const int total = unit_prefix<kWaves>(K, L.first, [&](int kk) {
-        const int k = M.order[kk], n = M.offset[k + 1] - M.offset[k];
-        return T.w_off[k] < 0 ? 0 : ((live_count(S, k) + 31) >> 5) * ((n + 63) >> 6);
-    });
-    for (int q = blockIdx.x; q < total; q += gridDim.x) {
-        const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
+    const int total = product_units(S, L.first, 64 * MT, 32);
+    for (int q = product_start(); q < total; q += product_stride()) {
+        const ProductRef ref = product_ref(S, L.first, q, 64 * MT);
+        const int k = ref.k, rb = ref.row_block, g0 = ref.group * 32;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
-        const int cnt = uniform(live_count(S, k)), groups = (cnt + 31) >> 5;
-        const int local = q - uniform(L.first[kk]), rb = local / groups, g0 = (local - rb * groups) * 32;
+        const int cnt = uniform(live_count(S, k));
         const int w0 = uniform(T.word_off[k]);
         __syncthreads();      // the previous unit is done with L
         if (threadIdx.x < 32) {
@@ -125,86 +183,70 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         int env[2];
         env[0] = L.env[col];
         env[1] = L.env[16 + col];
-        const int rt = 4 * rb + wave, rts = (n + 15) >> 4;
-        floatx4 acc[2][2][3];     // [W, d W][column tile][component]
+        const int rt0 = (4 * rb + wave) * MT, rts = (n + 15) >> 4;
+        floatx4 acc[2 * MT][2][3];     // [row tile, W or d W][column tile][component]
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < 2 * MT; ++m)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         const bool slow = matrix_overflows(M, S.model.alpha[k], k);
         if (dec && !slow) {
-            const int myenv = (wave & 1) ? env[1] : env[0], safe = max(myenv, 0);
-            const float *me = p.grad_u + (size_t)safe * N + base;
-            const unsigned long long *mymask = S.itm.mask + (size_t)safe * T.NW + w0;
-            float raw[3][8];
-            unsigned bits = 0;
-            auto fetch = [&](int s0) {
-                const int j0 = 32 * (s0 + (wave >> 1)) + 8 * gq;
-                const bool in = myenv >= 0 && j0 < n;
-                bits = in ? ~(unsigned)(mymask[j0 >> 6] >> (j0 & 63)) & 0xffu : 0u;      // passive nodes
+            const bool half = matrix_half(S, k);
+            const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
+            const unsigned long long *mask = S.itm.mask + (size_t)safe * T.NW + w0;
+            const size_t at = (size_t)safe * N + base;
+            const uint4 *wa[2 * MT];
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (in) load8(me + c * EN, j0, n, raw[c]);
-            };
-            auto put = [&](int buf) {
+            for (int m = 0; m < MT; ++m) {      // rows beyond the patch repeat its last tile
+                const size_t w_at = T.w_off[k] + (size_t)min(rt0 + m, rts - 1) * KS * (half ? 2 : 3) * 64 + lane;
+                wa[2 * m] = S.tab.w + w_at;
+                wa[2 * m + 1] = S.tab.wd + w_at;
+            }
+            if (half) {
+                auto exponent = [&](int e) { return top_exp(p.b.grad_max[(size_t)max(e, 0) * K + k]); };
+                product_loop<2 * MT, true, true>(L.b, wa, p.grad_u, at, EN, mask, pow2(exponent(myenv)), myenv >= 0, n, KS, acc);
+                const int ew[2] = {weight_exp(S, k), distance_weight_exp(S, k)};
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    bf16x8 b[3];
+                for (int t = 0; t < 2; ++t) {
+                    const int s = exponent(env[t]);
 #pragma unroll
-                    for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
-                    split_bf16x3(raw[c], b);
+                    for (int m = 0; m < 2 * MT; ++m)
 #pragma unroll
-                    for (int y = 0; y < 3; ++y) L.b[buf][wave >> 1][3 * (wave & 1) + c][y][lane] = b[y];
+                        for (int c = 0; c < 3; ++c)
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) acc[m][t][c][x] = ldexpf(acc[m][t][c][x], -(s + ew[m & 1]));
                 }
-            };
-            const size_t at = T.w_off[k] + (size_t)min(rt, rts - 1) * KS * 3 * 64 + lane;
-            const uint4 *wa[2] = {S.tab.w + at, S.tab.wd + at};
-            uint4 a[2][2][3];
-            auto fetch_a = [&](int s, uint4 (&x)[2][3]) {
+            } else {
 #pragma unroll
-                for (int m = 0; m < 2; ++m)
+                for (int m = 0; m < MT; ++m) {      // one row tile at a time: three parts of two would not fit the registers
+                    const uint4 *const w2[2] = {wa[2 * m], wa[2 * m + 1]};
+                    floatx4 a2[2][2][3];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) x[m][c] = wa[m][(size_t)(s * 3 + c) * 64];
-            };
-            auto mul = [&](int buf, int ds, const uint4 (&x)[2][3]) {
+                    for (int i = 0; i < 12; ++i) a2[i / 6][i / 3 % 2][i % 3] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                    product_loop<2, true, false>(L.b, w2, p.grad_u, at, EN, mask, 1.0f, myenv >= 0, n, KS, a2);
 #pragma unroll
-                for (int f = 0; f < 6; ++f) {
-                    bf16x8 b[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) b[c] = L.b[buf][ds][f][c][lane];
-#pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        const bf16x8 y[3] = {__builtin_bit_cast(bf16x8, x[m][0]), __builtin_bit_cast(bf16x8, x[m][1]),
-                                             __builtin_bit_cast(bf16x8, x[m][2])};
-                        acc[m][f / 3][f % 3] = mfma_bf16x3(y, b, acc[m][f / 3][f % 3]);
-                    }
+                    for (int i = 0; i < 12; ++i) acc[2 * m + i / 6][i / 3 % 2][i % 3] = a2[i / 6][i / 3 % 2][i % 3];
+                    __syncthreads();      // L.b is done with
                 }
-            };
-            fetch(0);
-            fetch_a(0, a[0]);
-            put(0);
-            for (int s0 = 0, buf = 0; s0 < KS; s0 += 2, buf ^= 1) {
-                __syncthreads();
-                fetch_a(min(s0 + 1, KS - 1), a[1]);
-                if (s0 + 2 < KS) fetch(s0 + 2);
-                mul(buf, 0, a[0]);
-                fetch_a(min(s0 + 2, KS - 1), a[0]);
-                if (s0 + 1 < KS) mul(buf, 1, a[1]);
-                if (s0 + 2 < KS) put(buf ^ 1);
             }
         }
-        if (rt >= rts) continue;      // no barrier before the next unit's first
-        const int i0 = 16 * rt + 4 * gq;
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int e = env[t];
-            double da = 0.0;
-            if (e >= 0 && i0 < n) da = finish_rows(p, k, e, base, i0, n - i0, acc[0][t], acc[1][t], dec, slow);
-            da += __shfl_xor(da, 16);
-            da += __shfl_xor(da, 32);
-            if (e >= 0) p.b.alpha_part[(size_t)e * T.NP + T.part_off[k] + rt] = da;      // the same in the 4 lane groups
+        for (int m = 0; m < MT; ++m) {
+            const int rt = rt0 + m;
+            if (rt >= rts) break;      // no barrier before the next unit's first
+            const int i0 = 16 * rt + 4 * gq;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int e = env[t];
+                double da = 0.0;
+                if (e >= 0 && i0 < n)
+                    da = finish_rows(p, k, e, base, i0, n - i0, acc[2 * m][t], acc[2 * m + 1][t], dec, slow);
+                da += __shfl_xor(da, 16);
+                da += __shfl_xor(da, 32);
+                if (e >= 0) p.b.alpha_part[(size_t)e * T.NP + T.part_off[k] + rt] = da;      // the same in the 4 lane groups
+            }
         }
     }
 }
@@ -1004,7 +1046,10 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     launch_front(pl, f, st);
     if (pl.tile.n_near) {
         // as in the forward: wide tiles once they give every CU work
-        if (n_envs >= 128) hipLaunchKernelGGL(k_adj_wide, dim3(2 * f.cus), dim3(kWG), 0, st, p);
+        if (f.wide && dec)
+            hipLaunchKernelGGL(k_grad_max, dim3(blocks((items + kWaves - 1) / kWaves, 8 * cus)), dim3(kWG), 0, st, p);
+        if (n_envs >= 1024) hipLaunchKernelGGL(k_adj_wide<2>, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
+        else if (f.wide) hipLaunchKernelGGL(k_adj_wide<1>, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_adj_narrow, dim3(blocks((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
                                dim3(kWG), 0, st, p);

@@ -485,11 +485,11 @@ __device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *
     for (int j = 0; j < n; ++j) {
         if (!((mask[j >> 6] >> (j & 63)) & 1ull)) continue;
         float d;
-        const float w = decay_weight(M.pos[base + j] - M.pos[base + i], M.pos[N + base + j] - M.pos[N + base + i],
+        const double w = decay_weight_wide(M.pos[base + j] - M.pos[base + i], M.pos[N + base + j] - M.pos[N + base + i],
                                      M.pos[2 * N + base + j] - M.pos[2 * N + base + i], hi, lo, d);
-        a0 += (double)w * u[j];      // products beyond FP32's range stay finite
-        a1 += (double)w * u[EN + j];
-        a2 += (double)w * u[2 * EN + j];
+        a0 += w * u[j];
+        a1 += w * u[EN + j];
+        a2 += w * u[2 * EN + j];
     }
     // element x of the four (no register indexed at run time)
 #pragma unroll
@@ -550,18 +550,20 @@ __device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, in
 }
 
 // Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs (two column
-// tiles per component: column l & 15 is an env).  Per K step a wave issues
-// 36 MT MFMAs on 3 MT A fragments from L2, requested a step ahead, and 18 B
-// fragments from LDS; the B fragments are split once per workgroup, two K steps
-// at a time, while the MFMAs of the previous two run.  Bound by the matrix
-// cores (6 BF16 products per FP32 one) and, in the epilogue, by the VALU.
+// tiles per component: column l & 15 is an env).  Bound by the matrix cores in
+// the loop (4096 hands: 8.9 M MFMAs, 116 us of all of them at full rate) and by
+// the VALU in the epilogue (five operations per node, env and channel of the
+// residual).  A taller tile reads and splits each env's values for more rows;
+// patches are padded to it and there are fewer units, so it pays once there are
+// many: 4096 hands 290 us at MT = 2 and 254 at MT = 4, 16384 hands 1116 and 937.
 constexpr int kWideEnvs = 32;
 
 struct WideLds {
     int first[kMaxPatches + 1];
     int env[kWideEnvs];
+    int exp[kWideEnvs];               // scale exponents of their values
     union {
-        bf16x8 b[2][2][6][3][64];     // [buffer][K step][3 column tile + component][part][lane]
+        ProductB b;
         struct {                      // after the K loop
             float c4[kWideEnvs][68];
             float w5[3][64], b5[4];
@@ -580,16 +582,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const bool dec = step_decay(p), res = step_residual(p);
     const float *src = uhat_source(p);
     const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
-    const int total = unit_prefix<kWaves>(K, L.first, [&](int kk) {
-        const int k = M.order[kk], n = M.offset[k + 1] - M.offset[k];
-        if (T.w_off[k] < 0) return 0;
-        return ((live_count(p, k) + kWideEnvs - 1) / kWideEnvs) * ((n + kRows - 1) / kRows);
-    });
-    for (int q = blockIdx.x; q < total; q += gridDim.x) {
-        const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
+    const int total = product_units(p, L.first, kRows, kWideEnvs);
+    for (int q = product_start(); q < total; q += product_stride()) {
+        const ProductRef ref = product_ref(p, L.first, q, kRows);
+        const int k = ref.k, rb = ref.row_block, g0 = ref.group * kWideEnvs;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
-        const int cnt = uniform(live_count(p, k)), groups = (cnt + kWideEnvs - 1) / kWideEnvs;
-        const int local = q - uniform(L.first[kk]), rb = local / groups, g0 = (local - rb * groups) * kWideEnvs;
+        const int cnt = uniform(live_count(p, k));
         const int w0 = uniform(T.word_off[k]);
         __syncthreads();      // the previous unit is done with L
         if (threadIdx.x < kWideEnvs) {
@@ -609,71 +607,55 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
                 for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         const bool slow = matrix_overflows(M, p.model.alpha[k], k);
+        const bool half = matrix_half(p, k);
         if (dec && !slow) {
-            // fragment f = 3 wave .. 3 wave + 2 of a pair of K steps: step f / 6, column tile and component f % 6:
-            // this wave's step is wave / 2, its column tile wave % 2, its fragments the three components
-            const int myenv = (wave & 1) ? env[1] : env[0], safe = max(myenv, 0);
-            const float *me = src + (size_t)safe * N + base;
-            const unsigned long long *mymask = p.itm.mask + (size_t)safe * T.NW + w0;
-            float raw[3][8];
-            unsigned bits = 0;
-            auto fetch = [&](int s0) {      // values and bits are requested together
-                const int j0 = 32 * (s0 + (wave >> 1)) + 8 * gq;
-                const bool in = myenv >= 0 && j0 < n;
-                bits = in ? (unsigned)(mymask[j0 >> 6] >> (j0 & 63)) & 0xffu : 0u;
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    if (in) load8(me + c * EN, j0, n, raw[c]);
-            };
-            auto put = [&](int buf) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    bf16x8 b[3];
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
-                    split_bf16x3(raw[c], b);
-#pragma unroll
-                    for (int y = 0; y < 3; ++y) L.b[buf][wave >> 1][3 * (wave & 1) + c][y][lane] = b[y];
-                }
-            };
+            const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
+            const size_t at = (size_t)safe * N + base;
+            const unsigned long long *mask = p.itm.mask + (size_t)safe * T.NW + w0;
             const uint4 *wa[MT];
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
                 const int mt = min((row0 >> 4) + m, ((n + 15) >> 4) - 1);      // rows beyond the patch repeat its last tile
-                wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * 3 * 64 + lane;
+                wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * (half ? 2 : 3) * 64 + lane;
             }
-            uint4 a[2][MT][3];
-            auto fetch_a = [&](int s, uint4 (&x)[MT][3]) {
+            if (half) {
+                {
+                    const int j = threadIdx.x >> 3, e = L.env[j], nw = (n + 63) >> 6;
+                    float m = 0.0f;
+                    for (int w = threadIdx.x & 7; w < nw && e >= 0; w += 8)
+                        if (p.itm.mask[(size_t)e * T.NW + w0 + w]) m = fmaxf(m, p.itm.umax[(size_t)e * T.NW + w0 + w]);
 #pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) x[m][c] = wa[m][(size_t)(s * 3 + c) * 64];
-            };
-            auto mul = [&](int buf, int ds, const uint4 (&x)[MT][3]) {
-#pragma unroll
-                for (int f = 0; f < 6; ++f) {
-                    bf16x8 b[3];
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) b[c] = L.b[buf][ds][f][c][lane];
-#pragma unroll
-                    for (int m = 0; m < MT; ++m) {
-                        const bf16x8 y[3] = {__builtin_bit_cast(bf16x8, x[m][0]), __builtin_bit_cast(bf16x8, x[m][1]),
-                                             __builtin_bit_cast(bf16x8, x[m][2])};
-                        acc[m][f / 3][f % 3] = mfma_bf16x3(y, b, acc[m][f / 3][f % 3]);
-                    }
+                    for (int o = 1; o < 8; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+                    L.exp[j] = top_exp(m);      // the same in the 8 lanes
                 }
-            };
-            fetch(0);
-            fetch_a(0, a[0]);
-            put(0);
-            for (int s0 = 0, buf = 0; s0 < KS; s0 += 2, buf ^= 1) {
-                __syncthreads();          // this pair is in L.b[buf]; the other buffer is free
-                fetch_a(min(s0 + 1, KS - 1), a[1]);
-                if (s0 + 2 < KS) fetch(s0 + 2);
-                mul(buf, 0, a[0]);
-                fetch_a(min(s0 + 2, KS - 1), a[0]);
-                if (s0 + 1 < KS) mul(buf, 1, a[1]);
-                if (s0 + 2 < KS) put(buf ^ 1);
+                __syncthreads();
+                product_loop<MT, false, true>(L.b, wa, src, at, EN, mask, pow2(L.exp[mine]), myenv >= 0, n, KS, acc);
+                const int ew = weight_exp(p, k);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int s = -(ew + L.exp[16 * t + col]);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) acc[m][t][c][x] = ldexpf(acc[m][t][c][x], s);
+                }
+            } else {
+                constexpr int kStep = MT > 2 ? 2 : MT;      // three parts of four row tiles would not fit the registers
+#pragma unroll
+                for (int m0 = 0; m0 < MT; m0 += kStep) {
+                    const uint4 *w2[kStep];
+                    floatx4 a2[kStep][2][3];
+#pragma unroll
+                    for (int i = 0; i < 6 * kStep; ++i) a2[i / 6][i / 3 % 2][i % 3] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int m = 0; m < kStep; ++m) w2[m] = wa[m0 + m];
+                    product_loop<kStep, false, false>(L.b, w2, src, at, EN, mask, 1.0f, myenv >= 0, n, KS, a2);
+#pragma unroll
+                    for (int i = 0; i < 6 * kStep; ++i) acc[m0 + i / 6][i / 3 % 2][i % 3] = a2[i / 6][i / 3 % 2][i % 3];
+                    __syncthreads();      // L.b is done with
+                }
             }
         }
         __syncthreads();      // L.b is done with
@@ -1076,6 +1058,8 @@ void shape_step(const Plan &pl, StepParams &p) {
     // listed.  A launch costs 5-7 us; on one 32 x 32 pad the whole step takes
     // about 50, and the listing of 256 items would take as long as visiting them.
     p.dense = p.items <= 256;
+    // Wide tiles from 128 envs on: below, they would leave compute units idle.
+    p.wide = p.E >= 128;
     p.splits = contact_splits(pl, p.E);
 }
 
@@ -1132,8 +1116,10 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     launch_front(pl, p, st);
     if (step_residual(p)) launch_pool(pl, p, st);
     if (pl.tile.n_near) {
-        if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(2 * cus), dim3(kWG), 0, st, p);
-        else if (n_envs >= 128) hipLaunchKernelGGL(k_prop_wide<1>, dim3(2 * cus), dim3(kWG), 0, st, p);
+        // tile heights: see k_prop_wide
+        if (n_envs >= 4096) hipLaunchKernelGGL(k_prop_wide<4>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
+        else if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
+        else if (p.wide) hipLaunchKernelGGL(k_prop_wide<1>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_prop_narrow, dim3((unsigned)std::min<long long>((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
                                dim3(kWG), 0, st, p);

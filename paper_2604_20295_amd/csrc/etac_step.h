@@ -18,6 +18,7 @@ struct StepParams {
     int splits;              // workgroups per env of the contact pass
     int dense;               // 1: every item is listed (no k_live), those without contact are passed over
     int table_units, matrix_units;
+    int wide;                // 1: products of the decay matrices in wide tiles
     int cus;                 // compute units of the device
     long long items, words;  // E K, E NW
     const int8_t *cobj_in;   // propagate-only: given contact results
@@ -137,7 +138,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
             }
         }
     }
-    const bool want_umax = p.itm.mask && step_residual(p);
+    const bool residual = p.itm.mask && step_residual(p), want_umax = residual || (p.itm.mask && p.wide);
     for (int w0 = 0; w0 < NW; w0 += kScan * p.splits) {
         // words w0 + s, w0 + s + splits, ... of patches with candidates
         const int mine = w0 + s + p.splits * (int)threadIdx.x;
@@ -230,7 +231,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         }
         __syncthreads();      // the list is rewritten
     }
-    if (want_umax)
+    if (residual)
         for (int k = wave; k < K; k += kWaves)
             if (uniform(L.cnt[k])) p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
     int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
@@ -483,15 +484,30 @@ __device__ __forceinline__ void split_bf16x3(const float (&x)[8], bf16x8 (&b)[3]
     for (int c = 0; c < 3; ++c) b[c] = __builtin_bit_cast(bf16x8, o[c]);
 }
 
-__device__ __forceinline__ float decay_weight(float dx, float dy, float dz, float nb_hi, float nb_lo, float &d) {
+// Distance d and exponent t + tl of a pair's weight 2^(t + tl), to 2^-24 of
+// the weight: d + dl is the root of s, dl = (s - d^2) / (2 d).
+__device__ __forceinline__ void decay_exponent(float dx, float dy, float dz, float nb_hi, float nb_lo, float &d, float &t,
+                                               float &tl) {
     const float s = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
     d = __builtin_amdgcn_sqrtf(s);
-    // d + dl is the root of s: dl = (s - d^2) / (2 d)
     const float dl = d > 0.0f ? 0.5f * fmaf(-d, d, s) * __builtin_amdgcn_rcpf(d) : 0.0f;
-    const float t = nb_hi * d;
-    const float tl = fmaf(nb_hi, d, -t) + fmaf(nb_lo, d, nb_hi * dl);
+    t = nb_hi * d;
+    tl = fmaf(nb_hi, d, -t) + fmaf(nb_lo, d, nb_hi * dl);
+}
+
+__device__ __forceinline__ float decay_weight(float dx, float dy, float dz, float nb_hi, float nb_lo, float &d) {
+    float t, tl;
+    decay_exponent(dx, dy, dz, nb_hi, nb_lo, d, t, tl);
     const float w = __builtin_amdgcn_exp2f(t);
     return fmaf(w, 0.69314718f * tl, w);
+}
+
+// The same beyond FP32's range, for the pair-by-pair sums.
+__device__ __forceinline__ double decay_weight_wide(float dx, float dy, float dz, float nb_hi, float nb_lo, float &d) {
+    float t, tl;
+    decay_exponent(dx, dy, dz, nb_hi, nb_lo, d, t, tl);
+    const float ti = rintf(t), w = __builtin_amdgcn_exp2f(t - ti);
+    return ldexp((double)fmaf(w, 0.69314718f * tl, w), (int)ti);
 }
 
 // -alpha log2(e) as a sum of two floats.
@@ -499,6 +515,47 @@ __device__ __forceinline__ void decay_rate(float alpha, float &hi, float &lo) {
     const double b = -(double)alpha * 1.4426950408889634;
     hi = (float)b;
     lo = (float)(b - (double)hi);
+}
+
+// Weights of patch k are at most 2^growth: 0 unless alpha < 0.
+__device__ __forceinline__ float matrix_growth(const MeshDev &M, float alpha, int k) {
+    return alpha < 0.0f ? -alpha * 1.4427f * 2.0f * M.bound[k].w : 0.0f;
+}
+
+// Whether a weight could overflow (alpha < 0 on a wide patch): the matrix then
+// holds infinities, which a product would spread to nodes that have no such
+// pair; such a patch is summed pair by pair.
+__device__ __forceinline__ bool matrix_overflows(const MeshDev &M, float alpha, int k) {
+    return matrix_growth(M, alpha, k) > 120.0f;
+}
+
+// Format of a patch's matrices.  In wide tiles the matrix cores bound the
+// product, and two FP16 parts with three products of parts replace three BF16
+// parts with six: 22 bits and a sign of the remainder, an error of 2^-24 as
+// FP32's own, for weights down to 2^-17 of the largest, below that at most
+// 2^-39 of the largest.  Where weights grow with distance (alpha < 0) by more
+// than 2^12 the sums of near nodes alone could lie below that: BF16 parts,
+// which have FP32's range.  Narrow tiles wait on loads and keep BF16 (FP16
+// would first need the range of every env's values).
+// 4096 hands: transposed product 556 us in BF16, 429 us in FP16; forward 376 and
+// 298 us.
+__device__ __forceinline__ bool matrix_half(const StepParams &p, int k) {
+    return p.wide && matrix_growth(p.mesh, p.model.alpha[k], k) <= 12.0f;
+}
+
+// Scale exponents of the FP16 parts: the largest W, d W and value of an env
+// are put below 2^15.
+__device__ __forceinline__ int weight_exp(const StepParams &p, int k) {
+    return 15 - (int)ceilf(matrix_growth(p.mesh, p.model.alpha[k], k));
+}
+__device__ __forceinline__ int top_exp(float bound) {
+    if (!(bound > 0.0f) || !(bound <= 3.0e38f)) return 0;
+    int e;
+    (void)frexpf(bound, &e);
+    return min(15 - e, 126);
+}
+__device__ __forceinline__ int distance_weight_exp(const StepParams &p, int k) {
+    return weight_exp(p, k) + min(top_exp(2.0f * p.mesh.bound[k].w), 100) - 15;
 }
 
 __device__ void matrix_row_tile(const StepParams &p, int unit) {
@@ -513,8 +570,26 @@ __device__ void matrix_row_tile(const StepParams &p, int unit) {
     const int i = 16 * unit + (lane & 15);
     const int gi = base + min(i, n - 1);
     const float px = M.pos[gi], py = M.pos[N + gi], pz = M.pos[2 * N + gi];
-    const size_t at = p.tile.w_off[k] + (size_t)unit * KS * 3 * 64 + lane;
+    const bool half = matrix_half(p, k);
+    const int P = half ? 2 : 3;
+    const float sw = pow2(weight_exp(p, k)), sd = pow2(distance_weight_exp(p, k));
+    const size_t at = p.tile.w_off[k] + (size_t)unit * KS * P * 64 + lane;
     uint4 *w = p.tab.w + at, *wd = p.tab.wd + at;
+    auto store = [&](uint4 *o, int s, float scale, float (&v)[8]) {
+        if (half) {
+            half8 h, l;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] *= scale;
+            split8(v, h, l);
+            o[(size_t)(2 * s) * 64] = __builtin_bit_cast(uint4, h);
+            o[(size_t)(2 * s + 1) * 64] = __builtin_bit_cast(uint4, l);
+        } else {
+            bf16x8 b[3];
+            split_bf16x3(v, b);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o[(size_t)(3 * s + c) * 64] = __builtin_bit_cast(uint4, b[c]);
+        }
+    };
     for (int s = wave; s < KS; s += kWaves) {
         const int j0 = 32 * s + 8 * (lane >> 4);
         float x[8], y[8];
@@ -526,15 +601,8 @@ __device__ void matrix_row_tile(const StepParams &p, int unit) {
             x[e] = (i < n && j0 + e < n) ? v : 0.0f;
             y[e] = x[e] * d;
         }
-        bf16x8 b[3];
-        split_bf16x3(x, b);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) w[(size_t)(s * 3 + c) * 64] = __builtin_bit_cast(uint4, b[c]);
-        if (p.adjoint) {
-            split_bf16x3(y, b);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) wd[(size_t)(s * 3 + c) * 64] = __builtin_bit_cast(uint4, b[c]);
-        }
+        store(w, s, sw, x);
+        if (p.adjoint) store(wd, s, sd, y);
     }
 }
 
@@ -569,6 +637,41 @@ __device__ int unit_prefix(int K, int *first, F per) {
     return uniform(first[K]);
 }
 
+// Units of a product of a patch's decay matrix with the envs in contact: row
+// blocks times groups of envs.  Workgroups go to the eight XCDs in turn, each
+// with an L2 of its own (4 MB; the matrices of a 1024-node patch take 4 MB
+// each, its envs' columns 7 MB at 600 envs): XCD x takes every fourth row
+// block and every second group, so that over a patch it reads a quarter of the
+// matrix and half of the columns, the row blocks of a group together
+// (4096 hands, transposed product: 600 us with units in patch order, 591 us).
+struct ProductRef {
+    int k, row_block, group;
+};
+
+constexpr int kXcds = 8, kXcdRows = 4, kXcdGroups = 2;
+
+__device__ __forceinline__ int residue_count(int n, int first, int step) { return n > first ? (n - first + step - 1) / step : 0; }
+
+// This XCD's first row block and first group in the patch of rank kk: turned
+// from patch to patch, so that remainders fall on every XCD.
+__device__ __forceinline__ int xcd_row(int kk) { return ((int)(blockIdx.x % kXcds) + kk) % kXcdRows; }
+__device__ __forceinline__ int xcd_group(int kk) { return ((int)(blockIdx.x % kXcds) / kXcdRows + kk / kXcdRows) % kXcdGroups; }
+
+// This XCD's units (whole workgroup; ends with a barrier).
+__device__ int product_units(const StepParams &p, int (&first)[kMaxPatches + 1], int rows, int envs) {
+    const MeshDev &M = p.mesh;
+    return unit_prefix<kWaves>(M.K, first, [&](int kk) {
+        const int k = M.order[kk], groups = (live_count(p, k) + envs - 1) / envs;
+        if (p.tile.w_off[k] < 0) return 0;
+        const int blocks = (M.offset[k + 1] - M.offset[k] + rows - 1) / rows;
+        return residue_count(blocks, xcd_row(kk), kXcdRows) * residue_count(groups, xcd_group(kk), kXcdGroups);
+    });
+}
+
+// Units are strided over the XCD's workgroups.
+__device__ __forceinline__ int product_start() { return blockIdx.x / kXcds; }
+__device__ __forceinline__ int product_stride() { return gridDim.x / kXcds; }
+
 // Queue position (patch rank) of unit u: the last rank whose first unit is <= u.
 __device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
     int lo = 0, hi = K - 1;
@@ -599,6 +702,17 @@ __device__ __forceinline__ float matvec64(const float *wt, float x, float bias, 
 // Where Eq. 1 reads the active nodes' u_hat: the caller's own on given contact
 // results, else the step's output, whose active entries are u_hat.
 __device__ __forceinline__ const float *uhat_source(const StepParams &p) { return p.uhat_in ? p.uhat_in : p.u; }
+
+__device__ __forceinline__ ProductRef product_ref(const StepParams &p, const int (&first)[kMaxPatches + 1], int q, int rows) {
+    const int kk = unit_rank(first, p.mesh.K, q), k = uniform(p.mesh.order[kk]);
+    const int blocks = (uniform(p.mesh.offset[k + 1]) - uniform(p.mesh.offset[k]) + rows - 1) / rows;
+    const int mine = residue_count(blocks, xcd_row(kk), kXcdRows);
+    const int local = q - uniform(first[kk]), g = local / mine;      // the row blocks of a group run together
+    return ProductRef{k, xcd_row(kk) + kXcdRows * (local - g * mine), xcd_group(kk) + kXcdGroups * g};
+}
+
+// Grid of such a kernel: a whole number of workgroups for each XCD.
+inline int product_grid(int cus) { return (2 * cus + kXcds - 1) / kXcds * kXcds; }
 
 // ---------------------------------------------------------------------------
 // products of a decay matrix
@@ -632,11 +746,138 @@ __device__ __forceinline__ void load8(const float *x, int j0, int n, float (&v)[
     }
 }
 
-// Whether a weight of patch k could overflow (alpha < 0 on a wide patch): the
-// matrix then holds infinities, which a product would spread to nodes that
-// have no such pair; such a patch is summed pair by pair.
-__device__ __forceinline__ bool matrix_overflows(const MeshDev &M, float alpha, int k) {
-    return alpha < 0.0f && -alpha * 1.4427f * 2.0f * M.bound[k].w > 120.0f;
+// A wave's share of a product of NA row tiles of decay matrices with 32 envs'
+// values (two column tiles of three components): acc[m][t][c] over all K steps
+// of 32 nodes.  The workgroup's four waves split the B fragments of two K steps
+// (this wave's: step wave / 2, column tile wave % 2) into LDS while the MFMAs
+// of the two before run, the MFMAs of one K step with the splits between them:
+// an MFMA takes 16 cycles, 12 of which a SIMD has for other instructions.  A
+// fragments come from L2 a step ahead, values two pairs ahead.  `me`, `mask`:
+// this lane's env (has: there is one); PASSIVE takes the nodes without contact.
+// Whole workgroup; ends before the last pair's reads of B are done.
+using ProductB = uint4[2][2][6][3][64];      // [buffer][K step][3 column tile + component][part][lane]
+
+template <int NA, bool PASSIVE, bool HALF>
+__device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&wa)[NA], const float *src, size_t at, size_t EN,
+                                             const unsigned long long *mask, float scale, bool has, int n, int KS,
+                                             floatx4 (&acc)[NA][2][3]) {
+    constexpr int P = HALF ? 2 : 3, kProducts = HALF ? 3 : 6;
+    const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), gq = lane >> 4;
+    float raw[3][8];
+    unsigned long long word = 0;
+    int j0 = 0;
+    auto fetch = [&](int s0) {
+        j0 = 32 * (s0 + (wave >> 1)) + 8 * gq;
+        const int j = min(j0, 32 * KS - 8);
+        word = mask[j >> 6];
+        // values beyond the patch are masked; past the array's end only the last env's last component could reach
+        const size_t start = 2 * EN + at + j, safe = min(start, 3 * EN - 8);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float *x = src + (c < 2 ? c * EN + at + j : safe);
+            floatx4 a, b;
+            __builtin_memcpy(&a, x, 16);
+            __builtin_memcpy(&b, x + 4, 16);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { raw[c][e] = a[e]; raw[c][4 + e] = b[e]; }
+        }
+        if (start != safe)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v = src[min(start + e, 3 * EN - 1)];
+                asm volatile("" : "+v"(v));      // waited for here, not where the branches meet
+                raw[2][e] = v;
+            }
+    };
+    auto put = [&](int buf) {
+        const int left = has ? max(min(n - j0, 8), 0) : 0;
+        const unsigned bits = (unsigned)((PASSIVE ? ~word : word) >> (j0 & 63)) & ((1u << left) - 1u);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            uint4(&o)[3][64] = B[buf][wave >> 1][3 * (wave & 1) + c];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? (HALF ? raw[c][x] * scale : raw[c][x]) : 0.0f;
+            if (HALF) {
+                half8 h, l;
+                split8(raw[c], h, l);
+                o[0][lane] = __builtin_bit_cast(uint4, h);
+                o[1][lane] = __builtin_bit_cast(uint4, l);
+            } else {
+                bf16x8 b[3];
+                split_bf16x3(raw[c], b);
+#pragma unroll
+                for (int y = 0; y < 3; ++y) o[y][lane] = __builtin_bit_cast(uint4, b[y]);
+            }
+        }
+    };
+    uint4 a[2][NA][P];
+    auto fetch_a = [&](int s, uint4 (&x)[NA][P]) {
+#pragma unroll
+        for (int m = 0; m < NA; ++m)
+#pragma unroll
+            for (int c = 0; c < P; ++c) x[m][c] = wa[m][(size_t)(s * P + c) * 64];
+    };
+    auto mul = [&](int buf, int ds, const uint4 (&x)[NA][P]) {
+        uint4 b[2][P];
+#pragma unroll
+        for (int c = 0; c < P; ++c) b[0][c] = B[buf][ds][0][c][lane];
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            if (f < 5)
+#pragma unroll
+                for (int c = 0; c < P; ++c) b[(f + 1) & 1][c] = B[buf][ds][f + 1][c][lane];
+#pragma unroll
+            for (int m = 0; m < NA; ++m) {
+                floatx4 &o = acc[m][f / 3][f % 3];
+                if constexpr (HALF) {
+                    o = mfma_split(__builtin_bit_cast(half8, x[m][0]), __builtin_bit_cast(half8, x[m][1]),
+                                   __builtin_bit_cast(half8, b[f & 1][0]), __builtin_bit_cast(half8, b[f & 1][1]), o);
+                } else {
+                    bf16x8 y[3], z[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        y[c] = __builtin_bit_cast(bf16x8, x[m][c]);
+                        z[c] = __builtin_bit_cast(bf16x8, b[f & 1][c]);
+                    }
+                    o = mfma_bf16x3(y, z, o);
+                }
+            }
+        }
+    };
+    fetch(0);
+    fetch_a(0, a[0]);
+    fetch_a(min(1, KS - 1), a[1]);
+    put(0);
+    fetch(2);
+    for (int s0 = 0, buf = 0; s0 < KS; s0 += 2, buf ^= 1) {
+        __syncthreads();          // this pair is in B[buf]; the other buffer is free
+        // a step beyond the last has zeros in B
+        mul(buf, 0, a[0]);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * P, 0);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+            __builtin_amdgcn_sched_group_barrier(0x008, kProducts * NA, 0);
+            if (f < 4) __builtin_amdgcn_sched_group_barrier(0x100, P, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_a(min(s0 + 2, KS - 1), a[0]);
+        mul(buf, 1, a[1]);
+        put(buf ^ 1);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 * P, 1);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+#pragma unroll
+            for (int i = 0; i < kProducts * NA; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+                __builtin_amdgcn_sched_group_barrier(0x002, NA > 2 ? 2 : 6 / NA, 1);
+            }
+            if (f < 4) __builtin_amdgcn_sched_group_barrier(0x100, P, 1);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x200, 3 * P, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        fetch_a(min(s0 + 3, KS - 1), a[1]);
+        fetch(s0 + 4);
+    }
 }
 
 }  // namespace etac
