@@ -313,10 +313,24 @@ __device__ __forceinline__ int wave_max_int(int v) {
     for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
     return v;
 }
+// Values of other lanes of the row of 16 by DPP, without the latency of LDS:
+// lane ^ 1, ^ 2, ^ 7 (mirrored half row), ^ 8 (rotated by 8), ^ 15 (mirrored row).
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor7 = 0x141, kDppXor8 = 0x128, kDppXor15 = 0x140;
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false); }
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return __int_as_float(dpp<CTRL>(__float_as_int(v))); }
+
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
+    v = fmaxf(v, dpp<kDppXor1>(v));
+    v = fmaxf(v, dpp<kDppXor2>(v));
+    v = fmaxf(v, dpp<kDppXor7>(v));
+    v = fmaxf(v, dpp<kDppXor15>(v));
+    // rows 0 and 1, 2 and 3, then the halves
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // Certified cutoff of the pair sums of Eq. 1 on far patches.  A run of 32 nodes

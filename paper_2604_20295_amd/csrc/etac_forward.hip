@@ -200,9 +200,36 @@ struct ActiveLds {
     uint16_t slot[64 * kActiveWords];
 };
 
+// Largest of two (value, node) pairs, the lower node on ties.
+__device__ __forceinline__ void take_max(float &v, int &ix, float v2, int i2) {
+    const bool take = (v2 > v) | ((v2 == v) & (i2 < ix));
+    v = take ? v2 : v;
+    ix = take ? i2 : ix;
+}
+
+// A step of the reduction of H pairs per lane over 16 lanes: lanes keep the
+// half of their pairs that their `bit` names and hand the other half to a lane
+// of the other half.
+template <int H, int CTRL>
+__device__ __forceinline__ void halve_max(float (&v)[16], int (&ix)[16], bool bit) {
+#pragma unroll
+    for (int i = 0; i < H / 2; ++i) {
+        const float keep = bit ? v[H / 2 + i] : v[i], give = bit ? v[i] : v[H / 2 + i];
+        const int ikeep = bit ? ix[H / 2 + i] : ix[i], igive = bit ? ix[i] : ix[H / 2 + i];
+        v[i] = keep;
+        ix[i] = ikeep;
+        take_max(v[i], ix[i], dpp<CTRL>(give), dpp<CTRL>(igive));
+    }
+}
+
 // Largest feature of the active nodes among `words` words from word wf of the
 // item: its active nodes in order, 32 at a time through the encoder on the
 // matrix cores, weights in registers.  One wave; lane c returns channel c.
+// Nodes beyond the last repeat it.  Bound by the VALU (splits and maxima, 9 per
+// feature) and the dependent chain of a unit's start, so words and ranges are
+// loaded at once, no load of the loop is under a branch, and the 16 lanes of a
+// row are reduced by exchanging halves (15 exchanges of a pair instead of 64).
+// 4096 hands (3.8 M active nodes): 317 us without these, 208 us.
 __device__ unsigned long long pool_active(const StepParams &p, ActiveLds &L, const EncW &W, float rb1, float rb2, int s1,
                                           int s2, int k, int e, int base, int nw, int w0, int wf, int words) {
     const MeshDev &M = p.mesh;
@@ -210,132 +237,123 @@ __device__ unsigned long long pool_active(const StepParams &p, ActiveLds &L, con
     const size_t EN = (size_t)p.E * N;
     const unsigned long long *mask = p.itm.mask + (size_t)e * p.tile.NW + w0;
     const float *um = p.itm.umax + (size_t)e * p.tile.NW + w0;
+    const unsigned long long mine = mask[wf + min(lane, words - 1)];
+    float umax = 0.0f;
+    for (int w = lane; w < nw; w += 64) {
+        const unsigned long long m = mask[w];
+        const float v = um[w];      // stale in words without contact
+        umax = m ? fmaxf(umax, v) : umax;
+    }
     int total = 0;
     wave_sync();
 #pragma unroll
     for (int t = 0; t < kActiveWords; ++t) {
-        if (t >= words) break;
-        const unsigned long long m = mask[wf + t];
-        const unsigned long long act = ((unsigned long long)uniform((unsigned)(m >> 32)) << 32) | uniform((unsigned)m);
+        const unsigned long long act =
+            t < words ? ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(mine >> 32), t) << 32) |
+                            (unsigned)__builtin_amdgcn_readlane((int)mine, t)
+                      : 0ull;
         if ((act >> lane) & 1ull) L.slot[total + lanes_below(act)] = (uint16_t)(64 * t + lane);
         total += __popcll(act);
     }
     if (total == 0) return 0ull;
-    float umax = 0.0f;
-    for (int w = lane; w < nw; w += 64)
-        if (mask[w]) umax = fmaxf(umax, um[w]);
     umax = wave_max(umax);
     const int ax = uniform(range_exp(fmaxf(item_xbound(M, k, umax), 1.0f)));
     const int a1 = s1 + ax, af = s2 + a1;
-    const float xmul = pow2(ax);
     L.b1s[lane] = rb1 * pow2(a1);
     L.b2s[lane] = rb2 * pow2(af);
     wave_sync();
-    const float o0 = M.origin[3 * k], o1 = M.origin[3 * k + 1], o2 = M.origin[3 * k + 2];
-    floatx4 mx[4];
-    int mi[4][4];
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { mx[ot][r] = -1.0f; mi[ot][r] = 0x7fffffff; }
-    // raw inputs of the next two tiles are requested while these run (lane
-    // group 0 holds eight, group 1 the ninth)
+    // input = raw * mul + add; lane group 1 holds the ninth input and zeros
+    const float xmul = pow2(ax), mul = gq == 1 ? 0.0f : xmul;
+    const float add[3] = {gq == 1 ? 0.0f : -M.origin[3 * k] * xmul, -M.origin[3 * k + 1] * mul, -M.origin[3 * k + 2] * mul};
+    const float *uh = uhat_source(p) + (size_t)e * N + base + 64 * wf, *pos = M.pos + base + 64 * wf;
+    const float *nrm = M.nrm + base + 64 * wf, *in0 = gq == 1 ? uh + 2 * EN : pos;
     float raw[2][8];
     int next[2];
-    auto fetch = [&](int t0) {
+    auto fetch = [&](int t0) {      // inputs of the next two tiles, requested while these run
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int j = min(t0 + 16 * u + (lane & 15), total - 1);
-            next[u] = L.slot[j];
-            const int g = base + 64 * wf + next[u];
-            const float *uh = uhat_source(p) + (size_t)e * N + g;
-            if (gq == 0) {
+            const int g = next[u] = L.slot[min(t0 + 16 * u + (lane & 15), total - 1)];
+            raw[u][0] = in0[g];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    raw[u][c] = M.pos[(size_t)c * N + g];
-                    raw[u][3 + c] = M.nrm[(size_t)c * N + g];
-                }
-                raw[u][6] = uh[0];
-                raw[u][7] = uh[EN];
-            } else if (gq == 1) {
-                raw[u][0] = uh[2 * EN];
-            }
+            for (int c = 1; c < 3; ++c) raw[u][c] = pos[(size_t)c * N + g];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) raw[u][3 + c] = nrm[(size_t)c * N + g];
+            raw[u][6] = uh[g];
+            raw[u][7] = uh[EN + g];
         }
     };
     fetch(0);
+    // a feature is at least 0 (ReLU), which every node without a larger one has
+    float mx[16];
+    int mi[16];
+    const int first = uniform((int)L.slot[0]);
+#pragma unroll
+    for (int o = 0; o < 16; ++o) { mx[o] = 0.0f; mi[o] = first; }
     for (int t0 = 0; t0 < total; t0 += 32) {
-        half8 xh[2], xl[2];
+        half8 in[2];
         int node[2];
-        bool valid[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            valid[u] = t0 + 16 * u + (lane & 15) < total;
-            node[u] = 64 * wf + next[u];
             float x[8];
+            x[0] = fmaf(raw[u][0], xmul, add[0]);
+            x[1] = fmaf(raw[u][1], mul, add[1]);
+            x[2] = fmaf(raw[u][2], mul, add[2]);
 #pragma unroll
-            for (int c = 0; c < 8; ++c) x[c] = 0.0f;
-            if (valid[u] && gq == 0) {
-                x[0] = (raw[u][0] - o0) * xmul;
-                x[1] = (raw[u][1] - o1) * xmul;
-                x[2] = (raw[u][2] - o2) * xmul;
-#pragma unroll
-                for (int c = 3; c < 8; ++c) x[c] = raw[u][c] * xmul;
-            } else if (valid[u] && gq == 1) {
-                x[0] = raw[u][0] * xmul;
-            }
-            split8(x, xh[u], xl[u]);
+            for (int c = 3; c < 8; ++c) x[c] = raw[u][c] * mul;
+            in[u] = pack_inputs(x);
+            node[u] = next[u];
         }
-        if (t0 + 32 < total) fetch(t0 + 32);
+        fetch(t0 + 32);
         floatx4 f[2][4];
-        encode<2>(W, L.b1s, L.b2s, xh, xl, f);
+        encode<2>(W, L.b1s, L.b2s, in, f);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
-            if (valid[u])
 #pragma unroll
-                for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (f[u][ot][r] > mx[ot][r]) { mx[ot][r] = f[u][ot][r]; mi[ot][r] = node[u]; }
-    }
-    // over the 16 nodes of a row; lowest node on ties
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float v = mx[ot][r];
-            int ix = mi[ot][r];
-#pragma unroll
-            for (int off = 1; off <= 8; off <<= 1) {
-                const float v2 = __shfl_xor(v, off);
-                const int i2 = __shfl_xor(ix, off);
-                if (v2 > v || (v2 == v && i2 < ix)) { v = v2; ix = i2; }
+            for (int o = 0; o < 16; ++o) {
+                const float v = f[u][o >> 2][o & 3];
+                const bool take = v > mx[o];
+                mx[o] = take ? v : mx[o];
+                mi[o] = take ? node[u] : mi[o];
             }
-            L.v[ot * 16 + 4 * gq + r] = v;      // identical in the row's lanes
-            L.ix[ot * 16 + 4 * gq + r] = ix;
-        }
+    }
+    // over the 16 nodes of a row, the lowest node on ties: lane l of the row
+    // ends with output tile l / 4, row 4 gq + l % 4
+    halve_max<16, kDppXor8>(mx, mi, lane & 8);
+    halve_max<8, kDppXor7>(mx, mi, lane & 4);
+    halve_max<4, kDppXor2>(mx, mi, lane & 2);
+    halve_max<2, kDppXor1>(mx, mi, lane & 1);
+    const int ch = ((lane >> 2) & 3) * 16 + 4 * gq + (lane & 3);
+    L.v[ch] = mx[0];
+    L.ix[ch] = mi[0];
     wave_sync();
-    const unsigned long long key = pool_key(L.v[lane] * pow2(-af), L.ix[lane]);
+    const unsigned long long key = pool_key(L.v[lane] * pow2(-af), 64 * wf + L.ix[lane]);
     wave_sync();
     return key;
 }
 
-// Pooled feature of an item (lane c on channel c) to its record and through
-// the global MLP.
-__device__ __forceinline__ void pool_finish(const StepParams &p, size_t item, unsigned long long key) {
+// Pooled feature v of an item, the node it came from and g' (lane c on channel
+// c) to its record and the adjoint's vectors.
+__device__ __forceinline__ void keep_pool(const StepParams &p, size_t item, float v, unsigned node, float gp) {
     const int lane = lane_id();
-    const float *phi = p.model.phi;
-    const float v = __uint_as_float((unsigned)(key >> 32));
     if (p.saved) {
         uint32_t *rec = p.saved + item * kSavedWords;
         rec[lane] = __float_as_uint(v);
-        rec[64 + lane] = ~(unsigned)key;
+        rec[64 + lane] = node;
     }
-    const float gp = fmaxf(matvec64(p.tab.w3t, v, phi[kB3 + lane]), 0.0f);
     if (p.ivec) {
         p.ivec[item * 256 + 64 + lane] = gp;
         p.ivec[item * 256 + 192 + lane] = v;
     }
-    p.itm.c4[item * 64 + lane] = matvec64(p.tab.w4t, gp, phi[kB4 + lane]);
+}
+
+// Partial product of a vector's C channels from c0 on (x: lane c holds channel
+// c) with the weights w of this lane's row.
+template <int C>
+__device__ __forceinline__ float dot_lanes(const float (&w)[C], float x, int c0) {
+    float a = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) a += w[c] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), c0 + c));
+    return a;
 }
 
 // The item of live-list unit q when patch k's lists hold `per` units per env.
@@ -405,32 +423,58 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
-__global__ __launch_bounds__(kWG) void k_pool_finish(StepParams p) {
+// Global MLP of the items, a wave at a time, the weights of both layers in
+// registers: read again for every item they cost four trips to L2 a layer.
+// 16384 hands (36000 items): 48 us like that, 40 us now; four pads in contact
+// 10 and 5 us.
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k_pool_finish(StepParams p) {
     __shared__ int first[kMaxPatches + 1];
-    const int K = p.mesh.K, wave = uniform(threadIdx.x >> 6);
+    const int K = p.mesh.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    const float *phi = p.model.phi;
+    float w3[8][8], w4[8][8];      // partial sums of eight channels, as k_pool's
+#pragma unroll
+    for (int c = 0; c < 64; ++c) w3[c / 8][c % 8] = p.tab.w3t[c * 64 + lane];
+#pragma unroll
+    for (int c = 0; c < 64; ++c) w4[c / 8][c % 8] = p.tab.w4t[c * 64 + lane];
+    const float b3 = phi[kB3 + lane], b4 = phi[kB4 + lane];
     const int total = item_units(p, first, 1 << 20);
     const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
     for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
         const ItemRef it = item_ref(p, first, q, 1 << 20);
         const size_t item = (size_t)it.e * K + it.k;
         if (p.dense && uniform(na[item]) == 0) continue;
-        unsigned long long key;
+        float v;
+        unsigned node;
         if (p.recall) {      // the forward's record
             const uint32_t *rec = p.recall + item * kSavedWords;
-            key = ((unsigned long long)rec[lane_id()] << 32) | (unsigned)~rec[64 + lane_id()];
+            v = __uint_as_float(rec[lane]);
+            node = rec[64 + lane];
         } else {
-            key = p.itm.pool[item * 64 + lane_id()];
+            const unsigned long long key = p.itm.pool[item * 64 + lane];
+            v = __uint_as_float((unsigned)(key >> 32));
+            node = ~(unsigned)key;
         }
-        pool_finish(p, item, key);
+        float s = b3;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) s += dot_lanes<8>(w3[g], v, 8 * g);
+        const float gp = fmaxf(s, 0.0f);
+        s = b4;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) s += dot_lanes<8>(w4[g], gp, 8 * g);
+        p.itm.c4[item * 64 + lane] = s;
+        keep_pool(p, item, v, node, gp);
     }
 }
 
 // The same in one launch, a workgroup of eight waves per item, for batches of
-// few small patches, where a launch costs more than the idle waves.
+// few small patches, where a launch costs more than the idle waves.  Latency-
+// bound: the layers of the global MLP are split over the waves, their weights
+// loaded at the start (one pad: 24.1 us with one wave reading them, 16.8 us).
 constexpr int kPoolWaves = 8, kPoolWords = 4;
 
 struct PoolLds {
     unsigned long long key[64];
+    float part[2][kPoolWaves][64];
     union {
         PassiveLds<kPoolWords> pas;
         ActiveLds act;
@@ -446,7 +490,16 @@ __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu
     const int s1 = uniform(p.tab.scale[0]), s2 = uniform(p.tab.scale[1]);
     EncW W;
     load_encoder(phi, s1, s2, W);
-    const float rb1 = phi[kB1 + lane], rb2 = phi[kB2 + lane];
+    const float rb1 = phi[kB1 + lane], rb2 = phi[kB2 + lane], b3 = phi[kB3 + lane], b4 = phi[kB4 + lane];
+    // the global MLP's layers are split over the waves by input channels
+    constexpr int kShare = 64 / kPoolWaves;
+    const int c0 = kShare * wave;
+    float w3[kShare], w4[kShare];
+#pragma unroll
+    for (int c = 0; c < kShare; ++c) {
+        w3[c] = p.tab.w3t[(c0 + c) * 64 + lane];
+        w4[c] = p.tab.w4t[(c0 + c) * 64 + lane];
+    }
     for (int q = blockIdx.x; q < p.E * K; q += gridDim.x) {
         const int e = q / K, k = q - e * K;
         const size_t item = (size_t)q;
@@ -465,7 +518,23 @@ __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu
             if (key) atomicMax(&L.key[lane], key);
         }
         __syncthreads();
-        if (wave == 0) pool_finish(p, item, L.key[lane]);
+        const unsigned long long key = L.key[lane];
+        const float v = __uint_as_float((unsigned)(key >> 32));
+        L.part[0][wave][lane] = dot_lanes<kShare>(w3, v, c0);
+        __syncthreads();
+        float s = b3;
+#pragma unroll
+        for (int w = 0; w < kPoolWaves; ++w) s += L.part[0][w][lane];
+        const float gp = fmaxf(s, 0.0f);
+        L.part[1][wave][lane] = dot_lanes<kShare>(w4, gp, c0);
+        __syncthreads();
+        if (wave == 0) {
+            s = b4;
+#pragma unroll
+            for (int w = 0; w < kPoolWaves; ++w) s += L.part[1][w][lane];
+            p.itm.c4[item * 64 + lane] = s;
+            keep_pool(p, item, v, ~(unsigned)key, gp);
+        }
     }
 }
 
@@ -1086,7 +1155,7 @@ void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st) {
         hipLaunchKernelGGL(k_pool_active, dim3((unsigned)std::min((p.words / kActiveWords + p.items) / kWaves + 1, 2 * cus)),
                            dim3(kWG), 0, st, p);
     }
-    hipLaunchKernelGGL(k_pool_finish, dim3((unsigned)std::min(p.items / kWaves + 1, 8 * cus)), dim3(kWG), 0, st, p);
+    hipLaunchKernelGGL(k_pool_finish, dim3((unsigned)std::min(p.items / kWaves + 1, 3 * cus)), dim3(kWG), 0, st, p);
 }
 
 void launch_far_lists(const StepParams &p, bool passive, hipStream_t st) {

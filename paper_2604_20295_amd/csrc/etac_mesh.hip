@@ -118,11 +118,6 @@ __host__ __device__ __forceinline__ double closest_tri(double q0, double q1, dou
 // minima read lane by lane.  Every lane of the wave must be active; every
 // lane gets the result.
 template <int CTRL>
-__device__ __forceinline__ int dpp(int v) {
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
-}
-
-template <int CTRL>
 __device__ __forceinline__ double dpp(double v) {
     const int lo = dpp<CTRL>(__double2loint(v)), hi = dpp<CTRL>(__double2hiint(v));
     return __hiloint2double(hi, lo);
@@ -134,18 +129,18 @@ __device__ __forceinline__ double read_lane(double v, int l) {
 }
 
 __device__ __forceinline__ double wave_min(double v) {
-    v = fmin(v, dpp<0xb1>(v));    // quad_perm [1, 0, 3, 2]
-    v = fmin(v, dpp<0x4e>(v));    // quad_perm [2, 3, 0, 1]
-    v = fmin(v, dpp<0x141>(v));   // row_half_mirror
-    v = fmin(v, dpp<0x140>(v));   // row_mirror
+    v = fmin(v, dpp<kDppXor1>(v));
+    v = fmin(v, dpp<kDppXor2>(v));
+    v = fmin(v, dpp<kDppXor7>(v));
+    v = fmin(v, dpp<kDppXor15>(v));
     return fmin(fmin(read_lane(v, 0), read_lane(v, 16)), fmin(read_lane(v, 32), read_lane(v, 48)));
 }
 
 __device__ __forceinline__ int wave_min(int v) {
-    v = min(v, dpp<0xb1>(v));
-    v = min(v, dpp<0x4e>(v));
-    v = min(v, dpp<0x141>(v));
-    v = min(v, dpp<0x140>(v));
+    v = min(v, dpp<kDppXor1>(v));
+    v = min(v, dpp<kDppXor2>(v));
+    v = min(v, dpp<kDppXor7>(v));
+    v = min(v, dpp<kDppXor15>(v));
     return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
                min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
 }
@@ -153,10 +148,10 @@ __device__ __forceinline__ int wave_min(int v) {
 // Wave-wide sum in a fixed order (pairwise within rows, then the four row
 // sums), the same value in every lane.
 __device__ __forceinline__ double wave_sum(double v) {
-    v = v + dpp<0xb1>(v);
-    v = v + dpp<0x4e>(v);
-    v = v + dpp<0x141>(v);
-    v = v + dpp<0x140>(v);
+    v = v + dpp<kDppXor1>(v);
+    v = v + dpp<kDppXor2>(v);
+    v = v + dpp<kDppXor7>(v);
+    v = v + dpp<kDppXor15>(v);
     return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 

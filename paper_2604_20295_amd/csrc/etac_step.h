@@ -273,9 +273,11 @@ __device__ __forceinline__ void load_frag64(const float *w, int stride, float mu
         }
 }
 
-// Encoder weights of one wave in registers.
+// Encoder weights of one wave in registers.  Layer 1 has nine inputs: the three
+// products of its FP16 parts share the 32 slots of one K step (lane group 0
+// hi W hi x, 2 hi W lo x, 3 lo W hi x of inputs 0-7; group 1 all three of input 8).
 struct EncW {
-    half8 w1h[4], w1l[4], w2h[4][2], w2l[4][2];
+    half8 w1[4], w2h[4][2], w2l[4][2];
 };
 
 __device__ __forceinline__ void load_encoder(const float *phi, int s1, int s2, EncW &W) {
@@ -283,42 +285,52 @@ __device__ __forceinline__ void load_encoder(const float *phi, int s1, int s2, E
     const float e1 = pow2(s1);
 #pragma unroll
     for (int ot = 0; ot < 4; ++ot) {
+        const float *row = phi + kW1 + (ot * 16 + (lane & 15)) * 9;
         float x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int in = 8 * q + e;
-            x[e] = in < 9 ? phi[kW1 + (ot * 16 + (lane & 15)) * 9 + (in < 9 ? in : 0)] * e1 : 0.0f;
-        }
-        split8(x, W.w1h[ot], W.w1l[ot]);
+        for (int e = 0; e < 8; ++e) x[e] = row[q == 1 ? 8 : e] * e1;
+        half8 h, l;
+        split8(x, h, l);
+        const _Float16 zero = 0;
+        const half8 ninth = {h[0], h[0], l[0], zero, zero, zero, zero, zero};
+        W.w1[ot] = q == 1 ? ninth : (q == 3 ? l : h);
     }
     load_frag64(phi + kW2, 64, pow2(s2), W.w2h, W.w2l);
 }
 
-// The encoder of NT 16-node tiles from register weights: the MFMA sequence of
-// every accumulator is hi hi, hi lo, lo hi per K step.  b1, b2: scaled biases in LDS.
+// Layer 1's B operand of a node (this lane's part).  x: inputs 0-7 of the node;
+// in lane group 1 input 8 and zeros.
+__device__ __forceinline__ half8 pack_inputs(const float (&x)[8]) {
+    const int q = lane_id() >> 4;
+    half8 h, l;
+    split8(x, h, l);
+    uint4t a = __builtin_bit_cast(uint4t, h), b = __builtin_bit_cast(uint4t, l);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = q == 2 ? b[e] : a[e];
+    const unsigned lo = __builtin_bit_cast(uint4t, l)[0];
+    b[0] = q == 1 ? (a[0] & 0xffffu) | (lo << 16) : b[0];
+    b[1] = q == 1 ? a[0] & 0xffffu : b[1];
+    return __builtin_bit_cast(half8, b);
+}
+
+// The encoder of NT 16-node tiles from register weights, without the last
+// ReLU.  b1, b2: scaled biases in LDS.
 template <int NT>
-__device__ __forceinline__ void encode(const EncW &W, const float *b1, const float *b2, const half8 (&xh)[NT],
-                                       const half8 (&xl)[NT], floatx4 (&f)[NT][4]) {
+__device__ __forceinline__ void encode(const EncW &W, const float *b1, const float *b2, const half8 (&x)[NT],
+                                       floatx4 (&f)[NT][4]) {
     const int gq = lane_id() >> 4;
-    floatx4 h1[NT][4];
-#pragma unroll
-    for (int ot = 0; ot < 4; ++ot) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(&b1[ot * 16 + 4 * gq]);
-#pragma unroll
-        for (int u = 0; u < NT; ++u) h1[u][ot] = b;
-    }
-#pragma unroll
-    for (int u = 0; u < NT; ++u) {
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xh[u], h1[u][ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = mfma16(W.w1h[ot], xl[u], h1[u][ot]);
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) h1[u][ot] = relu4(mfma16(W.w1l[ot], xh[u], h1[u][ot]));
-    }
     half8 bh[NT][2], bl[NT][2];
+    {
+        floatx4 h1[NT][4];
 #pragma unroll
-    for (int u = 0; u < NT; ++u) split_chain(h1[u], bh[u], bl[u]);
+        for (int ot = 0; ot < 4; ++ot) {
+            const floatx4 b = *reinterpret_cast<const floatx4 *>(&b1[ot * 16 + 4 * gq]);
+#pragma unroll
+            for (int u = 0; u < NT; ++u) h1[u][ot] = relu4(mfma16(W.w1[ot], x[u], b));
+        }
+#pragma unroll
+        for (int u = 0; u < NT; ++u) split_chain(h1[u], bh[u], bl[u]);
+    }
 #pragma unroll
     for (int ot = 0; ot < 4; ++ot) {
         const floatx4 b = *reinterpret_cast<const floatx4 *>(&b2[ot * 16 + 4 * gq]);
@@ -336,10 +348,6 @@ __device__ __forceinline__ void encode(const EncW &W, const float *b1, const flo
 #pragma unroll
             for (int ot = 0; ot < 4; ++ot) f[u][ot] = mfma16(W.w2l[ot][s], bh[u][s], f[u][ot]);
         }
-#pragma unroll
-    for (int u = 0; u < NT; ++u)
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) f[u][ot] = relu4(f[u][ot]);
 }
 
 // Features of the nodes of words w0, w0 + step, ...: a wave takes 16 nodes of
@@ -397,7 +405,7 @@ __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
         float x[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) x[e] = 0.0f;
-        if (valid && gq == 0) {
+        if (valid && gq != 1) {      // u_hat is zero
             const float xmul = pow2(ax);
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
@@ -405,10 +413,11 @@ __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
                 x[3 + a] = M.nrm[(size_t)a * N + start + j] * xmul;
             }
         }
-        half8 xh[1], xl[1];
-        split8(x, xh[0], xl[0]);
+        const half8 in[1] = {pack_inputs(x)};
         floatx4 f[1][4];
-        encode<1>(W, L.b1s, L.b2s, xh, xl, f);
+        encode<1>(W, L.b1s, L.b2s, in, f);
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) f[0][ot] = relu4(f[0][ot]);
         const float fmul = pow2(-af);
         if (valid)
 #pragma unroll
