@@ -569,14 +569,38 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
 // arg-max node.  Then lane f holds feature f: h1 of every channel's node, and
 // from dL/dpre2 = dg_c [g_c > 0] e_c its shares of dW2, dW1 and db1, summed in
 // registers over the wave's items.  Then again by channels: W1^T dL/dpre1
-// reaches u_hat of active arg-max nodes.
+// reaches u_hat of active arg-max nodes.  An item is one dependent chain, so
+// the weights are in LDS and everything it reads is requested first (4096
+// hands: 161 us with weights from L2 and loads in turn, 125 us).
 struct ItemLds {
     float w1u[64][4];                 // W1[:, 6..8]
     float x[kWaves][64][12];          // inputs of the channels' nodes, then the routed gradient
     float d[kWaves][64][4];           // dL/du_hat of the channels' nodes, and the node
     unsigned long long gate[kWaves][64];   // features of a channel's node with h1 > 0
-    float sum[kRouteWords];
+    union {
+        struct {
+            float w2[64][65];         // W2, rows and columns read without bank conflicts
+            float w3[64][64], w4[64][64];      // W3, W4[:, 64:]
+        };
+        float sum[kRouteWords];       // after the items
+    };
 };
+
+// sum_c w[c][lane] x_c, four partial sums of 16 terms in order.
+__device__ __forceinline__ float column_dot(const float (*w)[64], float x) {
+    const int lane = lane_id();
+    float s = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float a = 0.0f;
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+            a += w[16 * q + c][lane] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16 * q + c));
+        s += a;
+        reload_fence();
+    }
+    return s;
+}
 
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_item(AdjParams p) {
     __shared__ ItemLds L;
@@ -589,6 +613,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const float *phi = S.model.phi, *src = uhat_source(S);
     const int32_t *na = S.itm.n_act;
     const uint32_t *rec = S.recall ? S.recall : S.saved;
+    for (int i = threadIdx.x; i < 4096; i += kWG) {
+        L.w2[i >> 6][i & 63] = phi[kW2 + i];
+        L.w3[i >> 6][i & 63] = phi[kW3 + i];
+        L.w4[i >> 6][i & 63] = phi[kW4 + (i >> 6) * 128 + 64 + (i & 63)];
+    }
     for (int i = threadIdx.x; i < 256; i += kWG) L.w1u[i >> 2][i & 3] = (i & 3) < 3 ? phi[kW1 + (i >> 2) * 9 + 6 + (i & 3)] : 0.0f;
     const int total = unit_prefix<kWaves>(K, first, [&](int kk) { return live_count(S, M.order[kk]); });
     float w1[9];
@@ -607,46 +636,54 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (S.dense && uniform(na[item]) == 0) continue;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
         const int w0 = uniform(T.word_off[k]), hws = (n + 31) >> 5;
-        const float *sp = p.b.s4_part + ((size_t)e * 2 * T.NW + 2 * w0) * 64 + lane;
-        double sd = 0.0;
-#pragma unroll 8
-        for (int h = 0; h < hws; ++h) sd += (double)sp[(size_t)h * 64];
-        const float s4 = (float)sd;
+        // everything an item reads is requested before its first sums
         float *iv = p.b.ivec + item * 256 + lane;
         const float gp = iv[64], g = iv[192];
-        // opaque per item: the addresses of the weights' rows are formed where
-        // they are used instead of held in registers across the items
-        const float *wp = phi, *w2t = S.tab.w2t;
-        asm volatile("" : "+s"(wp), "+s"(w2t));
-        const float dgp = matvec64(wp + kW4 + 64, s4, 0.0f, 128);
+        const unsigned arg = rec[item * kSavedWords + 64 + lane];
+        const float *sp = p.b.s4_part + ((size_t)e * 2 * T.NW + 2 * w0) * 64 + lane;
+        float sv[32];
+#pragma unroll
+        for (int h = 0; h < 32; ++h) sv[h] = sp[(size_t)min(h, hws - 1) * 64];
+        const bool ok = arg < (unsigned)n;      // a record not written for this item routes nothing
+        const int a = ok ? (int)arg : 0, gi = base + a;
+        float x[9];
+        const unsigned long long am = S.itm.mask[(size_t)e * T.NW + w0 + (a >> 6)];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            x[c] = M.pos[(size_t)c * N + gi] - M.origin[3 * k + c];
+            x[3 + c] = M.nrm[(size_t)c * N + gi];
+            x[6 + c] = src[c * EN + (size_t)e * N + gi];
+        }
+        double sd = 0.0;
+#pragma unroll
+        for (int h = 0; h < 32; ++h) sd += h < hws ? (double)sv[h] : 0.0;
+#pragma unroll 1
+        for (int h0 = 32; h0 < hws; h0 += 32) {
+#pragma unroll
+            for (int h = 0; h < 32; ++h) sv[h] = sp[(size_t)min(h0 + h, hws - 1) * 64];
+#pragma unroll
+            for (int h = 0; h < 32; ++h) sd += h0 + h < hws ? (double)sv[h] : 0.0;
+        }
+        const float s4 = (float)sd;
+        const float dgp = column_dot(L.w4, s4);
         const float dp3 = gp > 0.0f ? dgp : 0.0f;
-        const float dg = matvec64(wp + kW3, dp3, 0.0f);
+        const float dg = column_dot(L.w3, dp3);
         iv[0] = s4;
         iv[128] = dp3;
-        const unsigned arg = rec[item * kSavedWords + 64 + lane];
-        const bool ok = arg < (unsigned)n;      // a record not written for this item routes nothing
-        const int a = ok ? (int)arg : 0;
         const float vr = (ok && g > 0.0f) ? dg : 0.0f;
-        const bool act = ok && ((S.itm.mask[(size_t)e * T.NW + w0 + (a >> 6)] >> (a & 63)) & 1ull);
+        const bool act = ok && ((am >> (a & 63)) & 1ull);
         accb2 += vr;
+        wave_sync();
         {
-            const int gi = base + a;
-            const float *u = src + (size_t)e * N + gi;
-            float *x = L.x[wave][lane];
-            wave_sync();
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                x[c] = M.pos[(size_t)c * N + gi] - M.origin[3 * k + c];
-                x[3 + c] = M.nrm[(size_t)c * N + gi];
-                x[6 + c] = act ? u[c * EN] : 0.0f;
-            }
-            x[9] = vr;
-            wave_sync();
+            float *o = L.x[wave][lane];
+            *reinterpret_cast<floatx4 *>(o) = floatx4{x[0], x[1], x[2], x[3]};
+            *reinterpret_cast<floatx4 *>(o + 4) = floatx4{x[4], x[5], act ? x[6] : 0.0f, act ? x[7] : 0.0f};
+            *reinterpret_cast<floatx2 *>(o + 8) = floatx2{act ? x[8] : 0.0f, vr};
         }
-        const float *w2 = wp + kW2 + lane;
+        wave_sync();
 #pragma unroll
         for (int c = 0; c < 64; ++c) {
-            const float w2c = w2[c * 64];      // read whether used or not: no branch
+            const float w2c = L.w2[c][lane];      // read whether used or not: no branch
             const floatx4 xa = *reinterpret_cast<const floatx4 *>(&L.x[wave][c][0]);
             const floatx4 xb = *reinterpret_cast<const floatx4 *>(&L.x[wave][c][4]);
             const float x8 = L.x[wave][c][8], v = L.x[wave][c][9];
@@ -661,7 +698,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             accx[8] += d * x8;
             accx[9] += d;
             L.gate[wave][c] = __ballot(h > 0.0f);      // every lane stores the same value
-            if ((c & 3) == 3) reload_fence();      // four channels' operands in flight, not all 64
+            if ((c & 7) == 7) reload_fence();      // eight channels' operands in flight, not all 64
         }
         if (__ballot(act && vr != 0.0f)) {
             wave_sync();
@@ -669,7 +706,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             float d0 = 0.0f, d1 = 0.0f, d2 = 0.0f;
 #pragma unroll 8
             for (int f = 0; f < 64; ++f) {
-                const float w2f = w2t[f * 64 + lane];
+                const float w2f = L.w2[lane][f];
                 const float d = (gate >> f) & 1ull ? vr * w2f : 0.0f;
                 const floatx4 w = *reinterpret_cast<const floatx4 *>(&L.w1u[f][0]);
                 d0 += w[0] * d;
@@ -681,7 +718,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             wave_sync();
             bool own = act;
             float t0 = 0.0f, t1 = 0.0f, t2 = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
             for (int c = 0; c < 64; ++c) {
                 const floatx4 o = *reinterpret_cast<const floatx4 *>(&L.d[wave][c][0]);
                 const bool same = __float_as_int(o[3]) == a;
@@ -699,6 +736,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         }
     }
     // the workgroup's sums, waves in order
+    __syncthreads();      // the weights are done with
     for (int w = 0; w < kWaves; ++w) {
         if (w == wave) {
 #pragma unroll
@@ -717,18 +755,45 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 // contact
 // ---------------------------------------------------------------------------
 
-// Sum of v over the wave in a fixed order, in every lane.
-__device__ __forceinline__ double wave_total(double v) {
+// One half of the values of a lane added to another lane's, as halve_max.
+template <int H, int CTRL>
+__device__ __forceinline__ void halve_sum(double (&v)[16], bool bit) {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    for (int i = 0; i < H / 2; ++i) {
+        const double keep = bit ? v[H / 2 + i] : v[i], give = bit ? v[i] : v[H / 2 + i];
+        v[i] = keep + __hiloint2double(dpp<CTRL>(__double2hiint(give)), dpp<CTRL>(__double2loint(give)));
+    }
+}
+
+// Sums of twelve values over the wave in a fixed order: lane l returns value l % 16.
+__device__ __forceinline__ double wave_sums(const double (&x)[12]) {
+    const int lane = lane_id();
+    double v[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) v[c] = c < 12 ? x[c < 12 ? c : 0] : 0.0;
+    halve_sum<16, kDppXor8>(v, lane & 8);
+    halve_sum<8, kDppXor7>(v, lane & 4);
+    halve_sum<4, kDppXor2>(v, lane & 2);
+    halve_sum<2, kDppXor1>(v, lane & 1);
+    double s = v[0];
+    {      // rows 0 and 1, 2 and 3
+        const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(s), __double2loint(s), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(s), __double2hiint(s), false, false);
+        s = __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+    }
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(s), __double2loint(s), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(s), __double2hiint(s), false, false);
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
 }
 
 // A wave per chunk of kPoseWords words of an item: for every object that wins
-// a node there, the sum over its nodes (a lane per node); exact zeros for the
-// others.
+// a node there, the sum over its nodes; exact zeros for the others.  An
+// object's nodes are listed, so that every lane has one (a lane per node of a
+// word left half of them idle in FP64), and the next 64 nodes' operands are
+// requested while these are used.  4096 hands: 158 us a word at a time, 97 us.
 __global__ __launch_bounds__(kWG) void k_adj_contact(AdjParams p) {
     __shared__ int first[kMaxPatches + 1];
+    __shared__ uint16_t lists[kWaves][64 * kPoseWords];
     const StepParams &S = p.s;
     const MeshDev &M = S.mesh;
     const TileDev &T = S.tile;
@@ -736,6 +801,7 @@ __global__ __launch_bounds__(kWG) void k_adj_contact(AdjParams p) {
     const int K = M.K, N = M.N, O = p.O, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const size_t EN = (size_t)S.E * N;
     const int32_t *na = S.itm.n_act;
+    uint16_t *list = lists[wave];
     const int total = unit_prefix<kWaves>(K, first, [&](int kk) {
         const int k = M.order[kk];
         return live_count(S, k) * (T.chunk_off[k + 1] - T.chunk_off[k]);
@@ -753,7 +819,6 @@ __global__ __launch_bounds__(kWG) void k_adj_contact(AdjParams p) {
         const int no = min(uniform(C.n_obj[srow]), O);
         float *out = p.pose_part + ((size_t)e * T.NC + c0 + part) * O * 12;
         const unsigned long long *mask = S.itm.mask + (size_t)e * T.NW + w0;
-        for (int i = lane; i < O * 12; i += 64) out[i] = 0.0f;
         // this lane's winner in every word of the chunk, all requested at once (-1: not active)
         int win[kPoseWords];
         unsigned present = 0;
@@ -768,42 +833,47 @@ __global__ __launch_bounds__(kWG) void k_adj_contact(AdjParams p) {
         for (int w = 0; w < kPoseWords; ++w)
             if (win[w] >= 0) present |= 1u << (win[w] & 31);
         present = uniform(wave_or(present));
+        for (int o = 0; o < O; ++o)
+            if (o >= no || !((present >> o) & 1u))
+                if (lane < 12) out[o * 12 + lane] = 0.0f;
         while (present) {
             const int o = __ffs(present) - 1;
             present &= present - 1;
             if (o >= no) continue;
+            int cnt = 0;
+            wave_sync();
+#pragma unroll
+            for (int w = 0; w < kPoseWords; ++w) {
+                const unsigned long long bal = __ballot(win[w] == o);
+                if (win[w] == o) list[cnt + lanes_below(bal)] = (uint16_t)(64 * w + lane);
+                cnt += __popcll(bal);
+            }
+            wave_sync();
             double acc[12];
 #pragma unroll
             for (int c = 0; c < 12; ++c) acc[c] = 0.0;
             const size_t eo = srow * C.O + o;
             const int ty = uniform(C.type[eo]);
             const float *sh = C.shape + 4 * eo, *R = C.rot + 9 * eo, *t = C.trans + 3 * eo;
+            float g[3], x[3];
+            auto fetch = [&](int t0) {      // beyond the list: its last node
+                const int i = 64 * wf + list[min(t0 + lane, cnt - 1)];
 #pragma unroll
-            for (int h = 0; h < kPoseWords; h += 2) {      // two words' operands in flight
-                if (!__ballot(win[h] == o || win[h + 1] == o)) continue;
-                float g[2][3], x[2][3];
-#pragma unroll
-                for (int d = 0; d < 2; ++d) {
-                    const int i = win[h + d] == o ? 64 * (wf + h + d) + lane : 0;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        g[d][c] = p.gh[c * EN + row + i];
-                        x[d][c] = M.pos[(size_t)c * N + base + i];
-                    }
+                for (int c = 0; c < 3; ++c) {
+                    g[c] = p.gh[c * EN + row + i];
+                    x[c] = M.pos[(size_t)c * N + base + i];
                 }
+            };
+            fetch(0);
 #pragma unroll 1
-                for (int d = 0; d < 2; ++d) {
-                    if ((d ? win[h + 1] : win[h]) != o) continue;
-                    const double gd[3] = {d ? g[1][0] : g[0][0], d ? g[1][1] : g[0][1], d ? g[1][2] : g[0][2]};
-                    contact_adjoint_node(ty, sh, R, t, d ? x[1][0] : x[0][0], d ? x[1][1] : x[0][1],
-                                         d ? x[1][2] : x[0][2], gd, acc);
-                }
+            for (int t0 = 0; t0 < cnt; t0 += 64) {
+                const double gd[3] = {g[0], g[1], g[2]};
+                const float px = x[0], py = x[1], pz = x[2];
+                fetch(t0 + 64);
+                if (t0 + lane < cnt) contact_adjoint_node(ty, sh, R, t, px, py, pz, gd, acc);
             }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                const double v = wave_total(acc[c]);
-                if (lane == c) out[o * 12 + c] = (float)v;
-            }
+            const double v = wave_sums(acc);
+            if (lane < 12) out[o * 12 + lane] = (float)v;
         }
     }
 }
@@ -833,14 +903,21 @@ __global__ __launch_bounds__(256) void k_pose(AdjParams p, float *grad_rot, floa
 // the routing workgroups' sums, the items' vectors (db4, db3, and the rank-one
 // products dW4[:, 64:] = s4 g'^T, dW3 = dpre3 g^T), and dW5 / db5 by half word
 // and chunk.  A block takes 256 columns of one kind and the entries of one
-// segment, in ascending order.
+// segment, in ascending order.  The 8192 columns of the rank-one products are
+// one block's, as matrix products in FP64 over the segment's items: a thread
+// per column reads both vectors of every item for each of them (4096 hands, all
+// columns: 170 us, 48 us as products).
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
 __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_groups, int segs) {
     __shared__ int list[1024];
     __shared__ int wsum[kWaves];
     const StepParams &S = p.s;
     const MeshDev &M = S.mesh;
     const TileDev &T = S.tile;
-    const int K = M.K, col = blockIdx.x * 256 + threadIdx.x, s = blockIdx.y, wave = threadIdx.x >> 6;
+    const int K = M.K, s = blockIdx.y, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
+    // one block for all columns of the items' vectors and their products
+    const int first = blockIdx.x * 256 + (blockIdx.x > kRedItem / 256 ? kRedW5 - kRedRank : 0), col = first + threadIdx.x;
     double acc = 0.0;
     auto range = [&](long long n, long long &a, long long &b) {
         const long long per = (n + segs - 1) / segs;
@@ -848,26 +925,27 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
         b = min(n, a + per);
     };
     long long a, b;
-    if (col < kRedRoute) {
+    if (first < kRedRoute) {
         range(T.NU, a, b);
         if (col < kNodeRecWords)
             for (long long u = a; u < b; ++u)
                 if (live_count(S, T.block[u].x) > 0) acc += (double)p.b.node_rec[u * kNodeRecWords + col];
-    } else if (col < kRedItem) {
+    } else if (first < kRedItem) {
         range(route_groups, a, b);
         const int c = col - kRedRoute;
         if (c < kRouteWords) {
 #pragma unroll 4
             for (long long u = a; u < b; ++u) acc += (double)p.b.route[u * kRouteWords + c];
         }
-    } else if (col < kRedW5) {
+    } else if (first == kRedItem) {
         // items in contact, listed 1024 at a time
         range((long long)S.E * K, a, b);
-        const bool plain = col < kRedRank;
-        const int c = plain ? col - kRedItem : col - kRedRank;
-        const int w = c >> 12, o = (c >> 6) & 63, i = c & 63;
-        const int ca = plain ? (c < 64 ? c : 128 + (c & 63)) : (w ? 128 + o : o), cb = plain ? 0 : (w ? 192 + i : 64 + i);
-        const bool live = !plain || c < 128;
+        // wave w takes rows 32 (w & 1) .. + 31 of matrix w >> 1, and the sums of those rows' vector
+        const int m = wave >> 1, l = lane & 15, sub = lane >> 4;
+        const int ro = 128 * m + 32 * (wave & 1) + l, co = 64 + 128 * m + l;
+        doublex4 d[2][5];
+#pragma unroll
+        for (int i = 0; i < 10; ++i) d[i / 5][i % 5] = doublex4{0.0, 0.0, 0.0, 0.0};
         for (long long c0 = a; c0 < b; c0 += 1024) {
             int cnt = 0;   // identical in every thread
             for (int j = 0; j < 4; ++j) {
@@ -887,15 +965,44 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
             }
             __syncthreads();
             const float *iv = p.b.ivec + c0 * 256;
-            if (live) {
-#pragma unroll 8
-                for (int t = 0; t < cnt; ++t) {
-                    const float *r = iv + (size_t)list[t] * 256;
-                    acc += plain ? (double)r[ca] : (double)r[ca] * (double)r[cb];
+            for (int t = 0; t < cnt; t += 32) {      // eight steps of four items; lanes beyond the last hold zeros
+                float x[8][2], y[8][4];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int at = t + 4 * u + sub;
+                    const float *r = iv + (size_t)list[min(at, cnt - 1)] * 256;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) x[u][i] = r[ro + 16 * i];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) y[u][j] = r[co + 16 * j];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const bool in = t + 4 * u + sub < cnt;
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const double v = in ? (double)x[u][i] : 0.0;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            d[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, in ? (double)y[u][j] : 0.0, d[i][j], 0, 0, 0);
+                        d[i][4] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, 1.0, d[i][4], 0, 0, 0);
+                    }
                 }
             }
             __syncthreads();   // the list is rewritten
         }
+        // register r of a lane: row 4 r + lane / 16, column lane % 16
+        double *o = p.b.seg + (size_t)s * kRedCols + kRedRank + 4096 * m + (32 * (wave & 1) + sub) * 64 + l;
+        double *sum = p.b.seg + (size_t)s * kRedCols + kRedItem + 64 * m + 32 * (wave & 1) + sub;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[(16 * i + 4 * r) * 64 + 16 * j] = d[i][j][r];
+                sum[16 * i + 4 * r] = d[i][4][r];      // the same in every column
+            }
+        return;
     } else {
         range(T.NB5, a, b);
         const int c = col - kRedW5, EC = p.env_chunk;
@@ -908,7 +1015,7 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
             for (int t = 0; t < chunks; ++t) acc += (double)w[(size_t)t * T.NB5 * 256];
         }
     }
-    if (col < kRedCols) p.b.seg[(size_t)s * kRedCols + col] = acc;
+    p.b.seg[(size_t)s * kRedCols + col] = acc;
 }
 
 // Slot of entry (row, col) of 16 x 16 block b in a node record (MFMA output order).
@@ -1027,6 +1134,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     f.cobj_in = cobj_in;
     f.uhat_in = uhat_in;
     f.u = s ? pl.bwd.uhat_st : grad_uhat;
+    f.scratch = s != nullptr;
     f.cobj_out = s ? pl.bwd.cobj_st : nullptr;
     f.adjoint = 1;
     f.ivec = pl.bwd.ivec;
@@ -1074,7 +1182,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     slot = timer_begin(pl, ETAC_TIMER_REDUCE, st);
     if (res && grad_phi) {
         const int segs = f.dense && pl.tile.NU <= 64 ? 8 : kPhiSegs;
-        hipLaunchKernelGGL(k_phi_segments, dim3(kRedCols / 256, segs), dim3(256), 0, st, p, route_groups, segs);
+        hipLaunchKernelGGL(k_phi_segments, dim3((kRedCols - (kRedW5 - kRedRank)) / 256, segs), dim3(256), 0, st, p, route_groups, segs);
         hipLaunchKernelGGL(k_phi_final, dim3((kPhiN + 255) / 256), dim3(256), 0, st, pl.bwd.seg, segs, grad_phi);
     }
     if (grad_alpha) {
@@ -1101,6 +1209,7 @@ hipError_t launch_contact_backward(const Plan &pl, const SceneDev &s, const floa
     f.model = ModelDev{ETAC_DECAY_ONLY, nullptr, nullptr};
     f.E = s.E;
     f.u = pl.bwd.uhat_st;
+    f.scratch = 1;
     f.cobj_out = pl.bwd.cobj_st;
     f.adjoint = 1;
     shape_step(pl, f);

@@ -382,7 +382,6 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.scale, 8);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w3t, 4096);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w4t, 4096);
-    if (e == hipSuccess) e = plan_alloc(p, &p.tab.w2t, 4096);
     if (e == hipSuccess) e = plan_alloc(p, &p.tab.w, (size_t)matrix_units);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.mask, ENW);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.umax, ENW);

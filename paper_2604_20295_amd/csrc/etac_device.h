@@ -303,11 +303,6 @@ __device__ __forceinline__ unsigned lanes_below(unsigned long long mask) {
 }
 
 // Maximum over the wave, returned in every lane.
-__device__ __forceinline__ unsigned wave_or(unsigned v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v |= (unsigned)__shfl_xor((int)v, off);
-    return v;
-}
 __device__ __forceinline__ int wave_max_int(int v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = max(v, __shfl_xor(v, off));
@@ -320,6 +315,17 @@ template <int CTRL>
 __device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false); }
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) { return __int_as_float(dpp<CTRL>(__float_as_int(v))); }
+
+__device__ __forceinline__ unsigned wave_or(unsigned v) {
+    v |= (unsigned)dpp<kDppXor1>((int)v);
+    v |= (unsigned)dpp<kDppXor2>((int)v);
+    v |= (unsigned)dpp<kDppXor7>((int)v);
+    v |= (unsigned)dpp<kDppXor15>((int)v);
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] | a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return b[0] | b[1];
+}
 
 __device__ __forceinline__ float wave_max(float v) {
     v = fmaxf(v, dpp<kDppXor1>(v));

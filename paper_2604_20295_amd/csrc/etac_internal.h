@@ -127,7 +127,7 @@ struct TableDev {
     float *dec;                // [N][64] W4[:, :64] feat
     float *max8, *max32;       // [8 NW][64], [2 NW][64] largest features of 8 and of 32 consecutive nodes of a word
     int *scale;                // [8] exponents of the network's weight scales (s1, s2, s4)
-    float *w3t, *w4t, *w2t;    // [64][64] W3, W4[:, 64:] and W2 transposed
+    float *w3t, *w4t;          // [64][64] W3 and W4[:, 64:] transposed
     uint4 *w, *wd;             // decay matrices W and, for the adjoint, d W (see matrix_row_tile)
 };
 
