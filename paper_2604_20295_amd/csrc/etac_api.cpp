@@ -398,8 +398,12 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = hipMemset(p.counter, 0, 4 * sizeof(unsigned));
     // regressor: rest outputs, and a pooled-feature row per item it may process
     if (e == hipSuccess) e = plan_alloc(p, &p.reg_rest, 8 * (size_t)K);
-    if (e == hipSuccess) e = plan_alloc(p, &p.reg_pooled, ((size_t)n_envs * K + K) * 256);
-    if (e == hipSuccess) e = plan_alloc(p, &p.reg_row, (size_t)n_envs * K + K);
+    size_t parts = 0;
+    for (int k = 0; k < K; ++k) parts += (mesh->patch_offset[k + 1] - mesh->patch_offset[k] + etac::kRegUnitNodes - 1) / etac::kRegUnitNodes;
+    if (e == hipSuccess) e = plan_alloc(p, &p.reg_pooled, ((size_t)n_envs + 1) * parts * 256);
+    if (e == hipSuccess) e = plan_alloc(p, &p.reg_ml, ((size_t)n_envs + 1) * parts);
+    if (e == hipSuccess) e = plan_alloc(p, &p.reg_live, EK);
+    if (e == hipSuccess) e = plan_alloc(p, &p.reg_cnt, (size_t)K);
 
     if (e == hipSuccess && (flags & ETAC_PLAN_BACKWARD)) {
         etac::BwdScratch &b = p.bwd;

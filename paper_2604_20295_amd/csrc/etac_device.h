@@ -312,7 +312,7 @@ __device__ __forceinline__ int wave_max_int(int v) {
 // lane ^ 1, ^ 2, ^ 7 (mirrored half row), ^ 8 (rotated by 8), ^ 15 (mirrored row).
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor7 = 0x141, kDppXor8 = 0x128, kDppXor15 = 0x140;
 template <int CTRL>
-__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false); }
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true); }
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) { return __int_as_float(dpp<CTRL>(__float_as_int(v))); }
 

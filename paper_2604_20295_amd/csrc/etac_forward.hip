@@ -1132,6 +1132,10 @@ void shape_step(const Plan &pl, StepParams &p) {
     p.splits = contact_splits(pl, p.E);
 }
 
+void launch_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt, hipStream_t st) {
+    hipLaunchKernelGGL(k_live, dim3(K), dim3(1024), 0, st, n_active, E, K, live, live_cnt);
+}
+
 void launch_front(const Plan &pl, const StepParams &p, hipStream_t st) {
     const int nt = p.table_units + p.matrix_units;
     const bool merged = p.dense && p.splits == 1 && nt > 0;
@@ -1140,7 +1144,7 @@ void launch_front(const Plan &pl, const StepParams &p, hipStream_t st) {
     if (p.cobj_in) launch_contact_items<true>(p, merged, nt, st);
     else launch_contact_items<false>(p, merged, nt, st);
     const int32_t *na = p.n_active ? p.n_active : pl.itm.n_act;
-    if (!p.dense) hipLaunchKernelGGL(k_live, dim3(pl.K), dim3(1024), 0, st, na, p.E, pl.K, pl.itm.live, pl.itm.live_cnt);
+    if (!p.dense) launch_live(na, p.E, pl.K, pl.itm.live, pl.itm.live_cnt, st);
 }
 
 void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st) {

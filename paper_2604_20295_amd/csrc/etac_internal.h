@@ -19,6 +19,7 @@ constexpr int kRouteWords = 4096 + 640 + 64;
 constexpr int kRouteGroups = 2;                   // routing workgroups per compute unit
 constexpr int kRedRoute = 37 * 256, kRedItem = kRedRoute + 19 * 256, kRedRank = kRedItem + 256,
               kRedW5 = kRedRank + 8192, kRedCols = kRedW5 + 256;
+constexpr int kRegUnitNodes = 256;               // nodes of a regressor unit
 constexpr int kAlphaSegs = 32;
 constexpr int kPhiSegs = 64;                      // segments of the parameter reduction
 constexpr int kMaxPatches = 1024;  // per-patch counters of the contact kernel live in LDS
@@ -208,8 +209,10 @@ struct Plan {
     HandDev *hand;         // null until etac_plan_set_hand (host copy of the device view)
     void *hand_mem;        // the hand's device block (one allocation)
     float *reg_rest;       // [K][8] regressor outputs of the patches at U = 0
-    float *reg_pooled;     // [E K + K][256] regressor pooled features, one row per processed item
-    int *reg_row;          // [E K + K] the item of each row
+    float *reg_pooled;     // [units][256] regressor: weighted sums of 256 nodes of an item
+    float2 *reg_ml;        // [units] their largest scores and sums of weights
+    int *reg_live;         // [K][E] envs in contact of the call's n_active
+    int *reg_cnt;          // [K]
 };
 
 // Open a timed span of timer k on stream st; returns the slot, or -1 when

@@ -3,18 +3,20 @@
 // PointNet-style network with a residual layer and attention pooling (the
 // regressor of the paper's appendix, "Modeling Real Sensors").
 //
+//   k_live         : the envs in contact on each patch.
 //   k_regress      : persistent, one workgroup of eight waves per CU with the
-//                    per-node layers' weights resident in LDS; every wave
-//                    claims whole items from a device work queue (largest
-//                    patches first), runs their 16-node tiles, two at a
-//                    time, through the per-node layers on MFMA with an online
-//                    softmax over the tiles, and appends the pooled feature
-//                    g as a row.
-//   k_regress_head : the head on every row, in FP32.
+//                    per-node layers' weights resident in LDS; a unit is 256
+//                    nodes of an item, taken by a wave (largest patches first,
+//                    one each and then from a device work queue): 16-node
+//                    tiles, two at a time, through the per-node layers on MFMA
+//                    with an online softmax over the tiles.  The unit's
+//                    maximum, sum of weights and weighted sum of features are
+//                    a row of scratch.
+//   k_regress_head : the rows of an item combined, and the head, in FP32.
 //   k_regress_fill : items without contact have U = 0 on the whole patch, so
 //                    their output is the patch's rest output, computed once
-//                    per patch (queue positions 0 .. K - 1, ahead of the E K
-//                    items) and copied here.
+//                    per patch (an item behind the patch's last env in
+//                    contact) and copied here.
 //
 // Per node:  x = [p - o_k, U] (6) -> h1 = relu(E1 x + e1) (64)
 //            -> h2 = relu(E2 h1 + e2) + h1 (64) -> f = relu(E3 h2 + e3) (256)
@@ -28,7 +30,7 @@
 // operands of A1 (f is held once, in 32 registers per tile); softmax
 // weights, pooling sums and the head are FP32.  FP16 rounding is relative
 // 2^-11 at most.
-#include "etac_device.h"
+#include "etac_step.h"
 
 namespace etac {
 
@@ -45,23 +47,30 @@ static_assert(kRegN == ETAC_REG_SIZE, "regressor parameter layout");
 constexpr float kTwoLog2e = 2.8853900817779268f;
 
 struct RegLds {
-    half8 e1h[4 * 64], e1l[4 * 64];              // [E1 | e1] split, inputs padded 7 -> 32 (x_6 = 1 carries e1)
+    half8 e1[4 * 64];                            // [E1 | e1] (x_6 = 1 carries e1): the three products of its split
+                                                 // parts share one K step: lane group 0 hi hi, 2 hi lo, 3 lo hi
     half8 e2[4 * 2 * 64];                        // E2 FP16, [ot][s][lane], chain order
     half8 e3[16 * 2 * 64];                       // E3 FP16, [ot][s][lane], 256 outputs
     half8 a1[8 * 8 * 64];                        // 2 log2(e) A1 in FP16, [ot][s][lane], 128 outputs over 256 inputs
     float be2[64], be3[256], ba1[128], wa2[128]; // e2, e3, 2 log2(e) a1, -2 a2
 };
 
+constexpr int kRegPasses = kRegUnitNodes / (16 * kRegNT);      // passes of a unit
+
 struct RegParams {
     MeshDev mesh;
     const float *reg;         // [ETAC_REG_SIZE]
     const float *u;           // [3][E][N]
-    const int32_t *n_active;  // [E][K]
-    float *pooled;            // [rows][256] pooled feature g of each processed item
-    int *row_item;            // [rows] its item: e K + k, or -1 - k for patch k's rest item
-    unsigned *counter;        // [4] work queue, retired workgroups, rows, rows of the last call
-    int E, n_pos;             // queue positions: K rest items, then the E K items
+    const int *live, *live_cnt;      // [K][E], [K] envs in contact
+    float *pooled;            // [units][256] weighted sum of a unit's features
+    float2 *ml;               // [units] its largest score and its sum of weights
+    unsigned *counter;        // [2] work queue, retired workgroups
+    int E;
 };
+
+__device__ __forceinline__ int reg_parts(const MeshDev &M, int k) {
+    return (M.offset[k + 1] - M.offset[k] + kRegUnitNodes - 1) / kRegUnitNodes;
+}
 
 __device__ void stage_regressor(RegLds &L, const float *R) {
     const int tid = threadIdx.x;
@@ -69,11 +78,10 @@ __device__ void stage_regressor(RegLds &L, const float *R) {
         const int lane = idx & 63, ot = idx >> 6, q = lane >> 4, o = ot * 16 + (lane & 15);
         float x[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int in = 8 * q + e;
-            x[e] = in < 6 ? R[kRE1 + o * 6 + in] : in == 6 ? R[kRe1 + o] : 0.0f;
-        }
-        split8(x, L.e1h[idx], L.e1l[idx]);
+        for (int e = 0; e < 8; ++e) x[e] = q == 1 ? 0.0f : e < 6 ? R[kRE1 + o * 6 + e] : e == 6 ? R[kRe1 + o] : 0.0f;
+        half8 h, l;
+        split8(x, h, l);
+        L.e1[idx] = q == 3 ? l : h;
     }
     for (int idx = tid; idx < 4 * 2 * 64; idx += kRegWG) {
         const int lane = idx & 63, s = (idx >> 6) & 1, ot = idx >> 7, q = lane >> 4;
@@ -136,20 +144,28 @@ __device__ __forceinline__ float fma_half(float w, unsigned h, float acc) {
 // Each weight fragment is read from LDS once per pass and used by every
 // tile; A1 runs output block by output block so that the tanh of one block
 // overlaps the MFMAs of the next.
-__device__ __forceinline__ void regress_tiles(const RegLds &L, const half8 (&xh)[kRegNT], const half8 (&xl)[kRegNT],
-                                              half8 (&fb)[kRegNT][8], float (&sc)[kRegNT]) {
+__device__ __forceinline__ void regress_tiles(const RegLds &L, const half8 (&x)[kRegNT], half8 (&fb)[kRegNT][8],
+                                              float (&sc)[kRegNT]) {
     constexpr int NT = kRegNT;
     reload_fence();
     const int lane = lane_id(), gq = lane >> 4;
     floatx4 h1[NT][4];
+    half8 v[8];
+    floatx4 b2[4];
     {
         const floatx4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+        half8 w[4];
 #pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            const half8 wh = L.e1h[ot * 64 + lane], wl = L.e1l[ot * 64 + lane];
+        for (int ot = 0; ot < 4; ++ot) w[ot] = L.e1[ot * 64 + lane];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) h1[i][ot] = relu4(mfma_split(wh, wl, xh[i], xl[i], z));
-        }
+        for (int t = 0; t < 8; ++t) v[t] = L.e2[t * 64 + lane];
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot) b2[ot] = *reinterpret_cast<const floatx4 *>(&L.be2[ot * 16 + 4 * gq]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ot = 0; ot < 4; ++ot)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) h1[i][ot] = relu4(mfma16(w[ot], x[i], z));
     }
     half8 b0[NT], b1[NT];   // h2 as FP16 B operands of E3
     {
@@ -161,72 +177,125 @@ __device__ __forceinline__ void regress_tiles(const RegLds &L, const half8 (&xh)
         }
         floatx4 h2[NT][4];
 #pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            const floatx4 bias = *reinterpret_cast<const floatx4 *>(&L.be2[ot * 16 + 4 * gq]);
-            const half8 w0 = L.e2[(ot * 2 + 0) * 64 + lane], w1 = L.e2[(ot * 2 + 1) * 64 + lane];
+        for (int ot = 0; ot < 4; ++ot)
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                h2[i][ot] = relu4(mfma16(w1, c1[i], mfma16(w0, c0[i], bias)));
+                h2[i][ot] = relu4(mfma16(v[2 * ot + 1], c1[i], mfma16(v[2 * ot], c0[i], b2[ot])));
 #pragma unroll
                 for (int r = 0; r < 4; ++r) h2[i][ot][r] += h1[i][ot][r];
             }
-        }
 #pragma unroll
         for (int i = 0; i < NT; ++i) {
             b0[i] = chain_f16(h2[i], 0);
             b1[i] = chain_f16(h2[i], 1);
         }
     }
-    reload_fence();
+    __builtin_amdgcn_sched_barrier(0);
+    // E3: the weights of the next two output tiles are requested, and the last
+    // two packed, while the MFMAs of these run
+    {
+        half8 w[2][4];
+        floatx4 bias[2][2], f[2][NT][2];
+        auto request = [&](int s, int b) {
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        floatx4 f[NT][2];
+            for (int j = 0; j < 2; ++j) {
+                bias[b][j] = *reinterpret_cast<const floatx4 *>(&L.be3[(2 * s + j) * 16 + 4 * gq]);
+                w[b][2 * j] = L.e3[((2 * s + j) * 2 + 0) * 64 + lane];
+                w[b][2 * j + 1] = L.e3[((2 * s + j) * 2 + 1) * 64 + lane];
+            }
+        };
+        auto pack = [&](int s, int b) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int ot = 2 * s + j;
-            const floatx4 bias = *reinterpret_cast<const floatx4 *>(&L.be3[ot * 16 + 4 * gq]);
-            const half8 w0 = L.e3[(ot * 2 + 0) * 64 + lane], w1 = L.e3[(ot * 2 + 1) * 64 + lane];
-#pragma unroll
-            for (int i = 0; i < NT; ++i) f[i][j] = mfma16(w1, b1[i], mfma16(w0, b0[i], bias));
-        }
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
-            uint4t v;
-            v[0] = pack_relu(f[i][0][0], f[i][0][1]);
-            v[1] = pack_relu(f[i][0][2], f[i][0][3]);
-            v[2] = pack_relu(f[i][1][0], f[i][1][1]);
-            v[3] = pack_relu(f[i][1][2], f[i][1][3]);
-            fb[i][s] = __builtin_bit_cast(half8, v);
-        }
-    }
-    reload_fence();
-    // a2 . tanh(z) = sum(a2) - 2 a2 . 1 / (1 + e^(2 z)); the constant sum(a2)
-    // (like a0) cancels in the softmax
-#pragma unroll
-    for (int i = 0; i < NT; ++i) sc[i] = 0.0f;
-#pragma unroll
-    for (int ot = 0; ot < 8; ++ot) {
-        const floatx4 bias = *reinterpret_cast<const floatx4 *>(&L.ba1[ot * 16 + 4 * gq]);
-        floatx4 t[NT];
-#pragma unroll
-        for (int i = 0; i < NT; ++i) t[i] = bias;
+            for (int i = 0; i < NT; ++i) {
+                uint4t v;
+                v[0] = pack_relu(f[b][i][0][0], f[b][i][0][1]);
+                v[1] = pack_relu(f[b][i][0][2], f[b][i][0][3]);
+                v[2] = pack_relu(f[b][i][1][0], f[b][i][1][1]);
+                v[3] = pack_relu(f[b][i][1][2], f[b][i][1][3]);
+                fb[i][s] = __builtin_bit_cast(half8, v);
+            }
+        };
+        request(0, 0);
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const half8 w = L.a1[(ot * 8 + s) * 64 + lane];
+            const int b = s & 1;
+            if (s < 7) request(s + 1, b ^ 1);
 #pragma unroll
-            for (int i = 0; i < NT; ++i) t[i] = mfma16(w, fb[i][s], t[i]);
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) f[b][i][j] = mfma16(w[b][2 * j], b0[i], bias[b][j]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int i = 0; i < NT; ++i) f[b][i][j] = mfma16(w[b][2 * j + 1], b1[i], f[b][i][j]);
+            if (s) pack(s - 1, b ^ 1);
+            if (s < 7) __builtin_amdgcn_sched_group_barrier(0x100, 6, 0);
+#pragma unroll
+            for (int i = 0; i < 4 * NT; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (s) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        const floatx4 c = *reinterpret_cast<const floatx4 *>(&L.wa2[ot * 16 + 4 * gq]);
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                sc[i] += c[r] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(t[i][r]));
+        pack(7, 1);
     }
+    // A1, output tile by output tile: the tanh of one tile between the MFMAs of
+    // the next, its weights requested a tile ahead.  a2 . tanh(z) = sum(a2) -
+    // 2 a2 . 1 / (1 + e^(2 z)); the constant sum(a2) (like a0) cancels in the
+    // softmax.
+#pragma unroll
+    for (int i = 0; i < NT; ++i) sc[i] = 0.0f;
+    {
+        half8 w[8];
+        floatx4 t[2][NT], c, bias;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) w[s] = L.a1[s * 64 + lane];
+        bias = *reinterpret_cast<const floatx4 *>(&L.ba1[4 * gq]);
+        c = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        auto tanhs = [&](const floatx4 (&x)[NT]) {
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    sc[i] += c[r] * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[i][r]));
+        };
+#pragma unroll
+        for (int ot = 0; ot < 8; ++ot) {
+            const int b = ot & 1;
+#pragma unroll
+            for (int i = 0; i < NT; ++i) t[b][i] = bias;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) t[b][i] = mfma16(w[s], fb[i][s], t[b][i]);
+                if (ot < 7) w[s] = L.a1[((ot + 1) * 8 + s) * 64 + lane];
+            }
+            if (ot < 7) bias = *reinterpret_cast<const floatx4 *>(&L.ba1[(ot + 1) * 16 + 4 * gq]);
+            if (ot) tanhs(t[b ^ 1]);
+            c = *reinterpret_cast<const floatx4 *>(&L.wa2[ot * 16 + 4 * gq]);
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+#pragma unroll
+                for (int i = 0; i < NT; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    if (ot) {
+                        __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
+                    }
+                }
+                if (ot < 7) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        tanhs(t[1]);
+    }
+    // over the four lanes of a node
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
-        sc[i] += __shfl_xor(sc[i], 16);
-        sc[i] += __shfl_xor(sc[i], 32);
+        const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(sc[i]), __float_as_uint(sc[i]), false, false);
+        sc[i] = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(sc[i]), __float_as_uint(sc[i]), false, false);
+        sc[i] = __uint_as_float(b[0]) + __uint_as_float(b[1]);
     }
 }
 
@@ -254,11 +323,10 @@ __device__ __forceinline__ float node_max(float v) {
     return v;
 }
 
-// One item on one wave: every 16-node tile of patch k through the per-node
-// layers, an online softmax over the tiles (running maximum m, per-lane
-// running sums of e^(s - m) and e^(s - m) f), then the pooled feature
-// g = sum w f / sum w appended as a row of p.pooled.
-__device__ void regress_item(const RegParams &p, const RegLds &L, int e, int k, bool rest) {
+// One unit on one wave: the 16-node tiles of part `part` of patch k through the
+// per-node layers, an online softmax over the tiles (running maximum m,
+// per-lane running sums of e^(s - m) and e^(s - m) f), to row `row`.
+__device__ void regress_unit(const RegParams &p, const RegLds &L, int e, int k, int part, bool rest, int row) {
     const MeshDev &M = p.mesh;
     const int N = M.N, lane = lane_id(), q = lane >> 4;
     const int base = M.offset[k], n = M.offset[k + 1] - base;
@@ -268,37 +336,39 @@ __device__ void regress_item(const RegParams &p, const RegLds &L, int e, int k, 
     floatx4 acc[16];
 #pragma unroll
     for (int ot = 0; ot < 16; ++ot) acc[ot] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int groups = (n + 16 * kRegNT - 1) / (16 * kRegNT);
-    for (int tg = 0; tg < groups; ++tg) {
-        half8 xh[kRegNT], xl[kRegNT];
+    const int groups = min((n + 16 * kRegNT - 1) / (16 * kRegNT), (part + 1) * kRegPasses);
+    // the next tiles' inputs are requested while these run; nodes beyond the
+    // patch repeat its last and get no weight
+    const float *pos = M.pos + base, *u = p.u + (size_t)e * N + base;
+    float raw[kRegNT][6];
+    auto fetch = [&](int tg) {
+#pragma unroll
+        for (int i = 0; i < kRegNT; ++i) {
+            const int j = min(16 * (kRegNT * tg + i) + (lane & 15), n - 1);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                raw[i][c] = pos[(size_t)c * N + j];
+                raw[i][3 + c] = u[(size_t)c * EN + j];
+            }
+        }
+    };
+    fetch(part * kRegPasses);
+    for (int tg = part * kRegPasses; tg < groups; ++tg) {
+        half8 x[kRegNT];
         bool valid[kRegNT];
 #pragma unroll
         for (int i = 0; i < kRegNT; ++i) {
-            const int j = 16 * (kRegNT * tg + i) + (lane & 15);
-            valid[i] = j < n;
-            float v[8];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) v[c] = 0.0f;
-            if (q == 0) {
-                v[6] = 1.0f;   // carries the bias e1
-                if (valid[i]) {
-                    const int gi = base + j;
-                    v[0] = M.pos[gi] - o0;
-                    v[1] = M.pos[N + gi] - o1;
-                    v[2] = M.pos[2 * N + gi] - o2;
-                    if (!rest) {
-                        const size_t en = (size_t)e * N + gi;
-                        v[3] = p.u[en];
-                        v[4] = p.u[EN + en];
-                        v[5] = p.u[2 * EN + en];
-                    }
-                }
-            }
-            split8(v, xh[i], xl[i]);
+            valid[i] = 16 * (kRegNT * tg + i) + (lane & 15) < n;
+            const float v[8] = {raw[i][0] - o0, raw[i][1] - o1, raw[i][2] - o2, rest ? 0.0f : raw[i][3],
+                                rest ? 0.0f : raw[i][4], rest ? 0.0f : raw[i][5], 1.0f, 0.0f};      // 1 carries the bias e1
+            half8 h, l;
+            split8(v, h, l);
+            x[i] = q == 2 ? l : h;
         }
+        fetch(tg + 1);
         half8 fb[kRegNT][8];
         float s[kRegNT];
-        regress_tiles(L, xh, xl, fb, s);
+        regress_tiles(L, x, fb, s);
         float mt = -INFINITY;
 #pragma unroll
         for (int i = 0; i < kRegNT; ++i) {
@@ -332,94 +402,143 @@ __device__ void regress_item(const RegParams &p, const RegLds &L, int e, int k, 
         }
     }
     // sums over the 16 node lanes: features 16 ot + 4 q + r in every lane of group q
-    const float inv = 1.0f / node_sum(l_run);
+    const float l = node_sum(l_run);
 #pragma unroll
     for (int ot = 0; ot < 16; ++ot)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[ot][r] = node_sum(acc[ot][r]) * inv;
-    const unsigned old = atomicAdd(&p.counter[2], lane == 0 ? 1u : 0u);
-    const unsigned row = (unsigned)__builtin_amdgcn_readlane((int)old, 0);
+        for (int r = 0; r < 4; ++r) acc[ot][r] = node_sum(acc[ot][r]);
     if ((lane & 15) == 0) {
         float *g = p.pooled + (size_t)row * 256 + 4 * q;
 #pragma unroll
         for (int ot = 0; ot < 16; ++ot) *reinterpret_cast<floatx4 *>(g + ot * 16) = acc[ot];
     }
-    if (lane == 0) p.row_item[row] = rest ? -1 - k : e * M.K + k;
+    if (lane == 0) p.ml[row] = make_float2(m_run, l);
 }
 
-// Persistent; every wave claims items on its own (no barrier per item).
+// Persistent; every wave takes units on its own (no barrier per unit).  Bound
+// by the per-node layers (116 MFMAs and about 500 VALU cycles' worth of
+// instructions per 16 nodes on either side of them).  Units of 256 nodes of the
+// items in contact alone: with whole items claimed from a queue of every (env,
+// patch), five of six of them without contact, 1024 hands spent 45 % of the
+// wave time in claims and had 1.1 items a wave (395 us; 280 us now; units of
+// 128 nodes 298 us).
 __global__ __launch_bounds__(kRegWG) void k_regress(RegParams p) {
     __shared__ RegLds L;
-    stage_regressor(L, p.reg);
-    __syncthreads();
+    __shared__ int first[kMaxPatches + 1];
     const MeshDev &M = p.mesh;
-    for (;;) {
+    const int wave = uniform(threadIdx.x >> 6);
+    stage_regressor(L, p.reg);
+    const int total = unit_prefix<kRegWaves>(M.K, first, [&](int kk) {
+        const int k = M.order[kk];
+        return (p.live_cnt[k] + 1) * reg_parts(M, k);
+    });
+    int pos = wave * gridDim.x + blockIdx.x;
+    while (pos < total) {
+        const int kk = unit_rank(first, M.K, pos), k = uniform(M.order[kk]);
+        const int parts = uniform(reg_parts(M, k)), local = pos - uniform(first[kk]);
+        const int it = local / parts;
+        const bool rest = it == uniform(p.live_cnt[k]);
+        regress_unit(p, L, rest ? 0 : uniform(p.live[(size_t)k * p.E + it]), k, local - it * parts, rest, pos);
         // one atomic for the wave (lane 0 adds 1), executed by every lane so
         // that no lane-dependent branch enters the loop; lane 0's old value
         // is the claimed position
         const unsigned old = atomicAdd(&p.counter[0], lane_id() == 0 ? 1u : 0u);
-        const unsigned pos = (unsigned)__builtin_amdgcn_readlane((int)old, 0);
-        if (pos >= (unsigned)p.n_pos) break;
-        int e = 0, k;
-        const bool rest = pos < (unsigned)M.K;   // rest items first, largest patches first
-        if (rest) {
-            k = M.order[pos];
-        } else {
-            queue_item(M, p.E, (int)pos - M.K, e, k);
-            if (uniform(p.n_active[(size_t)e * M.K + k]) == 0) continue;   // takes the rest output
-        }
-        regress_item(p, L, e, k, rest);
+        pos = (int)(gridDim.x * kRegWaves) + __builtin_amdgcn_readlane((int)old, 0);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
         const unsigned done = atomicAdd(&p.counter[1], 1u);
-        if (done == gridDim.x - 1) {   // last workgroup: publish the row count, reset the queue
-            atomicExch(&p.counter[3], atomicExch(&p.counter[2], 0u));
+        if (done == gridDim.x - 1) {   // last workgroup: reset the queue
             atomicExch(&p.counter[0], 0u);
             atomicExch(&p.counter[1], 0u);
         }
     }
 }
 
-// Head of every row: y = D2 relu(D1 g + d1) + d2 in FP32, 32 rows per
-// block pass; D1 streamed through LDS transposed in 32-column chunks.
-constexpr int kHeadRows = 32;
+// Pooled feature g = sum w f / sum w of every item from its units' rows, and
+// the head y = D2 relu(D1 g + d1) + d2, in FP32, kHeadRows items per block
+// pass; D1 streamed through LDS transposed in 32-column chunks, the next chunk
+// requested while one is used.  Latency-bound: 16 items a pass give 1024 hands
+// 145 blocks (32 items a pass and chunks loaded in turn: 34 us; 31 us).
+constexpr int kHeadRows = 16;
 
-__global__ __launch_bounds__(256) void k_regress_head(const float *reg, const float *pooled, const int *row_item,
-                                                      const unsigned *counter, int K, float *taxels, float *rest) {
+__global__ __launch_bounds__(256) void k_regress_head(RegParams p, float *taxels, float *rest) {
     __shared__ float G[kHeadRows][256];
     __shared__ float DT[32][129];
     __shared__ float H[kHeadRows][128];
+    __shared__ int items[kMaxPatches + 1], units[kMaxPatches + 1];
+    __shared__ int row0[kHeadRows], rows[kHeadRows], out[kHeadRows];
+    const MeshDev &M = p.mesh;
+    const float *reg = p.reg;
     const int tid = threadIdx.x, o = tid & 127, rh = tid >> 7;
-    const unsigned rows = counter[3];
-    for (unsigned b0 = blockIdx.x * kHeadRows; b0 < rows; b0 += gridDim.x * kHeadRows) {
-        __syncthreads();   // the previous pass is done with G and H
-        for (int idx = tid; idx < kHeadRows * 64; idx += 256) {
-            const int r = idx >> 6, c4 = idx & 63;
-            floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (b0 + r < rows) v = *reinterpret_cast<const floatx4 *>(pooled + (size_t)(b0 + r) * 256 + 4 * c4);
-            *reinterpret_cast<floatx4 *>(&G[r][4 * c4]) = v;
+    constexpr int kHalf = kHeadRows / 2;
+    const int total = unit_prefix<kWaves>(M.K, items, [&](int kk) { return p.live_cnt[M.order[kk]] + 1; });
+    unit_prefix<kWaves>(M.K, units, [&](int kk) {
+        const int k = M.order[kk];
+        return (p.live_cnt[k] + 1) * reg_parts(M, k);
+    });
+    for (int b0 = blockIdx.x * kHeadRows; b0 < total; b0 += gridDim.x * kHeadRows) {
+        __syncthreads();   // the previous pass is done with LDS
+        if (tid < kHeadRows) {
+            const int q = min(b0 + tid, total - 1);
+            int lo = 0, hi = M.K - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (items[mid] <= q) lo = mid;
+                else hi = mid - 1;
+            }
+            const int k = M.order[lo], local = q - items[lo], parts = reg_parts(M, k);
+            row0[tid] = units[lo] + local * parts;
+            rows[tid] = parts;
+            out[tid] = local == p.live_cnt[k] ? -1 - k : p.live[(size_t)k * p.E + local] * M.K + k;
         }
-        float a[16];
+        __syncthreads();
+        for (int idx = tid; idx < kHeadRows * 64; idx += 256) {
+            const int r = idx >> 6, c4 = idx & 63, f = row0[r], n = rows[r];
+            float m = p.ml[f].x;
+            for (int t = 1; t < n; ++t) m = fmaxf(m, p.ml[f + t].x);
+            float l = 0.0f;
+            floatx4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+            for (int t = 0; t < n; ++t) {
+                const float2 ml = p.ml[f + t];
+                const floatx4 a = *reinterpret_cast<const floatx4 *>(p.pooled + (size_t)(f + t) * 256 + 4 * c4);
+                const float w = __expf(ml.x - m);
+                l += w * ml.y;
+                v += w * a;
+            }
+            *reinterpret_cast<floatx4 *>(&G[r][4 * c4]) = v * (1.0f / l);
+        }
+        float a[kHalf];
         const float bias = reg[kRd1 + o];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) a[r] = bias;
+        for (int r = 0; r < kHalf; ++r) a[r] = bias;
+        float next[16];
+        auto request = [&](int c0) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const int idx = tid + 256 * t;
+                next[t] = reg[kRD1 + (idx >> 5) * 256 + c0 + (idx & 31)];
+            }
+        };
+        request(0);
 #pragma unroll 1
         for (int c0 = 0; c0 < 256; c0 += 32) {
             __syncthreads();   // G written; DT free
-#pragma unroll 4
-            for (int idx = tid; idx < 128 * 32; idx += 256) {
-                const int oo = idx >> 5, cc = idx & 31;
-                DT[cc][oo] = reg[kRD1 + oo * 256 + c0 + cc];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                const int idx = tid + 256 * t;
+                DT[idx & 31][idx >> 5] = next[t];
             }
             __syncthreads();
+            request(min(c0 + 32, 224));
 #pragma unroll 2
             for (int cc = 0; cc < 32; cc += 4) {
                 const float w0 = DT[cc][o], w1 = DT[cc + 1][o], w2 = DT[cc + 2][o], w3 = DT[cc + 3][o];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const floatx4 g = *reinterpret_cast<const floatx4 *>(&G[rh * 16 + r][c0 + cc]);
+                for (int r = 0; r < kHalf; ++r) {
+                    const floatx4 g = *reinterpret_cast<const floatx4 *>(&G[rh * kHalf + r][c0 + cc]);
                     a[r] += w0 * g[0];
                     a[r] += w1 * g[1];
                     a[r] += w2 * g[2];
@@ -428,18 +547,17 @@ __global__ __launch_bounds__(256) void k_regress_head(const float *reg, const fl
             }
         }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) H[rh * 16 + r][o] = relu1(a[r]);
+        for (int r = 0; r < kHalf; ++r) H[rh * kHalf + r][o] = relu1(a[r]);
         __syncthreads();
-        {
+        if (tid < kHeadRows * 8) {
             const int r = tid >> 3, j = tid & 7;
-            if (b0 + r < rows) {
+            if (b0 + r < total) {
                 float y = reg[kRd2 + j];
                 const float *d2 = reg + kRD2 + j * 128;
 #pragma unroll 8
                 for (int c = 0; c < 128; ++c) y += d2[c] * H[r][c];
-                const int it = row_item[b0 + r];
-                if (it >= 0) taxels[(size_t)it * 8 + j] = y;
-                else rest[(size_t)(-1 - it) * 8 + j] = y;
+                if (out[r] >= 0) taxels[(size_t)out[r] * 8 + j] = y;
+                else rest[(size_t)(-1 - out[r]) * 8 + j] = y;
             }
         }
     }
@@ -456,17 +574,16 @@ __global__ __launch_bounds__(256) void k_regress_fill(const int32_t *n_active, c
 hipError_t launch_regress(const Plan &pl, const float *reg, int n_envs, const float *u, const int32_t *n_active,
                           float *taxels, hipStream_t st) {
     if (n_envs == 0) return hipSuccess;
-    unsigned *ctr = pl.counter;
-    RegParams p{pl.mesh, reg, u, n_active, pl.reg_pooled, pl.reg_row, ctr, n_envs, pl.K + n_envs * pl.K};
-    const int grid = min(pl.cu_count, (p.n_pos + kRegWaves - 1) / kRegWaves);
+    const RegParams p{pl.mesh, reg, u, pl.reg_live, pl.reg_cnt, pl.reg_pooled, pl.reg_ml, pl.counter, n_envs};
+    const int items = pl.K + n_envs * pl.K;
     const int slot = timer_begin(pl, ETAC_TIMER_REGRESS, st);
-    hipLaunchKernelGGL(k_regress, dim3(grid), dim3(kRegWG), 0, st, p);
+    launch_live(n_active, n_envs, pl.K, pl.reg_live, pl.reg_cnt, st);
+    hipLaunchKernelGGL(k_regress, dim3(pl.cu_count), dim3(kRegWG), 0, st, p);
     hipError_t e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_REGRESS, slot, st);
     if (e != hipSuccess) return e;
-    const int head_grid = min(pl.cu_count, (p.n_pos + kHeadRows - 1) / kHeadRows);
-    hipLaunchKernelGGL(k_regress_head, dim3(head_grid), dim3(256), 0, st, reg, pl.reg_pooled, pl.reg_row, ctr, pl.K,
-                       taxels, pl.reg_rest);
+    hipLaunchKernelGGL(k_regress_head, dim3(min(2 * pl.cu_count, (items + kHeadRows - 1) / kHeadRows)), dim3(256), 0, st, p, taxels,
+                       pl.reg_rest);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t nt = (size_t)n_envs * pl.K * 8;

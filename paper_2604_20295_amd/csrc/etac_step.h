@@ -37,6 +37,7 @@ struct StepParams {
 // Shapes of a call's launches from its sizes (host), its tables, contact pass
 // and live lists, and its max-pool.
 void shape_step(const Plan &pl, StepParams &p);
+void launch_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt, hipStream_t st);
 void launch_front(const Plan &pl, const StepParams &p, hipStream_t st);
 void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st);
 void launch_far_lists(const StepParams &p, bool passive, hipStream_t st);
