@@ -256,25 +256,6 @@ __device__ __forceinline__ bool ball_reaches(const float4 &b, int type, const fl
     return d2 * (1.0f - 1e-5f) <= reach * reach;
 }
 
-// Primitives of item (e, k)'s scene row whose bounding ball may reach patch
-// k's bounding sphere (objects of other types, triangle meshes included, are
-// ignored).
-__device__ __forceinline__ unsigned cull_objects(const SceneDev &S, const MeshDev &M, int e, int k, size_t row) {
-    unsigned cand = 0;
-    const int no = min(S.n_obj[row], S.O);
-    const float4 b = M.bound[k];
-    for (int o = 0; o < no; ++o) {
-        const size_t eo = row * S.O + o;
-        if ((unsigned)S.type[eo] > (unsigned)ETAC_CAPSULE) continue;
-        if (ball_reaches(b, S.type[eo], S.shape + 4 * eo, S.trans + 3 * eo)) cand |= 1u << o;
-    }
-    return cand;
-}
-
-__device__ __forceinline__ unsigned cull_objects(const SceneDev &S, const MeshDev &M, int e, int k) {
-    return cull_objects(S, M, e, k, scene_row(S, e, k));
-}
-
 // ---------------------------------------------------------------------------
 // wave helpers
 // ---------------------------------------------------------------------------

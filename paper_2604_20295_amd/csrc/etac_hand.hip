@@ -6,13 +6,14 @@
 // (contact-reward equation) comes from per-item counts the contact pass
 // already produces.
 //
-//   k_hand_scene  : one thread per (env, patch) item, fills the item's row of
-//                   candidates (relative poses, FP64 then rounded to FP32,
-//                   culled against the patch's bounding sphere);
+//   k_hand_scene  : half a wave per (env, patch) item, a lane per object or
+//                   link, fills the item's row of candidates (relative poses,
+//                   FP64 then rounded to FP32, culled against the patch's
+//                   bounding sphere);
 //   k_hand_reward : one thread per env, n_a, touched links and r_contact;
-//   k_pose_hand   : one thread per (env, object or link), the chain rule
-//                   from the rows' relative-pose gradients to object and
-//                   link poses, summed in item and slot order in FP64.
+//   k_pose_hand   : a wave per env, the chain rule from the rows' relative-pose
+//                   gradients to object and link poses, summed in item and
+//                   slot order in FP64.
 // The fused step, the contact pass and the adjoint kernels run unchanged on
 // the rows (SceneDev with one row per item).
 #include "etac_device.h"
@@ -70,62 +71,65 @@ struct HandSceneParams {
     int n_items;
 };
 
-// Append one candidate to the item's row when its bounding ball may reach the
-// patch (the test cull_objects repeats on the row, on the same FP32 values).
-__device__ __forceinline__ void put_candidate(const HandSceneParams &p, size_t row, const float4 &b, int &n,
-                                              int8_t id, int type, const float *shape, const float Rr[9],
-                                              const float tr[3]) {
-    if (!ball_reaches(b, type, shape, tr)) return;
-    const size_t s = row * p.hand.cap + n;
-    p.hand.type[s] = type;
-    p.hand.src[s] = id;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) p.hand.shape[4 * s + i] = shape[i];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) p.hand.rot[9 * s + i] = Rr[i];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) p.hand.trans[3 * s + i] = tr[i];
-    ++n;
-}
+// Half a wave per item: lane t < O takes object t, lane O + j link j's
+// primitive (O + L <= 32).  Candidates are those whose bounding ball may reach
+// the patch, in lane order, objects first.  A thread per item went through them
+// one after the other, each a round trip to memory (1024 hands of 16 patches:
+// 25.6 us, 9.9 us now).
+constexpr int kSceneLanes = 32;
+static_assert(ETAC_MAX_OBJ + ETAC_MAX_LINKS <= kSceneLanes, "a lane per candidate");
 
 __global__ __launch_bounds__(256) void k_hand_scene(HandSceneParams p) {
-    const int item = blockIdx.x * 256 + threadIdx.x;
-    if (item >= p.n_items) return;
+    const int t = threadIdx.x & (kSceneLanes - 1);
+    const int at = blockIdx.x * (256 / kSceneLanes) + threadIdx.x / kSceneLanes;
+    const int item = min(at, p.n_items - 1);      // whole half waves beyond the last repeat it, without stores
     const MeshDev &M = p.mesh;
     const HandDev &H = p.hand;
     const int K = M.K, L = H.L, O = p.world.O;
     const int e = item / K, k = item - e * K;
     const int l = H.patch_link[k];
-    double Rl[9], tl[3];
-    load_pose(p.links.rot + ((size_t)e * L + l) * 9, p.links.trans + ((size_t)e * L + l) * 3, Rl, tl);
-    const float4 b = M.bound[k];
-    const size_t row = (size_t)item;
-    int n = 0;
-    // the env's objects (ids 0 .. O-1), then the other links' primitives (O + j)
-    const int no = min(p.world.n_obj[e], O);
-    for (int o = 0; o < no; ++o) {
-        const size_t eo = (size_t)e * O + o;
-        const int ty = p.world.type[eo];
-        if ((unsigned)ty > (unsigned)ETAC_CAPSULE) continue;
-        double Rw[9], tw[3];
-        load_pose(p.world.rot + 9 * eo, p.world.trans + 3 * eo, Rw, tw);
-        float Rr[9], tr[3];
-        relative_pose(Rl, tl, Rw, tw, Rr, tr);
-        put_candidate(p, row, b, n, (int8_t)o, ty, p.world.shape + 4 * eo, Rr, tr);
-    }
-    const int n_ext = n;
+    const bool is_obj = t < O, is_link = !is_obj && t - O < L;
+    const int j = is_link ? t - O : 0;
+    const size_t eo = (size_t)e * O + (is_obj ? t : 0);
     const unsigned pairs = H.collide[l] & ~(1u << l);
-    for (int j = 0; j < L; ++j) {
-        if (!((pairs >> j) & 1u) || (unsigned)H.ptype[j] > (unsigned)ETAC_CAPSULE) continue;
-        double Rj[9], tj[3], Rw[9], tw[3];
-        load_pose(p.links.rot + ((size_t)e * L + j) * 9, p.links.trans + ((size_t)e * L + j) * 3, Rj, tj);
-        primitive_world(Rj, tj, H.prot + 9 * j, H.ptrans + 3 * j, Rw, tw);
-        float Rr[9], tr[3];
-        relative_pose(Rl, tl, Rw, tw, Rr, tr);
-        put_candidate(p, row, b, n, (int8_t)(O + j), H.ptype[j], H.pshape + 4 * j, Rr, tr);
+    const int ty = is_obj ? p.world.type[eo] : H.ptype[j];
+    bool in = is_obj ? t < min(p.world.n_obj[e], O) : is_link && ((pairs >> j) & 1u);
+    in = in && (unsigned)ty <= (unsigned)ETAC_CAPSULE;
+    const float4 b = M.bound[k];
+    const float *sh = is_obj ? p.world.shape + 4 * eo : H.pshape + 4 * j;
+    double Rl[9], tl[3], Rj[9], tj[3], Rw[9], tw[3];
+    load_pose(p.links.rot + ((size_t)e * L + l) * 9, p.links.trans + ((size_t)e * L + l) * 3, Rl, tl);
+    load_pose(is_obj ? p.world.rot + 9 * eo : p.links.rot + ((size_t)e * L + j) * 9,
+              is_obj ? p.world.trans + 3 * eo : p.links.trans + ((size_t)e * L + j) * 3, Rj, tj);
+    primitive_world(Rj, tj, H.prot + 9 * j, H.ptrans + 3 * j, Rw, tw);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) Rw[i] = is_obj ? Rj[i] : Rw[i];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) tw[i] = is_obj ? tj[i] : tw[i];
+    float Rr[9], tr[3], shape[4];
+    relative_pose(Rl, tl, Rw, tw, Rr, tr);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) shape[i] = sh[i];
+    const bool take = in && ball_reaches(b, in ? ty : ETAC_SPHERE, shape, tr);
+    const unsigned long long both = __ballot(take);
+    const unsigned mine = (unsigned)(both >> (lane_id() & kSceneLanes));
+    if (at >= p.n_items) return;
+    const size_t row = (size_t)item;
+    if (take) {
+        const size_t s = row * p.hand.cap + __popc(mine & ((1u << t) - 1u));
+        p.hand.type[s] = ty;
+        p.hand.src[s] = (int8_t)t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p.hand.shape[4 * s + i] = shape[i];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) p.hand.rot[9 * s + i] = Rr[i];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) p.hand.trans[3 * s + i] = tr[i];
     }
-    H.n_obj[row] = n;
-    H.n_ext[row] = n_ext;
+    if (t == 0) {
+        H.n_obj[row] = __popc(mine);
+        H.n_ext[row] = __popc(mine & ((1u << O) - 1u));
+    }
 }
 
 hipError_t launch_hand_scene(const Plan &pl, const SceneDev &world, const LinksDev &links, SceneDev *rows,
@@ -137,7 +141,7 @@ hipError_t launch_hand_scene(const Plan &pl, const SceneDev &world, const LinksD
     rows->src = H.src;
     rows->n_ext = H.n_ext;
     if (p.n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hand_scene, dim3((p.n_items + 255) / 256), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(k_hand_scene, dim3((p.n_items + 256 / kSceneLanes - 1) / (256 / kSceneLanes)), dim3(256), 0, st, p);
     return hipGetLastError();
 }
 
@@ -178,8 +182,11 @@ hipError_t launch_hand_reward(const Plan &pl, int n_envs, const int32_t *n_touch
 //            (link j's primitive: dL/dRj += dL/dRw C_R^T + dL/dtw C_t^T,
 //             dL/dtj += dL/dtw);
 //   frame  : dL/dRl += Rw G'^T + (tw - tl) g'^T,  dL/dtl -= Rl g'.
-// One thread per (env, target), target an object (t < O) or link t - O;
-// contributions are added in item and slot order in FP64.
+// A wave per env.  Its slots in contact are listed 64 at a time; a lane forms
+// the two contributions of its slot, then a lane per component of a target (an
+// object, t < O, or link t - O) adds those of its target in item and slot
+// order, in FP64.  A thread per target that walked the slots itself waited for
+// each (1024 hands: 121 us, 13.5 us now).
 struct PoseHandParams {
     SceneDev world;
     LinksDev links;
@@ -192,99 +199,128 @@ struct PoseHandParams {
     float *grad_rot, *grad_trans, *grad_link_rot, *grad_link_trans;
 };
 
-__global__ __launch_bounds__(256) void k_pose_hand(PoseHandParams p) {
+struct PoseHandLds {
+    double src[64][13], frame[64][13];      // contributions of a slot to its source and its frame
+    double sum[ETAC_MAX_OBJ + ETAC_MAX_LINKS][12];
+    unsigned long long slots[ETAC_MAX_OBJ + ETAC_MAX_LINKS][2];      // a target's slots, as frame and as source
+    uint16_t list[64 * kMaxRowObj];         // slots of 64 patches
+};
+
+__global__ __launch_bounds__(64) void k_pose_hand(PoseHandParams p) {
+    __shared__ PoseHandLds S;
     const HandDev &H = p.hand;
-    const int O = p.world.O, L = H.L, T = O + L;
-    const int idx = blockIdx.x * 256 + threadIdx.x;
-    if (idx >= p.E * T) return;
-    const int e = idx / T, target = idx - e * T;
-    const bool is_link = target >= O;
-    const int tl_link = target - O;
-    double G[9], g[3];
+    const int O = p.world.O, L = H.L, T = O + L, e = blockIdx.x, lane = threadIdx.x;
+    for (int i = lane; i < T * 12; i += 64) S.sum[i / 12][i % 12] = 0.0;
+    for (int k0 = 0; k0 < p.K; k0 += 64) {
+        // slots of the patches in contact, in order
+        const int kl = min(k0 + lane, p.K - 1);
+        const size_t rl = (size_t)e * p.K + kl;
+        const int mine = k0 + lane < p.K && p.n_act[rl] > 0 ? min(H.n_obj[rl], H.cap) : 0;
+        int inc = mine;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) G[i] = 0.0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) g[i] = 0.0;
-    for (int k = 0; k < p.K; ++k) {
-        const size_t row = (size_t)e * p.K + k;
-        const int l = H.patch_link[k];
-        const bool frame = is_link && l == tl_link;
-        if (p.n_act[row] == 0) continue;
-        const int n = min(H.n_obj[row], H.cap);
-        double Rl[9], tl[3];
-        bool have_l = false;
-        for (int s = 0; s < n; ++s) {
-            const int src = H.src[row * H.cap + s];
-            if (!frame && src != target) continue;
-            if (!have_l) {
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_up(inc, off);
+            if (lane >= off) inc += v;
+        }
+        const int total = uniform(__shfl(inc, 63));
+        wave_sync();
+        for (int s = 0; s < mine; ++s) S.list[inc - mine + s] = (uint16_t)(lane * kMaxRowObj + s);
+        wave_sync();
+        for (int c0 = 0; c0 < total; c0 += 64) {
+            const int cnt = min(64, total - c0);
+            int to = -1, frame = -1;      // the targets of this lane's contributions
+            if (lane < cnt) {
+                const int slot = S.list[c0 + lane], k = k0 + slot / kMaxRowObj, s = slot % kMaxRowObj;
+                const size_t row = (size_t)e * p.K + k;
+                const int l = H.patch_link[k], src = H.src[row * H.cap + s];
+                double Rl[9], tl[3], Gp[9], tp[3];
                 load_pose(p.links.rot + ((size_t)e * L + l) * 9, p.links.trans + ((size_t)e * L + l) * 3, Rl, tl);
-                have_l = true;
-            }
-            double Gp[9], tp[3];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) Gp[i] = 0.0;
+                for (int i = 0; i < 9; ++i) Gp[i] = 0.0;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) tp[i] = 0.0;
-            for (int h = p.chunk_off[k]; h < p.chunk_off[k + 1]; ++h) {
-                const float *gp = p.part + (((size_t)e * p.NC + h) * H.cap + s) * 12;
+                for (int i = 0; i < 3; ++i) tp[i] = 0.0;
+                for (int h = p.chunk_off[k]; h < p.chunk_off[k + 1]; ++h) {
+                    const float *gp = p.part + (((size_t)e * p.NC + h) * H.cap + s) * 12;
 #pragma unroll
-                for (int i = 0; i < 9; ++i) Gp[i] += gp[i];
+                    for (int i = 0; i < 9; ++i) Gp[i] += gp[i];
 #pragma unroll
-                for (int i = 0; i < 3; ++i) tp[i] += gp[9 + i];
-            }
-            double GRw[9], gtw[3];
+                    for (int i = 0; i < 3; ++i) tp[i] += gp[9 + i];
+                }
+                double GRw[9], gtw[3];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
+                for (int a = 0; a < 3; ++a) {
 #pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    GRw[a * 3 + c] = Rl[a * 3 + 0] * Gp[0 * 3 + c] + Rl[a * 3 + 1] * Gp[1 * 3 + c] +
-                                     Rl[a * 3 + 2] * Gp[2 * 3 + c];
-                gtw[a] = Rl[a * 3 + 0] * tp[0] + Rl[a * 3 + 1] * tp[1] + Rl[a * 3 + 2] * tp[2];
-            }
-            double Rw[9], tw[3];
-            if (src < O) {
-                load_pose(p.world.rot + ((size_t)e * O + src) * 9, p.world.trans + ((size_t)e * O + src) * 3, Rw, tw);
-            } else {
-                const int j = src - O;
-                double Rj[9], tj[3];
-                load_pose(p.links.rot + ((size_t)e * L + j) * 9, p.links.trans + ((size_t)e * L + j) * 3, Rj, tj);
-                primitive_world(Rj, tj, H.prot + 9 * j, H.ptrans + 3 * j, Rw, tw);
-            }
-            if (frame) {
+                    for (int c = 0; c < 3; ++c)
+                        GRw[a * 3 + c] = Rl[a * 3 + 0] * Gp[0 * 3 + c] + Rl[a * 3 + 1] * Gp[1 * 3 + c] +
+                                         Rl[a * 3 + 2] * Gp[2 * 3 + c];
+                    gtw[a] = Rl[a * 3 + 0] * tp[0] + Rl[a * 3 + 1] * tp[1] + Rl[a * 3 + 2] * tp[2];
+                }
+                double Rw[9], tw[3];
+                if (src < O) {
+                    load_pose(p.world.rot + ((size_t)e * O + src) * 9, p.world.trans + ((size_t)e * O + src) * 3, Rw, tw);
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) S.src[lane][i] = GRw[i];
+                } else {
+                    const int j = src - O;
+                    const float *CR = H.prot + 9 * j, *Ct = H.ptrans + 3 * j;
+                    double Rj[9], tj[3];
+                    load_pose(p.links.rot + ((size_t)e * L + j) * 9, p.links.trans + ((size_t)e * L + j) * 3, Rj, tj);
+                    primitive_world(Rj, tj, CR, Ct, Rw, tw);
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+#pragma unroll
+                        for (int b = 0; b < 3; ++b)
+                            S.src[lane][a * 3 + b] = GRw[a * 3 + 0] * (double)CR[b * 3 + 0] + GRw[a * 3 + 1] * (double)CR[b * 3 + 1] +
+                                                     GRw[a * 3 + 2] * (double)CR[b * 3 + 2] + gtw[a] * (double)Ct[b];
+                }
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
 #pragma unroll
                     for (int b = 0; b < 3; ++b)
-                        G[a * 3 + b] += (Rw[a * 3 + 0] * Gp[b * 3 + 0] + Rw[a * 3 + 1] * Gp[b * 3 + 1] +
-                                         Rw[a * 3 + 2] * Gp[b * 3 + 2]) +
-                                        (tw[a] - tl[a]) * tp[b];
-                    g[a] -= gtw[a];
+                        S.frame[lane][a * 3 + b] = (Rw[a * 3 + 0] * Gp[b * 3 + 0] + Rw[a * 3 + 1] * Gp[b * 3 + 1] +
+                                                    Rw[a * 3 + 2] * Gp[b * 3 + 2]) + (tw[a] - tl[a]) * tp[b];
+                    S.frame[lane][9 + a] = -gtw[a];
+                    S.src[lane][9 + a] = gtw[a];
                 }
-            } else if (src < O) {
-#pragma unroll
-                for (int i = 0; i < 9; ++i) G[i] += GRw[i];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) g[i] += gtw[i];
-            } else {
-                const float *CR = H.prot + 9 * (src - O), *Ct = H.ptrans + 3 * (src - O);
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-#pragma unroll
-                    for (int b = 0; b < 3; ++b)
-                        G[a * 3 + b] += GRw[a * 3 + 0] * (double)CR[b * 3 + 0] + GRw[a * 3 + 1] * (double)CR[b * 3 + 1] +
-                                        GRw[a * 3 + 2] * (double)CR[b * 3 + 2] + gtw[a] * (double)Ct[b];
-                    g[a] += gtw[a];
-                }
+                to = src;
+                frame = O + l;
             }
+            unsigned long long as_frame = 0, as_src = 0;      // lane t: target t's slots
+            for (int t = 0; t < T; ++t) {
+                const unsigned long long f = __ballot(frame == t), o = __ballot(to == t && frame != t);
+                as_frame = lane == t ? f : as_frame;
+                as_src = lane == t ? o : as_src;
+            }
+            if (lane < T) {
+                S.slots[lane][0] = as_frame;
+                S.slots[lane][1] = as_src;
+            }
+            wave_sync();
+            for (int i = lane; i < T * 12; i += 64) {
+                const int t = i / 12, c = i - 12 * t;
+                double v = S.sum[t][c];
+                const unsigned long long f = S.slots[t][0];
+                for (unsigned long long m = f | S.slots[t][1]; m; m &= m - 1) {
+                    const int q = __ffsll(m) - 1;
+                    v += (f >> q) & 1ull ? S.frame[q][c] : S.src[q][c];
+                }
+                S.sum[t][c] = v;
+            }
+            wave_sync();
         }
     }
-    float *gr = is_link ? p.grad_link_rot + ((size_t)e * L + tl_link) * 9 : p.grad_rot + ((size_t)e * O + target) * 9;
-    float *gt = is_link ? p.grad_link_trans + ((size_t)e * L + tl_link) * 3
-                        : p.grad_trans + ((size_t)e * O + target) * 3;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) gr[i] = (float)G[i];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) gt[i] = (float)g[i];
+    wave_sync();
+    for (int i = lane; i < T * 12; i += 64) {
+        const int t = i / 12, c = i - 12 * t;
+        const float v = (float)S.sum[t][c];
+        if (t < O) {
+            if (c < 9) p.grad_rot[((size_t)e * O + t) * 9 + c] = v;
+            else p.grad_trans[((size_t)e * O + t) * 3 + c - 9] = v;
+        } else {
+            if (c < 9) p.grad_link_rot[((size_t)e * L + t - O) * 9 + c] = v;
+            else p.grad_link_trans[((size_t)e * L + t - O) * 3 + c - 9] = v;
+        }
+    }
 }
 
 hipError_t launch_pose_hand(const Plan &pl, const SceneDev &world, const LinksDev &links, float *grad_rot,
@@ -292,8 +328,7 @@ hipError_t launch_pose_hand(const Plan &pl, const SceneDev &world, const LinksDe
     if (world.E == 0) return hipSuccess;
     PoseHandParams p{world, links, *pl.hand, pl.hand->pose_part, pl.itm.n_act, pl.tile.chunk_off, pl.tile.NC,
                      world.E, pl.K, grad_rot, grad_trans, grad_link_rot, grad_link_trans};
-    const int nt = world.E * (world.O + pl.hand->L);
-    hipLaunchKernelGGL(k_pose_hand, dim3((nt + 255) / 256), dim3(256), 0, st, p);
+    hipLaunchKernelGGL(k_pose_hand, dim3(world.E), dim3(64), 0, st, p);
     return hipGetLastError();
 }
 

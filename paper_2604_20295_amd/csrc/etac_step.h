@@ -53,13 +53,18 @@ __device__ __forceinline__ int live_env(const StepParams &p, int k, int q) {
 
 constexpr int kScan = kWG;      // words listed at a time
 
+constexpr int kRowCache = 64;
+static_assert(ETAC_MAX_OBJ <= kRowCache, "the env's objects fit");
+
 struct ContactLds {
     int cnt[kMaxPatches];
     int tcnt[kMaxPatches];
     unsigned cand[kMaxPatches];
     int wsum[kWaves];
     int list[kScan];
-    ObjRow obj[ETAC_MAX_OBJ];
+    ObjRow obj[kRowCache];      // the env's objects, or its patches' rows of candidates
+    int16_t at[kMaxPatches];    // a patch's row in obj, -1: read from memory
+    int rows;
 };
 
 // Stores of four consecutive values at any 4-byte (winners: 1-byte) address.
@@ -96,11 +101,20 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         __syncthreads();
         if ((int)threadIdx.x < no) L.obj[threadIdx.x].reach2 = ball_reach2(L.obj[threadIdx.x].type, L.obj[threadIdx.x].shape);
     }
+    if (ROWS) {
+        if (threadIdx.x < 64) L.rows = 0;      // identical stores
+        __syncthreads();
+    }
     for (int k = threadIdx.x; k < K; k += kWG) {
         L.cnt[k] = 0;
         L.tcnt[k] = 0;
         unsigned c = FROM_INPUT ? ~0u : 0u;
-        if (!FROM_INPUT && ROWS) c = cull_objects(S, M, e, k);
+        if (!FROM_INPUT && ROWS) {      // a row holds candidates alone
+            const int n = min(S.n_obj[scene_row(S, e, k)], S.O);
+            c = n >= 32 ? ~0u : (1u << n) - 1u;
+            const int at = n ? atomicAdd(&L.rows, n) : 0;
+            L.at[k] = (int16_t)(at + n <= kRowCache ? at : -1);
+        }
         if (!FROM_INPUT && !ROWS) {
             const float4 b = M.bound[k];
             for (int o = 0; o < no; ++o) {
@@ -111,6 +125,25 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         L.cand[k] = c;
     }
     __syncthreads();
+    if (!FROM_INPUT && ROWS) {      // four patches' rows at a time, a wave each
+        for (int k = wave; k < K; k += kWaves) {
+            const unsigned c = uniform(L.cand[k]);
+            const int n = __popc(c), at = uniform((int)L.at[k]);
+            if (n == 0 || at < 0) continue;
+            const size_t r0 = scene_row(S, e, k) * S.O;
+            for (int t = lane; t < 17 * n; t += 64) {
+                const int o = t / 17, f = t - 17 * o;
+                ObjRow &r = L.obj[at + o];
+                if (f == 0) r.type = S.type[r0 + o];
+                else if (f < 5) r.shape[f - 1] = S.shape[4 * (r0 + o) + f - 1];
+                else if (f < 14) r.rot[f - 5] = S.rot[9 * (r0 + o) + f - 5];
+                else r.trans[f - 14] = S.trans[3 * (r0 + o) + f - 14];
+            }
+            wave_sync();
+            if (lane < n) L.obj[at + lane].reach2 = ball_reach2(L.obj[at + lane].type, L.obj[at + lane].shape);
+        }
+        __syncthreads();
+    }
     if (!FROM_INPUT && !p.scratch) {
         const floatx4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int i = 4 * (s * kWG + threadIdx.x); i < N; i += 4 * kWG * p.splits) {
@@ -197,7 +230,9 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
                 const unsigned c = uniform(L.cand[k]);
                 if (ROWS) {
                     const size_t srow = scene_row(S, e, k);
-                    best = contact_node(S, srow, c, px, py, pz, nx, ny, nz, u0, u1, u2);
+                    const int at = uniform((int)L.at[k]);
+                    best = at >= 0 ? contact_node(L.obj + at, c, px, py, pz, nx, ny, nz, u0, u1, u2)
+                                   : contact_node(S, srow, c, px, py, pz, nx, ny, nz, u0, u1, u2);
                     if (best >= 0) touch = S.n_ext && best < S.n_ext[srow];
                     id = best >= 0 && S.src ? S.src[srow * S.O + best] : (int8_t)best;
                 } else {
