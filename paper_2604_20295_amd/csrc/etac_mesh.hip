@@ -7,7 +7,7 @@
 //          clusters of 32 triangles by recursive splits of the triangle
 //          centroids, builds a conservative occupancy grid per mesh, and
 //          uploads it all.
-//   k_mesh_items : 512 nodes of an env per workgroup.  Primitives are tested
+//   k_mesh_items : 64 nodes of an env per workgroup.  Primitives are tested
 //          one node per lane.  For a mesh object the nodes inside its bounding
 //          ball and not in a cell of the grid that is certainly outside are
 //          queried one at a time by a whole wave: lanes take the clusters'
@@ -508,16 +508,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     }
 }
 
-// The contact pass.  A workgroup takes kMeshNodes nodes of an env, a thread two
-// of them.  For every mesh object in turn the nodes that may be inside it are
+// The contact pass.  A workgroup takes 64 nodes of an env, a lane of its first
+// wave each.  For every mesh object in turn the nodes that may be inside it are
 // listed in LDS, the workgroup's waves take the queries of the list in turn,
-// and each node's thread compares the result with its best.  A query is a
-// chain of dependent FP64 passes, so what counts is that every wave on the
-// chip has one: nodes in contact lie close together, and a wave that kept its
-// own nodes' queries had up to 64 of them while its neighbours had none
-// (256 hands with mesh objects: 1318 us with a workgroup per env and own
-// queries, 639 us like this).
-constexpr int kMeshNodes = 2 * kWG;
+// and each node's lane compares the result with its best.  A query is a chain
+// of dependent FP64 passes, and nodes in contact lie close together, so what
+// counts is how evenly the queries lie on the chip: 256 hands with mesh objects
+// take 1318 us with a workgroup per env, whose waves query their own nodes; with
+// the list, 640 us at 512 nodes a workgroup (half of the compute units idle at
+// the end) and 346 us at 64.  Bound by FP64 (three quarters of the cycles).
+constexpr int kMeshNodes = 64;
 
 struct MeshQuery {
     double depth, u0, u1, u2;
@@ -527,8 +527,7 @@ struct MeshQuery {
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_mesh_items(MeshContactParams p,
                                                                                                int chunks) {
     __shared__ MeshQuery res[kMeshNodes];
-    __shared__ uint16_t list[kMeshNodes];
-    __shared__ int wsum[2][kWaves];
+    __shared__ int list[kMeshNodes], total_s;
     __shared__ unsigned any;
     const int e = blockIdx.x / chunks, i0 = (blockIdx.x - e * chunks) * kMeshNodes;
     const MeshDev &M = p.mesh;
@@ -536,23 +535,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const size_t EN = (size_t)S.E * N, row = (size_t)e * N;
     const int no = uniform(min(S.n_obj[e], S.O));
-    int node[2], best[2], btri[2], kk[2];
-    unsigned cand[2];
-    float px[2], py[2], pz[2];
-    double bd[2], b0[2], b1[2], b2[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        node[h] = i0 + h * kWG + threadIdx.x;
-        const bool valid = node[h] < N;
-        const int i = valid ? node[h] : N - 1;
-        kk[h] = M.node_patch[i];
-        px[h] = M.pos[i];
-        py[h] = M.pos[N + i];
-        pz[h] = M.pos[2 * N + i];
-        cand[h] = valid ? ~0u : 0u;
-        best[h] = btri[h] = -1;
-        bd[h] = b0[h] = b1[h] = b2[h] = 0.0;
-    }
+    const int i = min(i0 + lane, N - 1);      // wave 0's lanes hold the nodes
+    const bool valid = wave == 0 && i0 + lane < N;
+    const int kn = M.node_patch[i];
+    const float px = M.pos[i], py = M.pos[N + i], pz = M.pos[2 * N + i];
+    int best = -1, btri = -1;
+    double bd = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
     // objects whose ball may reach the patches of this chunk's nodes
     if (threadIdx.x < 64) any = 0u;      // identical stores
     __syncthreads();
@@ -574,19 +562,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const float *sh = S.shape + 4 * eo;
         const float *R = S.rot + 9 * eo;
         const float *t = S.trans + 3 * eo;
+        const float dx = px - t[0], dy = py - t[1], dz = pz - t[2];
         if (ty >= ETAC_SPHERE && ty <= ETAC_CAPSULE) {
             const float rb = bounding_radius(ty, sh) * 1.001f + 1e-3f;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const float dx = px[h] - t[0], dy = py[h] - t[1], dz = pz[h] - t[2];
-                if (!cand[h] || dx * dx + dy * dy + dz * dz > rb * rb) continue;
-                const int i = node[h];
-                const Pen q = penetrate(ty, sh, R, t, px[h], py[h], pz[h], M.nrm[i], M.nrm[N + i], M.nrm[2 * N + i]);
-                if (q.inside && (best[h] < 0 || q.depth > bd[h])) {
-                    best[h] = o;
-                    btri[h] = -1;
-                    bd[h] = q.depth;
-                    b0[h] = q.u0; b1[h] = q.u1; b2[h] = q.u2;
+            if (valid && dx * dx + dy * dy + dz * dz <= rb * rb) {
+                const Pen q = penetrate(ty, sh, R, t, px, py, pz, M.nrm[i], M.nrm[N + i], M.nrm[2 * N + i]);
+                if (q.inside && (best < 0 || q.depth > bd)) {
+                    best = o;
+                    btri = -1;
+                    bd = q.depth;
+                    b0 = q.u0; b1 = q.u1; b2 = q.u2;
                 }
             }
             continue;
@@ -594,55 +579,35 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const int m = uniform(ty == ETAC_MESH ? mesh_of(sh, p.ms.M) : -1);
         if (m < 0) continue;
         const float rb = p.ms.radius[m] * 1.001f + 1e-3f;
-        const float4 g = p.ms.grid_lo[m];
-        const int4 gd = p.ms.grid_dim[m];
-        bool near[2];
-        unsigned long long bal[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const float dx = px[h] - t[0], dy = py[h] - t[1], dz = pz[h] - t[2];
-            near[h] = cand[h] && dx * dx + dy * dy + dz * dz <= rb * rb;
-            if (near[h]) {   // the occupancy grid rules out nodes certainly outside
-                const float qx = (R[0] * dx + R[3] * dy) + R[6] * dz;
-                const float qy = (R[1] * dx + R[4] * dy) + R[7] * dz;
-                const float qz = (R[2] * dx + R[5] * dy) + R[8] * dz;
-                const float gx = (qx - g.x) * g.w, gy = (qy - g.y) * g.w, gz = (qz - g.z) * g.w;
-                near[h] = gx >= 0.0f && gy >= 0.0f && gz >= 0.0f && gx < (float)gd.x && gy < (float)gd.y &&
-                          gz < (float)gd.z;
-                if (near[h]) {
-                    const int ix = min((int)gx, gd.x - 1), iy = min((int)gy, gd.y - 1);
-                    const int iz = min((int)gz, gd.z - 1);
-                    const unsigned bit = (unsigned)gd.w + (unsigned)((iz * gd.y + iy) * gd.x + ix);
-                    near[h] = (p.ms.grid_bits[bit >> 5] >> (bit & 31u)) & 1u;
-                }
+        bool near = valid && dx * dx + dy * dy + dz * dz <= rb * rb;
+        if (near) {   // the occupancy grid rules out nodes certainly outside
+            const float4 g = p.ms.grid_lo[m];
+            const int4 gd = p.ms.grid_dim[m];
+            const float qx = (R[0] * dx + R[3] * dy) + R[6] * dz;
+            const float qy = (R[1] * dx + R[4] * dy) + R[7] * dz;
+            const float qz = (R[2] * dx + R[5] * dy) + R[8] * dz;
+            const float gx = (qx - g.x) * g.w, gy = (qy - g.y) * g.w, gz = (qz - g.z) * g.w;
+            near = gx >= 0.0f && gy >= 0.0f && gz >= 0.0f && gx < (float)gd.x && gy < (float)gd.y && gz < (float)gd.z;
+            if (near) {
+                const int ix = min((int)gx, gd.x - 1), iy = min((int)gy, gd.y - 1), iz = min((int)gz, gd.z - 1);
+                const unsigned bit = (unsigned)gd.w + (unsigned)((iz * gd.y + iy) * gd.x + ix);
+                near = (p.ms.grid_bits[bit >> 5] >> (bit & 31u)) & 1u;
             }
-            bal[h] = __ballot(near[h]);
-            wsum[h][wave] = __popcll(bal[h]);      // identical in every lane
         }
+        const unsigned long long bal = __ballot(near);
+        const int at = (int)lanes_below(bal);
+        if (near) list[at] = i;
+        if (wave == 0) total_s = __popcll(bal);      // identical in every lane
         __syncthreads();
-        int off[2] = {0, 0}, total = 0, at[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                if (w == wave) off[h] = total;
-                total += wsum[h][w];
-            }
-        total = uniform(total);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            at[h] = off[h] + (int)lanes_below(bal[h]);
-            if (near[h]) list[at[h]] = (uint16_t)(h * kWG + threadIdx.x);
-        }
-        __syncthreads();
+        const int total = uniform(total_s);
         for (int q = wave; q < total; q += kWaves) {
-            const int i = i0 + uniform((int)list[q]);
+            const int n = uniform(list[q]);
             double q0, q1, q2;
             {
 #pragma clang fp contract(off)
-                const double d0 = (double)M.pos[i] - (double)t[0];
-                const double d1 = (double)M.pos[N + i] - (double)t[1];
-                const double d2 = (double)M.pos[2 * N + i] - (double)t[2];
+                const double d0 = (double)M.pos[n] - (double)t[0];
+                const double d1 = (double)M.pos[N + n] - (double)t[1];
+                const double d2 = (double)M.pos[2 * N + n] - (double)t[2];
                 q0 = ((double)R[0] * d0 + (double)R[3] * d1) + (double)R[6] * d2;
                 q1 = ((double)R[1] * d0 + (double)R[4] * d1) + (double)R[7] * d2;
                 q2 = ((double)R[2] * d0 + (double)R[5] * d1) + (double)R[8] * d2;
@@ -653,39 +618,34 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
             res[q] = MeshQuery{h.depth, h.u0, h.u1, h.u2, h.inside ? 1 : 0, tri};
         }
         __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-            if (near[h]) {
-                const MeshQuery &r = res[at[h]];
-                if (r.inside && (best[h] < 0 || r.depth > bd[h])) {
-                    best[h] = o;
-                    btri[h] = r.tri;
-                    bd[h] = r.depth;
-                    b0[h] = r.u0; b1[h] = r.u1; b2[h] = r.u2;
-                }
+        if (near) {
+            const MeshQuery &r = res[at];
+            if (r.inside && (best < 0 || r.depth > bd)) {
+                best = o;
+                btri = r.tri;
+                bd = r.depth;
+                b0 = r.u0; b1 = r.u1; b2 = r.u2;
             }
+        }
         __syncthreads();      // list and results are rewritten
     }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int i = node[h];
-        if (i < N) {
-            p.cobj[row + i] = (int8_t)best[h];
-            if (p.hit) p.hit[row + i] = best[h] >= 0 ? btri[h] : -1;
-            if (p.uhat) {
-                p.uhat[row + i] = (float)b0[h];
-                p.uhat[EN + row + i] = (float)b1[h];
-                p.uhat[2 * EN + row + i] = (float)b2[h];
-            }
+    if (wave != 0) return;
+    if (valid) {
+        p.cobj[row + i] = (int8_t)best;
+        if (p.hit) p.hit[row + i] = best >= 0 ? btri : -1;
+        if (p.uhat) {
+            p.uhat[row + i] = (float)b0;
+            p.uhat[EN + row + i] = (float)b1;
+            p.uhat[2 * EN + row + i] = (float)b2;
         }
-        // active nodes per patch: a wave's nodes lie on few patches (counts were zeroed)
-        unsigned long long act = __ballot(i < N && best[h] >= 0);
-        while (act) {
-            const int k = __builtin_amdgcn_readlane(kk[h], __ffsll(act) - 1);
-            const unsigned long long same = __ballot(i < N && best[h] >= 0 && kk[h] == k);
-            if (lane == 0) atomicAdd(&p.n_active[(size_t)e * K + k], __popcll(same));
-            act &= ~same;
-        }
+    }
+    // active nodes per patch: few patches in a wave (counts were zeroed)
+    unsigned long long act = __ballot(valid && best >= 0);
+    while (act) {
+        const int k = __builtin_amdgcn_readlane(kn, __ffsll(act) - 1);
+        const unsigned long long same = __ballot(valid && best >= 0 && kn == k);
+        if (lane == 0) atomicAdd(&p.n_active[(size_t)e * K + k], __popcll(same));
+        act &= ~same;
     }
 }
 
