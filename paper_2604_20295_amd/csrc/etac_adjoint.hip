@@ -347,11 +347,14 @@ __global__ __launch_bounds__(kWG) void k_adj_narrow(AdjParams p) {
 
 // Far patches: a workgroup takes 256 active nodes of an item in the spatial
 // order, a wave 64 of them, a lane one; the passive nodes' runs of 32 as in
-// the forward.
+// the forward.  An item has work in the tiles of its active nodes alone (6 of 64
+// on 16384-node patches): taken item by item, a workgroup's stride over the units
+// met the same tile every time, and one workgroup in ten had all of the work
+// (384 scenes of four such patches: 15000 us, tile by tile 1740 us).
 struct AdjFarLds {
     int first[kMaxPatches + 1];
-    float4 a[kWaves][32];
-    float2 b[kWaves][32];
+    float4 a[kWaves][64];
+    float2 b[kWaves][64];
 };
 
 __global__ __launch_bounds__(kWG) void k_adj_far(AdjParams p) {
@@ -370,12 +373,14 @@ __global__ __launch_bounds__(kWG) void k_adj_far(AdjParams p) {
     });
     for (int q = blockIdx.x; q < total; q += gridDim.x) {
         const int kk = unit_rank(L.first, K, q), k = uniform(M.order[kk]);
-        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, tiles = (n + kWG - 1) / kWG;
-        const int local = q - uniform(L.first[kk]), e = uniform(live_env(S, k, local / tiles));
+        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;
+        // tile by tile, so that the tiles beyond an item's active nodes fall on every workgroup
+        const int cnt = uniform(live_count(S, k)), local = q - uniform(L.first[kk]), tile = local / cnt;
+        const int e = uniform(live_env(S, k, local - tile * cnt));
         const size_t item = (size_t)e * K + k, row = (size_t)e * N + base;
         const int m = uniform(na[item]);
         if (m == 0) continue;
-        const int chunk = (local % tiles) * kWaves + wave, s = chunk * 64 + lane;
+        const int chunk = tile * kWaves + wave, s = chunk * 64 + lane;
         if (chunk * 64 >= n) continue;
         double *ap = p.b.alpha_part + (size_t)e * T.NP + T.part_off[k] + chunk;
         if (chunk * 64 >= m) {
@@ -391,49 +396,33 @@ __global__ __launch_bounds__(kWG) void k_adj_far(AdjParams p) {
             const float alpha = S.model.alpha[k], cut2 = cutoff_d2(alpha);
             float hi, lo;
             decay_rate(alpha, hi, lo);
-            float lx = px, ly = py, lz = pz, hx = px, hy = py, hz = pz;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                lx = fminf(lx, __shfl_xor(lx, off)); ly = fminf(ly, __shfl_xor(ly, off)); lz = fminf(lz, __shfl_xor(lz, off));
-                hx = fmaxf(hx, __shfl_xor(hx, off)); hy = fmaxf(hy, __shfl_xor(hy, off)); hz = fmaxf(hz, __shfl_xor(hz, off));
-            }
-            const float4 *box = S.itm.pbox + 2 * ((size_t)e * S.itm.NB + S.itm.box_off[k]);
+            const int np = n - m;
+            NearRuns runs(S.itm.pbox + 2 * ((size_t)e * S.itm.NB + S.itm.box_off[k]), (np + 31) >> 5, true, px, py, pz, cut2);
             const int *list = S.itm.plist + row;
-            const int np = n - m, nb = (np + 31) >> 5;
-            for (int b0 = 0; b0 < nb; b0 += 64) {
-                bool near = false;
-                if (b0 + lane < nb) {
-                    const float4 bl = box[2 * (b0 + lane)], bh = box[2 * (b0 + lane) + 1];
-                    const float dx = fmaxf(fmaxf(bl.x - hx, lx - bh.x), 0.0f);
-                    const float dy = fmaxf(fmaxf(bl.y - hy, ly - bh.y), 0.0f);
-                    const float dz = fmaxf(fmaxf(bl.z - hz, lz - bh.z), 0.0f);
-                    near = !(dx * dx + dy * dy + dz * dz >= cut2);
-                }
-                unsigned long long todo = __ballot(near);
-                while (todo) {
-                    const int b = b0 + __ffsll(todo) - 1;
-                    todo &= todo - 1;
-                    const int c = uniform(min(32, np - 32 * b));
-                    wave_sync();
-                    if (lane < c) {
-                        const int i = list[32 * b + lane], gi = base + i;
-                        L.a[wave][lane] = make_float4(M.pos[gi], M.pos[N + gi], M.pos[2 * N + gi], p.grad_u[row + i]);
-                        L.b[wave][lane] = make_float2(p.grad_u[EN + row + i], p.grad_u[2 * EN + row + i]);
-                    }
-                    wave_sync();
-                    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, t = 0.0f;
+            RunPair next;
+            next.fetch(runs, M, list, np, base, p.grad_u + row, EN);
+            while (next.r[0] >= 0) {
+                const int c[2] = {next.c[0], next.c[1]};
+                wave_sync();
+                L.a[wave][lane] = make_float4(next.x[0], next.x[1], next.x[2], next.x[3]);
+                L.b[wave][lane] = make_float2(next.x[4], next.x[5]);
+                wave_sync();
+                next.fetch(runs, M, list, np, base, p.grad_u + row, EN);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, t0 = 0.0f, t1 = 0.0f, t2 = 0.0f;
 #pragma unroll 4
-                    for (int i = 0; i < c; ++i) {
+                    for (int i = 32 * h; i < 32 * h + c[h]; ++i) {
                         const float4 pa = L.a[wave][i];
                         const float2 pb = L.b[wave][i];
                         const float dx = pa.x - px, dy = pa.y - py, dz = pa.z - pz;
                         const float d = __builtin_amdgcn_sqrtf(dx * dx + dy * dy + dz * dz);
-                        const float w = __builtin_amdgcn_exp2f(hi * d);
+                        const float w = __builtin_amdgcn_exp2f(hi * d), dw = d * w;
                         s0 += w * pa.w; s1 += w * pb.x; s2 += w * pb.y;
-                        t += d * w * (pa.w * ux + pb.x * uy + pb.y * uz);
+                        t0 += dw * pa.w; t1 += dw * pb.x; t2 += dw * pb.y;
                     }
                     a0 += s0; a1 += s1; a2 += s2;
-                    da -= t;
+                    da -= t0 * ux + t1 * uy + t2 * uz;
                 }
             }
         }
@@ -808,8 +797,8 @@ __global__ __launch_bounds__(kWG) void k_adj_contact(AdjParams p) {
     });
     for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
         const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]);
-        const int c0 = uniform(T.chunk_off[k]), nc = uniform(T.chunk_off[k + 1]) - c0;
-        const int local = q - uniform(first[kk]), e = uniform(live_env(S, k, local / nc)), part = local % nc;
+        const int c0 = uniform(T.chunk_off[k]), cnt_k = uniform(live_count(S, k));
+        const int local = q - uniform(first[kk]), part = local / cnt_k, e = uniform(live_env(S, k, local - part * cnt_k));
         const size_t item = (size_t)e * K + k;
         if (S.dense && uniform(na[item]) == 0) continue;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base;

@@ -700,7 +700,7 @@ etac_status etac_plan_autotune(etac_plan *plan, const etac_scene *scene, const e
         return h == hipSuccess ? ETAC_OK : hip_fail(h);
     };
     etac_status out = e == hipSuccess ? ETAC_OK : hip_fail(e);
-    // forward: workgroups per CU x work-queue batch
+    // forward: workgroups per CU x batch
     int bf_occ = p.wg_per_cu, bf_batch = p.batch;
     float bf_ms = 3.0e38f;
     static const int kOcc[] = {1, 2};

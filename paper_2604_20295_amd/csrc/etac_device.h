@@ -333,14 +333,6 @@ __device__ __forceinline__ float cutoff_d2(float alpha) {
     return (float)(d * d * (1.0 + 1e-6));
 }
 
-// Work-queue position q: patch order[q / E] (patches by node count, largest
-// first), env q % E.
-__device__ __forceinline__ void queue_item(const MeshDev &M, int E, int q, int &e, int &k) {
-    const int kk = q / E;
-    e = q - kk * E;
-    k = M.order[kk];
-}
-
 // ---------------------------------------------------------------------------
 // residual network Phi on MFMA with split-FP16 operands
 //

@@ -24,7 +24,7 @@ constexpr int kAlphaSegs = 32;
 constexpr int kPhiSegs = 64;                      // segments of the parameter reduction
 constexpr int kMaxPatches = 1024;  // per-patch counters of the contact kernel live in LDS
 constexpr int kDefaultWgPerCu = 2;
-constexpr int kDefaultBatch = 4;   // work-queue positions claimed per atomic
+constexpr int kDefaultBatch = 4;   // default of the batch knobs
 constexpr int kDefaultDecayWgPerCu = 3;
 constexpr int kDefaultNetBatch = 2;   // workgroups per CU of the decay-adjoint kernel
 

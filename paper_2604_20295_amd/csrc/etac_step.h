@@ -911,4 +911,59 @@ __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&w
     }
 }
 
+// The runs of 32 listed nodes whose boxes lie within the cutoff of the box of a
+// wave's own nodes, in order; uniform over the wave.
+struct NearRuns {
+    const float4 *box;
+    int count, b0 = -64;      // runs, first of the 64 that todo covers
+    float lx, ly, lz, hx, hy, hz, cut2;
+    unsigned long long todo = 0;
+
+    __device__ __forceinline__ NearRuns(const float4 *boxes, int runs, bool on, float px, float py, float pz, float cut)
+        : box(boxes), count(runs), cut2(cut) {
+        lx = -wave_max(on ? -px : -3.0e38f); ly = -wave_max(on ? -py : -3.0e38f); lz = -wave_max(on ? -pz : -3.0e38f);
+        hx = wave_max(on ? px : -3.0e38f); hy = wave_max(on ? py : -3.0e38f); hz = wave_max(on ? pz : -3.0e38f);
+    }
+    // The next run, -1 after the last.
+    __device__ __forceinline__ int take() {
+        while (!todo) {
+            b0 += 64;
+            if (b0 >= count) return -1;
+            const int b = b0 + lane_id();
+            const float4 bl = box[2 * min(b, count - 1)], bh = box[2 * min(b, count - 1) + 1];
+            const float dx = fmaxf(fmaxf(bl.x - hx, lx - bh.x), 0.0f);
+            const float dy = fmaxf(fmaxf(bl.y - hy, ly - bh.y), 0.0f);
+            const float dz = fmaxf(fmaxf(bl.z - hz, lz - bh.z), 0.0f);
+            todo = __ballot(b < count && !(dx * dx + dy * dy + dz * dz >= cut2));
+        }
+        const int b = b0 + __ffsll(todo) - 1;
+        todo &= todo - 1;
+        return uniform(b);
+    }
+};
+
+// Two runs' nodes, one per lane: positions and values, requested a pair of
+// runs ahead of their use (a run at a time, with its list and values read in
+// turn before its 32 pairs, waits for memory as long as it computes).
+struct RunPair {
+    int r[2], c[2];      // runs (-1: none) and their node counts
+    float x[6];
+
+    __device__ __forceinline__ void fetch(NearRuns &runs, const MeshDev &M, const int *list, int nodes, int base,
+                                          const float *v, size_t EN) {
+        r[0] = runs.take();
+        r[1] = r[0] >= 0 ? runs.take() : -1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) c[h] = r[h] >= 0 ? min(32, nodes - 32 * r[h]) : 0;
+        if (r[0] < 0) return;
+        const int lane = lane_id(), h = lane >> 5, run = h && c[1] ? r[1] : r[0], cnt = h && c[1] ? c[1] : c[0];
+        const int i = list[32 * run + min(lane & 31, cnt - 1)], g = base + i;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            x[a] = M.pos[(size_t)a * M.N + g];
+            x[3 + a] = v[a * EN + i];
+        }
+    }
+};
+
 }  // namespace etac
