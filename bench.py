@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Throughput of the ETac tactile step on one MI355X.
 
-One step = the whole hot path over one batch: the fused contact + propagation
+One step = the whole hot path over one batch: the contact + propagation
 forward (etac_step) and its adjoint (etac_step_backward, which recomputes
 contact) for every env of the workload, replayed from one HIP graph.
 Workload: 4096 envs of a 16-patch hand (7232 surface nodes per env, patch
@@ -37,6 +37,7 @@ ENC_MAC, DEC_MAC, GLOBAL_MAC = 9 * 64 + 64 * 64, 64 * 64 + 64 * 3, 2 * 64 * 64
 # real-sensor regressor: multiply-adds per node (E1, E2, E3, A1) and per item (head)
 REG_NODE_MAC, REG_HEAD_MAC = 6 * 64 + 64 * 64 + 64 * 256 + 256 * 128, 256 * 128 + 128 * 8
 PHI_SIZE = 17411
+MATRIX_NODES = 2048            # patches up to this size have a decay matrix
 # VALU issue: 256 CUs x 4 SIMDs x 16 lanes at 2.4 GHz = 39.3e12 lane slots/s
 # (78.6 TFLOP/s of unpacked FP32 FMA; packed FP32 is not used); exp2 and sqrt
 # issue at quarter rate (4 slots).  A decay pair of Eq. 1 takes, in the
@@ -274,6 +275,7 @@ def work_counts(mesh, n_active):
     m = n_active.astype(np.float64)
     hit = m > 0
     pairs = float(np.sum(m * (n - m)))
+    matrix_pairs = float(np.sum(np.where(n <= MATRIX_NODES, m * (n - m), 0.0)))
     enc_nodes = float(np.sum(np.where(hit, n, 0.0)))
     dec_nodes = float(np.sum(np.where(hit, n - m, 0.0)))
     items = float(np.sum(hit))
@@ -283,30 +285,36 @@ def work_counts(mesh, n_active):
     dist = {"mean": float(frac.mean()), "median": float(np.median(frac)), "p5": float(np.percentile(frac, 5)),
             "p95": float(np.percentile(frac, 95)), "in_5_30_pct": float(np.mean((frac >= 0.05) & (frac <= 0.30))),
             "hist_edges": edges, "hist_envs": [int(x) for x in np.histogram(frac, bins=edges)[0]]}
-    return dict(pairs=pairs, mlp_flop=mlp_flop, contacted_items=items, contacted_nodes=enc_nodes,
+    return dict(pairs=pairs, matrix_pairs=matrix_pairs, mlp_flop=mlp_flop, contacted_items=items, contacted_nodes=enc_nodes,
                 active=float(m.sum()), passive=dec_nodes, active_fraction=dist)
 
 
 def algorithmic_work(kernel, counts, E, N, K, O, mode):
-    """Algorithmic work of one launch of a kernel: FP32-equivalent network
-    flops (2 per multiply-add), decay pairs of Eq. 1, and the HBM bytes its
-    inputs and outputs must move (each once; the plan's scratch, such as the
-    adjoint's hand-over between its kernels and its per-item gradient
-    records, is not counted).  The adjoint reads dL/dU only on patches in
+    """Algorithmic work of one timed span ("k_step": the forward's kernels,
+    "k_bwd_decay": tables, contact and Eq. 1's adjoint, "k_bwd": the network's
+    and the contact's adjoint), counted per env and node as the path is
+    stated: FP32-equivalent network flops (2 per multiply-add), decay pairs of
+    Eq. 1, and the HBM bytes its inputs and outputs must move (each once; the
+    plan's scratch is not counted).  Pairs of patches with a decay matrix are
+    matrix products: three components, 2 flops each, and in the adjoint the
+    same again with d W.  The network's kernels do less than counted: passive
+    nodes are encoded once per call.  The adjoint reads dL/dU only on patches in
     contact (elsewhere U = 0 whatever the inputs)."""
     nodes = float(E) * N
     items = counts["contacted_items"]
     decay = mode != 2     # not residual-only
     net = mode != 1       # not decay-only
+    matrix = counts.get("matrix_pairs", 0.0) if decay else 0.0
+    pairs = counts["pairs"] - matrix if decay else 0.0
     if kernel == "k_contact":
         # contact winner (1 B) and u_hat (12 B) per node, active count per item
         return dict(mfma_flop=0.0, pairs=0.0, hbm_bytes=13.0 * nodes + 4.0 * E * K)
     if kernel == "k_step":
-        return dict(mfma_flop=counts["mlp_flop"] if net else 0.0, pairs=counts["pairs"] if decay else 0.0,
+        return dict(mfma_flop=(counts["mlp_flop"] if net else 0.0) + 6.0 * matrix, pairs=pairs,
                     hbm_bytes=13.0 * nodes + 4.0 * E * K)
     if kernel == "k_bwd_decay":
         # dL/dU of contacted patches in, dL/dalpha partial per item out
-        return dict(mfma_flop=0.0, pairs=counts["pairs"] if decay else 0.0,
+        return dict(mfma_flop=12.0 * matrix, pairs=pairs,
                     hbm_bytes=12.0 * counts["contacted_nodes"] + 4.0 * E * K)
     # k_bwd: on the passive nodes of contacted patches the network's forward
     # is recomputed (encoder and decoder) and both adjoint products run, 3x
@@ -316,7 +324,7 @@ def algorithmic_work(kernel, counts, E, N, K, O, mode):
     return dict(mfma_flop=bwd_flop if net else 0.0, pairs=0.0, hbm_bytes=12.0 * counts["passive"])
 
 
-REGRESSOR_SOURCES = ("etac_regress.hip", "etac_device.h", "etac_internal.h")
+REGRESSOR_SOURCES = ("etac_regress.hip", "etac_device.h", "etac_step.h", "etac_internal.h")
 
 
 def source_digest(kernel=None):
@@ -360,7 +368,7 @@ def roofline_of(kernel, avg_ms, work, workload="hand"):
     """Roofline of a kernel: the resource whose lower-bound time (work /
     peak) is largest names the bound; achieved = algorithmic work of one
     launch / its average device time.  mfma: FP32-equivalent flops of the
-    network, three split-FP16 passes each, against the dense FP16 peak; alu:
+    network and of the decay matrices, three split-FP16 passes each, against the dense FP16 peak; alu:
     decay pairs against the VALU issue ceiling (PAIR_CEILING); hbm: bytes
     against 8 TB/s."""
     t = avg_ms * 1e-3
@@ -792,7 +800,8 @@ def main():
         "vs_baseline": None,
         "dtype": "f32",
         "precision": {"contact": "FP64 predicate and penetration, FP32 results",
-                      "decay": "FP32 terms, FP64 block sums",
+                      "decay": "FP32 weights and values as three BF16 or two scaled FP16 parts on the matrix cores "
+                               "(2^-24 of a product), FP32 accumulation; FP64 block sums on patches over 2048 nodes",
                       "network": "FP32 operands as FP16 hi+lo pairs with power-of-two range scaling "
                                  "(hi*hi + hi*lo + lo*hi on FP16 MFMA, 22-bit operands), FP32 accumulation"},
         "data": "synthetic",

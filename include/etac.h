@@ -276,36 +276,32 @@ const char *etac_status_string(etac_status status);
 /* HIP error code of the most recent ETAC_ERR_HIP in this thread (0 if none). */
 int32_t etac_last_hip_error(void);
 
-/* Plan introspection: number of (env, patch) items, persistent grid size,
- * scratch bytes.  Any output pointer may be NULL. */
+/* Plan introspection: number of (env, patch) items, workgroups at the plan's
+ * occupancy, scratch bytes.  Any output pointer may be NULL. */
 etac_status etac_plan_info(const etac_plan *plan, int32_t *n_items, int32_t *grid,
                            int64_t *scratch_bytes);
 
-/* Launch-shape override for the autotuner: forward workgroups per CU (0 =
- * built-in default).  The forward's kernels choose their own shape from the
- * sizes of the call; the value is kept and reported, and changes no result. */
+/* Launch shape: workgroups per CU (0 = built-in default).  The kernels are
+ * shaped by the sizes of the call; the value is kept and reported, and changes
+ * neither launches nor results. */
 etac_status etac_plan_set_occupancy(etac_plan *plan, int32_t wg_per_cu);
 
-/* Work-queue granularity for the autotuner: (env, patch) items claimed per
- * queue atomic by the persistent kernels, 1 .. 64 (0 = built-in default).
- * Results do not depend on it.  ETAC_ERR_VALUE outside 0 .. 64. */
+/* Launch shape: items claimed at a time, 1 .. 64 (0 = built-in default); kept
+ * and reported as above.  ETAC_ERR_VALUE outside 0 .. 64. */
 etac_status etac_plan_set_batch(etac_plan *plan, int32_t items);
 
-/* Launch shape of the persistent kernels (autotuner knobs; 0 keeps the
- * current value): forward workgroups per CU (1 .. 8), forward work-queue
- * batch (1 .. 64), work-queue batch of the decay-adjoint kernel (1 .. 64),
- * workgroups per CU of the decay-adjoint kernel (1 .. 8), and items claimed
- * at a time by the network-adjoint kernel from its list of items with
- * contact (1 .. 64).  Results do not depend on them.  ETAC_ERR_VALUE outside
- * those ranges. */
+/* All five launch knobs (0 keeps the current value): forward workgroups per CU
+ * (1 .. 8) and batch (1 .. 64), batch (1 .. 64) and workgroups per CU (1 .. 8)
+ * of Eq. 1's adjoint, batch of the network's adjoint (1 .. 64).  Kept and
+ * reported as above.  ETAC_ERR_VALUE outside those ranges. */
 etac_status etac_plan_set_launch(etac_plan *plan, int32_t fwd_wg_per_cu, int32_t fwd_batch,
                                  int32_t bwd_batch, int32_t decay_wg_per_cu, int32_t net_batch);
 
 /* The current launch shape, in the order of etac_plan_set_launch (HOST int32[5]). */
 etac_status etac_plan_get_launch(const etac_plan *plan, int32_t *shape);
 
-/* Autotuner.  Times every candidate launch shape of the persistent kernels
- * on the caller's inputs (as for etac_step and etac_step_backward; all
+/* Autotuner.  Times every candidate setting of the launch knobs (which change
+ * no launch, see above) on the caller's inputs (as for etac_step and etac_step_backward; all
  * DEVICE pointers, outputs overwritten; `saved` may be NULL and is passed to
  * both calls) with HIP events over `reps` calls
  * (1 .. 1000) after a warm-up call, and keeps the fastest: forward
@@ -321,18 +317,18 @@ etac_status etac_plan_autotune(etac_plan *plan, const etac_scene *scene, const e
                                float *grad_phi, int32_t reps, int32_t *best, void *stream);
 
 /* Kernel timing (diagnostics, not part of the method).  With timing on, every
- * launch of a timed kernel made outside stream capture is bracketed by a pair
- * of HIP events recorded on the stream the kernel is launched on, so the
- * measured span is that kernel's own execution on the device.  The plan keeps
+ * timed part of a call made outside stream capture is bracketed by a pair of
+ * HIP events recorded on the stream it is launched on, so the measured span is
+ * the execution of its kernels on the device.  The plan keeps
  * the most recent ETAC_TIMER_SLOTS pairs per timer. */
 #define ETAC_TIMER_SLOTS 256
 typedef enum {
-    ETAC_TIMER_CONTACT = 0,   /* k_contact: contact only (etac_contact)                  */
+    ETAC_TIMER_CONTACT = 0,   /* contact only (etac_contact)                             */
     ETAC_TIMER_STEP = 1,      /* the kernels of one forward step or propagation, as one span */
-    ETAC_TIMER_BACKWARD = 2,  /* k_bwd: network and contact adjoint of contacted items   */
-    ETAC_TIMER_REDUCE = 3,    /* the fixed-order reductions that follow k_bwd, as one span */
-    ETAC_TIMER_BWD_DECAY = 4, /* k_bwd_decay: contact and Eq. 1 adjoint, before k_bwd     */
-    ETAC_TIMER_REGRESS = 5,   /* k_regress: the real-sensor regressor (etac_regress)      */
+    ETAC_TIMER_BACKWARD = 2,  /* network and contact adjoint of contacted items          */
+    ETAC_TIMER_REDUCE = 3,    /* the fixed-order reductions that follow                  */
+    ETAC_TIMER_BWD_DECAY = 4, /* tables, contact and Eq. 1 adjoint, before the network's */
+    ETAC_TIMER_REGRESS = 5,   /* the real-sensor regressor's per-node layers             */
     ETAC_TIMER_COUNT = 6
 } etac_timer;
 
