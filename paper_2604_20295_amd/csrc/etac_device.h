@@ -121,7 +121,6 @@ struct ObjRow {
     float shape[4], rot[9], trans[3];
     float reach2;      // square of the ball test's radius
 };
-constexpr int kObjWords = sizeof(ObjRow) / 4;
 
 // The ball that rules a node out in FP32, with a relative margin of 1e-3 (far
 // above FP32 rounding).
