@@ -562,7 +562,7 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
 // the weights are in LDS and everything it reads is requested first (4096
 // hands: 161 us with weights from L2 and loads in turn, 125 us).
 struct ItemLds {
-    float w1u[64][4];                 // W1[:, 6..8]
+    alignas(16) float w1u[64][4];     // W1[:, 6..8]
     float x[kWaves][64][12];          // inputs of the channels' nodes, then the routed gradient
     float d[kWaves][64][4];           // dL/du_hat of the channels' nodes, and the node
     unsigned long long gate[kWaves][64];   // features of a channel's node with h1 > 0
@@ -574,6 +574,9 @@ struct ItemLds {
         float sum[kRouteWords];       // after the items
     };
 };
+ETAC_LDS_ALIGNED(ItemLds, w1u);
+ETAC_LDS_ALIGNED(ItemLds, x);
+ETAC_LDS_ALIGNED(ItemLds, d);
 
 // sum_c w[c][lane] x_c, four partial sums of 16 terms in order.
 __device__ __forceinline__ float column_dot(const float (*w)[64], float x) {

@@ -227,6 +227,8 @@ struct NodeLds {
     float mx[kWaves];
     float b2[kWaves][64];
 };
+ETAC_LDS_ALIGNED(NodeLds, s4);
+ETAC_LDS_ALIGNED(NodeLds, tr);
 
 // Transposed weight fragments for the adjoint layers, in the chain order of
 // etac_device.h (K step s, lane group q, element e <-> output chain_k(s, q, e)),

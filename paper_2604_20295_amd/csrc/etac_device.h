@@ -2,6 +2,8 @@
 // predicate and the split-FP16 arithmetic of the residual network.
 #pragma once
 
+#include <cstddef>
+
 #include "etac_internal.h"
 
 namespace etac {
@@ -392,6 +394,10 @@ struct ItemScale {
     float xmul;          // 2^ax
 };
 
+// LDS members that are read four floats at a time start at 16-byte boundaries.
+#define ETAC_LDS_ALIGNED(type, member) \
+    static_assert(alignof(type) % 16 == 0 && offsetof(type, member) % 16 == 0, #type "::" #member " is read 16 bytes at a time")
+
 struct NetLds {
     half8 w1h[4 * 64], w1l[4 * 64];          // [ot][lane]    W1 2^s1, inputs padded 9 -> 32 (one K step)
     half8 w2h[4 * 2 * 64], w2l[4 * 2 * 64];  // [ot2][s][lane] W2 2^s2
@@ -404,6 +410,8 @@ struct NetLds {
     // W2^T 2^s2t)
     int s1, s2, s4, s4t, s2t;
 };
+ETAC_LDS_ALIGNED(NetLds, b1s);
+ETAC_LDS_ALIGNED(NetLds, b2s);
 
 typedef _Float16 half2t __attribute__((ext_vector_type(2)));
 typedef unsigned uint2t __attribute__((ext_vector_type(2)));

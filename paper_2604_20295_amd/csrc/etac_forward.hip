@@ -194,11 +194,13 @@ __device__ unsigned long long pool_passive(const StepParams &p, PassiveLds<PCW> 
 constexpr int kActiveWords = 8;
 
 struct ActiveLds {
-    float b1s[64], b2s[64];
+    alignas(16) float b1s[64], b2s[64];
     float v[64];
     int ix[64];
     uint16_t slot[64 * kActiveWords];
 };
+ETAC_LDS_ALIGNED(ActiveLds, b1s);
+ETAC_LDS_ALIGNED(ActiveLds, b2s);
 
 // Largest of two (value, node) pairs, the lower node on ties.
 __device__ __forceinline__ void take_max(float &v, int &ix, float v2, int i2) {
@@ -481,6 +483,7 @@ struct PoolLds {
         ActiveLds act;
     } w[kPoolWaves];
 };
+ETAC_LDS_ALIGNED(PoolLds, w);
 
 __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_pool(StepParams p) {
     __shared__ PoolLds L;
@@ -640,6 +643,8 @@ struct WideLds {
         };
     };
 };
+ETAC_LDS_ALIGNED(WideLds, c4);
+ETAC_LDS_ALIGNED(WideLds, w5);
 
 template <int MT>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_prop_wide(StepParams p) {
@@ -773,10 +778,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 // batches whose wide tiles would leave the chip idle.
 struct NarrowLds {
     int first[kMaxPatches + 1];
-    float w5[3][64], b5[4];
+    alignas(16) float w5[3][64], b5[4];
     floatx4 part[kWaves][3][64];
     floatx4 rpart[kWaves][3][64];
 };
+ETAC_LDS_ALIGNED(NarrowLds, w5);
 
 __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
     __shared__ NarrowLds L;
@@ -956,11 +962,13 @@ __global__ __launch_bounds__(1024) void k_far_list(StepParams p) {
 // and units item by item, 1990 us.
 struct FarLds {
     int first[kMaxPatches + 1];
-    float w5[3][64], b5[4];
+    alignas(16) float w5[3][64], b5[4];
     float c4[64];
     float4 a[kWaves][64];
     float2 b[kWaves][64];
 };
+ETAC_LDS_ALIGNED(FarLds, w5);
+ETAC_LDS_ALIGNED(FarLds, c4);
 
 __global__ __launch_bounds__(kWG) void k_prop_far(StepParams p) {
     __shared__ FarLds L;

@@ -54,6 +54,10 @@ struct RegLds {
     half8 a1[8 * 8 * 64];                        // 2 log2(e) A1 in FP16, [ot][s][lane], 128 outputs over 256 inputs
     float be2[64], be3[256], ba1[128], wa2[128]; // e2, e3, 2 log2(e) a1, -2 a2
 };
+ETAC_LDS_ALIGNED(RegLds, be2);
+ETAC_LDS_ALIGNED(RegLds, be3);
+ETAC_LDS_ALIGNED(RegLds, ba1);
+ETAC_LDS_ALIGNED(RegLds, wa2);
 
 constexpr int kRegPasses = kRegUnitNodes / (16 * kRegNT);      // passes of a unit
 
@@ -464,7 +468,7 @@ __global__ __launch_bounds__(kRegWG) void k_regress(RegParams p) {
 constexpr int kHeadRows = 16;
 
 __global__ __launch_bounds__(256) void k_regress_head(RegParams p, float *taxels, float *rest) {
-    __shared__ float G[kHeadRows][256];
+    __shared__ alignas(16) float G[kHeadRows][256];
     __shared__ float DT[32][129];
     __shared__ float H[kHeadRows][128];
     __shared__ int items[kMaxPatches + 1], units[kMaxPatches + 1];

@@ -291,8 +291,9 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
 // ---------------------------------------------------------------------------
 struct TableLds {
     float part[kWaves][64];
-    float bv[kWaves][64];
+    alignas(16) float bv[kWaves][64];
 };
+ETAC_LDS_ALIGNED(TableLds, bv);
 
 // Split weight fragments of a 64-input layer (rows `stride` floats apart),
 // straight from the packed parameters into registers.
@@ -394,8 +395,11 @@ __device__ __forceinline__ void encode(const EncW &W, const float *b1, const flo
 // spread over as many workgroups as there are words (up to two per CU).
 struct FeatLds {
     TableLds t;
-    float b1s[64], b2s[64];
+    alignas(16) float b1s[64], b2s[64];
 };
+ETAC_LDS_ALIGNED(FeatLds, t);
+ETAC_LDS_ALIGNED(FeatLds, b1s);
+ETAC_LDS_ALIGNED(FeatLds, b2s);
 
 __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
     const MeshDev &M = p.mesh;
