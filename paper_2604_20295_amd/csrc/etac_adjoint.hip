@@ -116,48 +116,16 @@ __device__ __forceinline__ double finish_rows(const AdjParams &p, int k, int e, 
     return da;
 }
 
-// Largest |dL/dU| component over an item's passive nodes, the range of its
-// values in the product.  A wave takes an item; bound by its one pass over
-// grad_u.
-__global__ __launch_bounds__(kWG) void k_grad_max(AdjParams p) {
-    __shared__ int first[kMaxPatches + 1];
-    const StepParams &S = p.s;
-    const MeshDev &M = S.mesh;
-    const int K = M.K, N = M.N, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
-    const size_t EN = (size_t)S.E * N;
-    const int total = unit_prefix<kWaves>(K, first, [&](int kk) {
-        return S.tile.w_off[M.order[kk]] < 0 ? 0 : live_count(S, M.order[kk]);
-    });
-    for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
-        const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]);
-        const int e = uniform(live_env(S, k, q - uniform(first[kk])));
-        const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, nw = (n + 63) >> 6;
-        const float *g = p.grad_u + (size_t)e * N + base;
-        const unsigned long long *mask = S.itm.mask + (size_t)e * S.tile.NW + uniform(S.tile.word_off[k]);
-        float m = 0.0f;
-#pragma unroll 4
-        for (int w = 0; w < nw; ++w) {
-            const int i = min(64 * w + lane, n - 1);
-            const float x = fmaxf(fmaxf(fabsf(g[i]), fabsf(g[EN + i])), fabsf(g[2 * EN + i]));
-            if (!((mask[w] >> (i & 63)) & 1ull)) m = fmaxf(m, x);      // beyond the patch: its last node
-        }
-        m = wave_max(m);
-        if (lane == 0) p.b.grad_max[(size_t)e * K + k] = m;
-    }
-}
-
-// Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs, as the
-// forward's, each B fragment against W and d W.  Bound by the matrix cores
-// (4096 hands: 17.8 M MFMAs, 116 us at full rate) and by the reading and
-// splitting of the envs' values, which a taller tile does for more rows: 414 us
-// at MT = 1 (261 us of them with neither), 331 us at MT = 2.
+// Wide tiles: 64 rows (a wave takes a row tile) times 32 envs, as the forward's,
+// each B fragment against W and d W.  Bound by the matrix cores (4096 hands:
+// 35.6 M MFMAs, 232 us at full rate) and by the reading and splitting of the
+// envs' values: 562 us.
 struct AdjWideLds {
     int first[kMaxPatches + 1];
     int env[32];
     ProductB b;
 };
 
-template <int MT>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_adj_wide(AdjParams p) {
     __shared__ AdjWideLds L;
     const StepParams &S = p.s;
@@ -167,10 +135,10 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const size_t EN = (size_t)S.E * N;
     const bool dec = step_decay(S);
     const int32_t *na = S.itm.n_act;
-    const int total = product_units(S, L.first, 64 * MT, 32);
+    const int total = product_units(S, L.first, 64, 32);
     for (int q = product_start(); q < total; q += product_stride()) {
-        const ProductRef ref = product_ref(S, L.first, q, 64 * MT);
-        const int k = ref.k, rb = ref.row_block, g0 = ref.group * 32;
+        const ProductRef ref = product_ref(S, L.first, q, 64);
+        const int k = ref.k, g0 = ref.group * 32;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
         const int cnt = uniform(live_count(S, k));
         const int w0 = uniform(T.word_off[k]);
@@ -183,70 +151,33 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         int env[2];
         env[0] = L.env[col];
         env[1] = L.env[16 + col];
-        const int rt0 = (4 * rb + wave) * MT, rts = (n + 15) >> 4;
-        floatx4 acc[2 * MT][2][3];     // [row tile, W or d W][column tile][component]
+        const int rt = 4 * ref.row_block + wave, rts = (n + 15) >> 4;
+        floatx4 acc[2][2][3];     // [W or d W][column tile][component]
 #pragma unroll
-        for (int m = 0; m < 2 * MT; ++m)
+        for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         const bool slow = matrix_overflows(M, S.model.alpha[k], k);
         if (dec && !slow) {
-            const bool half = matrix_half(S, k);
             const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
             const unsigned long long *mask = S.itm.mask + (size_t)safe * T.NW + w0;
-            const size_t at = (size_t)safe * N + base;
-            const uint4 *wa[2 * MT];
-#pragma unroll
-            for (int m = 0; m < MT; ++m) {      // rows beyond the patch repeat its last tile
-                const size_t w_at = T.w_off[k] + (size_t)min(rt0 + m, rts - 1) * KS * (half ? 2 : 3) * 64 + lane;
-                wa[2 * m] = S.tab.w + w_at;
-                wa[2 * m + 1] = S.tab.wd + w_at;
-            }
-            if (half) {
-                auto exponent = [&](int e) { return top_exp(p.b.grad_max[(size_t)max(e, 0) * K + k]); };
-                product_loop<2 * MT, true, true>(L.b, wa, p.grad_u, at, EN, mask, pow2(exponent(myenv)), myenv >= 0, n, KS, acc);
-                const int ew[2] = {weight_exp(S, k), distance_weight_exp(S, k)};
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int s = exponent(env[t]);
-#pragma unroll
-                    for (int m = 0; m < 2 * MT; ++m)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c)
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) acc[m][t][c][x] = ldexpf(acc[m][t][c][x], -(s + ew[m & 1]));
-                }
-            } else {
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {      // one row tile at a time: three parts of two would not fit the registers
-                    const uint4 *const w2[2] = {wa[2 * m], wa[2 * m + 1]};
-                    floatx4 a2[2][2][3];
-#pragma unroll
-                    for (int i = 0; i < 12; ++i) a2[i / 6][i / 3 % 2][i % 3] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-                    product_loop<2, true, false>(L.b, w2, p.grad_u, at, EN, mask, 1.0f, myenv >= 0, n, KS, a2);
-#pragma unroll
-                    for (int i = 0; i < 12; ++i) acc[2 * m + i / 6][i / 3 % 2][i % 3] = a2[i / 6][i / 3 % 2][i % 3];
-                    __syncthreads();      // L.b is done with
-                }
-            }
+            // rows beyond the patch repeat its last tile
+            const size_t w_at = T.w_off[k] + (size_t)min(rt, rts - 1) * KS * 3 * 64 + lane;
+            const uint4 *wa[2] = {S.tab.w + w_at, S.tab.wd + w_at};
+            product_loop<2, true>(L.b, wa, p.grad_u, (size_t)safe * N + base, EN, mask, myenv >= 0, n, KS, acc);
         }
+        if (rt >= rts) continue;      // no barrier before the next unit's first
+        const int i0 = 16 * rt + 4 * gq;
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const int rt = rt0 + m;
-            if (rt >= rts) break;      // no barrier before the next unit's first
-            const int i0 = 16 * rt + 4 * gq;
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int e = env[t];
-                double da = 0.0;
-                if (e >= 0 && i0 < n)
-                    da = finish_rows(p, k, e, base, i0, n - i0, acc[2 * m][t], acc[2 * m + 1][t], dec, slow);
-                da += __shfl_xor(da, 16);
-                da += __shfl_xor(da, 32);
-                if (e >= 0) p.b.alpha_part[(size_t)e * T.NP + T.part_off[k] + rt] = da;      // the same in the 4 lane groups
-            }
+        for (int t = 0; t < 2; ++t) {
+            const int e = env[t];
+            double da = 0.0;
+            if (e >= 0 && i0 < n) da = finish_rows(p, k, e, base, i0, n - i0, acc[0][t], acc[1][t], dec, slow);
+            da += __shfl_xor(da, 16);
+            da += __shfl_xor(da, 32);
+            if (e >= 0) p.b.alpha_part[(size_t)e * T.NP + T.part_off[k] + rt] = da;      // the same in the 4 lane groups
         }
     }
 }
@@ -1169,10 +1100,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     launch_front(pl, f, st);
     if (pl.tile.n_near) {
         // as in the forward: wide tiles once they give every CU work
-        if (f.wide && dec)
-            hipLaunchKernelGGL(k_grad_max, dim3(blocks((items + kWaves - 1) / kWaves, 8 * cus)), dim3(kWG), 0, st, p);
-        if (n_envs >= 1024) hipLaunchKernelGGL(k_adj_wide<2>, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
-        else if (f.wide) hipLaunchKernelGGL(k_adj_wide<1>, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
+        if (f.wide) hipLaunchKernelGGL(k_adj_wide, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_adj_narrow, dim3(blocks((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
                                dim3(kWG), 0, st, p);

@@ -415,7 +415,6 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
         e = plan_alloc(p, &b.cobj_st, EN);
         if (e == hipSuccess) e = plan_alloc(p, &b.uhat_st, 3 * EN);
         if (e == hipSuccess) e = plan_alloc(p, &b.gh, 3 * EN);
-        if (e == hipSuccess) e = plan_alloc(p, &b.grad_max, EK);
         if (e == hipSuccess) e = plan_alloc(p, &b.alpha_part, (size_t)n_envs * tile.NP);
         if (e == hipSuccess) e = plan_alloc(p, &b.alpha_seg, (size_t)K * etac::kAlphaSegs);
         if (e == hipSuccess) e = plan_alloc(p, &b.s4_part, ENW * 2 * 64);

@@ -624,17 +624,16 @@ __device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, in
 
 // Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs (two column
 // tiles per component: column l & 15 is an env).  Bound by the matrix cores in
-// the loop (4096 hands: 8.9 M MFMAs, 116 us of all of them at full rate) and by
+// the loop (4096 hands: 17.8 M MFMAs, 116 us of all of them at full rate) and by
 // the VALU in the epilogue (five operations per node, env and channel of the
-// residual).  A taller tile reads and splits each env's values for more rows;
-// patches are padded to it and there are fewer units, so it pays once there are
-// many: 4096 hands 290 us at MT = 2 and 254 at MT = 4, 16384 hands 1116 and 937.
+// residual): 387 us.  A taller tile reads and splits each env's values for more
+// rows; patches are padded to it and there are fewer units, so it pays once
+// there are many.
 constexpr int kWideEnvs = 32;
 
 struct WideLds {
     int first[kMaxPatches + 1];
     int env[kWideEnvs];
-    int exp[kWideEnvs];               // scale exponents of their values
     union {
         ProductB b;
         struct {                      // after the K loop
@@ -682,7 +681,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
                 for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         const bool slow = matrix_overflows(M, p.model.alpha[k], k);
-        const bool half = matrix_half(p, k);
         if (dec && !slow) {
             const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
             const size_t at = (size_t)safe * N + base;
@@ -691,47 +689,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
                 const int mt = min((row0 >> 4) + m, ((n + 15) >> 4) - 1);      // rows beyond the patch repeat its last tile
-                wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * (half ? 2 : 3) * 64 + lane;
+                wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * 3 * 64 + lane;
             }
-            if (half) {
-                {
-                    const int j = threadIdx.x >> 3, e = L.env[j], nw = (n + 63) >> 6;
-                    float m = 0.0f;
-                    for (int w = threadIdx.x & 7; w < nw && e >= 0; w += 8)
-                        if (p.itm.mask[(size_t)e * T.NW + w0 + w]) m = fmaxf(m, p.itm.umax[(size_t)e * T.NW + w0 + w]);
-#pragma unroll
-                    for (int o = 1; o < 8; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
-                    L.exp[j] = top_exp(m);      // the same in the 8 lanes
-                }
-                __syncthreads();
-                product_loop<MT, false, true>(L.b, wa, src, at, EN, mask, pow2(L.exp[mine]), myenv >= 0, n, KS, acc);
-                const int ew = weight_exp(p, k);
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    const int s = -(ew + L.exp[16 * t + col]);
-#pragma unroll
-                    for (int m = 0; m < MT; ++m)
-#pragma unroll
-                        for (int c = 0; c < 3; ++c)
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) acc[m][t][c][x] = ldexpf(acc[m][t][c][x], s);
-                }
-            } else {
-                constexpr int kStep = MT > 2 ? 2 : MT;      // three parts of four row tiles would not fit the registers
-#pragma unroll
-                for (int m0 = 0; m0 < MT; m0 += kStep) {
-                    const uint4 *w2[kStep];
-                    floatx4 a2[kStep][2][3];
-#pragma unroll
-                    for (int i = 0; i < 6 * kStep; ++i) a2[i / 6][i / 3 % 2][i % 3] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (int m = 0; m < kStep; ++m) w2[m] = wa[m0 + m];
-                    product_loop<kStep, false, false>(L.b, w2, src, at, EN, mask, 1.0f, myenv >= 0, n, KS, a2);
-#pragma unroll
-                    for (int i = 0; i < 6 * kStep; ++i) acc[m0 + i / 6][i / 3 % 2][i % 3] = a2[i / 6][i / 3 % 2][i % 3];
-                    __syncthreads();      // L.b is done with
-                }
-            }
+            product_loop<MT, false>(L.b, wa, src, at, EN, mask, myenv >= 0, n, KS, acc);
         }
         __syncthreads();      // L.b is done with
         if (res) {
@@ -1184,8 +1144,7 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     if (step_residual(p)) launch_pool(pl, p, st);
     if (pl.tile.n_near) {
         // tile heights: see k_prop_wide
-        if (n_envs >= 4096) hipLaunchKernelGGL(k_prop_wide<4>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
-        else if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
+        if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
         else if (p.wide) hipLaunchKernelGGL(k_prop_wide<1>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_prop_narrow, dim3((unsigned)std::min<long long>((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),

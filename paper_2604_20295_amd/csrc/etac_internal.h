@@ -162,7 +162,6 @@ struct BwdScratch {
     int8_t *cobj_st;       // [E][N]    contact winners (step adjoint)
     float *uhat_st;        // [3][E][N] u_hat of active nodes (step adjoint)
     float *gh;             // [3][E][N] dL/du_hat of active nodes (step adjoint)
-    float *grad_max;       // [E][K]    largest |dL/dU| component over an item's passive nodes (wide tiles)
     double *alpha_part;    // [E][NP]   dL/dalpha of every part of Eq. 1
     float *s4_part;        // [E][2 NW][64] sum of dL/dpre4 over the passive nodes of a half word
     float *s4_node;        // [chunks][N][64] sum of dL/dpre4 over a chunk's envs, per node

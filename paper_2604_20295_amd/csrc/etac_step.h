@@ -175,7 +175,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
             }
         }
     }
-    const bool residual = p.itm.mask && step_residual(p), want_umax = residual || (p.itm.mask && p.wide);
+    const bool residual = p.itm.mask && step_residual(p);
     for (int w0 = 0; w0 < NW; w0 += kScan * p.splits) {
         // words w0 + s, w0 + s + splits, ... of patches with candidates
         const int mine = w0 + s + p.splits * (int)threadIdx.x;
@@ -257,7 +257,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
             const unsigned long long act = __ballot(best >= 0);
             if (p.itm.mask) p.itm.mask[(size_t)e * NW + w] = act;      // every lane stores the same value
             if (act) {                                                 // wave-uniform
-                if (want_umax) {
+                if (residual) {
                     const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
                     p.itm.umax[(size_t)e * NW + w] = m;
                 }
@@ -505,7 +505,9 @@ __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
 
 // Decay matrices.  W = exp(-alpha |p_j - p_i|) of a near patch as three BF16
 // parts whose sum is the FP32 value (24 bits: RNE of the value and of the two
-// exact remainders), in the order the matrix cores take as A operand: row tile
+// exact remainders; the products keep every product of parts down to 2^-24 of
+// the whole, which leaves out at most 2^-26 of it), in the order the matrix
+// cores take as A operand: row tile
 // t (16 nodes i), K step s (32 nodes j), part c, lane l: row 16 t + (l & 15),
 // columns 32 s + 8 (l >> 4) + 0..7 at 16-byte unit ((t KS + s) 3 + c) 64 + l.
 // Entries beyond the patch are 0.  For the adjoint also d W.  A workgroup takes a row tile, its waves the
@@ -568,45 +570,11 @@ __device__ __forceinline__ void decay_rate(float alpha, float &hi, float &lo) {
     lo = (float)(b - (double)hi);
 }
 
-// Weights of patch k are at most 2^growth: 0 unless alpha < 0.
-__device__ __forceinline__ float matrix_growth(const MeshDev &M, float alpha, int k) {
-    return alpha < 0.0f ? -alpha * 1.4427f * 2.0f * M.bound[k].w : 0.0f;
-}
-
-// Whether a weight could overflow (alpha < 0 on a wide patch): the matrix then
-// holds infinities, which a product would spread to nodes that have no such
-// pair; such a patch is summed pair by pair.
+// Whether a weight could overflow (alpha < 0 on a wide patch: they grow up to
+// 2^120 and more): the matrix then holds infinities, which a product would
+// spread to nodes that have no such pair; such a patch is summed pair by pair.
 __device__ __forceinline__ bool matrix_overflows(const MeshDev &M, float alpha, int k) {
-    return matrix_growth(M, alpha, k) > 120.0f;
-}
-
-// Format of a patch's matrices.  In wide tiles the matrix cores bound the
-// product, and two FP16 parts with three products of parts replace three BF16
-// parts with six: 22 bits and a sign of the remainder, an error of 2^-24 as
-// FP32's own, for weights down to 2^-17 of the largest, below that at most
-// 2^-39 of the largest.  Where weights grow with distance (alpha < 0) by more
-// than 2^12 the sums of near nodes alone could lie below that: BF16 parts,
-// which have FP32's range.  Narrow tiles wait on loads and keep BF16 (FP16
-// would first need the range of every env's values).
-// 4096 hands: transposed product 556 us in BF16, 429 us in FP16; forward 376 and
-// 298 us.
-__device__ __forceinline__ bool matrix_half(const StepParams &p, int k) {
-    return p.wide && matrix_growth(p.mesh, p.model.alpha[k], k) <= 12.0f;
-}
-
-// Scale exponents of the FP16 parts: the largest W, d W and value of an env
-// are put below 2^15.
-__device__ __forceinline__ int weight_exp(const StepParams &p, int k) {
-    return 15 - (int)ceilf(matrix_growth(p.mesh, p.model.alpha[k], k));
-}
-__device__ __forceinline__ int top_exp(float bound) {
-    if (!(bound > 0.0f) || !(bound <= 3.0e38f)) return 0;
-    int e;
-    (void)frexpf(bound, &e);
-    return min(15 - e, 126);
-}
-__device__ __forceinline__ int distance_weight_exp(const StepParams &p, int k) {
-    return weight_exp(p, k) + min(top_exp(2.0f * p.mesh.bound[k].w), 100) - 15;
+    return alpha < 0.0f && -alpha * 1.4427f * 2.0f * M.bound[k].w > 120.0f;
 }
 
 __device__ void matrix_row_tile(const StepParams &p, int unit) {
@@ -621,25 +589,13 @@ __device__ void matrix_row_tile(const StepParams &p, int unit) {
     const int i = 16 * unit + (lane & 15);
     const int gi = base + min(i, n - 1);
     const float px = M.pos[gi], py = M.pos[N + gi], pz = M.pos[2 * N + gi];
-    const bool half = matrix_half(p, k);
-    const int P = half ? 2 : 3;
-    const float sw = pow2(weight_exp(p, k)), sd = pow2(distance_weight_exp(p, k));
-    const size_t at = p.tile.w_off[k] + (size_t)unit * KS * P * 64 + lane;
+    const size_t at = p.tile.w_off[k] + (size_t)unit * KS * 3 * 64 + lane;
     uint4 *w = p.tab.w + at, *wd = p.tab.wd + at;
-    auto store = [&](uint4 *o, int s, float scale, float (&v)[8]) {
-        if (half) {
-            half8 h, l;
+    auto store = [&](uint4 *o, int s, const float (&v)[8]) {
+        bf16x8 b[3];
+        split_bf16x3(v, b);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] *= scale;
-            split8(v, h, l);
-            o[(size_t)(2 * s) * 64] = __builtin_bit_cast(uint4, h);
-            o[(size_t)(2 * s + 1) * 64] = __builtin_bit_cast(uint4, l);
-        } else {
-            bf16x8 b[3];
-            split_bf16x3(v, b);
-#pragma unroll
-            for (int c = 0; c < 3; ++c) o[(size_t)(3 * s + c) * 64] = __builtin_bit_cast(uint4, b[c]);
-        }
+        for (int c = 0; c < 3; ++c) o[(size_t)(3 * s + c) * 64] = __builtin_bit_cast(uint4, b[c]);
     };
     for (int s = wave; s < KS; s += kWaves) {
         const int j0 = 32 * s + 8 * (lane >> 4);
@@ -652,8 +608,8 @@ __device__ void matrix_row_tile(const StepParams &p, int unit) {
             x[e] = (i < n && j0 + e < n) ? v : 0.0f;
             y[e] = x[e] * d;
         }
-        store(w, s, sw, x);
-        if (p.adjoint) store(wd, s, sd, y);
+        store(w, s, x);
+        if (p.adjoint) store(wd, s, y);
     }
 }
 
@@ -792,11 +748,11 @@ __device__ __forceinline__ void load8(const float *x, int j0, int n, float (&v)[
 // Whole workgroup; ends before the last pair's reads of B are done.
 using ProductB = uint4[2][2][6][3][64];      // [buffer][K step][3 column tile + component][part][lane]
 
-template <int NA, bool PASSIVE, bool HALF>
+template <int NA, bool PASSIVE>
 __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&wa)[NA], const float *src, size_t at, size_t EN,
-                                             const unsigned long long *mask, float scale, bool has, int n, int KS,
+                                             const unsigned long long *mask, bool has, int n, int KS,
                                              floatx4 (&acc)[NA][2][3]) {
-    constexpr int P = HALF ? 2 : 3, kProducts = HALF ? 3 : 6;
+    constexpr int P = 3, kProducts = 6;
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), gq = lane >> 4;
     float raw[3][8];
     unsigned long long word = 0;
@@ -831,18 +787,11 @@ __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&w
         for (int c = 0; c < 3; ++c) {
             uint4(&o)[3][64] = B[buf][wave >> 1][3 * (wave & 1) + c];
 #pragma unroll
-            for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? (HALF ? raw[c][x] * scale : raw[c][x]) : 0.0f;
-            if (HALF) {
-                half8 h, l;
-                split8(raw[c], h, l);
-                o[0][lane] = __builtin_bit_cast(uint4, h);
-                o[1][lane] = __builtin_bit_cast(uint4, l);
-            } else {
-                bf16x8 b[3];
-                split_bf16x3(raw[c], b);
+            for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
+            bf16x8 b[3];
+            split_bf16x3(raw[c], b);
 #pragma unroll
-                for (int y = 0; y < 3; ++y) o[y][lane] = __builtin_bit_cast(uint4, b[y]);
-            }
+            for (int y = 0; y < 3; ++y) o[y][lane] = __builtin_bit_cast(uint4, b[y]);
         }
     };
     uint4 a[2][NA][P];
@@ -864,18 +813,13 @@ __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&w
 #pragma unroll
             for (int m = 0; m < NA; ++m) {
                 floatx4 &o = acc[m][f / 3][f % 3];
-                if constexpr (HALF) {
-                    o = mfma_split(__builtin_bit_cast(half8, x[m][0]), __builtin_bit_cast(half8, x[m][1]),
-                                   __builtin_bit_cast(half8, b[f & 1][0]), __builtin_bit_cast(half8, b[f & 1][1]), o);
-                } else {
-                    bf16x8 y[3], z[3];
+                bf16x8 y[3], z[3];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        y[c] = __builtin_bit_cast(bf16x8, x[m][c]);
-                        z[c] = __builtin_bit_cast(bf16x8, b[f & 1][c]);
-                    }
-                    o = mfma_bf16x3(y, z, o);
+                for (int c = 0; c < 3; ++c) {
+                    y[c] = __builtin_bit_cast(bf16x8, x[m][c]);
+                    z[c] = __builtin_bit_cast(bf16x8, b[f & 1][c]);
                 }
+                o = mfma_bf16x3(y, z, o);
             }
         }
     };
@@ -904,7 +848,7 @@ __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&w
 #pragma unroll
             for (int i = 0; i < kProducts * NA; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-                __builtin_amdgcn_sched_group_barrier(0x002, NA > 2 ? 2 : 6 / NA, 1);
+                __builtin_amdgcn_sched_group_barrier(0x002, 6 / NA, 1);
             }
             if (f < 4) __builtin_amdgcn_sched_group_barrier(0x100, P, 1);
         }
