@@ -801,7 +801,7 @@ def main():
         "dtype": "f32",
         "precision": {"contact": "FP64 predicate and penetration, FP32 results",
                       "decay": "FP32 weights and values as three BF16 parts each (24 bits) on the matrix cores, "
-                               "FP32 accumulation; FP64 block sums on patches over 2048 nodes",
+                               "FP32 sums of 32 terms, added in FP64",
                       "network": "FP32 operands as FP16 hi+lo pairs with power-of-two range scaling "
                                  "(hi*hi + hi*lo + lo*hi on FP16 MFMA, 22-bit operands), FP32 accumulation"},
         "data": "synthetic",

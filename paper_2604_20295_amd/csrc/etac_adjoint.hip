@@ -30,31 +30,45 @@ namespace etac {
 // Eq. 1
 // ---------------------------------------------------------------------------
 
-// Pair-by-pair form of one active node, where a matrix would overflow.
-__device__ void pair_adjoint(const AdjParams &p, int k, int e, int j, float (&q)[3], double &da) {
+// Pair-by-pair form of one active node, where a matrix would overflow: the
+// sums with w and with d w.
+__device__ void pair_adjoint(const AdjParams &p, int k, int e, int j, double (&a)[3], double (&b)[3]) {
     const MeshDev &M = p.s.mesh;
     const int N = M.N, base = M.offset[k], n = M.offset[k + 1] - base;
     const size_t EN = (size_t)p.s.E * N, row = (size_t)e * N + base;
     const unsigned long long *mask = p.s.itm.mask + (size_t)e * p.s.tile.NW + p.s.tile.word_off[k];
-    const float *u = uhat_source(p.s) + row;
     float hi, lo;
     decay_rate(p.s.model.alpha[k], hi, lo);
-    double a[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) a[c] = b[c] = 0.0;
     for (int i = 0; i < n; ++i) {
         if ((mask[i >> 6] >> (i & 63)) & 1ull) continue;
         float d;
         const double w = decay_weight_wide(M.pos[base + i] - M.pos[base + j], M.pos[N + base + i] - M.pos[N + base + j],
                                      M.pos[2 * N + base + i] - M.pos[2 * N + base + j], hi, lo, d);
+#pragma unroll
         for (int c = 0; c < 3; ++c) {
             const double wg = w * (double)p.grad_u[c * EN + row + i];      // beyond FP32's range here
             a[c] += wg;
             b[c] += (double)d * wg;
         }
     }
-    da = 0.0;
-    for (int c = 0; c < 3; ++c) {
-        q[c] = (float)a[c];
-        da -= (double)u[c * EN + j] * b[c];
+}
+
+// The active rows of an env's four summed pair by pair (no register indexed at
+// run time).
+__device__ void pair_rows(const AdjParams &p, int k, int e, int i0, unsigned todo, doublex4 (&q)[3], doublex4 (&qd)[3]) {
+    for (; todo; todo &= todo - 1) {
+        const int row = __ffs(todo) - 1;
+        double a[3], b[3];
+        pair_adjoint(p, k, e, i0 + row, a, b);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                q[c][x] = x == row ? a[c] : q[c][x];
+                qd[c][x] = x == row ? b[c] : qd[c][x];
+            }
     }
 }
 
@@ -73,37 +87,21 @@ __device__ __forceinline__ floatx4 load4(const float *x, int left) {
 // gradient plus the decay part; active nodes only.  Returns their part of
 // dL/dalpha (qd: the sums with d w).
 __device__ __forceinline__ double finish_rows(const AdjParams &p, int k, int e, int base, int i0, int left,
-                                              const floatx4 (&q)[3], const floatx4 (&qd)[3], bool dec, bool slow) {
+                                              doublex4 (&q)[3], doublex4 (&qd)[3], bool dec, bool slow) {
     const int N = p.s.mesh.N, w0 = p.s.tile.word_off[k];
     const size_t EN = (size_t)p.s.E * N, at = (size_t)e * N + base + i0;
+    // bits beyond the patch are clear
     const unsigned act = (unsigned)(p.s.itm.mask[(size_t)e * p.s.tile.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
+    if (dec && slow) pair_rows(p, k, e, i0, act, q, qd);
     const float *u = uhat_source(p.s) + at;
-    floatx4 g[3], uh[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        g[c] = load4(p.grad_u + c * EN + at, left);
-        uh[c] = load4(u + c * EN, left);
-    }
     double da = 0.0;
-    floatx4 v[3] = {q[0], q[1], q[2]};
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        if (!((act >> x) & 1u) || !dec) continue;      // bits beyond the patch are clear
-        if (slow) {
-            double d;
-            float w[3];
-            pair_adjoint(p, k, e, i0 + x, w, d);
-            da += d;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) v[c][x] = w[c];
-        } else {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) da -= (double)uh[c][x] * (double)qd[c][x];
-        }
-    }
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const floatx4 o = dec ? g[c] + v[c] : g[c];
+        const floatx4 g = load4(p.grad_u + c * EN + at, left), uh = load4(u + c * EN, left);
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+            if (((act >> x) & 1u) && dec) da -= (double)uh[x] * qd[c][x];
+        const floatx4 o = dec ? __builtin_convertvector(widen(g) + q[c], floatx4) : g;
         float *out = p.gh + c * EN + at;
         if (act == 0xfu) {
             __builtin_memcpy(out, &o, 16);
@@ -118,8 +116,8 @@ __device__ __forceinline__ double finish_rows(const AdjParams &p, int k, int e, 
 
 // Wide tiles: 64 rows (a wave takes a row tile) times 32 envs, as the forward's,
 // each B fragment against W and d W.  Bound by the matrix cores (4096 hands:
-// 35.6 M MFMAs, 232 us at full rate) and by the reading and splitting of the
-// envs' values: 562 us.
+// 35.6 M MFMAs, 232 us at full rate) and the VALU beside them (the FP64 sums, and
+// the reading and splitting of the envs' values): 672 us, 562 us with FP32 sums.
 struct AdjWideLds {
     int first[kMaxPatches + 1];
     int env[32];
@@ -152,13 +150,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         env[0] = L.env[col];
         env[1] = L.env[16 + col];
         const int rt = 4 * ref.row_block + wave, rts = (n + 15) >> 4;
-        floatx4 acc[2][2][3];     // [W or d W][column tile][component]
+        doublex4 acc[2][2][3];     // [W or d W][column tile][component]
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int c = 0; c < 3; ++c) acc[m][t][c] = doublex4{0.0, 0.0, 0.0, 0.0};
         const bool slow = matrix_overflows(M, S.model.alpha[k], k);
         if (dec && !slow) {
             const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
@@ -166,7 +164,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             // rows beyond the patch repeat its last tile
             const size_t w_at = T.w_off[k] + (size_t)min(rt, rts - 1) * KS * 3 * 64 + lane;
             const uint4 *wa[2] = {S.tab.w + w_at, S.tab.wd + w_at};
-            product_loop<2, true>(L.b, wa, p.grad_u, (size_t)safe * N + base, EN, mask, myenv >= 0, n, KS, acc);
+            product_loop<2, true, 2>(L.b, wa, p.grad_u, (size_t)safe * N + base, EN, mask, myenv >= 0, n, KS, acc);
         }
         if (rt >= rts) continue;      // no barrier before the next unit's first
         const int i0 = 16 * rt + 4 * gq;
@@ -185,7 +183,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 // Narrow tiles: 16 rows times 16 envs, the K steps split over four waves.
 struct AdjNarrowLds {
     int first[kMaxPatches + 1];
-    floatx4 part[kWaves][6][64];
+    doublex4 part[kWaves][6][64];
 };
 
 __global__ __launch_bounds__(kWG) void k_adj_narrow(AdjParams p) {
@@ -210,11 +208,11 @@ __global__ __launch_bounds__(kWG) void k_adj_narrow(AdjParams p) {
         int e = g0 + col < cnt ? live_env(S, k, g0 + col) : -1;
         if (e >= 0 && S.dense && na[(size_t)e * K + k] == 0) e = -1;
         if (!__ballot(e >= 0)) continue;      // the same in every wave
-        floatx4 acc[2][3];
+        doublex4 acc[2][3];
 #pragma unroll
         for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) acc[m][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int c = 0; c < 3; ++c) acc[m][c] = doublex4{0.0, 0.0, 0.0, 0.0};
         const bool slow = matrix_overflows(M, S.model.alpha[k], k);
         if (dec && !slow) {
             const size_t at = T.w_off[k] + (size_t)rt * KS * 3 * 64 + lane;
@@ -252,7 +250,7 @@ __global__ __launch_bounds__(kWG) void k_adj_narrow(AdjParams p) {
 #pragma unroll
                 for (int m = 0; m < 2; ++m)
 #pragma unroll
-                    for (int c = 0; c < 3; ++c) acc[m][c] = mfma_bf16x3(y[m], b[c], acc[m][c]);
+                    for (int c = 0; c < 3; ++c) acc[m][c] += widen(mfma_bf16x3(y[m], b[c], floatx4{0.0f, 0.0f, 0.0f, 0.0f}));
             }
         }
         __syncthreads();          // the previous unit is done with L.part
@@ -263,7 +261,7 @@ __global__ __launch_bounds__(kWG) void k_adj_narrow(AdjParams p) {
             const int i0 = 16 * rt + 4 * gq;
 #pragma unroll
             for (int f = 0; f < 6; ++f) {
-                floatx4 v = L.part[0][f][lane];
+                doublex4 v = L.part[0][f][lane];
                 for (int w = 1; w < kWaves; ++w) v += L.part[w][f][lane];
                 acc[f / 3][f % 3] = v;
             }
@@ -830,8 +828,6 @@ __global__ __launch_bounds__(256) void k_pose(AdjParams p, float *grad_rot, floa
 // one block's, as matrix products in FP64 over the segment's items: a thread
 // per column reads both vectors of every item for each of them (4096 hands, all
 // columns: 170 us, 48 us as products).
-typedef double doublex4 __attribute__((ext_vector_type(4)));
-
 __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_groups, int segs) {
     __shared__ int list[1024];
     __shared__ int wsum[kWaves];

@@ -546,7 +546,7 @@ __global__ __launch_bounds__(64 * kPoolWaves) __attribute__((amdgpu_waves_per_eu
 // U of the passive nodes: near patches
 // ---------------------------------------------------------------------------
 // Eq. 1 of one node over the active nodes of its item, pair by pair.
-__device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *src, floatx4 (&s)[3], int x) {
+__device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *src, double (&s)[3]) {
     const MeshDev &M = p.mesh;
     const int N = M.N, base = M.offset[k], n = M.offset[k + 1] - base;
     const size_t EN = (size_t)p.E * N;
@@ -554,20 +554,36 @@ __device__ void pair_sum(const StepParams &p, int k, int e, int i, const float *
     const float *u = src + (size_t)e * N + base;
     float hi, lo;
     decay_rate(p.model.alpha[k], hi, lo);
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+    s[0] = s[1] = s[2] = 0.0;
     for (int j = 0; j < n; ++j) {
         if (!((mask[j >> 6] >> (j & 63)) & 1ull)) continue;
         float d;
         const double w = decay_weight_wide(M.pos[base + j] - M.pos[base + i], M.pos[N + base + j] - M.pos[N + base + i],
                                      M.pos[2 * N + base + j] - M.pos[2 * N + base + i], hi, lo, d);
-        a0 += w * u[j];
-        a1 += w * u[EN + j];
-        a2 += w * u[2 * EN + j];
+        s[0] += w * u[j];
+        s[1] += w * u[EN + j];
+        s[2] += w * u[2 * EN + j];
     }
-    // element x of the four (no register indexed at run time)
+}
+
+// Bit x: row i0 + x of an env's four rows is a passive node of the patch.
+__device__ __forceinline__ unsigned passive_rows(const StepParams &p, int e, int w0, int i0, int n) {
+    if (e < 0 || i0 >= n) return 0u;
+    const unsigned act = (unsigned)(p.itm.mask[(size_t)e * p.tile.NW + w0 + (i0 >> 6)] >> (i0 & 63));
+    return ~act & (n - i0 >= 4 ? 0xfu : (1u << (n - i0)) - 1u);
+}
+
+// The rows of `todo` summed pair by pair (no register indexed at run time).
+__device__ void pair_rows(const StepParams &p, int k, int e, int i0, unsigned todo, const float *src, doublex4 (&a)[3]) {
+    for (; todo; todo &= todo - 1) {
+        const int row = __ffs(todo) - 1;
+        double s[3];
+        pair_sum(p, k, e, i0 + row, src, s);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-        if (t == x) { s[0][t] = (float)a0; s[1][t] = (float)a1; s[2][t] = (float)a2; }
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) a[c][x] = x == row ? s[c] : a[c][x];
+    }
 }
 
 // Residual of NT envs on the four nodes whose decoder rows z points at, over
@@ -606,12 +622,11 @@ __device__ __forceinline__ void stage_w5(const StepParams &p, float (*w5)[64], f
 
 // U of four consecutive nodes of one env: decay part a, residual r; active
 // nodes (their bits) and rows beyond the patch are left alone.
-__device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, int left, const floatx4 (&a)[3],
+__device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, int left, const doublex4 (&a)[3],
                                            const floatx4 (&r)[3], bool dec, bool res) {
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        floatx4 v = dec ? a[c] : r[c];
-        if (dec && res) v += r[c];
+        const floatx4 v = dec ? __builtin_convertvector(res ? a[c] + widen(r[c]) : a[c], floatx4) : r[c];
         if (act == 0 && left >= 4) {
             __builtin_memcpy(o + c * EN, &v, 16);
         } else {
@@ -625,10 +640,11 @@ __device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, in
 // Wide tiles: 64 MT rows (a wave takes MT row tiles) times 32 envs (two column
 // tiles per component: column l & 15 is an env).  Bound by the matrix cores in
 // the loop (4096 hands: 17.8 M MFMAs, 116 us of all of them at full rate) and by
-// the VALU in the epilogue (five operations per node, env and channel of the
-// residual): 387 us.  A taller tile reads and splits each env's values for more
-// rows; patches are padded to it and there are fewer units, so it pays once
-// there are many.
+// the VALU: the FP64 sums there, and five operations per node, env and channel
+// of the residual in the epilogue.  A taller tile reads and splits each env's
+// values for more rows; patches are padded to it and there are fewer units, so it
+// pays once there are many: 4096 hands 530 us at MT = 1 and 410 at MT = 2, 16384
+// hands 2020 and 1520 (three row tiles would not fit the registers).
 constexpr int kWideEnvs = 32;
 
 struct WideLds {
@@ -673,13 +689,13 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         env[0] = L.env[col];
         env[1] = L.env[16 + col];
         const int row0 = rb * kRows + wave * 16 * MT;
-        floatx4 acc[MT][2][3];
+        doublex4 acc[MT][2][3];
 #pragma unroll
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int c = 0; c < 3; ++c) acc[m][t][c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int c = 0; c < 3; ++c) acc[m][t][c] = doublex4{0.0, 0.0, 0.0, 0.0};
         const bool slow = matrix_overflows(M, p.model.alpha[k], k);
         if (dec && !slow) {
             const int mine = 16 * (wave & 1) + col, myenv = L.env[mine], safe = max(myenv, 0);
@@ -691,8 +707,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
                 const int mt = min((row0 >> 4) + m, ((n + 15) >> 4) - 1);      // rows beyond the patch repeat its last tile
                 wa[m] = p.tab.w + T.w_off[k] + (size_t)mt * KS * 3 * 64 + lane;
             }
-            product_loop<MT, false>(L.b, wa, src, at, EN, mask, myenv >= 0, n, KS, acc);
+            product_loop<MT, false, 1>(L.b, wa, src, at, EN, mask, myenv >= 0, n, KS, acc);
         }
+        if (dec && slow)
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const int i0 = row0 + 16 * m + 4 * gq;
+                    pair_rows(p, k, env[t], i0, passive_rows(p, env[t], w0, i0, n), src, acc[m][t]);
+                }
         __syncthreads();      // L.b is done with
         if (res) {
             stage_w5(p, L.w5, L.b5);
@@ -723,12 +747,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
                 const int e = env[t];
                 if (e < 0 || i0 >= n) continue;
                 const unsigned act = (unsigned)(p.itm.mask[(size_t)e * T.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
-                if (dec && slow)
-#pragma unroll
-                    for (int x = 0; x < 4; ++x)
-                        if (i0 + x < n) pair_sum(p, k, e, i0 + x, src, acc[m][t], x);
                 store_rows(p.u + (size_t)e * N + base + i0, EN, act, n - i0, acc[m][t], r[t], dec, res);
             }
+            __builtin_amdgcn_sched_barrier(0);      // one row tile's operands at a time
         }
     }
 }
@@ -739,7 +760,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 struct NarrowLds {
     int first[kMaxPatches + 1];
     alignas(16) float w5[3][64], b5[4];
-    floatx4 part[kWaves][3][64];
+    doublex4 part[kWaves][3][64];
     floatx4 rpart[kWaves][3][64];
 };
 ETAC_LDS_ALIGNED(NarrowLds, w5);
@@ -769,11 +790,12 @@ __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
         int e = g0 + col < cnt ? live_env(p, k, g0 + col) : -1;
         if (e >= 0 && p.dense && na[(size_t)e * K + k] == 0) e = -1;
         if (!__ballot(e >= 0)) continue;      // the same in every wave
-        floatx4 acc[3], r[3];
+        doublex4 acc[3];
+        floatx4 r[3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            acc[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-            r[c] = acc[c];
+            acc[c] = doublex4{0.0, 0.0, 0.0, 0.0};
+            r[c] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
         }
         const bool slow = matrix_overflows(M, p.model.alpha[k], k);
         if (dec && !slow) {
@@ -807,7 +829,7 @@ __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
                 }
                 if (s + kWaves < KS) fetch(s + kWaves);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) acc[c] = mfma_bf16x3(y, b[c], acc[c]);
+                for (int c = 0; c < 3; ++c) acc[c] += widen(mfma_bf16x3(y, b[c], floatx4{0.0f, 0.0f, 0.0f, 0.0f}));
             }
         }
         const int i0 = 16 * mt + 4 * gq;
@@ -842,10 +864,7 @@ __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
                 }
             }
             const unsigned act = (unsigned)(p.itm.mask[(size_t)e * T.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
-            if (dec && slow)
-#pragma unroll
-                for (int x = 0; x < 4; ++x)
-                    if (i0 + x < n) pair_sum(p, k, e, i0 + x, src, acc, x);
+            if (dec && slow) pair_rows(p, k, e, i0, passive_rows(p, e, w0, i0, n), src, acc);
             store_rows(p.u + (size_t)e * N + base + i0, EN, act, n - i0, acc, r, dec, res);
         }
     }

@@ -712,7 +712,17 @@ __device__ __forceinline__ floatx4 mfma_bf16(const bf16x8 &a, const bf16x8 &b, f
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// acc += A B with three-part operands: every product of parts down to 2^-24 of
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ doublex4 widen(floatx4 v) { return __builtin_convertvector(v, doublex4); }
+
+__device__ __forceinline__ void pin(doublex4 &v, int x) {
+    double t = v[x];
+    asm volatile("" : "+v"(t));
+    v[x] = t;
+}
+
+// acc + A B with three-part operands: every product of parts down to 2^-24 of
 // the whole, smallest first.
 __device__ __forceinline__ floatx4 mfma_bf16x3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx4 acc) {
     acc = mfma_bf16(a[2], b[0], acc);
@@ -739,20 +749,20 @@ __device__ __forceinline__ void load8(const float *x, int j0, int n, float (&v)[
 
 // A wave's share of a product of NA row tiles of decay matrices with 32 envs'
 // values (two column tiles of three components): acc[m][t][c] over all K steps
-// of 32 nodes.  The workgroup's four waves split the B fragments of two K steps
-// (this wave's: step wave / 2, column tile wave % 2) into LDS while the MFMAs
-// of the two before run, the MFMAs of one K step with the splits between them:
-// an MFMA takes 16 cycles, 12 of which a SIMD has for other instructions.  A
-// fragments come from L2 a step ahead, values two pairs ahead.  `me`, `mask`:
+// of 32 nodes, the FP32 sum of a step added in FP64.  The workgroup's four waves
+// split the B fragments of two K steps (this wave's: step wave / 2, column tile
+// wave % 2) into LDS while the MFMAs of the two before run.  An MFMA takes 16
+// cycles, 12 of which a SIMD has for other instructions: a tile's sum is added
+// under the next tile's MFMAs, and the splits are spread over the second step's.
+// A fragments come from L2 AHEAD steps ahead, values two pairs ahead.  `mask`:
 // this lane's env (has: there is one); PASSIVE takes the nodes without contact.
 // Whole workgroup; ends before the last pair's reads of B are done.
 using ProductB = uint4[2][2][6][3][64];      // [buffer][K step][3 column tile + component][part][lane]
 
-template <int NA, bool PASSIVE>
+template <int NA, bool PASSIVE, int AHEAD>
 __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&wa)[NA], const float *src, size_t at, size_t EN,
                                              const unsigned long long *mask, bool has, int n, int KS,
-                                             floatx4 (&acc)[NA][2][3]) {
-    constexpr int P = 3, kProducts = 6;
+                                             doublex4 (&acc)[NA][2][3]) {
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), gq = lane >> 4;
     float raw[3][8];
     unsigned long long word = 0;
@@ -780,81 +790,78 @@ __device__ __forceinline__ void product_loop(ProductB &B, const uint4 *const (&w
                 raw[2][e] = v;
             }
     };
-    auto put = [&](int buf) {
+    auto put = [&](int buf, int c) {
         const int left = has ? max(min(n - j0, 8), 0) : 0;
         const unsigned bits = (unsigned)((PASSIVE ? ~word : word) >> (j0 & 63)) & ((1u << left) - 1u);
+        uint4(&o)[3][64] = B[buf][wave >> 1][3 * (wave & 1) + c];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            uint4(&o)[3][64] = B[buf][wave >> 1][3 * (wave & 1) + c];
+        for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
+        bf16x8 b[3];
+        split_bf16x3(raw[c], b);
 #pragma unroll
-            for (int x = 0; x < 8; ++x) raw[c][x] = (bits >> x) & 1u ? raw[c][x] : 0.0f;
-            bf16x8 b[3];
-            split_bf16x3(raw[c], b);
-#pragma unroll
-            for (int y = 0; y < 3; ++y) o[y][lane] = __builtin_bit_cast(uint4, b[y]);
-        }
+        for (int y = 0; y < 3; ++y) o[y][lane] = __builtin_bit_cast(uint4, b[y]);
     };
-    uint4 a[2][NA][P];
-    auto fetch_a = [&](int s, uint4 (&x)[NA][P]) {
+    uint4 ab[AHEAD][NA][3];
+    auto fetch_a = [&](int s, uint4 (&a)[NA][3]) {
 #pragma unroll
         for (int m = 0; m < NA; ++m)
 #pragma unroll
-            for (int c = 0; c < P; ++c) x[m][c] = wa[m][(size_t)(s * P + c) * 64];
+            for (int c = 0; c < 3; ++c) a[m][c] = wa[m][(size_t)(s * 3 + c) * 64];
     };
-    auto mul = [&](int buf, int ds, const uint4 (&x)[NA][P]) {
-        uint4 b[2][P];
+    auto mul = [&](int buf, int ds, const uint4 (&a)[NA][3]) {
+        uint4 b[2][3];
+        floatx4 o[2][NA];
+        auto fold = [&](int f) {
 #pragma unroll
-        for (int c = 0; c < P; ++c) b[0][c] = B[buf][ds][0][c][lane];
+            for (int m = 0; m < NA; ++m) {
+                doublex4 &s = acc[m][f / 3][f % 3];
+                s += widen(o[f & 1][m]);
+                // added here, not where the loop ends: the products of a step would all stay in registers
+#pragma unroll
+                for (int x = 0; x < 4; ++x) pin(s, x);
+            }
+        };
+#pragma unroll
+        for (int c = 0; c < 3; ++c) b[0][c] = B[buf][ds][0][c][lane];
 #pragma unroll
         for (int f = 0; f < 6; ++f) {
             if (f < 5)
 #pragma unroll
-                for (int c = 0; c < P; ++c) b[(f + 1) & 1][c] = B[buf][ds][f + 1][c][lane];
+                for (int c = 0; c < 3; ++c) b[(f + 1) & 1][c] = B[buf][ds][f + 1][c][lane];
 #pragma unroll
             for (int m = 0; m < NA; ++m) {
-                floatx4 &o = acc[m][f / 3][f % 3];
                 bf16x8 y[3], z[3];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    y[c] = __builtin_bit_cast(bf16x8, x[m][c]);
+                    y[c] = __builtin_bit_cast(bf16x8, a[m][c]);
                     z[c] = __builtin_bit_cast(bf16x8, b[f & 1][c]);
                 }
-                o = mfma_bf16x3(y, z, o);
+                o[f & 1][m] = mfma_bf16x3(y, z, floatx4{0.0f, 0.0f, 0.0f, 0.0f});
             }
+            if (f) fold(f - 1);
+            if (ds && !(f & 1)) put(buf ^ 1, f / 2);
+#pragma unroll
+            for (int i = 0; i < 6 * NA; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
+        fold(5);
     };
     fetch(0);
-    fetch_a(0, a[0]);
-    fetch_a(min(1, KS - 1), a[1]);
-    put(0);
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) fetch_a(min(s, KS - 1), ab[s]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) put(0, c);
     fetch(2);
     for (int s0 = 0, buf = 0; s0 < KS; s0 += 2, buf ^= 1) {
         __syncthreads();          // this pair is in B[buf]; the other buffer is free
         // a step beyond the last has zeros in B
-        mul(buf, 0, a[0]);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * P, 0);
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-            __builtin_amdgcn_sched_group_barrier(0x008, kProducts * NA, 0);
-            if (f < 4) __builtin_amdgcn_sched_group_barrier(0x100, P, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_a(min(s0 + 2, KS - 1), a[0]);
-        mul(buf, 1, a[1]);
-        put(buf ^ 1);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2 * P, 1);
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-#pragma unroll
-            for (int i = 0; i < kProducts * NA; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
-                __builtin_amdgcn_sched_group_barrier(0x002, 6 / NA, 1);
-            }
-            if (f < 4) __builtin_amdgcn_sched_group_barrier(0x100, P, 1);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x200, 3 * P, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch_a(min(s0 + 3, KS - 1), a[1]);
+        mul(buf, 0, ab[0]);
+        fetch_a(min(s0 + AHEAD, KS - 1), ab[0]);
+        mul(buf, 1, ab[AHEAD - 1]);
+        fetch_a(min(s0 + 1 + AHEAD, KS - 1), ab[AHEAD - 1]);
         fetch(s0 + 4);
     }
 }
