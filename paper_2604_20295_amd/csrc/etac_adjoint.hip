@@ -372,12 +372,13 @@ __global__ __launch_bounds__(kWG) void k_adj_far(AdjParams p) {
 
 // A wave takes 32 consecutive nodes (a half word) and the envs of one chunk in
 // contact on their patch; lane c holds channel c: W4 f of the 32 nodes and the
-// sums of dL/dpre4 over the envs stay in registers, the nodes' g are broadcast
-// from LDS.  Twelve VALU operations per env, passive node and channel; VALU-bound.
+// sums of dL/dpre4 over the envs stay in registers (FP64, as every sum over
+// envs), the nodes' g are broadcast from LDS.  Thirteen VALU operations per env,
+// passive node and channel; VALU-bound.
 struct PassLds {
     int first[kMaxPatches + 1];
     float4 g[kWaves][2][32];
-    float w5[kWaves][256];
+    double w5[kWaves][256];
 };
 
 __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
@@ -403,13 +404,14 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
         const int hw = 4 * nb + wave, i0 = 32 * hw;
         const int w0 = uniform(T.word_off[k]), left = max(0, min(32, n - i0));
         const unsigned all = left >= 32 ? ~0u : (1u << left) - 1u;
-        float z[32], s[32];
+        float z[32];
+        double s[32];
 #pragma unroll
         for (int i = 0; i < 32; ++i) {
             z[i] = S.tab.dec[(size_t)(base + min(i0 + i, n - 1)) * 64 + lane];
-            s[i] = 0.0f;
+            s[i] = 0.0;
         }
-        float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, b0 = 0.0f, b1 = 0.0f, b2 = 0.0f;
+        double w0s = 0.0, w1s = 0.0, w2s = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
         const int q0 = ch * EC, q1 = left ? min(cnt, q0 + EC) : q0;      // a wave beyond the patch has nothing to add
         // the next env's operands are requested while this one's are used
         float g0, g1, g2, c4;
@@ -433,13 +435,13 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
             if (lane < 32) {
                 const bool on = (pas >> lane) & 1u;
                 L.g[wave][buf][lane] = make_float4(g0, g1, g2, 0.0f);
-                b0 += on ? g0 : 0.0f;
-                b1 += on ? g1 : 0.0f;
-                b2 += on ? g2 : 0.0f;
+                b0 += (double)(on ? g0 : 0.0f);
+                b1 += (double)(on ? g1 : 0.0f);
+                b2 += (double)(on ? g2 : 0.0f);
             }
             wave_sync();
             if (qq + 1 < q1) fetch(qq + 1);
-            float s4 = 0.0f;
+            float s4 = 0.0f, a0 = 0.0f, a1 = 0.0f, a2 = 0.0f;      // over the nodes of one item
 #pragma unroll
             for (int i = 0; i < 32; ++i) {
                 if (!((pas >> i) & 1u)) continue;      // wave-uniform
@@ -448,15 +450,18 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
                 const float h = relu1(t);
                 const float v = w50 * g.x + w51 * g.y + w52 * g.z;
                 const float d = t > 0.0f ? v : 0.0f;
-                s[i] += d;
+                s[i] += (double)d;
                 s4 += d;
                 a0 += g.x * h;
                 a1 += g.y * h;
                 a2 += g.z * h;
             }
             p.b.s4_part[((size_t)ce * 2 * T.NW + 2 * w0 + hw) * 64 + lane] = s4;
+            w0s += (double)a0;
+            w1s += (double)a1;
+            w2s += (double)a2;
         }
-        float *so = p.b.s4_node + ((size_t)ch * N + base + i0) * 64 + lane;
+        double *so = p.b.s4_node + ((size_t)ch * N + base + i0) * 64 + lane;
 #pragma unroll
         for (int i = 0; i < 32; ++i)
             if (i < left) so[(size_t)i * 64] = s[i];
@@ -467,12 +472,12 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
             b2 += __shfl_xor(b2, off);
         }
         __syncthreads();      // the previous unit's sums are read
-        L.w5[wave][lane] = a0;
-        L.w5[wave][64 + lane] = a1;
-        L.w5[wave][128 + lane] = a2;
-        L.w5[wave][192 + lane] = lane == 0 ? b0 : lane == 1 ? b1 : lane == 2 ? b2 : 0.0f;
+        L.w5[wave][lane] = w0s;
+        L.w5[wave][64 + lane] = w1s;
+        L.w5[wave][128 + lane] = w2s;
+        L.w5[wave][192 + lane] = lane == 0 ? b0 : lane == 1 ? b1 : lane == 2 ? b2 : 0.0;
         __syncthreads();
-        float v = L.w5[0][threadIdx.x];
+        double v = L.w5[0][threadIdx.x];
         for (int w = 1; w < kWaves; ++w) v += L.w5[w][threadIdx.x];
         p.b.w5_part[((size_t)ch * T.NB5 + uniform(T.blk5_off[k]) + nb) * 256 + threadIdx.x] = v;
     }
@@ -486,10 +491,10 @@ __global__ __launch_bounds__(kWG) void k_adj_passive(AdjParams p) {
 // dpre3 = dg' [g' > 0], dg = W3^T dpre3, and the inputs of the channel's
 // arg-max node.  Then lane f holds feature f: h1 of every channel's node, and
 // from dL/dpre2 = dg_c [g_c > 0] e_c its shares of dW2, dW1 and db1, summed in
-// registers over the wave's items.  Then again by channels: W1^T dL/dpre1
+// registers over the wave's items, in FP64.  Then again by channels: W1^T dL/dpre1
 // reaches u_hat of active arg-max nodes.  An item is one dependent chain, so
 // the weights are in LDS and everything it reads is requested first (4096
-// hands: 161 us with weights from L2 and loads in turn, 125 us).
+// hands: 161 us with weights from L2 and loads in turn, 102 us).
 struct ItemLds {
     alignas(16) float w1u[64][4];     // W1[:, 6..8]
     float x[kWaves][64][12];          // inputs of the channels' nodes, then the routed gradient
@@ -500,7 +505,7 @@ struct ItemLds {
             float w2[64][65];         // W2, rows and columns read without bank conflicts
             float w3[64][64], w4[64][64];      // W3, W4[:, 64:]
         };
-        float sum[kRouteWords];       // after the items
+        double sum[kRouteWords];      // after the items
     };
 };
 ETAC_LDS_ALIGNED(ItemLds, w1u);
@@ -545,11 +550,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int c = 0; c < 9; ++c) w1[c] = phi[kW1 + lane * 9 + c];
     const float bias1 = phi[kB1 + lane];
-    float acc2[64], accx[10], accb2 = 0.0f;
+    double acc2[64], accx[10], accb2 = 0.0;      // over the wave's items
 #pragma unroll
-    for (int c = 0; c < 64; ++c) acc2[c] = 0.0f;
+    for (int c = 0; c < 64; ++c) acc2[c] = 0.0;
 #pragma unroll
-    for (int c = 0; c < 10; ++c) accx[c] = 0.0f;
+    for (int c = 0; c < 10; ++c) accx[c] = 0.0;
     for (int q = blockIdx.x * kWaves + wave; q < total; q += gridDim.x * kWaves) {
         const int kk = unit_rank(first, K, q), k = uniform(M.order[kk]);
         const int e = uniform(live_env(S, k, q - uniform(first[kk])));
@@ -593,7 +598,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
         iv[128] = dp3;
         const float vr = (ok && g > 0.0f) ? dg : 0.0f;
         const bool act = ok && ((am >> (a & 63)) & 1ull);
-        accb2 += vr;
+        accb2 += (double)vr;
         wave_sync();
         {
             float *o = L.x[wave][lane];
@@ -602,6 +607,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             *reinterpret_cast<floatx2 *>(o + 8) = floatx2{act ? x[8] : 0.0f, vr};
         }
         wave_sync();
+        float sx[10];      // this item's
+#pragma unroll
+        for (int c = 0; c < 10; ++c) sx[c] = 0.0f;
 #pragma unroll
         for (int c = 0; c < 64; ++c) {
             const float w2c = L.w2[c][lane];      // read whether used or not: no branch
@@ -612,15 +620,17 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             h += w1[0] * xa[0]; h += w1[1] * xa[1]; h += w1[2] * xa[2]; h += w1[3] * xa[3];
             h += w1[4] * xb[0]; h += w1[5] * xb[1]; h += w1[6] * xb[2]; h += w1[7] * xb[3];
             h += w1[8] * x8;
-            acc2[c] += v * relu1(h);
+            acc2[c] += (double)(v * relu1(h));
             const float d = h > 0.0f ? v * w2c : 0.0f;
-            accx[0] += d * xa[0]; accx[1] += d * xa[1]; accx[2] += d * xa[2]; accx[3] += d * xa[3];
-            accx[4] += d * xb[0]; accx[5] += d * xb[1]; accx[6] += d * xb[2]; accx[7] += d * xb[3];
-            accx[8] += d * x8;
-            accx[9] += d;
+            sx[0] += d * xa[0]; sx[1] += d * xa[1]; sx[2] += d * xa[2]; sx[3] += d * xa[3];
+            sx[4] += d * xb[0]; sx[5] += d * xb[1]; sx[6] += d * xb[2]; sx[7] += d * xb[3];
+            sx[8] += d * x8;
+            sx[9] += d;
             L.gate[wave][c] = __ballot(h > 0.0f);      // every lane stores the same value
             if ((c & 7) == 7) reload_fence();      // eight channels' operands in flight, not all 64
         }
+#pragma unroll
+        for (int c = 0; c < 10; ++c) accx[c] += (double)sx[c];
         if (__ballot(act && vr != 0.0f)) {
             wave_sync();
             const unsigned long long gate = L.gate[wave][lane];
@@ -661,11 +671,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int w = 0; w < kWaves; ++w) {
         if (w == wave) {
 #pragma unroll
-            for (int c = 0; c < 64; ++c) L.sum[c * 64 + lane] = (w ? L.sum[c * 64 + lane] : 0.0f) + acc2[c];
+            for (int c = 0; c < 64; ++c) L.sum[c * 64 + lane] = (w ? L.sum[c * 64 + lane] : 0.0) + acc2[c];
 #pragma unroll
             for (int c = 0; c < 10; ++c)
-                L.sum[4096 + c * 64 + lane] = (w ? L.sum[4096 + c * 64 + lane] : 0.0f) + accx[c];
-            L.sum[4736 + lane] = (w ? L.sum[4736 + lane] : 0.0f) + accb2;
+                L.sum[4096 + c * 64 + lane] = (w ? L.sum[4096 + c * 64 + lane] : 0.0) + accx[c];
+            L.sum[4736 + lane] = (w ? L.sum[4736 + lane] : 0.0) + accb2;
         }
         __syncthreads();
     }
@@ -854,7 +864,7 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
         const int c = col - kRedRoute;
         if (c < kRouteWords) {
 #pragma unroll 4
-            for (long long u = a; u < b; ++u) acc += (double)p.b.route[u * kRouteWords + c];
+            for (long long u = a; u < b; ++u) acc += p.b.route[u * kRouteWords + c];
         }
     } else if (first == kRedItem) {
         // items in contact, listed 1024 at a time
@@ -929,9 +939,9 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
         for (long long h = a; h < b; ++h) {
             while (T.blk5_off[k + 1] <= h) ++k;
             const int chunks = (live_count(S, k) + EC - 1) / EC;
-            const float *w = p.b.w5_part + (size_t)h * 256 + c;
+            const double *w = p.b.w5_part + (size_t)h * 256 + c;
 #pragma unroll 8
-            for (int t = 0; t < chunks; ++t) acc += (double)w[(size_t)t * T.NB5 * 256];
+            for (int t = 0; t < chunks; ++t) acc += w[(size_t)t * T.NB5 * 256];
         }
     }
     p.b.seg[(size_t)s * kRedCols + col] = acc;
@@ -1084,7 +1094,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     f.saved = saved ? nullptr : pl.bwd.record;
     shape_step(pl, f);
     p.b = pl.bwd;
-    p.env_chunk = n_envs >= kEnvChunkSwitch ? kEnvChunk : kEnvChunkSmall;
+    p.env_chunk = env_chunk(n_envs, pl.tile.NB5);
     p.O = s ? s->O : 1;
     p.grad_u = grad_u;
     p.gh = s ? pl.bwd.gh : grad_uhat;
@@ -1111,7 +1121,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     const int route_groups = (int)blocks((items + kWaves - 1) / kWaves, kRouteGroups * cus);
     if (res) {
         launch_pool(pl, f, st);
-        hipLaunchKernelGGL(k_adj_passive, dim3(blocks((f.words / 2 + items) / p.env_chunk + pl.tile.NU + 1, 4 * cus)), dim3(kWG), 0, st, p);
+        hipLaunchKernelGGL(k_adj_passive, dim3(blocks((f.words / 2 + items) / p.env_chunk + pl.tile.NU + 1, 3 * cus)), dim3(kWG), 0, st, p);
         hipLaunchKernelGGL(k_adj_item, dim3(route_groups), dim3(kWG), 0, st, p);
         const hipError_t e = launch_adj_nodes(p, (int)blocks(pl.tile.NU, cus), st);
         if (e != hipSuccess) return e;

@@ -408,10 +408,12 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess && (flags & ETAC_PLAN_BACKWARD)) {
         etac::BwdScratch &b = p.bwd;
         const size_t EN = (size_t)n_envs * N;
-        // chunks of the largest batch: full-size chunks, or small ones of the batches below the switch
-        const int small = std::min(n_envs, etac::kEnvChunkSwitch - 1);
-        b.chunks = std::max((n_envs + etac::kEnvChunk - 1) / etac::kEnvChunk,
-                            (small + etac::kEnvChunkSmall - 1) / etac::kEnvChunkSmall);
+        // the most chunks of any batch: of the largest, or of the last one with shorter chunks
+        b.chunks = 1;
+        for (const int most : {255, 1023, n_envs}) {
+            const int E = std::min(n_envs, most), c = etac::env_chunk(E, tile.NB5);
+            b.chunks = std::max(b.chunks, (E + c - 1) / c);
+        }
         e = plan_alloc(p, &b.cobj_st, EN);
         if (e == hipSuccess) e = plan_alloc(p, &b.uhat_st, 3 * EN);
         if (e == hipSuccess) e = plan_alloc(p, &b.gh, 3 * EN);

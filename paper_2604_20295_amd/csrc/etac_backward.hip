@@ -419,13 +419,12 @@ __global__ __launch_bounds__(kWG) void k_adj_nodes(AdjParams p) {
             const int j = i >> 4, c = 4 * (i & 15);
             floatx4 o = {0.0f, 0.0f, 0.0f, 0.0f};
             if (j < cnt) {
-                const float *src = p.b.s4_node + (size_t)(base + i0 + j) * 64 + c;
+                const double *src = p.b.s4_node + (size_t)(base + i0 + j) * 64 + c;
                 double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 8
                 for (int t = 0; t < chunks; ++t) {
-                    const floatx4 v = *reinterpret_cast<const floatx4 *>(src + (size_t)t * N * 64);
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) a[x] += (double)v[x];
+                    for (int x = 0; x < 4; ++x) a[x] += src[(size_t)t * N * 64 + x];
                 }
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {

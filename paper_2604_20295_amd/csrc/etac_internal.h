@@ -154,8 +154,12 @@ struct ModelDev {
     const float *phi;      // [17411] or null in decay-only mode
 };
 
-// Envs per chunk of the passive network adjoint.
-constexpr int kEnvChunk = 32, kEnvChunkSmall = 8, kEnvChunkSwitch = 256;
+// Envs per chunk of the passive network adjoint, by the envs of the call and the
+// surface's 128-node blocks.  A chunk's sums are written and read once, so long
+// chunks move less, as long as there is a unit for every CU: 4096 hands, the
+// pass and the one that reads its sums 315 us at 32, 302 at 48; 301 hands of 16
+// patches 94 us at 32, 65 at 16.  Blocks alone fill the chip on large surfaces.
+inline int env_chunk(int E, int blocks) { return E >= 1024 ? 48 : E >= 256 || blocks >= 512 ? 16 : 8; }
 
 // Adjoint scratch (plan flag ETAC_PLAN_BACKWARD).
 struct BwdScratch {
@@ -164,16 +168,16 @@ struct BwdScratch {
     float *gh;             // [3][E][N] dL/du_hat of active nodes (step adjoint)
     double *alpha_part;    // [E][NP]   dL/dalpha of every part of Eq. 1
     float *s4_part;        // [E][2 NW][64] sum of dL/dpre4 over the passive nodes of a half word
-    float *s4_node;        // [chunks][N][64] sum of dL/dpre4 over a chunk's envs, per node
-    float *w5_part;        // [chunks][NB5][256] dW5 (192), db5 (3) of 128 nodes and a chunk
+    double *s4_node;       // [chunks][N][64] sum of dL/dpre4 over a chunk's envs, per node
+    double *w5_part;       // [chunks][NB5][256] dW5 (192), db5 (3) of 128 nodes and a chunk
     float *ivec;           // [E K][4][64] s4, g', dpre3, g per item
     uint32_t *record;      // [E K][kSavedWords] the adjoint's own pooling record
-    float *route;          // [workgroups][kRouteWords] parameter gradients of the max-pool's routes
+    double *route;         // [workgroups][kRouteWords] parameter gradients of the max-pool's routes
     float *node_rec;       // [NU][kNodeRecWords] parameter gradients of a block of nodes
     double *alpha_seg;     // [K][kAlphaSegs]
     double *seg;           // [kPhiSegs][kRedCols] segment sums of the parameter reduction
     float *pose_part;      // [E][NC][O][12] pose-gradient parts
-    int chunks;            // chunks s4_node and w5_part hold
+    int chunks;            // chunks s4_node and w5_part hold, of any batch the plan takes
 };
 
 // Event pairs bracketing kernel launches (etac_plan_set_timing).
