@@ -92,7 +92,7 @@ __device__ __forceinline__ double finish_rows(const AdjParams &p, int k, int e, 
     const size_t EN = (size_t)p.s.E * N, at = (size_t)e * N + base + i0;
     // bits beyond the patch are clear
     const unsigned act = (unsigned)(p.s.itm.mask[(size_t)e * p.s.tile.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
-    if (dec && slow) pair_rows(p, k, e, i0, act, q, qd);
+    if (dec && (slow || not_finite(q) || not_finite(qd))) pair_rows(p, k, e, i0, act, q, qd);
     const float *u = uhat_source(p.s) + at;
     double da = 0.0;
 #pragma unroll

@@ -709,13 +709,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
             }
             product_loop<MT, false, 1>(L.b, wa, src, at, EN, mask, myenv >= 0, n, KS, acc);
         }
-        if (dec && slow)
+        if (dec)
 #pragma unroll
             for (int m = 0; m < MT; ++m)
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     const int i0 = row0 + 16 * m + 4 * gq;
-                    pair_rows(p, k, env[t], i0, passive_rows(p, env[t], w0, i0, n), src, acc[m][t]);
+                    if (slow || not_finite(acc[m][t]))
+                        pair_rows(p, k, env[t], i0, passive_rows(p, env[t], w0, i0, n), src, acc[m][t]);
                 }
         __syncthreads();      // L.b is done with
         if (res) {
@@ -864,7 +865,7 @@ __global__ __launch_bounds__(kWG) void k_prop_narrow(StepParams p) {
                 }
             }
             const unsigned act = (unsigned)(p.itm.mask[(size_t)e * T.NW + w0 + (i0 >> 6)] >> (i0 & 63)) & 0xfu;
-            if (dec && slow) pair_rows(p, k, e, i0, passive_rows(p, e, w0, i0, n), src, acc);
+            if (dec && (slow || not_finite(acc))) pair_rows(p, k, e, i0, passive_rows(p, e, w0, i0, n), src, acc);
             store_rows(p.u + (size_t)e * N + base + i0, EN, act, n - i0, acc, r, dec, res);
         }
     }

@@ -722,6 +722,18 @@ __device__ __forceinline__ void pin(doublex4 &v, int x) {
     v[x] = t;
 }
 
+// Whether a sum is infinite or NaN: the parts of an infinity, or of a value that
+// rounds to one, are not finite, and their products with a weight's parts no
+// longer add up to the product.  Such rows are summed pair by pair.
+__device__ __forceinline__ bool not_finite(const doublex4 (&a)[3]) {
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) s += a[c][x];
+    return !(fabs(s) <= 1.7976931348623157e308);
+}
+
 // acc + A B with three-part operands: every product of parts down to 2^-24 of
 // the whole, smallest first.
 __device__ __forceinline__ floatx4 mfma_bf16x3(const bf16x8 (&a)[3], const bf16x8 (&b)[3], floatx4 acc) {
