@@ -79,10 +79,10 @@ struct HandSceneParams {
 constexpr int kSceneLanes = 32;
 static_assert(ETAC_MAX_OBJ + ETAC_MAX_LINKS <= kSceneLanes, "a lane per candidate");
 
-__global__ __launch_bounds__(256) void k_hand_scene(HandSceneParams p) {
+__global__ __launch_bounds__(256) void k_hand_scene(HandSceneParams p, long long group0) {
     const int t = threadIdx.x & (kSceneLanes - 1);
-    const int at = blockIdx.x * (256 / kSceneLanes) + threadIdx.x / kSceneLanes;
-    const int item = min(at, p.n_items - 1);      // whole half waves beyond the last repeat it, without stores
+    const long long at = (group0 + blockIdx.x) * (256 / kSceneLanes) + threadIdx.x / kSceneLanes;
+    const int item = (int)min(at, (long long)p.n_items - 1);      // whole half waves beyond the last repeat it, without stores
     const MeshDev &M = p.mesh;
     const HandDev &H = p.hand;
     const int K = M.K, L = H.L, O = p.world.O;
@@ -141,7 +141,9 @@ hipError_t launch_hand_scene(const Plan &pl, const SceneDev &world, const LinksD
     rows->src = H.src;
     rows->n_ext = H.n_ext;
     if (p.n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hand_scene, dim3((p.n_items + 256 / kSceneLanes - 1) / (256 / kSceneLanes)), dim3(256), 0, st, p);
+    launch_slices(((long long)p.n_items + 256 / kSceneLanes - 1) / (256 / kSceneLanes), [&](long long first, dim3 grid) {
+        hipLaunchKernelGGL(k_hand_scene, grid, dim3(256), 0, st, p, first);
+    });
     return hipGetLastError();
 }
 

@@ -218,6 +218,15 @@ struct Plan {
     int *reg_cnt;          // [K]
 };
 
+// Workgroups of a launch whose grid grows with the batch: a launch holds fewer
+// than 2^32 threads, so larger grids go in slices of this many.
+constexpr long long kMostGroups = 1 << 23;
+template <typename F>
+inline void launch_slices(long long groups, F launch) {
+    for (long long first = 0; first < groups; first += kMostGroups)
+        launch(first, dim3((unsigned)(groups - first < kMostGroups ? groups - first : kMostGroups)));
+}
+
 // Open a timed span of timer k on stream st; returns the slot, or -1 when
 // timing is off or the stream is being captured.
 inline int timer_begin(const Plan &p, int k, hipStream_t st) {

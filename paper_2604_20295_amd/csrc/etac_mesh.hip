@@ -525,11 +525,12 @@ struct MeshQuery {
 };
 
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_mesh_items(MeshContactParams p,
-                                                                                               int chunks) {
+                                                                                               int chunks, long long group0) {
     __shared__ MeshQuery res[kMeshNodes];
     __shared__ int list[kMeshNodes], total_s;
     __shared__ unsigned any;
-    const int e = blockIdx.x / chunks, i0 = (blockIdx.x - e * chunks) * kMeshNodes;
+    const long long group = group0 + blockIdx.x;
+    const int e = (int)(group / chunks), i0 = (int)(group - (long long)e * chunks) * kMeshNodes;
     const MeshDev &M = p.mesh;
     const SceneDev &S = p.scene;
     const int N = M.N, K = M.K, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
@@ -660,7 +661,9 @@ hipError_t launch_contact_mesh(const Plan &p, const MeshSetDev &ms, const SceneD
     MeshContactParams cp{p.mesh, s, ms, cobj, uhat, n_active, hit, nullptr, nullptr, nullptr, nullptr, nullptr};
     const int items = s.E * p.K, chunks = (p.N + kMeshNodes - 1) / kMeshNodes;
     hipLaunchKernelGGL(k_mesh_zero, dim3((items + 255) / 256), dim3(256), 0, st, n_active, items);
-    hipLaunchKernelGGL(k_mesh_items, dim3((unsigned)s.E * chunks), dim3(kWG), 0, st, cp, chunks);
+    launch_slices((long long)s.E * chunks, [&](long long first, dim3 grid) {
+        hipLaunchKernelGGL(k_mesh_items, grid, dim3(kWG), 0, st, cp, chunks, first);
+    });
     return hipGetLastError();
 }
 
