@@ -817,10 +817,20 @@ __global__ __launch_bounds__(256) void k_pose(AdjParams p, float *grad_rot, floa
     if (t >= p.s.E * O * 12) return;
     const int c = t % 12, eo = t / 12, o = eo % O, e = eo / O;
     double acc = 0.0;
-    for (int k = 0; k < K; ++k) {
-        if (p.s.itm.n_act[(size_t)e * K + k] == 0) continue;
-        for (int h = T.chunk_off[k]; h < T.chunk_off[k + 1]; ++h)
-            acc += (double)p.pose_part[(((size_t)e * T.NC + h) * O + o) * 12 + c];
+    for (int k0 = 0; k0 < K; k0 += 8) {
+        int n[8], h0[8], h1[8];      // eight patches' counts requested at once
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int k = min(k0 + t, K - 1);
+            n[t] = p.s.itm.n_act[(size_t)e * K + k];
+            h0[t] = T.chunk_off[k];
+            h1[t] = T.chunk_off[k + 1];
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (n[t] == 0 || k0 + t >= K) continue;
+            for (int h = h0[t]; h < h1[t]; ++h) acc += (double)p.pose_part[(((size_t)e * T.NC + h) * O + o) * 12 + c];
+        }
     }
     if (c < 9) grad_rot[(size_t)eo * 9 + c] = (float)acc;
     else grad_trans[(size_t)eo * 3 + (c - 9)] = (float)acc;
@@ -857,8 +867,14 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
     if (first < kRedRoute) {
         range(T.NU, a, b);
         if (col < kNodeRecWords)
-            for (long long u = a; u < b; ++u)
-                if (live_count(S, T.block[u].x) > 0) acc += (double)p.b.node_rec[u * kNodeRecWords + col];
+            for (long long u0 = a; u0 < b; u0 += 8) {
+                bool live[8];      // eight blocks' flags requested at once
+#pragma unroll
+                for (int t = 0; t < 8; ++t) live[t] = u0 + t < b && live_count(S, T.block[min(u0 + t, b - 1)].x) > 0;
+#pragma unroll
+                for (int t = 0; t < 8; ++t)
+                    if (live[t]) acc += (double)p.b.node_rec[(u0 + t) * kNodeRecWords + col];
+            }
     } else if (first < kRedItem) {
         range(route_groups, a, b);
         const int c = col - kRedRoute;
@@ -935,7 +951,13 @@ __global__ __launch_bounds__(256) void k_phi_segments(AdjParams p, int route_gro
     } else {
         range(T.NB5, a, b);
         const int c = col - kRedW5, EC = p.env_chunk;
+        // the patch of the segment's first block
         int k = 0;
+        for (int hi = K - 1; k < hi;) {
+            const int mid = (k + hi + 1) >> 1;
+            if (T.blk5_off[mid] <= a) k = mid;
+            else hi = mid - 1;
+        }
         for (long long h = a; h < b; ++h) {
             while (T.blk5_off[k + 1] <= h) ++k;
             const int chunks = (live_count(S, k) + EC - 1) / EC;

@@ -388,6 +388,11 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.n_act, EK);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.live, EK);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.live_cnt, (size_t)K);
+    const size_t split_envs = std::min(n_envs, etac::kSplitEnvs * p.cu_count);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.split_cnt, 2 * split_envs * K);
+    if (e == hipSuccess) e = plan_alloc(p, &p.itm.split_done, split_envs);
+    if (e == hipSuccess) e = hipMemset(p.itm.split_cnt, 0, 2 * split_envs * K * sizeof(int));
+    if (e == hipSuccess) e = hipMemset(p.itm.split_done, 0, split_envs * sizeof(unsigned));
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.pool, EK * 64);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.c4, EK * 64);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.alist, tile.n_far ? (size_t)n_envs * N : 1);
@@ -410,7 +415,7 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
         const size_t EN = (size_t)n_envs * N;
         // the most chunks of any batch: of the largest, or of the last one with shorter chunks
         b.chunks = 1;
-        for (const int most : {255, 1023, n_envs}) {
+        for (const int most : {255, 1023, 4095, n_envs}) {
             const int E = std::min(n_envs, most), c = etac::env_chunk(E, tile.NB5);
             b.chunks = std::max(b.chunks, (E + c - 1) / c);
         }

@@ -28,23 +28,14 @@ namespace etac {
 // ---------------------------------------------------------------------------
 template <bool FROM_INPUT, bool ROWS>
 __global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
-    __shared__ ContactLds L;
+    __shared__ ContactLds<ROWS> L;
     const int e = blockIdx.x / p.splits;
     contact_env<FROM_INPUT, ROWS>(p, L, e, blockIdx.x - e * p.splits);
 }
 
-// Tables, and zero counts where the contact pass adds to them.
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_tables(StepParams p) {
     __shared__ FeatLds L;
-    const int nt = p.table_units + p.matrix_units;
-    if (p.splits > 1) {
-        int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
-        for (size_t i = (size_t)blockIdx.x * kWG + threadIdx.x; i < (size_t)p.E * p.mesh.K; i += (size_t)gridDim.x * kWG) {
-            na[i] = 0;
-            if (p.n_touch) p.n_touch[i] = 0;
-        }
-    }
-    if ((int)blockIdx.x < nt) table_block(p, L, blockIdx.x);
+    table_block(p, L, blockIdx.x);
 }
 
 // Tables and contact in one launch: on small batches neither fills the chip
@@ -53,7 +44,7 @@ template <bool FROM_INPUT, bool ROWS>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_front(StepParams p) {
     __shared__ union {
         FeatLds feat;
-        ContactLds contact;
+        ContactLds<ROWS> contact;
     } L;
     const int nt = p.table_units + p.matrix_units;
     if ((int)blockIdx.x < nt) table_block(p, L.feat, blockIdx.x);
@@ -469,11 +460,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(3))) void k
     }
 }
 
-// The same in one launch, a workgroup of eight waves per item, for batches of
-// few small patches, where a launch costs more than the idle waves.  Latency-
+// The same in one launch, a workgroup of eight waves per item, in contact or not,
+// for batches of few items, where a launch costs more than the idle waves (24
+// hands, 384 items: 48 us in three launches, 19 us).  Latency-
 // bound: the layers of the global MLP are split over the waves, their weights
 // loaded at the start (one pad: 24.1 us with one wave reading them, 16.8 us).
-constexpr int kPoolWaves = 8, kPoolWords = 4;
+constexpr int kPoolWaves = 8, kPoolWords = 4, kPoolItems = 1024;
 
 struct PoolLds {
     unsigned long long key[64];
@@ -1056,7 +1048,7 @@ static void launch_contact_items(const StepParams &p, bool merged, int nt, hipSt
 // Workgroups per env of the contact pass: enough to fill the chip.
 static int contact_splits(const Plan &pl, int E) {
     int s = 1;
-    while (E * s < 4 * pl.cu_count && s * kWaves * 4 < pl.tile.NW) s *= 2;
+    while (E * s < kSplitEnvs * pl.cu_count && s * kWaves * 4 < pl.tile.NW) s *= 2;
     return s;
 }
 
@@ -1075,12 +1067,13 @@ hipError_t launch_contact_rows(const Plan &pl, const SceneDev &s, int8_t *cobj, 
     p.model = ModelDev{ETAC_DECAY_ONLY, nullptr, nullptr};
     p.E = s.E;
     p.splits = contact_splits(pl, s.E);
+    p.itm.split_cnt = pl.itm.split_cnt;
+    p.itm.split_done = pl.itm.split_done;
     p.u = uhat;
     p.cobj_out = cobj;
     p.n_active = n_active;
     p.n_touch = n_touch;
     const int slot = timer_begin(pl, ETAC_TIMER_CONTACT, st);
-    if (p.splits > 1) hipLaunchKernelGGL(k_tables, dim3(64), dim3(kWG), 0, st, p);      // counts to zero
     launch_contact_items<false>(p, false, 0, st);
     const hipError_t e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_CONTACT, slot, st);
@@ -1110,21 +1103,25 @@ void launch_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt
     hipLaunchKernelGGL(k_live, dim3(K), dim3(1024), 0, st, n_active, E, K, live, live_cnt);
 }
 
-void launch_front(const Plan &pl, const StepParams &p, hipStream_t st) {
+void launch_front(const Plan &pl, StepParams p, hipStream_t st) {
     const int nt = p.table_units + p.matrix_units;
+    // On surfaces of up to 16 words tables and contact share a launch.  On larger
+    // ones contact comes first, and only patches in contact get tables: one hand
+    // that touches one of 40 patches of 2048 nodes 316 us with all tables (the
+    // matrices alone are 1 GB), 93 us; one of 400 patches of 256 nodes 150 and 63.
     const bool merged = p.dense && p.splits == 1 && nt > 0;
-    if (!merged && (nt > 0 || p.splits > 1))
-        hipLaunchKernelGGL(k_tables, dim3(std::max(nt, 64)), dim3(kWG), 0, st, p);
     if (p.cobj_in) launch_contact_items<true>(p, merged, nt, st);
     else launch_contact_items<false>(p, merged, nt, st);
     const int32_t *na = p.n_active ? p.n_active : pl.itm.n_act;
     if (!p.dense) launch_live(na, p.E, pl.K, pl.itm.live, pl.itm.live_cnt, st);
+    p.touched = 1;
+    if (!merged && nt > 0) hipLaunchKernelGGL(k_tables, dim3(nt), dim3(kWG), 0, st, p);
 }
 
 void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st) {
     const long long cus = p.cus;
     if (!p.recall) {
-        if (p.dense && pl.tile.n_far == 0) {
+        if (p.items <= kPoolItems && pl.tile.n_far == 0) {
             hipLaunchKernelGGL(k_pool, dim3((unsigned)std::min(p.items, cus)), dim3(64 * kPoolWaves), 0, st, p);
             return;
         }

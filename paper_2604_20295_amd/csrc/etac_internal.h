@@ -23,6 +23,7 @@ constexpr int kRegUnitNodes = 256;               // nodes of a regressor unit
 constexpr int kAlphaSegs = 32;
 constexpr int kPhiSegs = 64;                      // segments of the parameter reduction
 constexpr int kMaxPatches = 1024;  // per-patch counters of the contact kernel live in LDS
+constexpr int kSplitEnvs = 4;      // envs per compute unit up to which an env's contact takes several workgroups
 constexpr int kDefaultWgPerCu = 2;
 constexpr int kDefaultBatch = 4;   // default of the batch knobs
 constexpr int kDefaultDecayWgPerCu = 3;
@@ -138,6 +139,8 @@ struct ItemDev {
     float *umax;               // [E][NW] largest |u_hat| component of each word
     int *n_act;                // [E][K] active counts where the caller takes none
     int *live, *live_cnt;      // [K][E] envs in contact on each patch, ascending; [K] how many
+    int *split_cnt;            // [envs][K][2] counts of an env's workgroups, [envs] workgroups done (zero between calls)
+    unsigned *split_done;
     unsigned long long *pool;  // [E K][64] max-pool of the items in contact: feature bits, then ~node (lowest node on ties)
     float *c4;                 // [E K][64] W4[:, 64:] g' + b4 of the items in contact
     int *alist;                // [E][N] far patches: active nodes in spatial order (patch-local)
@@ -158,8 +161,12 @@ struct ModelDev {
 // surface's 128-node blocks.  A chunk's sums are written and read once, so long
 // chunks move less, as long as there is a unit for every CU: 4096 hands, the
 // pass and the one that reads its sums 315 us at 32, 302 at 48; 301 hands of 16
-// patches 94 us at 32, 65 at 16.  Blocks alone fill the chip on large surfaces.
-inline int env_chunk(int E, int blocks) { return E >= 1024 ? 48 : E >= 256 || blocks >= 512 ? 16 : 8; }
+// patches 94 us at 32, 65 at 16.  Blocks alone fill the chip on large surfaces,
+// and on the smallest ones the chunks have to.
+inline int env_chunk(int E, int blocks) {
+    if (E >= 1024 && blocks >= 32) return 48;
+    return E >= 4096 ? 32 : E >= 256 || blocks >= 512 ? 16 : 8;
+}
 
 // Adjoint scratch (plan flag ETAC_PLAN_BACKWARD).
 struct BwdScratch {

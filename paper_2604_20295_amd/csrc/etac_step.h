@@ -18,6 +18,7 @@ struct StepParams {
     int splits;              // workgroups per env of the contact pass
     int dense;               // 1: every item is listed (no k_live), those without contact are passed over
     int table_units, matrix_units;
+    int touched;             // 1: tables come after the contact pass, of the patches in contact alone
     int wide;                // 1: products of the decay matrices in wide tiles
     int cus;                 // compute units of the device
     long long items, words;  // E K, E NW
@@ -38,7 +39,7 @@ struct StepParams {
 // and live lists, and its max-pool.
 void shape_step(const Plan &pl, StepParams &p);
 void launch_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt, hipStream_t st);
-void launch_front(const Plan &pl, const StepParams &p, hipStream_t st);
+void launch_front(const Plan &pl, StepParams p, hipStream_t st);
 void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st);
 void launch_far_lists(const StepParams &p, bool passive, hipStream_t st);
 
@@ -56,15 +57,16 @@ constexpr int kScan = kWG;      // words listed at a time
 constexpr int kRowCache = 64;
 static_assert(ETAC_MAX_OBJ <= kRowCache, "the env's objects fit");
 
+template <bool ROWS>
 struct ContactLds {
     int cnt[kMaxPatches];
-    int tcnt[kMaxPatches];
     unsigned cand[kMaxPatches];
     int wsum[kWaves];
     int list[kScan];
-    ObjRow obj[kRowCache];      // the env's objects, or its patches' rows of candidates
-    int16_t at[kMaxPatches];    // a patch's row in obj, -1: read from memory
-    int rows;
+    ObjRow obj[ROWS ? kRowCache : ETAC_MAX_OBJ];      // the env's objects, or its patches' rows of candidates
+    int tcnt[ROWS ? kMaxPatches : 1];
+    int16_t at[ROWS ? kMaxPatches : 1];               // a patch's row in obj, -1: read from memory
+    int rows, last;
 };
 
 // Stores of four consecutive values at any 4-byte (winners: 1-byte) address.
@@ -80,12 +82,30 @@ typedef unsigned uint1u __attribute__((aligned(1)));
 // of a node per lane, which ran at half the rate a fill of the same bytes does.
 // The adjoint, whose outputs are scratch, stores active nodes alone (4096 hands:
 // 115 us with all nodes, 87 us).
+// Given contact results leave nothing to list: a wave takes its words as they
+// come.
 template <bool FROM_INPUT, bool ROWS>
-__device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
+__device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int s) {
     const MeshDev &M = p.mesh;
     const SceneDev &S = p.scene;
     const int N = M.N, K = M.K, NW = p.tile.NW, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
+    constexpr bool direct = FROM_INPUT;
+    const int step = p.splits * kWaves;
+    int4 inf{};
+    float x[6];
+    auto fetch = [&](int w) {
+        inf = p.tile.word[w];
+        if (!FROM_INPUT) {
+            const int i = uniform(inf.y) + min(lane, uniform(inf.z) - 1);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                x[c] = M.pos[(size_t)c * N + i];
+                x[3 + c] = M.nrm[(size_t)c * N + i];
+            }
+        }
+    };
+    if (direct) fetch(min(s + p.splits * wave, NW - 1));
     int no = 0;
     if (!FROM_INPUT && !ROWS) {      // the env's objects: read once, then from LDS
         no = min(uniform(S.n_obj[e]), S.O);
@@ -107,7 +127,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
     }
     for (int k = threadIdx.x; k < K; k += kWG) {
         L.cnt[k] = 0;
-        L.tcnt[k] = 0;
+        if (ROWS) L.tcnt[k] = 0;
         unsigned c = FROM_INPUT ? ~0u : 0u;
         if (!FROM_INPUT && ROWS) {      // a row holds candidates alone
             const int n = min(S.n_obj[scene_row(S, e, k)], S.O);
@@ -144,7 +164,7 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         }
         __syncthreads();
     }
-    if (!FROM_INPUT && !p.scratch) {
+    if (!direct && !p.scratch) {
         const floatx4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int i = 4 * (s * kWG + threadIdx.x); i < N; i += 4 * kWG * p.splits) {
             unsigned c[4];
@@ -176,7 +196,68 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         }
     }
     const bool residual = p.itm.mask && step_residual(p);
-    for (int w0 = 0; w0 < NW; w0 += kScan * p.splits) {
+    // word w, whose geometry is in inf and x; `next`: the word to request meanwhile
+    auto take = [&](int w, int next) {
+        const int k = uniform(inf.x), i = uniform(inf.y) + lane;
+        const bool valid = lane < uniform(inf.z);
+        const float px = x[0], py = x[1], pz = x[2], nx = x[3], ny = x[4], nz = x[5];
+        if (next >= 0) fetch(next);
+        int best = -1;
+        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+        int8_t id = -1;
+        bool touch = false;
+        if (FROM_INPUT) {
+            if (valid && p.cobj_in[row + i] >= 0) {
+                best = 0;
+                u0 = p.uhat_in[row + i];
+                u1 = p.uhat_in[EN + row + i];
+                u2 = p.uhat_in[2 * EN + row + i];
+            }
+        } else if (valid) {
+            const unsigned c = uniform(L.cand[k]);
+            if (ROWS) {
+                const size_t srow = scene_row(S, e, k);
+                const int at = uniform((int)L.at[k]);
+                best = at >= 0 ? contact_node(L.obj + at, c, px, py, pz, nx, ny, nz, u0, u1, u2)
+                               : contact_node(S, srow, c, px, py, pz, nx, ny, nz, u0, u1, u2);
+                if (best >= 0) touch = S.n_ext && best < S.n_ext[srow];
+                id = best >= 0 && S.src ? S.src[srow * S.O + best] : (int8_t)best;
+            } else {
+                best = contact_node(L.obj, c, px, py, pz, nx, ny, nz, u0, u1, u2);
+                id = (int8_t)best;
+            }
+        }
+        if (FROM_INPUT && p.adjoint) {
+            if (valid) {
+                p.u[row + i] = 0.0f;
+                p.u[EN + row + i] = 0.0f;
+                p.u[2 * EN + row + i] = 0.0f;
+            }
+        } else if (valid && (best >= 0 || !p.scratch)) {
+            if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
+            if (p.u) {
+                __builtin_nontemporal_store(u0, p.u + row + i);
+                __builtin_nontemporal_store(u1, p.u + EN + row + i);
+                __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
+            }
+        }
+        const unsigned long long act = __ballot(best >= 0);
+        if (p.itm.mask) p.itm.mask[(size_t)e * NW + w] = act;      // every lane stores the same value
+        if (act) {                                                 // wave-uniform
+            if (residual) {
+                const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
+                p.itm.umax[(size_t)e * NW + w] = m;
+            }
+            const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
+            if (lane == 0) {
+                atomicAdd(&L.cnt[k], __popcll(act));
+                if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
+            }
+        }
+    };
+    if (direct)
+        for (int w = s + p.splits * wave; w < NW; w += step) take(w, w + step < NW ? w + step : -1);
+    for (int w0 = direct ? NW : 0; w0 < NW; w0 += kScan * p.splits) {
         // words w0 + s, w0 + s + splits, ... of patches with candidates
         const int mine = w0 + s + p.splits * (int)threadIdx.x;
         const bool in = mine < NW;
@@ -195,95 +276,51 @@ __device__ void contact_env(const StepParams &p, ContactLds &L, int e, int s) {
         if (hit) L.list[off + lanes_below(bal)] = mine;
         __syncthreads();
         // the next word's geometry is requested while this one is tested
-        int4 inf{};
-        float x[6];
-        auto fetch = [&](int t) {
-            inf = p.tile.word[uniform(L.list[t])];
-            if (!FROM_INPUT) {
-                const int i = uniform(inf.y) + min(lane, uniform(inf.z) - 1);
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    x[c] = M.pos[(size_t)c * N + i];
-                    x[3 + c] = M.nrm[(size_t)c * N + i];
-                }
-            }
-        };
-        if (wave < total) fetch(wave);
-        for (int t = wave; t < total; t += kWaves) {
-            const int w = uniform(L.list[t]);
-            const int k = uniform(inf.x), i = uniform(inf.y) + lane;
-            const bool valid = lane < uniform(inf.z);
-            const float px = x[0], py = x[1], pz = x[2], nx = x[3], ny = x[4], nz = x[5];
-            if (t + kWaves < total) fetch(t + kWaves);
-            int best = -1;
-            float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-            int8_t id = -1;
-            bool touch = false;
-            if (FROM_INPUT) {
-                if (valid && p.cobj_in[row + i] >= 0) {
-                    best = 0;
-                    u0 = p.uhat_in[row + i];
-                    u1 = p.uhat_in[EN + row + i];
-                    u2 = p.uhat_in[2 * EN + row + i];
-                }
-            } else if (valid) {
-                const unsigned c = uniform(L.cand[k]);
-                if (ROWS) {
-                    const size_t srow = scene_row(S, e, k);
-                    const int at = uniform((int)L.at[k]);
-                    best = at >= 0 ? contact_node(L.obj + at, c, px, py, pz, nx, ny, nz, u0, u1, u2)
-                                   : contact_node(S, srow, c, px, py, pz, nx, ny, nz, u0, u1, u2);
-                    if (best >= 0) touch = S.n_ext && best < S.n_ext[srow];
-                    id = best >= 0 && S.src ? S.src[srow * S.O + best] : (int8_t)best;
-                } else {
-                    best = contact_node(L.obj, c, px, py, pz, nx, ny, nz, u0, u1, u2);
-                    id = (int8_t)best;
-                }
-            }
-            if (FROM_INPUT && p.adjoint) {
-                if (valid) {
-                    p.u[row + i] = 0.0f;
-                    p.u[EN + row + i] = 0.0f;
-                    p.u[2 * EN + row + i] = 0.0f;
-                }
-            } else if (valid && (best >= 0 || !p.scratch)) {
-                if (!FROM_INPUT && p.cobj_out) __builtin_nontemporal_store(id, p.cobj_out + row + i);
-                if (p.u) {
-                    __builtin_nontemporal_store(u0, p.u + row + i);
-                    __builtin_nontemporal_store(u1, p.u + EN + row + i);
-                    __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
-                }
-            }
-            const unsigned long long act = __ballot(best >= 0);
-            if (p.itm.mask) p.itm.mask[(size_t)e * NW + w] = act;      // every lane stores the same value
-            if (act) {                                                 // wave-uniform
-                if (residual) {
-                    const float m = wave_max(fmaxf(fmaxf(fabsf(u0), fabsf(u1)), fabsf(u2)));
-                    p.itm.umax[(size_t)e * NW + w] = m;
-                }
-                const unsigned long long tb = ROWS ? __ballot(touch) : 0ull;
-                if (lane == 0) {
-                    atomicAdd(&L.cnt[k], __popcll(act));
-                    if (ROWS) atomicAdd(&L.tcnt[k], __popcll(tb));
-                }
-            }
-        }
+        if (wave < total) fetch(uniform(L.list[wave]));
+        for (int t = wave; t < total; t += kWaves)
+            take(uniform(L.list[t]), t + kWaves < total ? uniform(L.list[t + kWaves]) : -1);
         __syncthreads();      // the list is rewritten
     }
+    if (direct) __syncthreads();      // every wave has counted
     if (residual)
         for (int k = wave; k < K; k += kWaves)
             if (uniform(L.cnt[k])) p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
     int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
-    for (int k = threadIdx.x; k < K; k += kWG) {
-        const size_t it = (size_t)e * K + k;
-        if (p.splits == 1) {
+    if (p.splits == 1) {
+        for (int k = threadIdx.x; k < K; k += kWG) {
+            const size_t it = (size_t)e * K + k;
             na[it] = L.cnt[k];
             if (ROWS && p.n_touch) p.n_touch[it] = L.tcnt[k];
-        } else if (L.cnt[k]) {        // zeroed by k_tables
-            atomicAdd(&na[it], L.cnt[k]);
-            if (ROWS && p.n_touch && L.tcnt[k]) atomicAdd(&p.n_touch[it], L.tcnt[k]);
+        }
+        return;
+    }
+    // the env's workgroups add their counts; the last of them hands the sums out
+    // and leaves zeros for the next call
+    int *sum = p.itm.split_cnt + 2 * (size_t)e * K;
+    for (int k = threadIdx.x; k < K; k += kWG)
+        if (L.cnt[k]) {
+            // their old values are waited for: the additions are done before the
+            // workgroup reports (a fence would write the whole L2 back, 100 us)
+            int old = atomicAdd(&sum[2 * k], L.cnt[k]);
+            if (ROWS && L.tcnt[k]) old += atomicAdd(&sum[2 * k + 1], L.tcnt[k]);
+            asm volatile("" ::"v"(old));
+        }
+    __syncthreads();
+    if (threadIdx.x < 64) {      // wave 0: one addition, the same value in every lane
+        const unsigned old = atomicAdd(&p.itm.split_done[e], lane == 0 ? 1u : 0u);
+        L.last = __builtin_amdgcn_readlane((int)old, 0) == p.splits - 1;
+    }
+    __syncthreads();
+    if (!uniform(L.last)) return;
+    for (int k = threadIdx.x; k < K; k += kWG) {
+        const size_t it = (size_t)e * K + k;
+        na[it] = atomicExch(&sum[2 * k], 0);
+        if (ROWS) {
+            const int touched = atomicExch(&sum[2 * k + 1], 0);
+            if (p.n_touch) p.n_touch[it] = touched;
         }
     }
+    if (threadIdx.x == 0) atomicExch(&p.itm.split_done[e], 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -390,6 +427,17 @@ __device__ __forceinline__ void encode(const EncW &W, const float *b1, const flo
         }
 }
 
+// Whether any env is in contact on patch k, where the contact pass came first
+// (the same in every wave).
+__device__ __forceinline__ bool table_wanted(const StepParams &p, int k) {
+    if (!p.touched) return true;
+    if (!p.dense) return uniform(p.itm.live_cnt[k]) > 0;
+    const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    bool any = false;
+    for (int e = lane_id(); e < p.E; e += 64) any = any || na[(size_t)e * p.mesh.K + k] > 0;
+    return __ballot(any) != 0ull;
+}
+
 // Features of the nodes of words w0, w0 + step, ...: a wave takes 16 nodes of
 // the word.  Latency-bound: one dependent chain of three layers per word,
 // spread over as many workgroups as there are words (up to two per CU).
@@ -403,6 +451,9 @@ ETAC_LDS_ALIGNED(FeatLds, b2s);
 
 __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
     const MeshDev &M = p.mesh;
+    bool any = w0 == 0;      // the first block also writes what does not depend on the surface
+    for (int w = w0; w < p.tile.NW && !any; w += step) any = table_wanted(p, uniform(p.tile.word[w].x));
+    if (!any) return;
     const float *phi = p.model.phi;
     const int tid = threadIdx.x, lane = lane_id(), wave = uniform(tid >> 6), gq = lane >> 4, N = M.N;
     net_norms(L.t.part, phi);
@@ -434,6 +485,7 @@ __device__ void table_words(const StepParams &p, FeatLds &L, int w0, int step) {
     for (int w = w0; w < p.tile.NW; w += step) {
         const int4 inf = p.tile.word[w];
         const int k = uniform(inf.x), start = uniform(inf.y), cnt = uniform(inf.z);
+        if (!table_wanted(p, k)) continue;
         const int ax = uniform(range_exp(fmaxf(M.xbound[k], 1.0f)));
         const int a1 = s1 + ax, af = s2 + a1;
         __syncthreads();
@@ -582,6 +634,7 @@ __device__ void matrix_row_tile(const StepParams &p, int unit) {
     const int lane = lane_id(), wave = uniform(threadIdx.x >> 6), N = M.N;
     const int2 rt = p.tile.row_tile[unit];
     const int k = uniform(rt.x);
+    if (!table_wanted(p, k)) return;
     unit = uniform(rt.y);
     const int base = M.offset[k], n = M.offset[k + 1] - base, KS = (n + 31) >> 5;
     float hi, lo;
