@@ -33,6 +33,51 @@ __global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
     contact_env<FROM_INPUT, ROWS>(p, L, e, blockIdx.x - e * p.splits);
 }
 
+// The contact pass alone on small surfaces: a workgroup per env, a node per
+// thread, the objects read where they are tested.  It keeps nothing for later
+// kernels and has a third of k_contact_items' chain before the first node:
+// 16384 pads of 256 nodes 27 us, 38 in words; 1024 hands of 64 64-node patches 13
+// and 14; 256 pads of 4096 nodes 16, and 13 in words by several workgroups an env.
+__global__ __launch_bounds__(kWG) void k_contact_small(StepParams p) {
+    __shared__ int cnt[kMaxPatches];
+    __shared__ unsigned cand[kMaxPatches];
+    const MeshDev &M = p.mesh;
+    const SceneDev &S = p.scene;
+    const int e = blockIdx.x, N = M.N, K = M.K, no = min(S.n_obj[e], S.O);
+    const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
+    for (int k = threadIdx.x; k < K; k += kWG) {
+        const float4 b = M.bound[k];
+        unsigned c = 0;
+        for (int o = 0; o < no; ++o) {
+            const size_t eo = (size_t)e * S.O + o;
+            const int ty = S.type[eo];
+            if ((unsigned)ty <= (unsigned)ETAC_CAPSULE && ball_reaches(b, ty, S.shape + 4 * eo, S.trans + 3 * eo)) c |= 1u << o;
+        }
+        cnt[k] = 0;
+        cand[k] = c;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < N; i += kWG) {
+        float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+        const int k = M.node_patch[i];
+        const unsigned c = cand[k];
+        int best = -1;
+        if (c) {
+            best = contact_node(S, (size_t)e, c, M.pos[i], M.pos[N + i], M.pos[2 * N + i], M.nrm[i], M.nrm[N + i],
+                                M.nrm[2 * N + i], u0, u1, u2);
+            if (best >= 0) atomicAdd(&cnt[k], 1);
+        }
+        __builtin_nontemporal_store((int8_t)best, p.cobj_out + row + i);
+        if (p.u) {
+            __builtin_nontemporal_store(u0, p.u + row + i);
+            __builtin_nontemporal_store(u1, p.u + EN + row + i);
+            __builtin_nontemporal_store(u2, p.u + 2 * EN + row + i);
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < K; k += kWG) p.n_active[(size_t)e * K + k] = cnt[k];
+}
+
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_tables(StepParams p) {
     __shared__ FeatLds L;
     table_block(p, L, blockIdx.x);
@@ -1052,6 +1097,8 @@ static int contact_splits(const Plan &pl, int E) {
     return s;
 }
 
+constexpr int kSmallWords = 64;      // see k_contact_small
+
 hipError_t launch_contact(const Plan &p, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
                           hipStream_t st) {
     return launch_contact_rows(p, s, cobj, uhat, n_active, nullptr, st);
@@ -1074,7 +1121,9 @@ hipError_t launch_contact_rows(const Plan &pl, const SceneDev &s, int8_t *cobj, 
     p.n_active = n_active;
     p.n_touch = n_touch;
     const int slot = timer_begin(pl, ETAC_TIMER_CONTACT, st);
-    launch_contact_items<false>(p, false, 0, st);
+    if (!s.rows_per_env && pl.tile.NW <= (p.splits == 1 ? kSmallWords : kSmallWords / 2))
+        hipLaunchKernelGGL(k_contact_small, dim3(s.E), dim3(kWG), 0, st, p);
+    else launch_contact_items<false>(p, false, 0, st);
     const hipError_t e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_CONTACT, slot, st);
     return e;
