@@ -294,6 +294,7 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
         if (n <= etac::kNearNodes && (size_t)(matrix_units + units) * 16 <= etac::kDecayMatrixBytes) {
             w_off[k] = matrix_units;
             matrix_units += units;
+            tile.pairs += (long long)n * n;
             for (int t = 0; t < tiles; ++t) row_tile.push_back(make_int2(k, t));
             ++tile.n_near;
             continue;
@@ -388,11 +389,6 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.n_act, EK);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.live, EK);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.live_cnt, (size_t)K);
-    const size_t split_envs = std::min(n_envs, etac::kSplitEnvs * p.cu_count);
-    if (e == hipSuccess) e = plan_alloc(p, &p.itm.split_cnt, 2 * split_envs * K);
-    if (e == hipSuccess) e = plan_alloc(p, &p.itm.split_done, split_envs);
-    if (e == hipSuccess) e = hipMemset(p.itm.split_cnt, 0, 2 * split_envs * K * sizeof(int));
-    if (e == hipSuccess) e = hipMemset(p.itm.split_done, 0, split_envs * sizeof(unsigned));
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.pool, EK * 64);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.c4, EK * 64);
     if (e == hipSuccess) e = plan_alloc(p, &p.itm.alist, tile.n_far ? (size_t)n_envs * N : 1);

@@ -26,11 +26,11 @@ namespace etac {
 // ---------------------------------------------------------------------------
 // contact pass
 // ---------------------------------------------------------------------------
-template <bool FROM_INPUT, bool ROWS>
+template <bool FROM_INPUT, bool ROWS, bool DIRECT>
 __global__ __launch_bounds__(kWG) void k_contact_items(StepParams p) {
     __shared__ ContactLds<ROWS> L;
     const int e = blockIdx.x / p.splits;
-    contact_env<FROM_INPUT, ROWS>(p, L, e, blockIdx.x - e * p.splits);
+    contact_env<FROM_INPUT, ROWS, DIRECT>(p, L, e, blockIdx.x - e * p.splits);
 }
 
 // The contact pass alone on small surfaces: a workgroup per env, a node per
@@ -78,9 +78,21 @@ __global__ __launch_bounds__(kWG) void k_contact_small(StepParams p) {
     for (int k = threadIdx.x; k < K; k += kWG) p.n_active[(size_t)e * K + k] = cnt[k];
 }
 
+// Zero counts where several workgroups an env add to them.
+__device__ __forceinline__ void zero_counts(const StepParams &p) {
+    int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
+    for (size_t i = (size_t)blockIdx.x * kWG + threadIdx.x; i < (size_t)p.E * p.mesh.K; i += (size_t)gridDim.x * kWG) {
+        na[i] = 0;
+        if (p.n_touch) p.n_touch[i] = 0;
+    }
+}
+
+__global__ __launch_bounds__(kWG) void k_zero_counts(StepParams p) { zero_counts(p); }
+
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k_tables(StepParams p) {
     __shared__ FeatLds L;
-    table_block(p, L, blockIdx.x);
+    if (p.splits > 1 && !p.touched) zero_counts(p);
+    if ((int)blockIdx.x < p.table_units + p.matrix_units) table_block(p, L, blockIdx.x);
 }
 
 // Tables and contact in one launch: on small batches neither fills the chip
@@ -93,7 +105,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     } L;
     const int nt = p.table_units + p.matrix_units;
     if ((int)blockIdx.x < nt) table_block(p, L.feat, blockIdx.x);
-    else contact_env<FROM_INPUT, ROWS>(p, L.contact, blockIdx.x - nt, 0);
+    else contact_env<FROM_INPUT, ROWS, true>(p, L.contact, blockIdx.x - nt, 0);
 }
 
 // Envs in contact on patch blockIdx.x, ascending.
@@ -1077,18 +1089,31 @@ __global__ __launch_bounds__(kWG) void k_prop_far(StepParams p) {
     }
 }
 
-template <bool FROM_INPUT>
+template <bool FROM_INPUT, bool ROWS>
+static void launch_contact_items(const StepParams &p, bool merged, int nt, hipStream_t st) {
+    if (merged) {
+        hipLaunchKernelGGL((k_front<FROM_INPUT, ROWS>), dim3(nt + p.E), dim3(kWG), 0, st, p);
+        return;
+    }
+    const dim3 grid(p.E * p.splits);
+    if constexpr (!FROM_INPUT) {
+        if (p.tile.NW > kDirectWords) {
+            hipLaunchKernelGGL((k_contact_items<FROM_INPUT, ROWS, false>), grid, dim3(kWG), 0, st, p);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_contact_items<FROM_INPUT, ROWS, true>), grid, dim3(kWG), 0, st, p);
+}
+
 static void launch_contact_items(const StepParams &p, bool merged, int nt, hipStream_t st) {
     const bool rows = p.scene.rows_per_env != 0;
-    const dim3 grid(merged ? nt + p.E : p.E * p.splits);
-    if (merged) {
-        if (rows) hipLaunchKernelGGL((k_front<FROM_INPUT, true>), grid, dim3(kWG), 0, st, p);
-        else hipLaunchKernelGGL((k_front<FROM_INPUT, false>), grid, dim3(kWG), 0, st, p);
-    } else {
-        if (rows) hipLaunchKernelGGL((k_contact_items<FROM_INPUT, true>), grid, dim3(kWG), 0, st, p);
-        else hipLaunchKernelGGL((k_contact_items<FROM_INPUT, false>), grid, dim3(kWG), 0, st, p);
-    }
+    if (p.cobj_in) launch_contact_items<true, false>(p, merged, nt, st);
+    else if (rows) launch_contact_items<false, true>(p, merged, nt, st);
+    else launch_contact_items<false, false>(p, merged, nt, st);
 }
+
+constexpr long long kAllPairs = 8 << 20;      // weights, words of surfaces that get every table
+constexpr int kAllWords = 2048;
 
 // Workgroups per env of the contact pass: enough to fill the chip.
 static int contact_splits(const Plan &pl, int E) {
@@ -1096,8 +1121,6 @@ static int contact_splits(const Plan &pl, int E) {
     while (E * s < kSplitEnvs * pl.cu_count && s * kWaves * 4 < pl.tile.NW) s *= 2;
     return s;
 }
-
-constexpr int kSmallWords = 64;      // see k_contact_small
 
 hipError_t launch_contact(const Plan &p, const SceneDev &s, int8_t *cobj, float *uhat, int32_t *n_active,
                           hipStream_t st) {
@@ -1114,16 +1137,17 @@ hipError_t launch_contact_rows(const Plan &pl, const SceneDev &s, int8_t *cobj, 
     p.model = ModelDev{ETAC_DECAY_ONLY, nullptr, nullptr};
     p.E = s.E;
     p.splits = contact_splits(pl, s.E);
-    p.itm.split_cnt = pl.itm.split_cnt;
-    p.itm.split_done = pl.itm.split_done;
     p.u = uhat;
     p.cobj_out = cobj;
     p.n_active = n_active;
     p.n_touch = n_touch;
     const int slot = timer_begin(pl, ETAC_TIMER_CONTACT, st);
-    if (!s.rows_per_env && pl.tile.NW <= (p.splits == 1 ? kSmallWords : kSmallWords / 2))
+    if (!s.rows_per_env && pl.tile.NW <= (p.splits == 1 ? kDirectWords : kDirectWords / 2)) {
         hipLaunchKernelGGL(k_contact_small, dim3(s.E), dim3(kWG), 0, st, p);
-    else launch_contact_items<false>(p, false, 0, st);
+    } else {
+        if (p.splits > 1) hipLaunchKernelGGL(k_zero_counts, dim3(64), dim3(kWG), 0, st, p);
+        launch_contact_items(p, false, 0, st);
+    }
     const hipError_t e = hipGetLastError();
     timer_end(pl, ETAC_TIMER_CONTACT, slot, st);
     return e;
@@ -1154,17 +1178,22 @@ void launch_live(const int32_t *n_active, int E, int K, int *live, int *live_cnt
 
 void launch_front(const Plan &pl, StepParams p, hipStream_t st) {
     const int nt = p.table_units + p.matrix_units;
-    // On surfaces of up to 16 words tables and contact share a launch.  On larger
+    // On surfaces of up to 16 words tables and contact share a launch.  On large
     // ones contact comes first, and only patches in contact get tables: one hand
     // that touches one of 40 patches of 2048 nodes 316 us with all tables (the
-    // matrices alone are 1 GB), 93 us; one of 400 patches of 256 nodes 150 and 63.
+    // matrices alone are 1 GB), 90 us; one of 400 patches of 256 nodes 150 and 65.
+    // In between the tables are a launch's worth and clear the contact's counts,
+    // which would take a launch of their own.
     const bool merged = p.dense && p.splits == 1 && nt > 0;
-    if (p.cobj_in) launch_contact_items<true>(p, merged, nt, st);
-    else launch_contact_items<false>(p, merged, nt, st);
+    p.touched = !merged && (pl.tile.pairs > kAllPairs || pl.tile.NW > kAllWords);
+    if (!merged && (p.touched ? p.splits > 1 : nt > 0 || p.splits > 1)) {
+        if (p.touched || nt == 0) hipLaunchKernelGGL(k_zero_counts, dim3(64), dim3(kWG), 0, st, p);
+        else hipLaunchKernelGGL(k_tables, dim3(std::max(nt, 64)), dim3(kWG), 0, st, p);
+    }
+    launch_contact_items(p, merged, nt, st);
     const int32_t *na = p.n_active ? p.n_active : pl.itm.n_act;
     if (!p.dense) launch_live(na, p.E, pl.K, pl.itm.live, pl.itm.live_cnt, st);
-    p.touched = 1;
-    if (!merged && nt > 0) hipLaunchKernelGGL(k_tables, dim3(nt), dim3(kWG), 0, st, p);
+    if (p.touched && nt > 0) hipLaunchKernelGGL(k_tables, dim3(nt), dim3(kWG), 0, st, p);
 }
 
 void launch_pool(const Plan &pl, const StepParams &p, hipStream_t st) {

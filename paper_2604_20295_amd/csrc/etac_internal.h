@@ -120,6 +120,7 @@ struct TileDev {
     int n_near, n_far;         // patches of each kind
     int far_max;               // nodes of the largest far patch
     int near_rows;             // tiles of 16 nodes of the near patches
+    long long pairs;           // weights of the near patches
 };
 
 // What one model gives on the undeformed surface, whatever the env: rebuilt
@@ -139,8 +140,6 @@ struct ItemDev {
     float *umax;               // [E][NW] largest |u_hat| component of each word
     int *n_act;                // [E][K] active counts where the caller takes none
     int *live, *live_cnt;      // [K][E] envs in contact on each patch, ascending; [K] how many
-    int *split_cnt;            // [envs][K][2] counts of an env's workgroups, [envs] workgroups done (zero between calls)
-    unsigned *split_done;
     unsigned long long *pool;  // [E K][64] max-pool of the items in contact: feature bits, then ~node (lowest node on ties)
     float *c4;                 // [E K][64] W4[:, 64:] g' + b4 of the items in contact
     int *alist;                // [E][N] far patches: active nodes in spatial order (patch-local)

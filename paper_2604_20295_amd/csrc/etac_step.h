@@ -66,7 +66,7 @@ struct ContactLds {
     ObjRow obj[ROWS ? kRowCache : ETAC_MAX_OBJ];      // the env's objects, or its patches' rows of candidates
     int tcnt[ROWS ? kMaxPatches : 1];
     int16_t at[ROWS ? kMaxPatches : 1];               // a patch's row in obj, -1: read from memory
-    int rows, last;
+    int rows;
 };
 
 constexpr int kDirectWords = 64;
@@ -85,15 +85,17 @@ typedef unsigned uint1u __attribute__((aligned(1)));
 // The adjoint, whose outputs are scratch, stores active nodes alone (4096 hands:
 // 115 us with all nodes, 87 us).
 // A surface of few words, or given contact results, has nothing to list: a wave
-// takes its words as they come, the first one's geometry requested before the
-// objects are read (16384 pads of 256 nodes: 51 us, 38 us).
-template <bool FROM_INPUT, bool ROWS>
+// takes its words as they come (DIRECT), the first one's geometry requested before the
+// objects are read (16384 pads of 256 nodes: 51 us, 38 us).  Several workgroups of
+// an env add to its counts (one of them that hands out their sum last needs no
+// cleared counts, but 64 workgroups' turns at it take longer than that launch).
+template <bool FROM_INPUT, bool ROWS, bool DIRECT>
 __device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int s) {
     const MeshDev &M = p.mesh;
     const SceneDev &S = p.scene;
     const int N = M.N, K = M.K, NW = p.tile.NW, lane = lane_id(), wave = uniform(threadIdx.x >> 6);
     const size_t EN = (size_t)p.E * N, row = (size_t)e * N;
-    const bool direct = FROM_INPUT || NW <= kDirectWords;
+    static_assert(DIRECT || !FROM_INPUT, "given contact results are taken as they come");
     const int step = p.splits * kWaves;
     int4 inf{};
     float x[6];
@@ -108,7 +110,7 @@ __device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int
             }
         }
     };
-    if (direct) fetch(min(s + p.splits * wave, NW - 1));
+    if (DIRECT) fetch(min(s + p.splits * wave, NW - 1));
     int no = 0;
     if (!FROM_INPUT && !ROWS) {      // the env's objects: read once, then from LDS
         no = min(uniform(S.n_obj[e]), S.O);
@@ -167,7 +169,7 @@ __device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int
         }
         __syncthreads();
     }
-    if (!direct && !p.scratch) {
+    if (!DIRECT && !p.scratch) {
         const floatx4u zero = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int i = 4 * (s * kWG + threadIdx.x); i < N; i += 4 * kWG * p.splits) {
             unsigned c[4];
@@ -258,9 +260,9 @@ __device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int
             }
         }
     };
-    if (direct)
+    if (DIRECT)
         for (int w = s + p.splits * wave; w < NW; w += step) take(w, w + step < NW ? w + step : -1);
-    for (int w0 = direct ? NW : 0; w0 < NW; w0 += kScan * p.splits) {
+    for (int w0 = DIRECT ? NW : 0; w0 < NW; w0 += kScan * p.splits) {
         // words w0 + s, w0 + s + splits, ... of patches with candidates
         const int mine = w0 + s + p.splits * (int)threadIdx.x;
         const bool in = mine < NW;
@@ -284,46 +286,21 @@ __device__ void contact_env(const StepParams &p, ContactLds<ROWS> &L, int e, int
             take(uniform(L.list[t]), t + kWaves < total ? uniform(L.list[t + kWaves]) : -1);
         __syncthreads();      // the list is rewritten
     }
-    if (direct) __syncthreads();      // every wave has counted
+    if (DIRECT) __syncthreads();      // every wave has counted
     if (residual)
         for (int k = wave; k < K; k += kWaves)
             if (uniform(L.cnt[k])) p.itm.pool[((size_t)e * K + k) * 64 + lane] = 0ull;      // k_pool_* raise it
     int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
-    if (p.splits == 1) {
-        for (int k = threadIdx.x; k < K; k += kWG) {
-            const size_t it = (size_t)e * K + k;
-            na[it] = L.cnt[k];
-            if (ROWS && p.n_touch) p.n_touch[it] = L.tcnt[k];
-        }
-        return;
-    }
-    // the env's workgroups add their counts; the last of them hands the sums out
-    // and leaves zeros for the next call
-    int *sum = p.itm.split_cnt + 2 * (size_t)e * K;
-    for (int k = threadIdx.x; k < K; k += kWG)
-        if (L.cnt[k]) {
-            // their old values are waited for: the additions are done before the
-            // workgroup reports (a fence would write the whole L2 back, 100 us)
-            int old = atomicAdd(&sum[2 * k], L.cnt[k]);
-            if (ROWS && L.tcnt[k]) old += atomicAdd(&sum[2 * k + 1], L.tcnt[k]);
-            asm volatile("" ::"v"(old));
-        }
-    __syncthreads();
-    if (threadIdx.x < 64) {      // wave 0: one addition, the same value in every lane
-        const unsigned old = atomicAdd(&p.itm.split_done[e], lane == 0 ? 1u : 0u);
-        L.last = __builtin_amdgcn_readlane((int)old, 0) == p.splits - 1;
-    }
-    __syncthreads();
-    if (!uniform(L.last)) return;
     for (int k = threadIdx.x; k < K; k += kWG) {
         const size_t it = (size_t)e * K + k;
-        na[it] = atomicExch(&sum[2 * k], 0);
-        if (ROWS) {
-            const int touched = atomicExch(&sum[2 * k + 1], 0);
-            if (p.n_touch) p.n_touch[it] = touched;
+        if (p.splits == 1) {
+            na[it] = L.cnt[k];
+            if (ROWS && p.n_touch) p.n_touch[it] = L.tcnt[k];
+        } else if (L.cnt[k]) {        // zero before this launch
+            atomicAdd(&na[it], L.cnt[k]);
+            if (ROWS && p.n_touch && L.tcnt[k]) atomicAdd(&p.n_touch[it], L.tcnt[k]);
         }
     }
-    if (threadIdx.x == 0) atomicExch(&p.itm.split_done[e], 0u);
 }
 
 // ---------------------------------------------------------------------------
