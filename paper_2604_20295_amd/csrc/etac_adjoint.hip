@@ -135,7 +135,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int32_t *na = S.itm.n_act;
     const int total = product_units(S, L.first, 64, 32);
     for (int q = product_start(); q < total; q += product_stride()) {
-        const ProductRef ref = product_ref(S, L.first, q, 64);
+        const ProductRef ref = product_ref(S, L.first, q, 64, 32);
         const int k = ref.k, g0 = ref.group * 32;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
         const int cnt = uniform(live_count(S, k));

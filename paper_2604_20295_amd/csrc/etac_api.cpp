@@ -295,6 +295,7 @@ etac_status etac_plan_create(const etac_mesh *mesh, int32_t n_envs, int32_t max_
             w_off[k] = matrix_units;
             matrix_units += units;
             tile.pairs += (long long)n * n;
+            tile.near_blocks += (n + 127) / 128;
             for (int t = 0; t < tiles; ++t) row_tile.push_back(make_int2(k, t));
             ++tile.n_near;
             continue;

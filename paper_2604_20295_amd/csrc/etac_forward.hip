@@ -691,9 +691,9 @@ __device__ __forceinline__ void store_rows(float *o, size_t EN, unsigned act, in
 // the loop (4096 hands: 17.8 M MFMAs, 116 us of all of them at full rate) and by
 // the VALU: the FP64 sums there, and five operations per node, env and channel
 // of the residual in the epilogue.  A taller tile reads and splits each env's
-// values for more rows; patches are padded to it and there are fewer units, so it
-// pays once there are many: 4096 hands 530 us at MT = 1 and 410 at MT = 2, 16384
-// hands 2020 and 1520 (three row tiles would not fit the registers).
+// values for more rows: 4096 hands 530 us at MT = 1 and 410 at MT = 2, 16384 hands
+// 2020 and 1520 (three row tiles would not fit the registers).  Patches are padded
+// to it and there are fewer units: see tall_tiles.
 constexpr int kWideEnvs = 32;
 
 struct WideLds {
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
     const int total = product_units(p, L.first, kRows, kWideEnvs);
     for (int q = product_start(); q < total; q += product_stride()) {
-        const ProductRef ref = product_ref(p, L.first, q, kRows);
+        const ProductRef ref = product_ref(p, L.first, q, kRows, kWideEnvs);
         const int k = ref.k, rb = ref.row_block, g0 = ref.group * kWideEnvs;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
         const int cnt = uniform(live_count(p, k));
@@ -1217,6 +1217,18 @@ void launch_far_lists(const StepParams &p, bool passive, hipStream_t st) {
     else hipLaunchKernelGGL(k_far_list<false>, grid, dim3(1024), 0, st, p);
 }
 
+// Tiles of 128 rows in the wide product where they give every CU a unit and more,
+// if an object touches a patch, and are not padding: 1024 hands (342 units) 314
+// us, 326 in tiles of 64 rows; 4096 pads of 1024 nodes (1024 units) 335 and 398; but
+// 1024 of those pads (256 units) 158 and 150, 1024 hands of 64 64-node patches 105
+// and 98, 128 envs on forty patches of 2048 nodes, three in contact on each, 700 and
+// 660.
+static bool tall_tiles(const Plan &pl, const StepParams &p) {
+    const long long objects = std::min(p.cobj_in ? pl.max_obj : p.scene.O, pl.K);
+    const long long envs = p.E * objects / pl.K, groups = (envs + kWideEnvs - 1) / kWideEnvs;
+    return p.wide && envs >= kWideEnvs && pl.tile.near_blocks * groups > pl.cu_count && pl.tile.near_blocks * 128 <= pl.tile.near_rows * 20;
+}
+
 hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int n_envs,
                        const int8_t *cobj_in, const float *uhat_in, float *u, int8_t *cobj_out,
                        int32_t *n_active, uint32_t *saved, hipStream_t st, int32_t *n_touch) {
@@ -1238,8 +1250,7 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     launch_front(pl, p, st);
     if (step_residual(p)) launch_pool(pl, p, st);
     if (pl.tile.n_near) {
-        // tile heights: see k_prop_wide
-        if (n_envs >= 1024) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
+        if (tall_tiles(pl, p)) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
         else if (p.wide) hipLaunchKernelGGL(k_prop_wide<1>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_prop_narrow, dim3((unsigned)std::min<long long>((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),

@@ -121,6 +121,7 @@ struct TileDev {
     int far_max;               // nodes of the largest far patch
     int near_rows;             // tiles of 16 nodes of the near patches
     long long pairs;           // weights of the near patches
+    int near_blocks;           // 128-node blocks of the near patches
 };
 
 // What one model gives on the undeformed surface, whatever the env: rebuilt

@@ -697,6 +697,12 @@ __device__ __forceinline__ int residue_count(int n, int first, int step) { retur
 __device__ __forceinline__ int xcd_row(int kk) { return ((int)(blockIdx.x % kXcds) + kk) % kXcdRows; }
 __device__ __forceinline__ int xcd_group(int kk) { return ((int)(blockIdx.x % kXcds) / kXcdRows + kk / kXcdRows) % kXcdGroups; }
 
+// A patch of fewer row blocks or groups than the residues would leave XCDs
+// without any (4096 pads of 256 nodes: six of the eight at 256 rows): its units
+// go to the XCDs in turn.
+__device__ __forceinline__ bool xcd_residues(int blocks, int groups) { return blocks >= kXcdRows && groups >= kXcdGroups; }
+__device__ __forceinline__ int xcd_first(int kk) { return ((int)(blockIdx.x % kXcds) + kk) % kXcds; }
+
 // This XCD's units (whole workgroup; ends with a barrier).
 __device__ int product_units(const StepParams &p, int (&first)[kMaxPatches + 1], int rows, int envs) {
     const MeshDev &M = p.mesh;
@@ -704,6 +710,7 @@ __device__ int product_units(const StepParams &p, int (&first)[kMaxPatches + 1],
         const int k = M.order[kk], groups = (live_count(p, k) + envs - 1) / envs;
         if (p.tile.w_off[k] < 0) return 0;
         const int blocks = (M.offset[k + 1] - M.offset[k] + rows - 1) / rows;
+        if (!xcd_residues(blocks, groups)) return residue_count(blocks * groups, xcd_first(kk), kXcds);
         return residue_count(blocks, xcd_row(kk), kXcdRows) * residue_count(groups, xcd_group(kk), kXcdGroups);
     });
 }
@@ -727,11 +734,15 @@ __device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
 // results, else the step's output, whose active entries are u_hat.
 __device__ __forceinline__ const float *uhat_source(const StepParams &p) { return p.uhat_in ? p.uhat_in : p.u; }
 
-__device__ __forceinline__ ProductRef product_ref(const StepParams &p, const int (&first)[kMaxPatches + 1], int q, int rows) {
+__device__ __forceinline__ ProductRef product_ref(const StepParams &p, const int (&first)[kMaxPatches + 1], int q, int rows, int envs) {
     const int kk = unit_rank(first, p.mesh.K, q), k = uniform(p.mesh.order[kk]);
     const int blocks = (uniform(p.mesh.offset[k + 1]) - uniform(p.mesh.offset[k]) + rows - 1) / rows;
-    const int mine = residue_count(blocks, xcd_row(kk), kXcdRows);
-    const int local = q - uniform(first[kk]), g = local / mine;      // the row blocks of a group run together
+    const int groups = (uniform(live_count(p, k)) + envs - 1) / envs, local = q - uniform(first[kk]);
+    if (!xcd_residues(blocks, groups)) {
+        const int u = xcd_first(kk) + kXcds * local, g = u / blocks;
+        return ProductRef{k, u - g * blocks, g};
+    }
+    const int mine = residue_count(blocks, xcd_row(kk), kXcdRows), g = local / mine;      // the row blocks of a group run together
     return ProductRef{k, xcd_row(kk) + kXcdRows * (local - g * mine), xcd_group(kk) + kXcdGroups * g};
 }
 
