@@ -19,7 +19,8 @@ constexpr int kRouteWords = 4096 + 640 + 64;
 constexpr int kRouteGroups = 2;                   // routing workgroups per compute unit
 constexpr int kRedRoute = 37 * 256, kRedItem = kRedRoute + 19 * 256, kRedRank = kRedItem + 256,
               kRedW5 = kRedRank + 8192, kRedCols = kRedW5 + 256;
-constexpr int kRegUnitNodes = 256;               // nodes of a regressor unit
+constexpr int kRegUnitNodes = 256;               // nodes of a regressor unit, the least of a plan
+constexpr size_t kRegRows = 1 << 18;             // rows of 1 KB its units may take (or one per item)
 constexpr int kAlphaSegs = 32;
 constexpr int kPhiSegs = 64;                      // segments of the parameter reduction
 constexpr int kMaxPatches = 1024;  // per-patch counters of the contact kernel live in LDS
@@ -209,17 +210,14 @@ struct Plan {
     unsigned *counter;     // [4] regressor's work queue (self-resetting)
     BwdScratch bwd;
     bool has_bwd;
-    // device allocations owned by the plan
-    void *allocs[96];
-    int n_allocs;
-    char *arena;           // rest of the block small arrays are carved from
-    size_t arena_left;
+    void *mem;             // the plan's device block
     int64_t scratch_bytes;
     Timers *timers;        // null until timing is first turned on
     HandDev *hand;         // null until etac_plan_set_hand (host copy of the device view)
     void *hand_mem;        // the hand's device block (one allocation)
     float *reg_rest;       // [K][8] regressor outputs of the patches at U = 0
-    float *reg_pooled;     // [units][256] regressor: weighted sums of 256 nodes of an item
+    int reg_unit;          // nodes of a regressor unit
+    float *reg_pooled;     // [units][256] regressor: weighted sums of a unit of an item
     float2 *reg_ml;        // [units] their largest scores and sums of weights
     int *reg_live;         // [K][E] envs in contact of the call's n_active
     int *reg_cnt;          // [K]

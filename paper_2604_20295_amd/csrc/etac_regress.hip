@@ -6,7 +6,7 @@
 //   k_live         : the envs in contact on each patch.
 //   k_regress      : persistent, one workgroup of eight waves per CU with the
 //                    per-node layers' weights resident in LDS; a unit is 256
-//                    nodes of an item, taken by a wave (largest patches first,
+//                    nodes of an item (more in plans of very many), taken by a wave (largest patches first,
 //                    one each and then from a device work queue): 16-node
 //                    tiles, two at a time, through the per-node layers on MFMA
 //                    with an online softmax over the tiles.  The unit's
@@ -59,8 +59,6 @@ ETAC_LDS_ALIGNED(RegLds, be3);
 ETAC_LDS_ALIGNED(RegLds, ba1);
 ETAC_LDS_ALIGNED(RegLds, wa2);
 
-constexpr int kRegPasses = kRegUnitNodes / (16 * kRegNT);      // passes of a unit
-
 struct RegParams {
     MeshDev mesh;
     const float *reg;         // [ETAC_REG_SIZE]
@@ -69,11 +67,11 @@ struct RegParams {
     float *pooled;            // [units][256] weighted sum of a unit's features
     float2 *ml;               // [units] its largest score and its sum of weights
     unsigned *counter;        // [2] work queue, retired workgroups
-    int E;
+    int E, unit;              // nodes of a unit
 };
 
-__device__ __forceinline__ int reg_parts(const MeshDev &M, int k) {
-    return (M.offset[k + 1] - M.offset[k] + kRegUnitNodes - 1) / kRegUnitNodes;
+__device__ __forceinline__ int reg_parts(const RegParams &p, int k) {
+    return (p.mesh.offset[k + 1] - p.mesh.offset[k] + p.unit - 1) / p.unit;
 }
 
 __device__ void stage_regressor(RegLds &L, const float *R) {
@@ -340,7 +338,7 @@ __device__ void regress_unit(const RegParams &p, const RegLds &L, int e, int k, 
     floatx4 acc[16];
 #pragma unroll
     for (int ot = 0; ot < 16; ++ot) acc[ot] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    const int groups = min((n + 16 * kRegNT - 1) / (16 * kRegNT), (part + 1) * kRegPasses);
+    const int passes = p.unit / (16 * kRegNT), groups = min((n + 16 * kRegNT - 1) / (16 * kRegNT), (part + 1) * passes);
     // the next tiles' inputs are requested while these run; nodes beyond the
     // patch repeat its last and get no weight
     const float *pos = M.pos + base, *u = p.u + (size_t)e * N + base;
@@ -356,8 +354,8 @@ __device__ void regress_unit(const RegParams &p, const RegLds &L, int e, int k, 
             }
         }
     };
-    fetch(part * kRegPasses);
-    for (int tg = part * kRegPasses; tg < groups; ++tg) {
+    fetch(part * passes);
+    for (int tg = part * passes; tg < groups; ++tg) {
         half8 x[kRegNT];
         bool valid[kRegNT];
 #pragma unroll
@@ -434,12 +432,12 @@ __global__ __launch_bounds__(kRegWG) void k_regress(RegParams p) {
     stage_regressor(L, p.reg);
     const int total = unit_prefix<kRegWaves>(M.K, first, [&](int kk) {
         const int k = M.order[kk];
-        return (p.live_cnt[k] + 1) * reg_parts(M, k);
+        return (p.live_cnt[k] + 1) * reg_parts(p, k);
     });
     int pos = wave * gridDim.x + blockIdx.x;
     while (pos < total) {
         const int kk = unit_rank(first, M.K, pos), k = uniform(M.order[kk]);
-        const int parts = uniform(reg_parts(M, k)), local = pos - uniform(first[kk]);
+        const int parts = uniform(reg_parts(p, k)), local = pos - uniform(first[kk]);
         const int it = local / parts;
         const bool rest = it == uniform(p.live_cnt[k]);
         regress_unit(p, L, rest ? 0 : uniform(p.live[(size_t)k * p.E + it]), k, local - it * parts, rest, pos);
@@ -480,7 +478,7 @@ __global__ __launch_bounds__(256) void k_regress_head(RegParams p, float *taxels
     const int total = unit_prefix<kWaves>(M.K, items, [&](int kk) { return p.live_cnt[M.order[kk]] + 1; });
     unit_prefix<kWaves>(M.K, units, [&](int kk) {
         const int k = M.order[kk];
-        return (p.live_cnt[k] + 1) * reg_parts(M, k);
+        return (p.live_cnt[k] + 1) * reg_parts(p, k);
     });
     for (int b0 = blockIdx.x * kHeadRows; b0 < total; b0 += gridDim.x * kHeadRows) {
         __syncthreads();   // the previous pass is done with LDS
@@ -492,7 +490,7 @@ __global__ __launch_bounds__(256) void k_regress_head(RegParams p, float *taxels
                 if (items[mid] <= q) lo = mid;
                 else hi = mid - 1;
             }
-            const int k = M.order[lo], local = q - items[lo], parts = reg_parts(M, k);
+            const int k = M.order[lo], local = q - items[lo], parts = reg_parts(p, k);
             row0[tid] = units[lo] + local * parts;
             rows[tid] = parts;
             out[tid] = local == p.live_cnt[k] ? -1 - k : p.live[(size_t)k * p.E + local] * M.K + k;
@@ -578,7 +576,7 @@ __global__ __launch_bounds__(256) void k_regress_fill(const int32_t *n_active, c
 hipError_t launch_regress(const Plan &pl, const float *reg, int n_envs, const float *u, const int32_t *n_active,
                           float *taxels, hipStream_t st) {
     if (n_envs == 0) return hipSuccess;
-    const RegParams p{pl.mesh, reg, u, pl.reg_live, pl.reg_cnt, pl.reg_pooled, pl.reg_ml, pl.counter, n_envs};
+    const RegParams p{pl.mesh, reg, u, pl.reg_live, pl.reg_cnt, pl.reg_pooled, pl.reg_ml, pl.counter, n_envs, pl.reg_unit};
     const int items = pl.K + n_envs * pl.K;
     const int slot = timer_begin(pl, ETAC_TIMER_REGRESS, st);
     launch_live(n_active, n_envs, pl.K, pl.reg_live, pl.reg_cnt, st);
