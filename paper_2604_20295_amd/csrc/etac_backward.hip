@@ -42,29 +42,21 @@ __device__ __forceinline__ void split4(const floatx4 &v, half4 &hi, half4 &lo) {
     lo = __builtin_bit_cast(half4, l);
 }
 
-
-
-// Weight-gradient operands: NB N-form blocks of NT tiles, split and packed as
+// Weight-gradient operands: NB N-form blocks of a tile, split and packed as
 // K = 32 MFMA operands (lane group q holds k = 8 q .. 8 q + 7; any k order
 // contracts correctly as long as both operands use it).
-//   NT = 2: h = [hi of tile 0, hi of tile 1], l = the lo parts; the three
-//           split products hi*hi, hi*lo, lo*hi take one MFMA each.
-//   NT = 1: A operand h = [hi hi], l = [lo 0]; B operand h = [hi lo]; then
-//           A.h B.h = hi*hi + hi*lo and A.l B.h = lo*hi.
+// A operand h = [hi hi], l = [lo 0]; B operand h = [hi lo]; then A.h B.h =
+// hi*hi + hi*lo and A.l B.h = lo*hi.
 // Every accumulator sees only the 16x16x32 MFMA shape: chaining an
 // accumulator from that shape into the 16x16x16 one gave wrong gradients
 // with ROCm 7.2 hipcc for gfx950, so the 16x16x16 shape is not used.
-template <int NT, int NB, bool A_ROLE>
+template <int NB, bool A_ROLE>
 struct WOp {
-    static_assert(NT == 1 || NT == 2, "one or two tiles");
     half8 h[NB], l[NB];
-    __device__ __forceinline__ void set(int u, int j, const floatx4 &v) {
+    __device__ __forceinline__ void set(int j, const floatx4 &v) {
         half4 hi, lo;
         split4(v, hi, lo);
-        if constexpr (NT == 2) {
-            if (u == 0) { h[j].lo = hi; l[j].lo = lo; }
-            else { h[j].hi = hi; l[j].hi = lo; }
-        } else if constexpr (A_ROLE) {
+        if constexpr (A_ROLE) {
             h[j].lo = hi; h[j].hi = hi;
             l[j].lo = lo; l[j].hi = half4{0, 0, 0, 0};
         } else {
@@ -73,27 +65,19 @@ struct WOp {
     }
 };
 
-// acc[o][i] += sum over the tiles' nodes of A[o] (x) B[i], split passes
+// acc[o][i] += sum over the tile's nodes of A[o] (x) B[i], split passes
 // outermost.
-template <int NT, int NO, int NI>
-__device__ __forceinline__ void wgrad_tiles(const WOp<NT, NO, true> &A, const WOp<NT, NI, false> &B,
-                                            floatx4 (&acc)[NO][NI]) {
+template <int NO, int NI>
+__device__ __forceinline__ void wgrad_tile(const WOp<NO, true> &A, const WOp<NI, false> &B, floatx4 (&acc)[NO][NI]) {
 #pragma unroll
     for (int o = 0; o < NO; ++o)
 #pragma unroll
         for (int i = 0; i < NI; ++i) acc[o][i] = mfma16(A.h[o], B.h[i], acc[o][i]);
-    if constexpr (NT == 2) {
-#pragma unroll
-        for (int o = 0; o < NO; ++o)
-#pragma unroll
-            for (int i = 0; i < NI; ++i) acc[o][i] = mfma16(A.h[o], B.l[i], acc[o][i]);
-    }
 #pragma unroll
     for (int o = 0; o < NO; ++o)
 #pragma unroll
         for (int i = 0; i < NI; ++i) acc[o][i] = mfma16(A.l[o], B.h[i], acc[o][i]);
 }
-
 
 // N form of a T-form tile through the wave's LDS buffer, one 16 x 16 block
 // at a time: value (feature 4 q + r, node c) of a block is stored at row
@@ -211,7 +195,6 @@ __device__ __forceinline__ void layer64_tiles_n(const half8 *wh, const half8 *wl
     }
 }
 
-
 struct NodeLds {
     NetLds net;
     half8 w2th[4 * 2 * 64], w2tl[4 * 2 * 64];   // [it][s][lane] split fragments of W2^T
@@ -301,8 +284,8 @@ __device__ __forceinline__ void node_tiles(NodeLds &S, WGrad &G, int cnt, const 
     // dW4[:, :64] += dpre4 (x) f; f > 0 kept as bits (4 block + register)
     unsigned fmask[NT];
     {
-        WOp<NT, 4, true> A;
-        WOp<NT, 4, false> B;
+        WOp<4, true> A;
+        WOp<4, false> B;
 #pragma unroll
         for (int u = 0; u < NT; ++u) {
             floatx4 d4N[4], fN[4];
@@ -313,11 +296,11 @@ __device__ __forceinline__ void node_tiles(NodeLds &S, WGrad &G, int cnt, const 
             for (int ob = 0; ob < 4; ++ob) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) fmask[u] |= (fT[u][ob][r] > 0.0f ? 1u : 0u) << (4 * ob + r);
-                B.set(u, ob, fN[ob]);
-                A.set(u, ob, d4N[ob]);
+                B.set(ob, fN[ob]);
+                A.set(ob, d4N[ob]);
             }
         }
-        wgrad_tiles<NT, 4, 4>(A, B, G.w4);
+        wgrad_tile(A, B, G.w4);
     }
     // dL/df = W4[:, :64]^T dpre4
 #pragma unroll
@@ -338,9 +321,9 @@ __device__ __forceinline__ void node_tiles(NodeLds &S, WGrad &G, int cnt, const 
     floatx4 dh1N[NT][4];
     layer64_tiles_n<NT>(S.w2th, S.w2tl, sh, sl, dh1N);
     // dW2 += dpre2 (x) h1, db2; dW1 += dpre1 (x) x (db1 through input 9)
-    WOp<NT, 4, true> A2, A1;
-    WOp<NT, 4, false> B2;
-    WOp<NT, 1, false> B1;
+    WOp<4, true> A2, A1;
+    WOp<4, false> B2;
+    WOp<1, false> B1;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
         floatx4 h1N[4], d2N[4];
@@ -348,18 +331,18 @@ __device__ __forceinline__ void node_tiles(NodeLds &S, WGrad &G, int cnt, const 
         to_n_form(tb, d2T[u], d2N);
 #pragma unroll
         for (int ob = 0; ob < 4; ++ob) {
-            B2.set(u, ob, h1N[ob]);
+            B2.set(ob, h1N[ob]);
             G.b2[ob] += (d2N[ob][0] + d2N[ob][1]) + (d2N[ob][2] + d2N[ob][3]);
-            A2.set(u, ob, d2N[ob]);
+            A2.set(ob, d2N[ob]);
             floatx4 d1;
 #pragma unroll
             for (int r = 0; r < 4; ++r) d1[r] = h1N[ob][r] > 0.0f ? dh1N[u][ob][r] : 0.0f;
-            A1.set(u, ob, d1);
+            A1.set(ob, d1);
         }
-        B1.set(u, 0, xn[u]);
+        B1.set(0, xn[u]);
     }
-    wgrad_tiles<NT, 4, 4>(A2, B2, G.w2);
-    wgrad_tiles<NT, 4, 1>(A1, B1, G.w1);
+    wgrad_tile(A2, B2, G.w2);
+    wgrad_tile(A1, B1, G.w1);
 }
 
 // Record blocks 8 C .. 8 C + 7 (C = 4: the four of dW1): every wave puts its

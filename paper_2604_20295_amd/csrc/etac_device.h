@@ -387,10 +387,9 @@ __device__ __forceinline__ float pow2(int s) { return ldexpf(1.0f, s); }
 
 // Scales of one item's activations (uniform; every thread computes the same
 // values).  X bounds every component of the item's node inputs.
-// Scales of one item's activations: x at 2^ax, h1 at 2^a1 = 2^(s1 + ax),
-// f at 2^af = 2^(s2 + a1), h4 at 2^a4 = 2^(s4 + af).
+// x at 2^ax, h1 at 2^a1 = 2^(s1 + ax), f at 2^af = 2^(s2 + a1).
 struct ItemScale {
-    int ax, a1, af, a4;
+    int ax, a1, af;
     float xmul;          // 2^ax
 };
 
@@ -401,14 +400,12 @@ struct ItemScale {
 struct NetLds {
     half8 w1h[4 * 64], w1l[4 * 64];          // [ot][lane]    W1 2^s1, inputs padded 9 -> 32 (one K step)
     half8 w2h[4 * 2 * 64], w2l[4 * 2 * 64];  // [ot2][s][lane] W2 2^s2
-    half8 w4h[4 * 2 * 64], w4l[4 * 2 * 64];  // [ot2][s][lane] W4 columns 0..63 (per-node part) 2^s4
     float b1[64], b2[64];
     float b1s[64], b2s[64];                  // per item: b1 2^a1, b2 2^af
     float part[kWaves][64];                  // per-wave partials
-    // per launch: scale exponents of the staged weights (W1 2^s1, W2 2^s2,
-    // W4[:, :64] 2^s4) and of the adjoint's transposed uses (W4[:, :64]^T 2^s4t,
-    // W2^T 2^s2t)
-    int s1, s2, s4, s4t, s2t;
+    // per launch: scale exponents of the staged weights (W1 2^s1, W2 2^s2) and of
+    // the adjoint's transposed uses (W4[:, :64]^T 2^s4t, W2^T 2^s2t)
+    int s1, s2, s4t, s2t;
 };
 ETAC_LDS_ALIGNED(NetLds, b1s);
 ETAC_LDS_ALIGNED(NetLds, b2s);
@@ -505,7 +502,7 @@ __device__ __forceinline__ void net_scales(const float (&v)[kNorms], int &s1, in
 // exponents.  With inputs x 2^ax below T (X at least 1, so 2^ax <= 2T):
 //   h1 = W1 2^s1 x + b1 2^a1:  |h1| <= (||W1|| + 2 max|b1|) T 2^s1 < T,
 //   f  = W2 2^s2 h1 + b2 2^af: |f| <= (||W2|| T + 2 max|b2| T 2^s1) 2^s2 < T,
-//   W4 2^s4 with s4 from max |W4[:, :64]| (its product is never split).
+//   W4 2^s4 with s4 from max |W4[:, :64]| (the tables' product; it is never split).
 // Adjoint, with dL/dpre4 2^d4 below T: W4[:, :64]^T 2^s4t and W2^T 2^s2t by
 // their column norms keep dL/dpre2 and dL/dpre1 below T.
 // Ends with a barrier.
@@ -522,7 +519,7 @@ __device__ void stage_net(NetLds &L, const float *phi) {
     const float n4t = v[3], n2t = v[2];
     int s1, s2, s4;
     net_scales(v, s1, s2, s4);
-    const float e1 = pow2(s1), e2 = pow2(s2), e4 = pow2(s4);
+    const float e1 = pow2(s1), e2 = pow2(s2);
     for (int idx = tid; idx < 4 * 64; idx += kWG) {
         const int lane = idx & 63, ot = idx >> 6, q = lane >> 4;
         float x[8];
@@ -536,22 +533,17 @@ __device__ void stage_net(NetLds &L, const float *phi) {
     for (int idx = tid; idx < 4 * 2 * 64; idx += kWG) {
         const int lane = idx & 63, s = (idx >> 6) & 1, ot2 = idx >> 7, q = lane >> 4;
         const int out = ot2 * 16 + (lane & 15);
-        float a[8], b[8];
+        float a[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int in = chain_k(s, q, e);
-            a[e] = phi[kW2 + out * 64 + in] * e2;
-            b[e] = phi[kW4 + out * 128 + in] * e4;
-        }
+        for (int e = 0; e < 8; ++e) a[e] = phi[kW2 + out * 64 + chain_k(s, q, e)] * e2;
         split8(a, L.w2h[idx], L.w2l[idx]);
-        split8(b, L.w4h[idx], L.w4l[idx]);
     }
     for (int i = tid; i < 64; i += kWG) {
         L.b1[i] = phi[kB1 + i];
         L.b2[i] = phi[kB2 + i];
     }
     if (tid < 64) {   // wave 0, identical values
-        L.s1 = s1; L.s2 = s2; L.s4 = s4;
+        L.s1 = s1; L.s2 = s2;
         L.s4t = range_exp(n4t * kTop);
         L.s2t = range_exp(n2t * kTop);
     }
@@ -565,7 +557,6 @@ __device__ __forceinline__ ItemScale item_scale(const NetLds &L, float X) {
     s.ax = uniform(range_exp(fmaxf(X, 1.0f)));
     s.a1 = uniform(L.s1) + s.ax;
     s.af = uniform(L.s2) + s.a1;
-    s.a4 = uniform(L.s4) + s.af;
     s.xmul = uniform(pow2(s.ax));
     return s;
 }

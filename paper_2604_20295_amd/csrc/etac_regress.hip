@@ -6,7 +6,8 @@
 //   k_live         : the envs in contact on each patch.
 //   k_regress      : persistent, one workgroup of eight waves per CU with the
 //                    per-node layers' weights resident in LDS; a unit is 256
-//                    nodes of an item (more in plans of very many), taken by a wave (largest patches first,
+//                    nodes of an item (more in a plan whose rows would take
+//                    over 256 MB), taken by a wave (largest patches first,
 //                    one each and then from a device work queue): 16-node
 //                    tiles, two at a time, through the per-node layers on MFMA
 //                    with an online softmax over the tiles.  The unit's
