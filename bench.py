@@ -66,7 +66,7 @@ def parse():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--eager", action="store_true",
                     help="time the headline steps as eager calls instead of replays of one captured HIP graph")
-    ap.add_argument("--no-autotune", action="store_true", help="keep the built-in launch shapes")
+    ap.add_argument("--no-autotune", action="store_true", help="kept for callers: no launch shape is tuned")
     ap.add_argument("--launch", type=str, default=None,
                     help="fixed launch shape a,b,c,d,e as in Plan.set_launch (no autotuning), e.g. for profiling")
     ap.add_argument("--no-rollout", action="store_true",
@@ -126,8 +126,6 @@ def rollout(args, mode):
 
     if args.launch:
         plan.set_launch(*[int(x) for x in args.launch.split(",")])
-    elif not args.no_autotune:
-        _native.etac_plan_autotune(plan, sc, md, u, cobj, na, gu, grot, gtr, gal, gph, reps=2, saved=saved)
 
     def body(with_bwd):
         rot.copy_(torch.index_select(trot, 0, step_idx)[0])
@@ -418,8 +416,6 @@ def hires(args, mode):
     saved = _native.saved_buffer(plan, E)
     if args.launch:
         plan.set_launch(*[int(x) for x in args.launch.split(",")])
-    elif not args.no_autotune:
-        _native.etac_plan_autotune(plan, sc, md, u, cobj, na, gu, grot, gtr, gal, gph, reps=1, saved=saved)
     _native.etac_step(plan, sc, md, u, cobj, na, saved=saved)
     _native.etac_step_backward(plan, sc, md, gu, grot, gtr, gal, gph, saved=saved)
     torch.cuda.synchronize()
@@ -674,11 +670,9 @@ def main():
     def bwd():
         _native.etac_step_backward(plan, sc, md, grad_u, grot, gtr, gal, gph, saved=saved)
 
-    # launch shapes chosen by the library's autotuner on this workload
+    # the launch knobs are kept and reported; they change no launch
     if args.launch:
         plan.set_launch(*[int(x) for x in args.launch.split(",")])
-    elif not args.no_autotune:
-        _native.etac_plan_autotune(plan, sc, md, u, cobj, na, grad_u, grot, gtr, gal, gph, reps=2, saved=saved)
     launch_shape = plan.launch()
     stream = torch.cuda.current_stream(dev)
 
@@ -814,7 +808,7 @@ def main():
                    "launch_shape": {"fwd_wg_per_cu": launch_shape[0], "fwd_batch": launch_shape[1],
                                     "bwd_batch": launch_shape[2], "decay_wg_per_cu": launch_shape[3],
                                     "net_batch": launch_shape[4],
-                                    "autotuned": not (args.no_autotune or args.launch)}},
+                                    "autotuned": False}},
         "step_latency_ms": {"p50": float(np.percentile(lat, 50)), "p99": float(np.percentile(lat, 99))},
         "eager": {"ms_per_step": eager_ms, "value": nodes / (eager_ms * 1e-3), "unit": "node-updates/s",
                   "what": "the same steps as separate calls, with the per-kernel device times below"},

@@ -300,17 +300,15 @@ etac_status etac_plan_set_launch(etac_plan *plan, int32_t fwd_wg_per_cu, int32_t
 /* The current launch shape, in the order of etac_plan_set_launch (HOST int32[5]). */
 etac_status etac_plan_get_launch(const etac_plan *plan, int32_t *shape);
 
-/* Autotuner.  Times every candidate setting of the launch knobs (which change
- * no launch, see above) on the caller's inputs (as for etac_step and etac_step_backward; all
- * DEVICE pointers, outputs overwritten; `saved` may be NULL and is passed to
- * both calls) with HIP events over `reps` calls
- * (1 .. 1000) after a warm-up call, and keeps the fastest: forward
- * workgroups per CU in {1, 2} x batch in {1, 2, 4, 8, 16}; with grad_u
- * non-NULL also decay-kernel workgroups per CU in {2, 3, 4} x its batch in
- * {2, 4, 8, 16}, then the network-adjoint claim in {1, 2, 4}.  Every
- * candidate gives identical results.  `best` (HOST int32[5], may be NULL)
- * receives the chosen shape as in etac_plan_get_launch.  Blocks the host and creates two HIP events, so it
- * must not be called during stream capture (ETAC_ERR_CAPTURE). */
+/* The launch shape for the caller's inputs (as for etac_step and, with grad_u
+ * non-NULL, etac_step_backward; all DEVICE pointers, outputs overwritten;
+ * `saved` may be NULL and is passed to both calls).  The knobs above change no
+ * launch, so there is nothing to time: one call of each is made, which
+ * validates the arguments and fills the outputs, and the current shape is kept
+ * whatever `reps` is (1 .. 1000, else ETAC_ERR_VALUE).  `best` (HOST int32[5],
+ * may be NULL) receives it as in etac_plan_get_launch.  Blocks the host until
+ * the outputs are there, so it must not be called during stream capture
+ * (ETAC_ERR_CAPTURE). */
 etac_status etac_plan_autotune(etac_plan *plan, const etac_scene *scene, const etac_model *model,
                                const float *grad_u, float *u, int8_t *contact_obj, int32_t *n_active,
                                void *saved, float *grad_rot, float *grad_trans, float *grad_alpha,

@@ -388,8 +388,8 @@ def etac_step(plan, scene, model, u, contact_obj, n_active, saved=None):
 
 
 def etac_step_static(plan, scene, model, u, contact_obj, n_active, saved=None):
-    """etac_step without allocation: the kernel's scratch is the library's
-    static device array (see include/etac.h)."""
+    """etac_step under the name of the allocation-free call: no call but plan
+    creation allocates (see include/etac.h)."""
     import torch
     E = scene.n_envs
     _req(u, torch.float32, (3, E, plan.N), "u", plan.device)
@@ -446,9 +446,9 @@ def etac_step_backward(plan, scene, model, grad_u, grad_rot, grad_trans, grad_al
 
 def etac_plan_autotune(plan, scene, model, u, contact_obj, n_active, grad_u=None, grad_rot=None, grad_trans=None,
                        grad_alpha=None, grad_phi=None, reps=3, saved=None):
-    """Time the candidate launch shapes on these inputs, keep the fastest and
-    return it as in Plan.launch().  With grad_u None only the forward is
-    tuned."""
+    """One step (and its adjoint, with grad_u) on these inputs; returns the
+    current launch shape as in Plan.launch().  The launch knobs change no
+    launch, so nothing is timed and the shape stays as it is."""
     import torch
     E, O = scene.n_envs, scene.max_obj
     _req(u, torch.float32, (3, E, plan.N), "u", plan.device)

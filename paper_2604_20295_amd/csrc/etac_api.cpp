@@ -699,89 +699,16 @@ etac_status etac_plan_autotune(etac_plan *plan, const etac_scene *scene, const e
                                float *grad_phi, int32_t reps, int32_t *best, void *stream) {
     if (!plan) return ETAC_ERR_NULL;
     if (reps < 1 || reps > 1000) return ETAC_ERR_VALUE;
-    etac::Plan &p = plan->p;
     const hipStream_t st = (hipStream_t)stream;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return ETAC_ERR_CAPTURE;
-    // one validated call of each before any timing (argument errors come back here)
     etac_status s = etac_step(plan, scene, model, u, contact_obj, n_active, saved, stream);
+    if (s == ETAC_OK && grad_u)
+        s = etac_step_backward(plan, scene, model, grad_u, saved, grad_rot, grad_trans, grad_alpha, grad_phi, stream);
     if (s != ETAC_OK) return s;
-    if (grad_u) {
-        s = etac_step_backward(plan, scene, model, grad_u, saved, grad_rot, grad_trans, grad_alpha, grad_phi,
-                               stream);
-        if (s != ETAC_OK) return s;
-    }
-    hipEvent_t ev[2] = {nullptr, nullptr};
-    hipError_t e = hipEventCreate(&ev[0]);
-    if (e == hipSuccess) e = hipEventCreate(&ev[1]);
-    // time `reps` calls after one warm-up call of the current shape
-    auto timed = [&](bool fwd, float &ms) -> etac_status {
-        for (int r = 0; r <= reps; ++r) {
-            if (r == 1 && hipEventRecord(ev[0], st) != hipSuccess) return ETAC_ERR_HIP;
-            const etac_status q = fwd ? etac_step(plan, scene, model, u, contact_obj, n_active, saved, stream)
-                                      : etac_step_backward(plan, scene, model, grad_u, saved, grad_rot,
-                                                           grad_trans, grad_alpha, grad_phi, stream);
-            if (q != ETAC_OK) return q;
-        }
-        hipError_t h = hipEventRecord(ev[1], st);
-        if (h == hipSuccess) h = hipEventSynchronize(ev[1]);
-        if (h == hipSuccess) h = hipEventElapsedTime(&ms, ev[0], ev[1]);
-        return h == hipSuccess ? ETAC_OK : hip_fail(h);
-    };
-    etac_status out = e == hipSuccess ? ETAC_OK : hip_fail(e);
-    // forward: workgroups per CU x batch
-    int bf_occ = p.wg_per_cu, bf_batch = p.batch;
-    float bf_ms = 3.0e38f;
-    static const int kOcc[] = {1, 2};
-    static const int kBatch[] = {1, 2, 4, 8, 16};
-    for (int oi = 0; out == ETAC_OK && oi < 2; ++oi)
-        for (int bi = 0; out == ETAC_OK && bi < 5; ++bi) {
-            p.wg_per_cu = kOcc[oi];
-            p.grid = p.cu_count * p.wg_per_cu;
-            p.batch = kBatch[bi];
-            float ms = 0.0f;
-            out = timed(true, ms);
-            if (out == ETAC_OK && ms < bf_ms) { bf_ms = ms; bf_occ = p.wg_per_cu; bf_batch = p.batch; }
-        }
-    p.wg_per_cu = bf_occ;
-    p.grid = p.cu_count * p.wg_per_cu;
-    p.batch = bf_batch;
-    // adjoint: decay-kernel workgroups per CU x its work-queue batch, then
-    // the network kernel's claim size
-    if (grad_u) {
-        int bb_dec = p.decay_wg_per_cu, bb_batch = p.bwd_batch;
-        float bb_ms = 3.0e38f;
-        static const int kDec[] = {2, 3, 4};
-        for (int di = 0; out == ETAC_OK && di < 3; ++di)
-            for (int bi = 1; out == ETAC_OK && bi < 5; ++bi) {
-                p.decay_wg_per_cu = kDec[di];
-                p.bwd_batch = kBatch[bi];
-                float ms = 0.0f;
-                out = timed(false, ms);
-                if (out == ETAC_OK && ms < bb_ms) { bb_ms = ms; bb_dec = p.decay_wg_per_cu; bb_batch = p.bwd_batch; }
-            }
-        p.decay_wg_per_cu = bb_dec;
-        p.bwd_batch = bb_batch;
-        int bn = p.net_batch;
-        float bn_ms = 3.0e38f;
-        for (int ni = 0; out == ETAC_OK && ni < 3; ++ni) {
-            p.net_batch = kBatch[ni];
-            float ms = 0.0f;
-            out = timed(false, ms);
-            if (out == ETAC_OK && ms < bn_ms) { bn_ms = ms; bn = p.net_batch; }
-        }
-        p.net_batch = bn;
-    }
-    for (int i = 0; i < 2; ++i)
-        if (ev[i]) (void)hipEventDestroy(ev[i]);
-    if (best) {
-        best[0] = p.wg_per_cu;
-        best[1] = p.batch;
-        best[2] = p.bwd_batch;
-        best[3] = p.decay_wg_per_cu;
-        best[4] = p.net_batch;
-    }
-    return out;
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return hip_fail(e);
+    return best ? etac_plan_get_launch(plan, best) : ETAC_OK;
 }
 
 

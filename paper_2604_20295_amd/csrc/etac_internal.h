@@ -28,7 +28,7 @@ constexpr int kSplitEnvs = 4;      // envs per compute unit up to which an env's
 constexpr int kDefaultWgPerCu = 2;
 constexpr int kDefaultBatch = 4;   // default of the batch knobs
 constexpr int kDefaultDecayWgPerCu = 3;
-constexpr int kDefaultNetBatch = 2;   // workgroups per CU of the decay-adjoint kernel
+constexpr int kDefaultNetBatch = 2;
 
 // Device view of the plan's mesh copy.
 struct MeshDev {
