@@ -324,8 +324,9 @@ __device__ __forceinline__ float wave_max(float v) {
 // Certified cutoff of the pair sums of Eq. 1 on far patches.  A run of 32 nodes
 // is passed over when its box lies further than D from the box of the wave's
 // own nodes, where exp(-alpha D) = 2^-50: every weight left out is below 2^-50,
-// so a sum changes by less than 2^-50 times the sum of its |terms|, far below
-// FP32 rounding of the sums themselves.
+// so a sum changes by less than 2^-50 times the sum of the |u_hat| that it left
+// out (of |dL/dU| in the adjoint).  Where every term lies beyond D the sum
+// becomes 0.
 constexpr double kCutLog2 = 50.0;
 // D^2 for the item's alpha, rounded up (no cutoff when alpha <= 0).
 __device__ __forceinline__ float cutoff_d2(float alpha) {

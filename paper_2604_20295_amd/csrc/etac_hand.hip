@@ -14,7 +14,7 @@
 //   k_pose_hand   : a wave per env, the chain rule from the rows' relative-pose
 //                   gradients to object and link poses, summed in item and
 //                   slot order in FP64.
-// The fused step, the contact pass and the adjoint kernels run unchanged on
+// The step, the contact pass and the adjoint kernels run unchanged on
 // the rows (SceneDev with one row per item).
 #include "etac_device.h"
 
