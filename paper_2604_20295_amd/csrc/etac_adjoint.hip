@@ -134,8 +134,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const bool dec = step_decay(S);
     const int32_t *na = S.itm.n_act;
     const int total = product_units(S, L.first, 64, 32);
-    for (int q = product_start(); q < total; q += product_stride()) {
-        const ProductRef ref = product_ref(S, L.first, q, 64, 32);
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const ProductRef ref = product_ref(S, L.first, q, 64);
         const int k = ref.k, g0 = ref.group * 32;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
         const int cnt = uniform(live_count(S, k));
@@ -1128,7 +1128,7 @@ hipError_t launch_backward(const Plan &pl, const SceneDev *s, const ModelDev &m,
     launch_front(pl, f, st);
     if (pl.tile.n_near) {
         // as in the forward: wide tiles once they give every CU work
-        if (f.wide) hipLaunchKernelGGL(k_adj_wide, dim3(product_grid(f.cus)), dim3(kWG), 0, st, p);
+        if (f.wide) hipLaunchKernelGGL(k_adj_wide, dim3(2 * f.cus), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_adj_narrow, dim3(blocks((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
                                dim3(kWG), 0, st, p);

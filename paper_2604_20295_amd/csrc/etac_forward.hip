@@ -722,8 +722,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(2))) void k
     const float *src = uhat_source(p);
     const int32_t *na = p.n_active ? p.n_active : p.itm.n_act;
     const int total = product_units(p, L.first, kRows, kWideEnvs);
-    for (int q = product_start(); q < total; q += product_stride()) {
-        const ProductRef ref = product_ref(p, L.first, q, kRows, kWideEnvs);
+    for (int q = blockIdx.x; q < total; q += gridDim.x) {
+        const ProductRef ref = product_ref(p, L.first, q, kRows);
         const int k = ref.k, rb = ref.row_block, g0 = ref.group * kWideEnvs;
         const int base = uniform(M.offset[k]), n = uniform(M.offset[k + 1]) - base, KS = (n + 31) >> 5;
         const int cnt = uniform(live_count(p, k));
@@ -1250,8 +1250,8 @@ hipError_t launch_step(const Plan &pl, const SceneDev *s, const ModelDev &m, int
     launch_front(pl, p, st);
     if (step_residual(p)) launch_pool(pl, p, st);
     if (pl.tile.n_near) {
-        if (tall_tiles(pl, p)) hipLaunchKernelGGL(k_prop_wide<2>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
-        else if (p.wide) hipLaunchKernelGGL(k_prop_wide<1>, dim3(product_grid(cus)), dim3(kWG), 0, st, p);
+        if (tall_tiles(pl, p)) hipLaunchKernelGGL(k_prop_wide<2>, dim3((unsigned)(2 * cus)), dim3(kWG), 0, st, p);
+        else if (p.wide) hipLaunchKernelGGL(k_prop_wide<1>, dim3((unsigned)(2 * cus)), dim3(kWG), 0, st, p);
         else
             hipLaunchKernelGGL(k_prop_narrow, dim3((unsigned)std::min<long long>((long long)((n_envs + 15) / 16) * pl.tile.near_rows, 4 * cus)),
                                dim3(kWG), 0, st, p);

@@ -678,46 +678,28 @@ __device__ int unit_prefix(int K, int *first, F per) {
 }
 
 // Units of a product of a patch's decay matrix with the envs in contact: row
-// blocks times groups of envs.  Workgroups go to the eight XCDs in turn, each
-// with an L2 of its own (4 MB; the matrices of a 1024-node patch take 4 MB
-// each, its envs' columns 7 MB at 600 envs): XCD x takes every fourth row
-// block and every second group, so that over a patch it reads a quarter of the
-// matrix and half of the columns, the row blocks of a group together
-// (4096 hands, transposed product: 600 us with units in patch order, 591 us).
+// blocks times groups of envs, the row blocks of a group after one another.
+// Workgroups stride over the units of all patches, so no part of the chip runs
+// dry before another, whatever the patches' sizes (dealt by residues of row block
+// and group, six of the eight XCDs had none of one 256-node patch).  Workgroups go
+// to the XCDs in turn: where a patch has a multiple of eight row blocks, an XCD
+// keeps to an eighth of its matrix.  Shares of an XCD's own of row blocks and
+// groups gain nothing on it (4096 hands, forward and transposed product: 419 and
+// 669 us, 411 and 667 like this; 16384 hands, forward: 1528 and 1554, whose runs
+// differ by 40).
 struct ProductRef {
     int k, row_block, group;
 };
 
-constexpr int kXcds = 8, kXcdRows = 4, kXcdGroups = 2;
-
-__device__ __forceinline__ int residue_count(int n, int first, int step) { return n > first ? (n - first + step - 1) / step : 0; }
-
-// This XCD's first row block and first group in the patch of rank kk: turned
-// from patch to patch, so that remainders fall on every XCD.
-__device__ __forceinline__ int xcd_row(int kk) { return ((int)(blockIdx.x % kXcds) + kk) % kXcdRows; }
-__device__ __forceinline__ int xcd_group(int kk) { return ((int)(blockIdx.x % kXcds) / kXcdRows + kk / kXcdRows) % kXcdGroups; }
-
-// A patch of fewer row blocks or groups than the residues would leave XCDs
-// without any (4096 pads of 256 nodes: six of the eight at 256 rows): its units
-// go to the XCDs in turn.
-__device__ __forceinline__ bool xcd_residues(int blocks, int groups) { return blocks >= kXcdRows && groups >= kXcdGroups; }
-__device__ __forceinline__ int xcd_first(int kk) { return ((int)(blockIdx.x % kXcds) + kk) % kXcds; }
-
-// This XCD's units (whole workgroup; ends with a barrier).
+// The units (whole workgroup; ends with a barrier).
 __device__ int product_units(const StepParams &p, int (&first)[kMaxPatches + 1], int rows, int envs) {
     const MeshDev &M = p.mesh;
     return unit_prefix<kWaves>(M.K, first, [&](int kk) {
         const int k = M.order[kk], groups = (live_count(p, k) + envs - 1) / envs;
         if (p.tile.w_off[k] < 0) return 0;
-        const int blocks = (M.offset[k + 1] - M.offset[k] + rows - 1) / rows;
-        if (!xcd_residues(blocks, groups)) return residue_count(blocks * groups, xcd_first(kk), kXcds);
-        return residue_count(blocks, xcd_row(kk), kXcdRows) * residue_count(groups, xcd_group(kk), kXcdGroups);
+        return (M.offset[k + 1] - M.offset[k] + rows - 1) / rows * groups;
     });
 }
-
-// Units are strided over the XCD's workgroups.
-__device__ __forceinline__ int product_start() { return blockIdx.x / kXcds; }
-__device__ __forceinline__ int product_stride() { return gridDim.x / kXcds; }
 
 // Queue position (patch rank) of unit u: the last rank whose first unit is <= u.
 __device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
@@ -734,20 +716,12 @@ __device__ __forceinline__ int unit_rank(const int *first, int K, int u) {
 // results, else the step's output, whose active entries are u_hat.
 __device__ __forceinline__ const float *uhat_source(const StepParams &p) { return p.uhat_in ? p.uhat_in : p.u; }
 
-__device__ __forceinline__ ProductRef product_ref(const StepParams &p, const int (&first)[kMaxPatches + 1], int q, int rows, int envs) {
+__device__ __forceinline__ ProductRef product_ref(const StepParams &p, const int (&first)[kMaxPatches + 1], int q, int rows) {
     const int kk = unit_rank(first, p.mesh.K, q), k = uniform(p.mesh.order[kk]);
     const int blocks = (uniform(p.mesh.offset[k + 1]) - uniform(p.mesh.offset[k]) + rows - 1) / rows;
-    const int groups = (uniform(live_count(p, k)) + envs - 1) / envs, local = q - uniform(first[kk]);
-    if (!xcd_residues(blocks, groups)) {
-        const int u = xcd_first(kk) + kXcds * local, g = u / blocks;
-        return ProductRef{k, u - g * blocks, g};
-    }
-    const int mine = residue_count(blocks, xcd_row(kk), kXcdRows), g = local / mine;      // the row blocks of a group run together
-    return ProductRef{k, xcd_row(kk) + kXcdRows * (local - g * mine), xcd_group(kk) + kXcdGroups * g};
+    const int local = q - uniform(first[kk]), group = local / blocks;
+    return ProductRef{k, local - group * blocks, group};
 }
-
-// Grid of such a kernel: a whole number of workgroups for each XCD.
-inline int product_grid(int cus) { return (2 * cus + kXcds - 1) / kXcds * kXcds; }
 
 // ---------------------------------------------------------------------------
 // products of a decay matrix

@@ -1,7 +1,6 @@
 """The wide products' units on surfaces of few row blocks or few envs in
-contact, where they are dealt to the chiplets in turn instead of by residues,
-and on either side of the change of tile height: forward and adjoint against
-the FP64 oracle on sampled envs, and no node of any env left out."""
+contact and on either side of the change of tile height: forward and adjoint
+against the FP64 oracle on sampled envs, and no node of any env left out."""
 import numpy as np
 import pytest
 
