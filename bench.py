@@ -28,8 +28,9 @@ if ROOT not in sys.path:
 import numpy as np
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, GB/s
-F16_MFMA_PEAK_TFLOPS = 2500.0  # dense FP16 matrix (the MFMA the network kernels issue)
+F16_MFMA_PEAK_TFLOPS = 2500.0  # dense FP16 and BF16 matrix (the MFMA the kernels issue)
 MFMA_PASSES = 3                # split-FP16 products per FP32-equivalent product (hi*hi + hi*lo + lo*hi)
+MATRIX_PASSES = 6              # products of three BF16 parts per FP32-equivalent product of a decay matrix
 # network multiply-adds: encoder per node (9 -> 64 -> 64), decoder per passive
 # node (the per-node half of W4, 64 -> 64, and W5, 64 -> 3; the g' half of W4
 # is one vector per item), global MLP per item (W3 and the g' half of W4)
@@ -294,8 +295,8 @@ def algorithmic_work(kernel, counts, E, N, K, O, mode):
     stated: FP32-equivalent network flops (2 per multiply-add), decay pairs of
     Eq. 1, and the HBM bytes its inputs and outputs must move (each once; the
     plan's scratch is not counted).  Pairs of patches with a decay matrix are
-    matrix products: three components, 2 flops each, and in the adjoint the
-    same again with d W.  The network's kernels do less than counted: passive
+    matrix products (matrix_flop, a part of mfma_flop): three components, 2
+    flops each, and in the adjoint the same again with d W.  The network's kernels do less than counted: passive
     nodes are encoded once per call.  The adjoint reads dL/dU only on patches in
     contact (elsewhere U = 0 whatever the inputs)."""
     nodes = float(E) * N
@@ -308,11 +309,11 @@ def algorithmic_work(kernel, counts, E, N, K, O, mode):
         # contact winner (1 B) and u_hat (12 B) per node, active count per item
         return dict(mfma_flop=0.0, pairs=0.0, hbm_bytes=13.0 * nodes + 4.0 * E * K)
     if kernel == "k_step":
-        return dict(mfma_flop=(counts["mlp_flop"] if net else 0.0) + 6.0 * matrix, pairs=pairs,
+        return dict(mfma_flop=(counts["mlp_flop"] if net else 0.0) + 6.0 * matrix, matrix_flop=6.0 * matrix, pairs=pairs,
                     hbm_bytes=13.0 * nodes + 4.0 * E * K)
     if kernel == "k_bwd_decay":
         # dL/dU of contacted patches in, dL/dalpha partial per item out
-        return dict(mfma_flop=12.0 * matrix, pairs=pairs,
+        return dict(mfma_flop=12.0 * matrix, matrix_flop=12.0 * matrix, pairs=pairs,
                     hbm_bytes=12.0 * counts["contacted_nodes"] + 4.0 * E * K)
     # k_bwd: on the passive nodes of contacted patches the network's forward
     # is recomputed (encoder and decoder) and both adjoint products run, 3x
@@ -366,12 +367,15 @@ def roofline_of(kernel, avg_ms, work, workload="hand"):
     """Roofline of a kernel: the resource whose lower-bound time (work /
     peak) is largest names the bound; achieved = algorithmic work of one
     launch / its average device time.  mfma: FP32-equivalent flops of the
-    network and of the decay matrices, three split-FP16 passes each, against the dense FP16 peak; alu:
-    decay pairs against the VALU issue ceiling (PAIR_CEILING); hbm: bytes
-    against 8 TB/s."""
+    network, three split-FP16 passes each, and of the decay matrices, six passes
+    of BF16 parts each, against the dense FP16 peak; alu: decay pairs of
+    patches without a matrix against the VALU issue ceiling (PAIR_CEILING);
+    hbm: bytes against 8 TB/s."""
     t = avg_ms * 1e-3
     ceiling = PAIR_CEILING_BWD if kernel == "k_bwd_decay" else PAIR_CEILING
-    lb = {"mfma": MFMA_PASSES * work["mfma_flop"] / (F16_MFMA_PEAK_TFLOPS * 1e12),
+    matrix = work.get("matrix_flop", 0.0)
+    passed = MFMA_PASSES * (work["mfma_flop"] - matrix) + MATRIX_PASSES * matrix
+    lb = {"mfma": passed / (F16_MFMA_PEAK_TFLOPS * 1e12),
           "alu": work["pairs"] / ceiling,
           "hbm": work["hbm_bytes"] / (HBM_PEAK_GBS * 1e9)}
     bound = max(lb, key=lb.get)
@@ -384,7 +388,7 @@ def roofline_of(kernel, avg_ms, work, workload="hand"):
     traffic = measured_traffic(kernel, workload)
     return {"bound": bound, "kernel": kernel, "achieved": round(achieved, 3), "peak": round(peak, 3), "unit": unit,
             "frac": round(achieved / peak, 5), "traffic": traffic, "avg_ms": round(avg_ms, 4),
-            "mfma_passes": MFMA_PASSES if bound == "mfma" else None,
+            "mfma_passes": round(passed / work["mfma_flop"], 3) if bound == "mfma" else None,
             "lower_bound_ms": {k: round(v * 1e3, 4) for k, v in lb.items()},
             "work_per_launch": work}
 
@@ -753,7 +757,7 @@ def main():
     n_c, ms_c = plan.kernel_time(_native.ETAC_TIMER_CONTACT)
     plan.set_timing(False)
     kernel_avg["k_contact"] = ms_c / n_c
-    # plain forward: contact, then propagation from the stored contact (two launches)
+    # plain forward: contact, then propagation from the stored contact
     uo = torch.empty_like(u)
     for _ in range(2):
         _native.etac_contact(plan, sc, cobj, uhat, na)
@@ -823,11 +827,15 @@ def main():
         "contact_only": {"value": nodes / (kernel_avg["k_contact"] * 1e-3), "unit": "node-updates/s",
                          "ms": kernel_avg["k_contact"]},
         "plain_forward": {"ms_per_step": plain_fwd_ms, "value": nodes / (plain_fwd_ms * 1e-3),
-                          "unit": "node-updates/s", "what": "etac_contact then etac_propagate (two launches)",
+                          "unit": "node-updates/s", "what": "etac_contact then etac_propagate",
                           "fwd_bwd_over_plain_forward": step_ms / plain_fwd_ms},
+        # active-passive pairs per second of the whole span; the issue ceilings
+        # bound only those of patches without a decay matrix
         "decay_pairs_per_s": {"k_step": counts["pairs"] / (kernel_avg["k_step"] * 1e-3),
                               "k_bwd_decay": counts["pairs"] / (kernel_avg["k_bwd_decay"] * 1e-3),
-                              "issue_ceiling_fwd": PAIR_CEILING, "issue_ceiling_bwd": PAIR_CEILING_BWD},
+                              "share_in_matrix_products": counts["matrix_pairs"] / max(counts["pairs"], 1.0),
+                              "issue_ceiling_pair_sums_fwd": PAIR_CEILING,
+                              "issue_ceiling_pair_sums_bwd": PAIR_CEILING_BWD},
     }
 
     if args.calib_steps > 0:

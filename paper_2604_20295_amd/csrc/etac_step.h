@@ -25,7 +25,7 @@ struct StepParams {
     const int8_t *cobj_in;   // propagate-only: given contact results
     const float *uhat_in;
     float *u;                // [3][E][N]
-    int8_t *cobj_out;        // [E][N] (fused step)
+    int8_t *cobj_out;        // [E][N] (whole step)
     int32_t *n_active;       // [E][K]
     int32_t *n_touch;        // [E][K] active nodes won by external objects (hand), or null
     uint32_t *saved;         // [E K][kSavedWords] pooling record written for the adjoint, or null
